@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkeydiff.so")
-SOURCES = ["attention.hip", "evict.hip", "keydiff_abi.hip"]
+SOURCES = ["attention.hip", "few.hip", "evict.hip", "keydiff_abi.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     "-ffp-contract=off",   # the deciding score is plain IEEE double arithmetic

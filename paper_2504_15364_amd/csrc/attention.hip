@@ -10,8 +10,8 @@
 // contiguous range of 64-key tiles (split-KV); the splits are merged by
 // log-sum-exp in step_post (or the merge kernel).  Workgroup ids map KV heads
 // round-robin so that the workgroups of one head share an XCD and its L2.
-// Variants: HELP (few query rows: waves without one copy tiles and score rows), ALT on
-// top of it (one wave's worth of rows: two waves take alternate key tiles), and the
+// Variants: HELP (workgroups whose last waves have no query row: those copy tiles and score
+// rows; with at most 32 rows per head another kernel runs, few.hip), and the
 // carrying kernel whose first workgroups run another cache's pending selection.
 //
 // Data path.  K and V tiles stream global -> LDS asynchronously
@@ -162,7 +162,7 @@ __device__ __forceinline__ void loads_landed(u32x2 &x, u32x4 (&w)[A][B])
 // HELP: some waves of a workgroup may have no query row at all (few query rows: decode); such a
 // wave takes no part in the attention, it copies its share of every tile and scores rows.
 constexpr int MAIN_WAVES = 8;
-template <int D, bool HELP, bool ALT>
+template <int D, bool HELP>
 __device__ __forceinline__ void step_main_body(const StepParams &p, const int block_id)
 {
     constexpr int NW = MAIN_WAVES;   // waves per workgroup
@@ -195,9 +195,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     const int tid = threadIdx.x, lane = tid & 63;
     // the wave index as a scalar: what follows from it (buffer pieces, roles, branches) is then
     // scalar arithmetic and scalar branches instead of per-lane values and execution masks
-    // (not in the alternating mode, whose two roles the compiler then turns into two copies of the
-    // loop body and spills)
-    const int wave = ALT ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
     const int BH = p.batch * p.hkv;
     int id = block_id;
@@ -343,34 +341,25 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     // the wave's piece of the two ring buffers that tiles t0 + 2 and t0 + 3 will use later (with
     // the K swizzle), and read from there into registers.  Loading the B-operand layout directly
     // would touch 32 rows per instruction.
-    // ALT (a HELP kernel whose workgroup has a single wave's worth of query rows: decode): waves 0 and 1
-    // both hold those rows and take alternate key tiles -- in every step one of them forms S^T of its
-    // next tile while the other turns the logits of its current tile into weights and multiplies
-    // with V, so the two halves of a step run side by side on two SIMDs.  Each keeps its own
-    // running maximum, row sum and output and writes them as a partial of its own: to the merge
-    // the two look like two more key splits (p.psplits = 2 p.splits).
-    static_assert(!ALT || HELP, "alternating waves are a mode of the kernel with helper waves");
-    constexpr bool alt = ALT;
-    const int wave_q = alt ? 0 : wave;                // whose query rows this wave holds
     int mrow[NQ], qg[NQ], qj[NQ], vis[NQ];
     bool valid[NQ];
     bf16x8 qreg[NQ][NC];
 #pragma unroll
     for (int a = 0; a < NQ; ++a) {
-        mrow[a] = mt * TM + wave_q * (32 * NQ) + 32 * a + l32;
+        mrow[a] = mt * TM + wave * (32 * NQ) + 32 * a + l32;
         valid[a] = mrow[a] < Mtot;
         qg[a] = valid[a] ? mrow[a] / p.Bt : 0;
         qj[a] = valid[a] ? mrow[a] % p.Bt : 0;
         vis[a] = p.len + qj[a] + 1;  // rows [0, vis) are visible: all cached rows, block rows 0..j
     }
-    const bool active = !HELP || (alt ? wave < 2 : mt * TM + wave * (32 * NQ) < Mtot);   // wave uniform
+    const bool active = !HELP || mt * TM + wave * (32 * NQ) < Mtot;   // wave uniform
     constexpr int QROWS = 32 * NQ, QBYTES = QROWS * ROWB;
     static_assert(NW * QBYTES <= 2 * 2 * TILE_B && (2 * TILE_B) % QBYTES == 0, "query staging uses two ring buffers");
     const int qoff = wave * QBYTES, qhalf = qoff / (2 * TILE_B);
     unsigned char *qwave = smem + (size_t)((t0 + 2 + qhalf) % STAGES) * 2 * TILE_B + (qoff - qhalf * 2 * TILE_B);
     {
         const char *qhead = reinterpret_cast<const char *>(p.q + (size_t)(b * p.hq + kvh * p.G) * p.Bt * D);
-        const int m0 = mt * TM + wave_q * QROWS;   // first row of the wave
+        const int m0 = mt * TM + wave * QROWS;   // first row of the wave
         if (m0 + QROWS <= Mtot) {
             // every row exists: one base address for the wave, a 32-bit offset per lane and copy
             const int r0 = lane / UPR;
@@ -719,7 +708,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     // Which waves score when some have no query rows: only those, so that the waves carrying the
     // attention do not also carry the score.  A scoring wave takes the passes (RPP consecutive rows
     // each) sidx, sidx + nscore, ... of every tile its workgroup owns.
-    const int nactive = !HELP ? NW : alt ? 2 : min(NW, (Mtot - mt * TM + 32 * NQ - 1) / (32 * NQ));
+    const int nactive = !HELP ? NW : min(NW, (Mtot - mt * TM + 32 * NQ - 1) / (32 * NQ));
     const int nscore = nactive < NW ? NW - nactive : NW;
     const int sidx = nactive < NW ? wave - nactive : wave;   // negative: this wave does not score
     auto score_tile_shared = [&](int t) {
@@ -812,7 +801,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
             if ((lane & 15) == 0) red[wave][lane >> 4] = sq;
         }
         KD_TL(6);   // anchor formed
-        if (active && !(alt && wave == 1)) {   // (ALT: tile t0 is wave 0's; wave 1 starts with t0 + 1 inside the loop)
+        if (active) {
             qk_tile(smem + (size_t)(t0 % STAGES) * 2 * TILE_B, s);
             if (t0 >= tint) mask_tile(s, t0 * TILE_KEYS);
             float mloc[NQ];
@@ -891,65 +880,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
             if (scoring && t % p.mtiles == mt) score_tile(t);
             return;
         }
-        if constexpr (ALT) {
-            // this wave's half of the step: the tile after this one is mine -> its logits; this tile is
-            // mine -> its weights and the product with V
-            auto fetch_ahead = [&]() {
-                if (NEXT) {
-#pragma unroll
-                    for (int c = 0; c < LPW; ++c) {
-                        if (COPY == 1) issue_copy_cached(t + STAGES - 1, c);
-                        if (COPY == 2 && t + STAGES - 1 < t1) issue_copy(t + STAGES - 1, c);
-                    }
-                }
-            };
-            const bool mine = ((t - t0) & 1) == wave;   // wave uniform
-            if (mine) {
-                // per 16-key chunk: its V^T fragments are requested, its weights formed (the MFMAs of
-                // the chunk before run meanwhile), then its MFMAs issued
-                constexpr int SPK = NS / 4;   // slices per chunk (NQ == 1)
-                static_assert(NQ == 1, "the alternating mode is written for one query block per wave");
-                bf16x8 vfr[2][NDB];
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) vfr[0][db] = read_v(tV, db);
-#pragma unroll
-                for (int kc = 0; kc < 4; ++kc) {
-                    if (kc + 1 < 4) {
-#pragma unroll
-                        for (int db = 0; db < NDB; ++db) vfr[(kc + 1) & 1][db] = read_v(tV, (kc + 1) * NDB + db);
-                    }
-                    // the chunk's slices step by step, not slice by slice: the SPK instructions of a step
-                    // are independent of each other, so none waits for the one before it (this wave is
-                    // alone on its SIMD for the length of the chain)
-                    float fa[SPK][SL], fe[SPK][SL];
-#pragma unroll
-                    for (int i = 0; i < SPK; ++i) slice_F(s, kc * SPK + i, fa[i]);
-#pragma unroll
-                    for (int i = 0; i < SPK; ++i) slice_E(fa[i], fe[i]);
-#pragma unroll
-                    for (int i = 0; i < SPK; ++i) slice_C(fe[i], kc * SPK + i, pk);
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db)
-                        oacc[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[kc & 1][db], pk[0][kc], oacc[0][db], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            } else if (NEXT) {
-                qk_tile(tK, s);
-                if (MASKED) mask_tile(s, (t + 1) * TILE_KEYS);
-                float mloc[NQ];
-                tile_max(s, mloc);
-                new_reference(mloc);
-            }
-            // the wave's share of the copies of tile t + 3 goes out after its half of the step, not before it: a
-            // copy can sit in front of a full memory queue for a third of the time the half takes, and the
-            // step ends when the slower of the two waves is done (the tile is not needed for two more steps)
-            fetch_ahead();
-#ifdef KD_TIMELINE
-            if (t == t0 + 2) KD_TL(17);   // wave 0: weights and product with V of its tile done
-            if (t == t0 + 3) KD_TL(21);   // wave 0: logits of its next tile done
-#endif
-            return;
-        } else {
         if (NEXT) {
 #pragma unroll
             for (int i = 0; i < KAHEAD; ++i) kf[i] = read_k(tK, i);
@@ -1029,7 +959,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (NEXT) {
             new_reference(mloc);
         }
-        }   // !ALT
     };
     // Four loops, so that the common iterations carry no decisions: (1) tile t + 1 unmasked and tile
     // t + 3 entirely cached; (2) tile t + 1 unmasked, nothing left to fetch; (3) the general case
@@ -1042,7 +971,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     f32x16 s2[NQ][2];
     auto step1 = [&](int t, auto next_tag, auto masked_tag, auto copy_tag) {
         step(t, s, s2, next_tag, masked_tag, copy_tag);
-        if (!ALT && decltype(next_tag)::value) {   // (alternating waves keep their logits in s throughout)
+        if (decltype(next_tag)::value) {
 #pragma unroll
             for (int a = 0; a < NQ; ++a) {
                 s[a][0] = s2[a][0];
@@ -1093,9 +1022,8 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
             const float lsum = lrun[a][0] + lrun[a][1];
             const float ltot = sum_halves(lsum);
             const float inv = ltot > 0.f ? 1.f / ltot : 0.f;   // a row of a split may see no key at all
-            const int blk = (mt * TM + wave_q * (32 * NQ)) / 32 + a;
-            const int spo = alt ? 2 * sp + wave : sp;   // ALT: the two waves' results are two partials
-            _Float16 *base = p.part_o + ((((size_t)spo * BH + bh) * nblk + blk) * SLABS * 64 + lane) * 4;
+            const int blk = (mt * TM + wave * (32 * NQ)) / 32 + a;
+            _Float16 *base = p.part_o + ((((size_t)sp * BH + bh) * nblk + blk) * SLABS * 64 + lane) * 4;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -1106,7 +1034,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                     __hip_atomic_store(reinterpret_cast<uint64_t *>(base + (size_t)(4 * db + jj) * 64 * 4),
                                        __builtin_bit_cast(uint64_t, o), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-            if (h == 0 && valid[a]) p.part_ml[(size_t)spo * BH * Mtot + (size_t)bh * Mtot + mrow[a]] = make_float2(mref[a], ltot);
+            if (h == 0 && valid[a]) p.part_ml[(size_t)sp * BH * Mtot + (size_t)bh * Mtot + mrow[a]] = make_float2(mref[a], ltot);
         }
     } else if (active) {
         // A single split writes the bf16 output itself.  Accumulator element e of d-block db is
@@ -1141,7 +1069,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                 }
         }
         // rows of this wave: m = mbase .. mbase + WROWS - 1, contiguous in `out`
-        const int mbase = mt * TM + wave_q * WROWS;
+        const int mbase = mt * TM + wave * WROWS;
         unsigned char *gbase = reinterpret_cast<unsigned char *>(p.out + ((size_t)(b * p.hq + kvh * p.G) * p.Bt + mbase) * D);
         constexpr int RPI = 1024 / ROWB;   // rows one wave-wide 16-byte-per-lane store covers
 #pragma unroll
@@ -1208,15 +1136,14 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 #endif
 }
 
-template <int D, bool HELP, bool ALT>
+template <int D, bool HELP>
 __global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_kernel(StepParams p)
 {
     warm_arguments<sizeof(StepParams)>();
-    step_main_body<D, HELP, ALT>(p, (int)blockIdx.x);
+    step_main_body<D, HELP>(p, (int)blockIdx.x);
 }
 
-// step_main with passengers (8-wave workgroups, with or without helper waves, not the alternating
-// mode): the first `ncarry` workgroups run the pending selection and
+// step_main with passengers (with or without helper waves): the first `ncarry` workgroups run the pending selection and
 // compaction of another cache (one head each, parameters `cy`), the rest are the workgroups of
 // step_main proper.  A selection is a chain of short dependent stages that keeps one compute unit
 // busy per head for about half as long as the attention keeps the others busy: launched this way
@@ -1236,7 +1163,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepPara
         else select_and_compact<D, false, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
-    step_main_body<D, HELP, false>(p, (int)blockIdx.x - ncarry);
+    step_main_body<D, HELP>(p, (int)blockIdx.x - ncarry);
 }
 
 // The same with a third kind of workgroup behind the selection's: `ride.nshift` workgroups that shift
@@ -1268,7 +1195,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
         shift_range<D, CARRY_THREADS>(ride.p, ride.flags, ride.nchunks, ride.epoch, i % heads, i / heads, ride.parts);
         return;
     }
-    step_main_body<D, false, false>(p, (int)blockIdx.x - ncarry - nshift);
+    step_main_body<D, false>(p, (int)blockIdx.x - ncarry - nshift);
 }
 
 static size_t main_lds_bytes(int D) { return (size_t)STAGES * 2 * TILE_KEYS * D * 2; }
@@ -1287,12 +1214,10 @@ hipError_t configure_main_kernels()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
                             (int)main_lds_bytes(D));                                               \
     if (e != hipSuccess) return e;
-    KD_SET((step_main_kernel<128, false, false>), 128)
-    KD_SET((step_main_kernel<128, true, false>), 128)
-    KD_SET((step_main_kernel<128, true, true>), 128)
-    KD_SET((step_main_kernel<64, false, false>), 64)
-    KD_SET((step_main_kernel<64, true, false>), 64)
-    KD_SET((step_main_kernel<64, true, true>), 64)
+    KD_SET((step_main_kernel<128, false>), 128)
+    KD_SET((step_main_kernel<128, true>), 128)
+    KD_SET((step_main_kernel<64, false>), 64)
+    KD_SET((step_main_kernel<64, true>), 64)
 #undef KD_SET
 #define KD_SET(fn)                                                                                  \
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -1316,14 +1241,11 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
     const int grid = p.batch * p.hkv * p.mtiles * p.splits;
     const size_t lds = main_lds_bytes(p.D);
     const bool help = main_runs_help(p);
-    const bool alt = p.psplits != p.splits;   // two waves share the key tiles: planned only for 8-wave helper launches
-    if (alt && !(help && p.NW == 8 && p.psplits == 2 * p.splits)) return hipErrorInvalidValue;
+    if (p.few) return hipErrorInvalidValue;
 #define KD_GO(DD)                                                                                          \
-    if (help) hipLaunchKernelGGL((step_main_kernel<DD, true, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);  \
-    else hipLaunchKernelGGL((step_main_kernel<DD, false, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);
-    if (alt && p.D == 128) hipLaunchKernelGGL((step_main_kernel<128, true, true>), dim3(grid), dim3(512), lds, s, p);
-    else if (alt && p.D == 64) hipLaunchKernelGGL((step_main_kernel<64, true, true>), dim3(grid), dim3(512), lds, s, p);
-    else if (p.D == 128 && p.NW == MAIN_WAVES) { KD_GO(128) }
+    if (help) hipLaunchKernelGGL((step_main_kernel<DD, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);  \
+    else hipLaunchKernelGGL((step_main_kernel<DD, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);
+    if (p.D == 128 && p.NW == MAIN_WAVES) { KD_GO(128) }
     else if (p.D == 64 && p.NW == MAIN_WAVES) { KD_GO(64) }
 #undef KD_GO
     else return hipErrorInvalidValue;
@@ -1333,7 +1255,7 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
 bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
-    return p.NW == 8 && p.psplits == p.splits && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
+    return p.NW == 8 && !p.few && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
            carry_need(cy, false) <= CARRY_DYN_MAX && ncarry > 0;
 }
 
@@ -1363,7 +1285,7 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
 bool can_host_shift(const StepParams &p, const StepParams &shifted)
 {
     const int E = shifted.n - shifted.N;
-    return p.NW == 8 && p.psplits == p.splits && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
+    return p.NW == 8 && !p.few && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
 }
 
 hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, const ShiftRide &ride, hipStream_t s)

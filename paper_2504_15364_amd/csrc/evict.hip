@@ -202,6 +202,83 @@ __device__ __forceinline__ void merge_rows(const StepParams &p, size_t gid)
     *reinterpret_cast<bf16x4 *>(p.out + ((size_t)(b * p.hq + kvh * p.G + g) * p.Bt + j) * D + d0) = o;
 }
 
+// The merge of step_few's partials (float, [psplits][BH][G * Bt][D], each normalised by its row sum): one
+// workgroup per head, a thread per four output values and share of the splits.  What bounds it is the
+// trip to memory: the splits are dealt over the threads that are left (with 4 rows of 128 eight ways), so
+// that 32 splits are one round of loads, not 32 loads in a row, and the shares are added up through LDS.
+template <int D>
+__device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int bh)
+{
+    constexpr int MB = 8;                       // splits requested together
+    const int BH = p.batch * p.hkv, Mtot = p.G * p.Bt;
+    const int items = Mtot * (D / 4);           // at most POST_THREADS (32 rows of 128)
+    const int shares = min(POST_THREADS / items, p.psplits);
+    const int it = (int)threadIdx.x % items, share = (int)threadIdx.x / items;
+    const float *part = reinterpret_cast<const float *>(p.part_o) + (size_t)bh * Mtot * D + (size_t)it * 4;
+    const float2 *mls = p.part_ml + (size_t)bh * Mtot + it / (D / 4);
+    const size_t pstride = (size_t)BH * Mtot * D, mstride = (size_t)BH * Mtot;
+    float mx = -INFINITY, Lsum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (share < shares) {
+        for (int s0 = share; s0 < p.psplits; s0 += MB * shares) {
+            float2 ml[MB];
+            f32x4 o[MB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const int s_ = s0 + i * shares;
+                const bool live = s_ < p.psplits;
+                ml[i] = live ? mls[(size_t)s_ * mstride] : make_float2(-INFINITY, 0.f);
+                o[i] = live ? *reinterpret_cast<const f32x4 *>(part + (size_t)s_ * pstride) : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            float bm = mx;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) bm = fmaxf(bm, ml[i].x);
+            const float down = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - bm);
+            mx = bm;
+            Lsum *= down;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] *= down;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const float w = ml[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - mx) * ml[i].y;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r] += w * o[i][r];
+                Lsum += w;
+            }
+        }
+    }
+    if (shares > 1) {   // uniform
+        float *mine = lds + (size_t)threadIdx.x * 6;
+        mine[0] = mx;
+        mine[1] = Lsum;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[2 + r] = acc[r];
+        __syncthreads();
+        if (share > 0) return;
+        float bm = mx;
+        for (int s_ = 1; s_ < shares; ++s_) bm = fmaxf(bm, lds[(size_t)(it + s_ * items) * 6]);
+        const float down = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - bm);
+        Lsum *= down;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] *= down;
+        for (int s_ = 1; s_ < shares; ++s_) {
+            const float *o = lds + (size_t)(it + s_ * items) * 6;
+            const float w = o[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(o[0] - bm);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] += w * o[2 + r];
+            Lsum += w * o[1];
+        }
+    } else if (share > 0) {
+        return;
+    }
+    const float inv = 1.f / Lsum;
+    const int b = bh / p.hkv, kvh = bh % p.hkv;
+    bf16x4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = (__bf16)(acc[r] * inv);
+    *reinterpret_cast<bf16x4 *>(p.out + (size_t)(b * p.hq + kvh * p.G) * p.Bt * D + (size_t)it * 4) = o;
+}
+
 // The merge as a kernel of its own (a step whose eviction is deferred has nothing else to run
 // here): small workgroups, so that the rows spread over every compute unit.
 // Workgroup i takes head i % BH, like the workgroups of step_main: on a chip whose workgroups go
@@ -245,7 +322,9 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
         __syncthreads();
         if (threadIdx.x == 0) tl[0] = wall_clock64();
 #endif
-        merge_rows<D>(p, (size_t)(blockIdx.x - n_select) * POST_THREADS + threadIdx.x);
+        static_assert(sizeof(PostShared) >= POST_THREADS * 6 * sizeof(float), "the merge of step_few's partials uses the selection's tables");
+        if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), (int)blockIdx.x - n_select);
+        else merge_rows<D>(p, (size_t)(blockIdx.x - n_select) * POST_THREADS + threadIdx.x);
 #ifdef KD_TIMELINE
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
@@ -503,10 +582,13 @@ static bool post_resident(const StepParams &p)
 
 
 hipError_t configure_main_kernels();
+hipError_t configure_few_kernels();
 
 hipError_t configure_kernels()
 {
     hipError_t e = configure_main_kernels();
+    if (e != hipSuccess) return e;
+    e = configure_few_kernels();
     if (e != hipSuccess) return e;
     static_assert(MAX_CAP / 8 + LISTS_LDS_MAX + 16 <= POST_DYN_MAX, "the non-resident selection always fits");
     const void *post_fns[] = {reinterpret_cast<const void *>(step_post_kernel<128, true>),
@@ -533,6 +615,12 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
 {
     const int grid = (p.do_evict ? p.batch * p.hkv : 0) + p.merge_wgs;
     if (grid == 0) return hipSuccess;
+    if (!p.do_evict && p.few) {
+        if (p.D == 128) hipLaunchKernelGGL((step_post_kernel<128, false>), dim3(grid), dim3(POST_THREADS), 0, s, p);
+        else if (p.D == 64) hipLaunchKernelGGL((step_post_kernel<64, false>), dim3(grid), dim3(POST_THREADS), 0, s, p);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     if (!p.do_evict) {   // merge only
         const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (p.D / 8) * 64;
         const int mgrid = p.batch * p.hkv * (int)((per_head + MERGE_THREADS - 1) / MERGE_THREADS);
@@ -570,7 +658,7 @@ hipError_t launch_merge_shift(const StepParams &pm, const StepParams &ps, int32_
     const size_t merge_threads = (size_t)pm.batch * pm.hkv * ((pm.G * pm.Bt + 31) / 32) * (pm.D / 8) * 64;
     const int mw = (int)((merge_threads + ORD_THREADS - 1) / ORD_THREADS);
     const int grid = mw + ps.batch * ps.hkv * nchunks;
-    if (ps.n - ps.N > ORD_THREADS * ORD_ROWS || pm.D != ps.D || pm.psplits < 2) return hipErrorInvalidValue;
+    if (ps.n - ps.N > ORD_THREADS * ORD_ROWS || pm.D != ps.D || pm.psplits < 2 || pm.few) return hipErrorInvalidValue;
     if (pm.D == 128) hipLaunchKernelGGL((merge_shift_kernel<128>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, ps, flags, nchunks, epoch, mw);
     else if (pm.D == 64) hipLaunchKernelGGL((merge_shift_kernel<64>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, ps, flags, nchunks, epoch, mw);
     else return hipErrorInvalidValue;

@@ -17,6 +17,8 @@
 namespace kd {
 
 constexpr int TILE_KEYS = 64;       // keys per attention K/V tile
+constexpr int FEW_KEYS = 32;        // keys per wave and tile in step_few
+constexpr int FEW_ROWS = 32;        // query rows per KV head up to which a step runs step_few instead of step_main
 constexpr int POST_THREADS = 1024;  // workgroup size of step_post
 constexpr int SCORE_THREADS = 256;  // workgroup size of step_score
 constexpr int SCORE_ROWS = 128;     // rows per step_score workgroup: 32 per wave
@@ -57,8 +59,9 @@ struct StepParams {
     // sizes
     int batch, hq, hkv, G, D, Bt, len, n, N, B, cap;
     int splits, mtiles, ntiles, NW;      // NW: waves (of 32 query rows) per step_main workgroup
-    int psplits;                     // partials per output row the merge adds up: splits, or 2 * splits when two
-                                     // waves of a workgroup take alternate tiles of its key range (decode)
+    int psplits;                     // partials per output row the merge adds up (1: none, the attention writes `out`)
+    int few;                         // the step runs step_few (at most FEW_ROWS query rows per KV head): its partials are
+                                     // float [psplits][BH][G * Bt][D] in part_o
     int edge_cost;                   // weight (in plain tiles: 1 or 2) of a tile holding rows of the block when
                                      // the key tiles are divided over the splits
     int score_chunks;                // step_score workgroups per head
@@ -76,6 +79,8 @@ struct StepParams {
 
 hipError_t configure_kernels();      // one-time function attributes (dynamic LDS sizes)
 hipError_t launch_step_main(const StepParams &p, hipStream_t s);
+// the same step where a KV head has at most FEW_ROWS query rows (p.few set by the plan)
+hipError_t launch_step_few(const StepParams &p, hipStream_t s);
 // step_main of `p` whose first workgroups run the selection and compaction `cy` describes (the
 // parameters of an earlier step of another cache; for the ORDERED layout the caller still launches
 // the row shift afterwards); can_carry says whether the pair fits

@@ -320,13 +320,12 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
         uint64_t gbest = 0;
         bool known = false;
         if (use_rec) {
-            if (tid == 0) {
+            if (wave == 0) {
+                // the lanes share the records (a workgroup of the attention left each), then fold
                 const uint64_t *recs = reinterpret_cast<const uint64_t *>(sh.hist);
                 uint64_t b0 = 0;
                 bool tie = false;
-                for (int s_ = 0; s_ < p.splits; ++s_) {
-                    const uint64_t ob = recs[2 * s_];
-                    const bool ot = recs[2 * s_ + 1] != 0;
+                auto fold = [&](uint64_t ob, bool ot) {   // (no record is folded in twice)
                     const uint32_t hb = (uint32_t)(b0 >> 32), ho = (uint32_t)(ob >> 32);
                     if (ho > hb) {
                         b0 = ob;
@@ -335,10 +334,19 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
                         tie = true;
                         b0 = ob > b0 ? ob : b0;
                     }
+                };
+                for (int s_ = lane; s_ < p.splits; s_ += 64) fold(recs[2 * s_], recs[2 * s_ + 1] != 0);
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t lo = __shfl_xor((uint32_t)b0, off), hi = __shfl_xor((uint32_t)(b0 >> 32), off);
+                    const bool ot = __shfl_xor((int)tie, off) != 0;
+                    fold(((uint64_t)hi << 32) | lo, ot);
                 }
+                if (lane == 0) {
                 sh.sel_cnt = (b0 != 0 && !tie) ? 1u : 0u;
                 sh.tb = (int)(uint32_t)b0;
                 if (b0 != 0 && !tie) evbits[(uint32_t)b0 >> 5] |= 1u << ((uint32_t)b0 & 31);
+                }
             }
             __syncthreads();
             known = sh.sel_cnt != 0;   // uniform

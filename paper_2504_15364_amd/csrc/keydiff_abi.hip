@@ -125,7 +125,7 @@ Layout make_layout(const keydiff_config_t *c)
     const int max_mtiles = (G * c->block_B + 127) / 128;
     const size_t by_tiles = (kTargetWorkgroups + BH * max_mtiles + BH) * 256;
     const size_t Mpad_max = (size_t)((G * c->block_B + 31) / 32 * 32);                               // blocks of 32 rows
-    const size_t by_rows = (kTargetWorkgroups + 2 * BH) * Mpad_max * (G * c->block_B <= 32 ? 2 : 1);  // two partials per workgroup
+    const size_t by_rows = (kTargetWorkgroups + 2 * BH) * Mpad_max * (G * c->block_B <= kd::FEW_ROWS ? 2 : 1);  // (step_few: float partials)
     L.max_part_rows = (int)(by_tiles < by_rows ? by_tiles : by_rows);
     const size_t chunks = (L.cap + kd::CHUNK_ROWS - 1) / kd::CHUNK_ROWS;
     off = 0;
@@ -283,14 +283,27 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     const int Mtot = p.G * p.Bt;
     // Workgroups of eight waves x 32 query rows, one per compute unit.  Where the rows of a head do
     // not fill the last workgroup its idle waves help (copy tiles, score rows); measured against
-    // 4-wave workgroups at 64 and 128 rows per head: 29.6 vs 44.3 and 31.4 vs 47.2 us per step.  With at
-    // most one wave's worth of rows (decode) two waves share the key tiles of the range between them.
-    const bool alt = Mtot <= 32;
+    // 4-wave workgroups at 64 and 128 rows per head: 29.6 vs 44.3 and 31.4 vs 47.2 us per step.
     p.NW = 8;
     const int TM = 32 * p.NW;
     p.mtiles = (Mtot + TM - 1) / TM;
     p.ntiles = (p.n + kd::TILE_KEYS - 1) / kd::TILE_KEYS;
     const int target = c->L.target_wgs / 2;   // the compute units of the chip
+    p.few = Mtot <= kd::FEW_ROWS;
+    if (p.few) {
+        // Few query rows (the generation phase): every wave of a workgroup takes 32-key tiles of its own, so
+        // a range needs eight tiles to keep its waves busy; never more workgroups than compute units.
+        const int nt = (p.n + kd::FEW_KEYS - 1) / kd::FEW_KEYS;
+        p.mtiles = (Mtot + 15) / 16;
+        int splits = target / (BH * p.mtiles);
+        if (splits > (nt + 7) / 8) splits = (nt + 7) / 8;
+        if (splits < 1) splits = 1;
+        // the float partials take two of the scratch buffer's fp16 rows each
+        while (splits > 1 && 2l * splits * BH * Mtot > c->L.max_part_rows) --splits;
+        p.splits = p.psplits = splits;
+        p.merge_wgs = splits > 1 ? BH : 0;
+        return;
+    }
     // 8-wave workgroups run one per compute unit: rounding the split count up would push the last
     // workgroups into a second pass over the chip that doubles the kernel's duration
     int splits = target / (BH * p.mtiles);
@@ -302,10 +315,8 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     if (splits < 1) splits = 1;
     // partial rows must fit the scratch sized at init
     const int Mpad = (Mtot + 31) / 32 * 32;   // partials are stored in blocks of 32 rows
-    const int per = alt ? 2 : 1;              // partials a workgroup leaves per row
-    while (splits > 1 && (long)per * splits * BH * Mpad > c->L.max_part_rows) --splits;
-    p.splits = splits;
-    p.psplits = per * splits;
+    while (splits > 1 && (long)splits * BH * Mpad > c->L.max_part_rows) --splits;
+    p.splits = p.psplits = splits;
     // a tile with rows of the block counts as two plain ones when the tiles are dealt out (it takes
     // about 1.4 times as long, and an equal share would make its split the last to end); every split
     // must still span at least one tile, which a span of 2 * edge_cost cost units guarantees
@@ -449,7 +460,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     // Generation phase: the attention launch's scoring waves (the kernels with helper waves) leave the
     // arg-max of the scores per workgroup, and the selection reads the row to evict off those records.
     if (evict && n - N == 1 && cf.window_W == 0 && cf.layout == KEYDIFF_LAYOUT_FILL &&
-        p.mtiles * 32 * p.NW - p.G * p.Bt >= 32 && (size_t)p.batch * p.hkv * p.splits <= (size_t)c->L.target_wgs + p.batch * p.hkv)
+        (p.few || p.mtiles * 32 * p.NW - p.G * p.Bt >= 32) && (size_t)p.batch * p.hkv * p.splits <= (size_t)c->L.target_wgs + p.batch * p.hkv)
         p.argmax_rec = reinterpret_cast<unsigned long long *>(work + c->L.off_argmax);
 
     // ---- launches from here on
@@ -488,6 +499,8 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
         } else if (riding) {
             KD_LAUNCH(kd::launch_step_main_carry(p, carry->pend, s), "step_main kernel (with carried selection)");
             carry->pending = false;
+        } else if (p.few) {
+            KD_LAUNCH(kd::launch_step_few(p, s), "step_few kernel");
         } else {
             KD_LAUNCH(kd::launch_step_main(p, s), "step_main kernel");
         }

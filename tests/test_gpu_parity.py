@@ -799,3 +799,37 @@ def test_argument_errors_enqueue_nothing():
     lib = kd.load_library()
     assert lib.keydiff_prefill_block(cache._h, None, None, None, 1, 0, None, None, None) == kd.binding.EINVAL
     assert cache.len == 0 and cache.status() == 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,N,sizes", [
+    (8, 2, 128, 2077, (1, 4, 5, 8, 3)),        # 4, 16, 20, 32 and 12 query rows a head: one and two row tiles, several key tiles a wave
+    (14, 2, 128, 290, (1, 2, 3, 4, 5)),        # 7, 14, 21, 28 rows, then 35: the last step runs the other kernel
+    (32, 2, 64, 515, (1, 2, 1)),               # 16 and 32 rows
+    (3, 3, 64, 1031, (32, 17, 16, 31, 1)),     # blocks of many rows, masked inside
+    (5, 1, 128, 31, (1, 2, 3, 6)),             # fewer keys than a tile
+], ids=["g4", "g7", "g16", "g1", "short"])
+@pytest.mark.parametrize("anchor", [kd.ANCHOR_MEAN_KEY, kd.ANCHOR_MEAN_UNIT_KEY], ids=["mean", "unit"])
+def test_steps_with_few_query_rows(hq, hkv, d, N, sizes, anchor):
+    # at most 32 query rows per KV head take a kernel of their own: edges of its row tiles, of its 32-key tiles and of
+    # the ranges its waves and workgroups split, after a prompt in large blocks; scores are asked for in every other step
+    B, steps = 96, 3 * len(sizes)
+    T = N + steps * max(sizes) + B
+    w = get_config("llama32_3b").small(n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prompt_T=T)
+    data = make_layer(w, seed=1000 + N)
+    cache, oc = make_pair(w, N, B, layout=kd.LAYOUT_FILL, anchor_mode=anchor)
+    t, plan = 0, [min(B, N - s) for s in range(0, N, B)] + [sizes[i % len(sizes)] for i in range(steps)]
+    for i, Bt in enumerate(plan):
+        q, k, v = (block_of(data[x], t, Bt)[None] for x in ("q", "k", "v"))
+        n = cache.len + Bt
+        sc = torch.empty((1, hkv, n), dtype=torch.float32, device="cuda") if i % 2 else None
+        rows = torch.cat([cache.positions().cpu(), torch.arange(t, t + Bt, dtype=torch.int32).expand(1, hkv, Bt)], -1)
+        out = cache.prefill_block(to_dev(q), to_dev(k), to_dev(v), t, scores_out=sc)
+        ref, osc, ev = oc.prefill_block(q, k, v, t, want_scores=True)
+        assert np.abs(bf16_out_to_f32(out) - ref).max() <= ATTN_ATOL, (i, Bt)
+        if sc is not None and ev > 0:
+            got = np.take_along_axis(sc.cpu().numpy(), np.argsort(rows.numpy(), axis=-1, kind="stable"), axis=-1)
+            assert np.allclose(got, osc, rtol=SCORE_RTOL, atol=SCORE_ATOL), (i, Bt)
+        check_state(cache, oc, f"step {i} of {Bt} tokens")
+        t += Bt
+    assert cache.status() == 0
+    cache.close()
