@@ -1159,8 +1159,8 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepPara
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         PostShared &sh = *reinterpret_cast<PostShared *>(smem);
         unsigned char *dyn = smem + carry_shared_bytes();
-        if (cy_res) select_and_compact<D, true, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
-        else select_and_compact<D, false, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
+        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
+        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
     step_main_body<D, HELP>(p, (int)blockIdx.x - ncarry);
@@ -1186,8 +1186,8 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         PostShared &sh = *reinterpret_cast<PostShared *>(smem);
         unsigned char *dyn = smem + carry_shared_bytes();
-        if (cy_res) select_and_compact<D, true, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
-        else select_and_compact<D, false, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
+        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
+        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
     if ((int)blockIdx.x < ncarry + nshift) {

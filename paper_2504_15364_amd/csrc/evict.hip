@@ -306,9 +306,9 @@ __global__ __launch_bounds__(SCORE_THREADS) void step_score_kernel(StepParams p)
 }
 
 // step_post: workgroups [0, BH) select and compact one head each (when this step evicts); the
-// rest merge the attention partials.  RES: the selection works on LDS copies of the head's scores
-// and positions (they fit next to its other tables).
-template <int D, bool RES>
+// rest merge the attention partials.  SRC: 16-byte loads of scores (and of positions) a thread of the
+// selection holds in registers; 0: it reads them from memory where it needs them at all.
+template <int D, int SRC>
 __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
 {
     warm_arguments<sizeof(StepParams)>();
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
 #endif
         return;
     }
-    select_and_compact<D, RES, POST_THREADS>(p, sh, smem_raw, (int)blockIdx.x);
+    select_and_compact<D, SRC, POST_THREADS>(p, sh, smem_raw, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------- ordered compaction
@@ -570,16 +570,10 @@ __global__ void load_pos_kernel(const int32_t *src, int32_t *dst, int cap, int l
 // ---------------------------------------------------------------------- launchers
 constexpr size_t LISTS_LDS_MAX = 48 * 1024;
 
-bool lists_fit_lds(int n, int N) { return n > N && (size_t)(n - N) * 16 <= LISTS_LDS_MAX; }
+bool lists_fit_lds(int n, int N) { return n > N && (size_t)(n - N) * 8 <= LISTS_LDS_MAX; }
 
 // dynamic LDS a step_post launch may ask for next to its static tables (160 KB per compute unit)
-constexpr size_t POST_DYN_MAX = 160 * 1024 - sizeof(PostShared) - 1024;
-
-static bool post_resident(const StepParams &p)
-{
-    return select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, true) <= POST_DYN_MAX;
-}
-
+constexpr size_t POST_DYN_MAX = 64 * 1024;
 
 hipError_t configure_main_kernels();
 hipError_t configure_few_kernels();
@@ -591,10 +585,12 @@ hipError_t configure_kernels()
     e = configure_few_kernels();
     if (e != hipSuccess) return e;
     static_assert(MAX_CAP / 8 + LISTS_LDS_MAX + 16 <= POST_DYN_MAX, "the non-resident selection always fits");
-    const void *post_fns[] = {reinterpret_cast<const void *>(step_post_kernel<128, true>),
-                              reinterpret_cast<const void *>(step_post_kernel<128, false>),
-                              reinterpret_cast<const void *>(step_post_kernel<64, true>),
-                              reinterpret_cast<const void *>(step_post_kernel<64, false>)};
+    const void *post_fns[] = {reinterpret_cast<const void *>(step_post_kernel<128, 3>),
+                              reinterpret_cast<const void *>(step_post_kernel<128, 0>),
+                              reinterpret_cast<const void *>(step_post_kernel<64, 3>),
+                              reinterpret_cast<const void *>(step_post_kernel<64, 0>),
+                              reinterpret_cast<const void *>(step_post_kernel<128, 5>),
+                              reinterpret_cast<const void *>(step_post_kernel<64, 5>)};
     for (const void *fn : post_fns) {
         e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)POST_DYN_MAX);
         if (e != hipSuccess) return e;
@@ -616,8 +612,8 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
     const int grid = (p.do_evict ? p.batch * p.hkv : 0) + p.merge_wgs;
     if (grid == 0) return hipSuccess;
     if (!p.do_evict && p.few) {
-        if (p.D == 128) hipLaunchKernelGGL((step_post_kernel<128, false>), dim3(grid), dim3(POST_THREADS), 0, s, p);
-        else if (p.D == 64) hipLaunchKernelGGL((step_post_kernel<64, false>), dim3(grid), dim3(POST_THREADS), 0, s, p);
+        if (p.D == 128) hipLaunchKernelGGL((step_post_kernel<128, 0>), dim3(grid), dim3(POST_THREADS), 0, s, p);
+        else if (p.D == 64) hipLaunchKernelGGL((step_post_kernel<64, 0>), dim3(grid), dim3(POST_THREADS), 0, s, p);
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
@@ -630,12 +626,18 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
         return hipGetLastError();
     }
     if (p.n > 32 * POST_THREADS) return hipErrorInvalidValue;   // a thread owns one word of the eviction bitmap
-    const bool res = post_resident(p) && !p.argmax_rec;   // (the arg-max records make the copies of the scores unnecessary)
-    const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, res);
-    if (p.D == 128 && res) hipLaunchKernelGGL((step_post_kernel<128, true>), dim3(grid), dim3(POST_THREADS), lds, s, p);
-    else if (p.D == 128) hipLaunchKernelGGL((step_post_kernel<128, false>), dim3(grid), dim3(POST_THREADS), lds, s, p);
-    else if (p.D == 64 && res) hipLaunchKernelGGL((step_post_kernel<64, true>), dim3(grid), dim3(POST_THREADS), lds, s, p);
-    else if (p.D == 64) hipLaunchKernelGGL((step_post_kernel<64, false>), dim3(grid), dim3(POST_THREADS), lds, s, p);
+    // Three 16-byte loads of scores (and of positions) a thread up to 12288 rows, five up to 20480; the registers hold no
+    // more beside the rows that may move, so larger caches are read from memory in every pass.  With the arg-max
+    // records of the attention launch the scores are hardly ever looked at.
+    const int src = p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
+    const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
+#define KD_GO(DD)                                                                                                      \
+    if (src == 0) hipLaunchKernelGGL((step_post_kernel<DD, 0>), dim3(grid), dim3(POST_THREADS), lds, s, p);             \
+    else if (src == 3) hipLaunchKernelGGL((step_post_kernel<DD, 3>), dim3(grid), dim3(POST_THREADS), lds, s, p);        \
+    else hipLaunchKernelGGL((step_post_kernel<DD, 5>), dim3(grid), dim3(POST_THREADS), lds, s, p);
+    if (p.D == 128) { KD_GO(128) }
+    else if (p.D == 64) { KD_GO(64) }
+#undef KD_GO
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -2,16 +2,21 @@
 // the kernels that can run it: step_post (one workgroup of 1024 threads per head) and the variant of
 // step_main that carries another cache's pending eviction (workgroups of 512 threads).
 //
-// One workgroup copies the head's scores and positions into LDS once (asynchronously, no registers),
-// bins the scores into a 4096-bin LDS histogram (a monotone map of the float), scans it for the bin
+// One workgroup takes the head's scores and positions once -- into registers (step_post) or into LDS
+// (asynchronously, the passenger) -- bins the scores into a 4096-bin LDS histogram (a monotone map of the float), scans it for the bin
 // that holds the E-th largest score, evicts everything above that bin and ranks the few rows inside
 // it exactly by (score bits, position): equal scores keep the lower position.  It then compacts the
 // cache and takes the evicted keys out of ksum.
 //
-// The passes over the rows are short rolled loops over the LDS copy.  As a passenger the selection
+// The passenger's passes over the rows are short rolled loops over the LDS copy.  As a passenger the selection
 // runs on one compute unit per head, whose instruction cache nothing has warmed, while the
 // attention saturates the memory system: with the rows in registers and every pass unrolled
-// (25 KB of straight-line code) it spent most of its time waiting for its own instructions.
+// (25 KB of straight-line code) it spent most of its time waiting for its own instructions.  In step_post,
+// where sixteen waves share the fetch and the caller waits for the end, the registers are the shorter way, and
+// the evicted keys are requested as soon as their list is known, ahead of the scan that ranks holes and movers
+// (measured, 8 heads, 4096 rows, 128 evicted: 12.9 -> 10.6 us a launch; 16896 rows, 512 evicted, where the
+// scores were read from memory in every pass before: 34 -> 24 us).  Not kept: the destinations of the tail rows
+// worked out ahead of the barrier (1 us slower), the kernel's own code requested into L2 at its start (slower).
 #pragma once
 #include "kd_kernels.h"
 #include "kd_device.h"
@@ -26,7 +31,6 @@ typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CAND_MAX = 1024;  // rows of the threshold bin ranked in LDS; more fall back to a radix select
 constexpr int MAX_SELECT_WAVES = POST_THREADS / 64;   // PostShared is laid out for the largest workgroup
-constexpr int TAIL_WORDS = 72;                      // bitmap words the tail rows [N, n) may span on the fast path
 constexpr int CARRY_THREADS = 512;                  // workgroup size of the step_main variant that carries a selection
 constexpr int SELECT_TAILU = 8;                     // 16-byte units of the tail rows [N, n) a thread keeps in registers
 
@@ -46,7 +50,7 @@ __device__ __forceinline__ int score_bin(float s)
 
 struct PostShared {
     uint32_t hist[HIST_BINS];  // score histogram of the head (a monotone map of the float)
-    uint32_t wave_tot[MAX_SELECT_WAVES];
+    uint32_t wave_tot[MAX_SELECT_WAVES], wave_tot2[MAX_SELECT_WAVES];
     uint64_t wave_tot64[MAX_SELECT_WAVES];
     uint32_t radix_hist[256];
     uint32_t sel_bin, sel_rank, sel_cnt;
@@ -57,7 +61,6 @@ struct PostShared {
     uint32_t cand_key[CAND_MAX];
     int32_t cand_pos[CAND_MAX];
     double colsum[MAX_SELECT_WAVES][128];
-    uint32_t tail_word[TAIL_WORDS], tail_base[TAIL_WORDS];  // mover bitmap words of rows >= N and movers before each
 };
 
 // bytes of dynamic LDS a carried selection places PostShared in, ahead of its bitmap and lists
@@ -83,28 +86,13 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x)
     x += dpp_fetch<0x143, 0xC>(x);
     return x;
 }
-__device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t x)
-{
-#define KD_STEP64(CTRL, MASK)                                                                   \
-    x += ((uint64_t)dpp_fetch<CTRL, MASK>((uint32_t)(x >> 32)) << 32) | dpp_fetch<CTRL, MASK>((uint32_t)x);
-    KD_STEP64(0x111, 0xF)
-    KD_STEP64(0x112, 0xF)
-    KD_STEP64(0x114, 0xF)
-    KD_STEP64(0x118, 0xF)
-    KD_STEP64(0x142, 0xA)
-    KD_STEP64(0x143, 0xC)
-#undef KD_STEP64
-    return x;
-}
-
-// exclusive prefix sum over the workgroup (32-bit, or three packed 21-bit counters in 64 bits)
+// exclusive prefix sum over the workgroup; `wave_tot`: LDS words of the waves that no thread still reads
 template <int THREADS, typename T>
 __device__ __forceinline__ T block_exclusive_scan_t(T v, T *wave_tot, T *total)
 {
     constexpr int NWAVES = THREADS / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const T inc = wave_inclusive_scan(v);
-    __syncthreads();  // wave_tot free for reuse
     if (lane == 63) wave_tot[wave] = inc;
     __syncthreads();
     T base = 0, tot = 0;
@@ -200,29 +188,35 @@ __device__ void radix_select_in_bin(const StepParams &p, PostShared &sh, const f
     __syncthreads();
 }
 
+// Where the passes over the rows find scores and positions: in memory, in LDS copies, or in the registers of
+// the thread that owns the row (SRC = the number of 16-byte loads per thread: rows 4 (q THREADS + tid) .. + 3)
+constexpr int SRC_MEMORY = 0, SRC_LDS = -1;
+
 // bytes of dynamic LDS the selection of a step uses behind PostShared: the eviction bitmap, the
-// lists (when they fit) and, for the resident variant, the copies of the scores and positions
+// lists (when they fit) and, for the passenger, the copies of the scores and positions
 __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool lists_in_lds, bool resident)
 {
     size_t b = ((size_t)((n + 31) / 32) * 4 + 15) & ~(size_t)15;
-    if (lists_in_lds) b += (size_t)(n - N) * 16;
+    if (lists_in_lds) b += (size_t)(n - N) * 8;
     if (resident) b += (size_t)cap * 8;
     return b;
 }
 
 // ------------------------------------------------------------- select + compaction
-// `dyn`: dynamic LDS of select_dyn_bytes(...) bytes, 16-byte aligned.  The lists are three arrays of
-// E row indices (evicted | holes | movers) and the mover rank of every tail row: in LDS when they
-// fit, else in the scratch buffer.
-// RES: the head's scores and positions are copied into LDS once and every pass reads the copy;
-// otherwise (caches too large for that) the passes read them from memory.
-// The caller keeps n <= 32 * THREADS (a thread owns one word of the eviction bitmap).
-template <int D, bool RES, int THREADS>
-__device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh)
+// `dyn`: dynamic LDS of select_dyn_bytes(...) bytes, 16-byte aligned.  The lists are two arrays of
+// E row indices (evicted rows | evicted rows below N in ascending order): in LDS when they fit, else in the
+// scratch buffer.
+// The caller keeps n <= 32 * THREADS (a thread owns one word of the eviction bitmap) and, with SRC > 0,
+// n <= 4 * SRC * THREADS.
+// (inlined: outlined, the parameter block would be passed through scratch memory)
+template <int D, int SRC, int THREADS>
+__device__ __forceinline__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh)
 {
     constexpr int UPR = D / 8;
-    constexpr int TAILU = SELECT_TAILU;
+    constexpr int TAILU = SRC > 3 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (the registers the rows' scores leave)
     constexpr int NWAVES = THREADS / 64;
+    constexpr bool RES = SRC == SRC_LDS;
+    constexpr int NQ4 = SRC > 0 ? SRC : 1;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = p.n - p.N;
@@ -236,23 +230,39 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
     int32_t *lists = p.lists + (size_t)bh * 4 * p.B;
     if (p.lists_in_lds) {
         lists = reinterpret_cast<int32_t *>(dyn + dyn_off);
-        dyn_off += (size_t)E * 16;
+        dyn_off += (size_t)E * 8;
     }
     float *sc_l = reinterpret_cast<float *>(dyn + dyn_off);
     int32_t *pos_l = reinterpret_cast<int32_t *>(dyn + dyn_off + (size_t)p.cap * 4);
-    // what the passes read: the LDS copies (as LDS pointers, so that the loops use ds_read) or memory
+    // the LDS copies as LDS pointers, so that the loops use ds_read
     typedef __attribute__((address_space(3))) const float lds_cf32;
     typedef __attribute__((address_space(3))) const int32_t lds_ci32;
     lds_cf32 *sc_s = (lds_cf32 *)sc_l;
     lds_ci32 *pos_s = (lds_ci32 *)pos_l;
-    auto SC = [&](int i) -> float {
-        if constexpr (RES) return sc_s[i];
-        else return sc_g[i];
+    f32x4 sreg[NQ4];
+    i32x4 preg[NQ4];
+    // visit(row, score, position, k) for every row this thread owns, the k-th of at most 32
+    auto row_of = [&](int k) { return SRC > 0 ? 4 * ((k >> 2) * THREADS + tid) + (k & 3) : tid + k * THREADS; };
+    auto for_rows = [&](auto &&visit) {
+        if constexpr (SRC > 0) {
+#pragma unroll
+            for (int q = 0; q < NQ4; ++q) {
+                if (q * 4 * THREADS >= p.n) break;   // uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = 4 * (q * THREADS + tid) + e;
+                    if (i < p.n) visit(i, sreg[q][e], preg[q][e], 4 * q + e);
+                }
+            }
+        } else {
+#pragma unroll 2
+            for (int i = tid, k = 0; i < p.n; i += THREADS, ++k) {
+                if constexpr (RES) visit(i, (float)sc_s[i], (int32_t)pos_s[i], k);
+                else visit(i, sc_g[i], pos[i], k);
+            }
+        }
     };
-    auto PS = [&](int i) -> int32_t {
-        if constexpr (RES) return pos_s[i];
-        else return pos[i];
-    };
+    auto exempt = [&](int32_t pi) { return p.window_W > 0 && pi >= p.window_pos_min; };
     KD_TL_DECL
     KD_TL(0);
 #ifdef KD_TIMELINE
@@ -264,9 +274,21 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
 
     // ---- 0. every load that does not depend on the selection is issued here, so that the chain
     // below costs one memory round trip now and one for the evicted rows later: the scores and
-    // positions of all rows (asynchronous copies into LDS, 1 KB per wave and instruction; the buffers
-    // hold a multiple of four rows), the running key sum, and (FILL layout) the K/V rows [N, n), the
-    // only ones that can move, into registers.
+    // positions of all rows (into registers, or by asynchronous copies into LDS, 1 KB per wave and
+    // instruction; the buffers hold a multiple of four rows), the running key sum, and (FILL layout) the
+    // K/V rows [N, n), the only ones that can move, into registers.
+    if constexpr (SRC > 0) {
+#pragma unroll
+        for (int q = 0; q < NQ4; ++q) {
+            const int i = 4 * (q * THREADS + tid);
+            sreg[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            preg[q] = i32x4{0, 0, 0, 0};
+            if (i < p.n) {
+                sreg[q] = *reinterpret_cast<const f32x4 *>(sc_g + i);
+                preg[q] = *reinterpret_cast<const i32x4 *>(pos + i);
+            }
+        }
+    }
     if (RES) {
         const int nchunks = (p.cap * 4 + 1023) / 1024;
         for (int c = wave; c < 2 * nchunks; c += NWAVES) {      // wave uniform
@@ -355,17 +377,15 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
         if (!known) {
         uint64_t best = 0;   // 0: no row (every real key is larger: orderable() of a finite score is > 0)
         int besti = -1;
-#pragma unroll 2
-        for (int i = tid; i < p.n; i += THREADS) {
-            const int32_t pi = PS(i);
-            if (!(p.window_W > 0 && pi >= p.window_pos_min)) {
-                const uint64_t key = ((uint64_t)orderable(SC(i)) << 32) | (uint32_t)pi;
+        for_rows([&](int i, float s, int32_t pi, int) {
+            if (!exempt(pi)) {
+                const uint64_t key = ((uint64_t)orderable(s) << 32) | (uint32_t)pi;
                 if (key > best) {
                     best = key;
                     besti = i;
                 }
             }
-        }
+        });
         uint64_t wbest = best;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -424,11 +444,18 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
             if (tid < D) p.ksum_next[(size_t)bh * D + tid] = ksum_old - sh.colsum[0][tid];
             KD_SEL_RETURN;
         }
+        // (ORDERED, or no tail row in registers: the evicted row goes the way of the others below; where nothing
+        // could be evicted -- impossible -- the list stays empty and the count check reports it)
+        if (tid == 0 && gbest != 0) {
+            lists[0] = sh.tb;
+            sh.nev = 1;
+        }
+        __syncthreads();
     } else {
     // ---- 1. histogram of the non-exempt scores in LDS
-#pragma unroll 2
-    for (int i = tid; i < p.n; i += THREADS)
-        if (!(p.window_W > 0 && PS(i) >= p.window_pos_min)) atomicAdd(&sh.hist[score_bin(SC(i))], 1u);
+    for_rows([&](int, float s, int32_t pi, int) {
+        if (!exempt(pi)) atomicAdd(&sh.hist[score_bin(s)], 1u);
+    });
     __syncthreads();
     KD_TL(3);   // scores binned
 
@@ -461,13 +488,16 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
     KD_TL(4);   // threshold bin known
 
     // above the bin -> evicted, inside it -> candidate for the exact ranking
-#pragma unroll 2
-    for (int i = tid; i < p.n; i += THREADS) {
-        const int32_t pi = PS(i);
-        const float s = SC(i);
+    auto evict = [&](int i) {   // marks row i and appends it to the (unordered) list
+        atomicOr(&evbits[i >> 5], 1u << (i & 31));
+        const uint32_t at = atomicAdd(&sh.nev, 1u);
+        if (at < (uint32_t)E) lists[at] = i;
+    };
+    uint32_t mine_above = 0;   // the thread's rows above the bin: listed after the pass, so that the pass itself waits for nothing
+    for_rows([&](int i, float s, int32_t pi, int k) {
         // bin of the row, -1 if it cannot be evicted (exempt)
-        const int sb = !(p.window_W > 0 && pi >= p.window_pos_min) ? score_bin(s) : -1;
-        if (sb > tb) atomicOr(&evbits[i >> 5], 1u << (i & 31));
+        const int sb = !exempt(pi) ? score_bin(s) : -1;
+        if (sb > tb) mine_above |= 1u << k;
         else if (sb == tb) {
             const uint32_t c = atomicAdd(&sh.ncand, 1u);
             if (c < CAND_MAX) {
@@ -476,7 +506,8 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
                 sh.cand_pos[c] = pi;
             }
         }
-    }
+    });
+    for (; mine_above; mine_above &= mine_above - 1) evict(row_of(__ffs(mine_above) - 1));
     __syncthreads();
     const uint32_t ncand = sh.ncand;
     KD_TL(5);   // candidates collected
@@ -497,98 +528,86 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
                 }
                 rank += (uint32_t)__popcll(__ballot(gt));
             }
-            if (lane == 0 && rank < need) {
-                const uint32_t i = sh.cand_slot[c];
-                atomicOr(&evbits[i >> 5], 1u << (i & 31));
-            }
+            if (lane == 0 && rank < need) evict((int)sh.cand_slot[c]);
         }
         __syncthreads();
     } else {
         radix_select_in_bin<THREADS>(p, sh, RES ? sc_l : sc_g, RES ? pos_l : pos, evbits, tb, need);
+        for_rows([&](int i, float s, int32_t, int) {   // (it marks rows of the bin; they join the list here)
+            if (score_bin(s) == tb && ((evbits[i >> 5] >> (i & 31)) & 1u)) {
+                const uint32_t at = atomicAdd(&sh.nev, 1u);
+                if (at < (uint32_t)E) lists[at] = i;
+            }
+        });
+        __syncthreads();
     }
     }   // E > 1
-    KD_TL(6);   // ranking done: the eviction bitmap is final
+    KD_TL(6);   // ranking done: the eviction bitmap and the list of evicted rows are final
 
-    // ---- 4. ordered lists: thread t owns bitmap word t = rows [32 t, 32 t + 32)
-    const int own0 = min(p.n, 32 * tid), own1 = min(p.n, own0 + 32);
-    const uint32_t valid = own1 - own0 == 32 ? 0xFFFFFFFFu : ((1u << (own1 - own0)) - 1u);
-    const uint32_t low = own0 + 32 <= p.N ? 0xFFFFFFFFu : (own0 >= p.N ? 0u : ((1u << (p.N - own0)) - 1u));  // rows < N
-    const uint32_t evw = tid < nwords ? (evbits[tid] & valid) : 0u;
-    const uint32_t holew = evw & low, movew = ~evw & ~low & valid;
-    uint64_t tot3;
-    const uint64_t ex3 = block_exclusive_scan_t<THREADS, uint64_t>((uint64_t)__popc(evw) | ((uint64_t)__popc(holew) << 21) |
-                                                    ((uint64_t)__popc(movew) << 42),
-                                                sh.wave_tot64, &tot3);
-    constexpr uint64_t M21 = (1ull << 21) - 1;
-    uint32_t eb = (uint32_t)(ex3 & M21);
-    const uint32_t hm_h = (uint32_t)((ex3 >> 21) & M21), hm_m = (uint32_t)((ex3 >> 42) & M21);
-    const uint32_t tot_ev = (uint32_t)(tot3 & M21), nholes = (uint32_t)((tot3 >> 21) & M21),
-                   nmov = (uint32_t)((tot3 >> 42) & M21);
+    int32_t *evlist = lists, *holes = lists + E;
     // an impossible count is reported and nothing is moved (keeps every index in range)
-    const bool sane = tot_ev == (uint32_t)E && nholes == nmov;
-    if (!sane) {
+    if (sh.nev != (uint32_t)E) {   // uniform
         if (tid == 0) atomicOr(p.status, STATUS_SELECT_COUNT);
         KD_SEL_RETURN;
     }
-    // evicted rows | holes (evicted rows below N) | movers (kept rows from N on) | rank of tail row N + r
-    // among the movers (-1: evicted)
-    int32_t *evlist = lists, *holes = lists + E, *movers = lists + 2 * E, *mrank = lists + 3 * E;
-    const bool tail_par = E <= THREADS && (nwords - (p.N >> 5)) <= TAIL_WORDS;
+
+    // ---- 4. evicted rows before each row: thread t owns bitmap word t = rows [32 t, 32 t + 32).  From that
+    // count follow the destinations of the ORDERED layout, and of the FILL layout the rank of a hole (all evicted
+    // rows below it are holes) and of a mover.  The evicted keys are requested before the scan, so that their
+    // trip to memory runs under it; the sum of unit keys depends on the order of its terms in the last bit of
+    // a double, so there the list is put in order first.
+    constexpr int RPW = 64 / UPR;
+    const int eu = lane % UPR, erl = lane / UPR;
+    // the rows of up to EV_BATCH rounds are requested together: one memory round trip, not one per round
+    constexpr int EV_BATCH = 4;
+    u32x4 wv[EV_BATCH];
+    auto request = [&](int rb0) {
+#pragma unroll
+        for (int b = 0; b < EV_BATCH; ++b) {
+            const int r = rb0 + b * NWAVES * RPW + erl;
+            wv[b] = u32x4{0u, 0u, 0u, 0u};
+            if (r < E) wv[b] = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + eu * 8);
+        }
+    };
+    const bool sorted = p.anchor_mode == 1;   // uniform
+    if (!sorted) request(wave * RPW);
+    uint32_t *word_base = sh.cand_slot;   // the candidate arrays are free by now
+    static_assert(MAX_CAP / 32 <= CAND_MAX, "one count per bitmap word");
     {
-        uint32_t hb = hm_h, mb = hm_m, e2 = eb;
-        for (uint32_t w = evw; w; w &= w - 1) {
-            const int i = own0 + __ffs(w) - 1;
-            evlist[e2++] = i;
-            if (i < p.N) holes[hb++] = i;
-            else mrank[i - p.N] = -1;
-        }
-        // The tail rows [N, n) sit in a few words that are mostly movers: those words and their
-        // mover counts before them go to LDS, and one thread per tail row finishes below.
-        const int tw = tid - (p.N >> 5);
-        if (tail_par) {
-            if (tw >= 0 && tid < nwords) {
-                sh.tail_word[tw] = movew;
-                sh.tail_base[tw] = mb;
-            }
-        } else {
-            for (uint32_t w = movew; w; w &= w - 1) {
-                const int i = own0 + __ffs(w) - 1;
-                mrank[i - p.N] = (int32_t)mb;
-                movers[mb++] = i;
-            }
-        }
+        uint32_t tot_ev;
+        const uint32_t eb = block_exclusive_scan_t<THREADS, uint32_t>(tid < nwords ? (uint32_t)__popc(evbits[tid]) : 0u, sh.wave_tot2, &tot_ev);
+        if (tid < nwords) word_base[tid] = eb;
     }
     __syncthreads();
-    if (tail_par && tid < E) {
-        const int row = p.N + tid, tw = (row >> 5) - (p.N >> 5), bit = row & 31;
-        const uint32_t mw = sh.tail_word[tw];
-        if ((mw >> bit) & 1u) {
-            const uint32_t r = sh.tail_base[tw] + (uint32_t)__popc(mw & ((1u << bit) - 1u));
-            mrank[tid] = (int32_t)r;
-            movers[r] = row;
-        }   // an evicted tail row got its -1 above
+    auto before = [&](int i) { return (int)(word_base[i >> 5] + (uint32_t)__popc(evbits[i >> 5] & ((1u << (i & 31)) - 1u))); };
+    auto evicted = [&](int i) { return ((evbits[i >> 5] >> (i & 31)) & 1u) != 0; };
+    const int nholes = before(p.N);   // (row N exists: n > N)
+    if (sorted) {
+        // (the list is rewritten from the bitmap, thread by word)
+        if (tid < nwords) {
+            int at = (int)word_base[tid];
+            for (uint32_t w = evbits[tid]; w; w &= w - 1) evlist[at++] = 32 * tid + __ffs(w) - 1;
+        }
+        __syncthreads();
+        request(wave * RPW);
     }
-    // (the ranks are first read after the barrier inside step 5)
-    KD_TL(7);   // lists written
+    if (p.layout == 1)
+        for (int r = tid; r < E; r += THREADS) {
+            const int i = evlist[r];
+            if (i < p.N) holes[before(i)] = i;
+        }
+    // rank of tail row N + r among the movers (rows from N on that stay), -1 if it is evicted: mover k goes to hole k
+    auto mover = [&](int r) { return evicted(p.N + r) ? -1 : r - (before(p.N + r) - nholes); };
+    KD_TL(7);   // holes listed
 
     // ---- 5. take the evicted keys out of the running key sum (before rows are overwritten).
     // UPR lanes share an evicted row (16 bytes each); a wave holds 64/UPR rows at a time.
     {
-        constexpr int RPW = 64 / UPR;
-        const int u = lane % UPR, rl = lane / UPR;
         double acc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-        // the rows of up to EV_BATCH rounds are requested together: one memory round trip, not one per round
-        constexpr int EV_BATCH = 4;
         for (int rb0 = wave * RPW; rb0 < E; rb0 += EV_BATCH * NWAVES * RPW) {  // uniform per wave
-            u32x4 wv[EV_BATCH];
-#pragma unroll
-            for (int b = 0; b < EV_BATCH; ++b) {
-                const int r = rb0 + b * NWAVES * RPW + rl;
-                wv[b] = u32x4{0u, 0u, 0u, 0u};
-                if (r < E) wv[b] = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + u * 8);
-            }
+            if (rb0 != wave * RPW) request(rb0);
 #pragma unroll
             for (int b = 0; b < EV_BATCH; ++b) {
                 if (rb0 + b * NWAVES * RPW >= E) break;   // uniform
@@ -611,25 +630,22 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
                 for (int i = 0; i < 8; ++i) acc[i] += (p.anchor_mode == 1) ? x[i] * inv : x[i];
             }
         }
-        // fold the rows of the wave (lanes with equal u), then the waves
+        // fold the rows of the wave (lanes with equal eu), then the waves
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
+            if constexpr (UPR == 16) acc[i] = sum_over_rows_f64(acc[i]);
+            else {
 #pragma unroll
-            for (int off = UPR; off < 64; off <<= 1) acc[i] += shfl_xor_f64(acc[i], off);
+                for (int off = UPR; off < 64; off <<= 1) acc[i] += shfl_xor_f64(acc[i], off);
+            }
         }
-        if (rl == 0) {
+        if (erl == 0) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sh.colsum[wave][u * 8 + i] = acc[i];
+            for (int i = 0; i < 8; ++i) sh.colsum[wave][eu * 8 + i] = acc[i];
         }
         __syncthreads();   // also: every evicted row has been read before the compaction overwrites it
-        if (tid < D) {
-            double s = 0.0;
-#pragma unroll
-            for (int w = 0; w < NWAVES; ++w) s += sh.colsum[w][tid];
-            p.ksum_next[(size_t)bh * D + tid] = ksum_old - s;
-        }
     }
-    KD_TL(8);   // evicted rows read, key sum stored
+    KD_TL(8);   // evicted rows read
 
     // ---- 6. compaction
     if (p.layout == 1) {
@@ -641,47 +657,74 @@ __device__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned
                 const int w = q * THREADS + tid;
                 if (q * THREADS < 2 * E * UPR && w < 2 * E * UPR) {
                     const int which = w >= E * UPR, rem = w - which * E * UPR;
-                    const int mr = mrank[rem / UPR];
+                    const int mr = mover(rem / UPR);
                     if (mr >= 0)
                         *reinterpret_cast<u32x4 *>((which ? vb : kb) + (size_t)holes[mr] * D + (rem % UPR) * 8) = tailv[q];
                 }
             }
         } else {
-            const int nmove = (int)nholes;
-            for (int w = tid; w < nmove * UPR * 2; w += THREADS) {
+            for (int w = tid; w < E * UPR * 2; w += THREADS) {
                 const int r = w / (UPR * 2), rem = w % (UPR * 2);
-                const int u = rem % UPR;
+                const int u = rem % UPR, mr = mover(r);
                 uint16_t *base_ptr = rem < UPR ? kb : vb;
-                const u32x4 val = *reinterpret_cast<const u32x4 *>(base_ptr + (size_t)movers[r] * D + u * 8);
-                *reinterpret_cast<u32x4 *>(base_ptr + (size_t)holes[r] * D + u * 8) = val;
+                if (mr >= 0)
+                    *reinterpret_cast<u32x4 *>(base_ptr + (size_t)holes[mr] * D + u * 8) =
+                        *reinterpret_cast<const u32x4 *>(base_ptr + (size_t)(p.N + r) * D + u * 8);
             }
         }
-        for (int r = tid; r < (int)nholes; r += THREADS) pos[holes[r]] = p.pos0 + (movers[r] - p.len);
+        for (int r = tid; r < E; r += THREADS) {
+            const int mr = mover(r);
+            if (mr >= 0) pos[holes[mr]] = p.pos0 + (p.N + r - p.len);
+        }
     } else {
         // ORDERED: kept row i moves to i - (evicted rows before i); positions are compacted here, the
-        // K/V rows by compact_ordered_kernel.  The evicted count before a row comes from the bitmap
-        // and the per-word counts of the scan.  A position lands at or below the row it came from,
-        // and the rows are taken in ascending chunks: reading from the LDS copy nothing can be
-        // overwritten before it is read; reading from memory, a chunk is read, then (barrier) written.
-        uint32_t *word_base = sh.cand_slot;   // the candidate arrays are free by now
-        static_assert(MAX_CAP / 32 <= CAND_MAX, "one count per bitmap word");
-        if (tid < nwords) word_base[tid] = eb;
-        __syncthreads();
+        // K/V rows by compact_ordered_kernel.  A position lands at or below the row it came from: from registers or
+        // the LDS copy nothing can be overwritten before it is read; reading from memory, the rows are taken in
+        // ascending chunks, each read, then (barrier) written.
         int32_t *dst = p.dstmap + (size_t)bh * p.cap;
-        for (int i0 = 0; i0 < p.n; i0 += THREADS) {   // uniform
-            const int i = i0 + tid;
-            const int32_t pi = i < p.n ? PS(i) : 0;
-            if (!RES) __syncthreads();
-            if (i < p.n) {
-                const uint32_t word = evbits[i >> 5], bit = (uint32_t)i & 31u;
-                if ((word >> bit) & 1u) dst[i] = -1;
-                else {
-                    const int to = i - (int)(word_base[i >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u)));
-                    dst[i] = to;
-                    pos[to] = pi;
+        if constexpr (SRC > 0) {
+#pragma unroll
+            for (int q = 0; q < NQ4; ++q) {
+                const int i = 4 * (q * THREADS + tid);
+                if (i < p.n) {   // (the four rows share a bitmap word; the buffers hold a multiple of four rows)
+                    const uint32_t word = evbits[i >> 5], bit = (uint32_t)i & 31u;
+                    int to = i - (int)(word_base[i >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u)));
+                    i32x4 d;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool gone = ((word >> (bit + e)) & 1u) != 0;
+                        d[e] = gone ? -1 : to;
+                        if (!gone && i + e < p.n) pos[to] = preg[q][e];
+                        to += gone ? 0 : 1;
+                    }
+                    *reinterpret_cast<i32x4 *>(dst + i) = d;
+                }
+            }
+        } else {
+            for (int i0 = 0; i0 < p.n; i0 += THREADS) {   // uniform
+                const int i = i0 + tid;
+                int32_t pi = 0;
+                if (i < p.n) {
+                    if constexpr (RES) pi = pos_s[i];
+                    else pi = pos[i];
+                }
+                if (!RES) __syncthreads();
+                if (i < p.n) {
+                    if (evicted(i)) dst[i] = -1;
+                    else {
+                        const int to = i - before(i);
+                        dst[i] = to;
+                        pos[to] = pi;
+                    }
                 }
             }
         }
+    }
+    if (tid < D) {   // (the sums of the waves were published by the barrier above; stored last, off the moves' way)
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < NWAVES; ++w) s += sh.colsum[w][tid];
+        p.ksum_next[(size_t)bh * D + tid] = ksum_old - s;
     }
     KD_TL(9);   // moves issued
 #ifdef KD_TIMELINE
