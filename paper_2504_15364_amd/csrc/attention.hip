@@ -103,11 +103,6 @@ __device__ __forceinline__ float max_halves(float x)
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return max3_raw(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[0]));
 }
-__device__ __forceinline__ float sum_halves(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 template <int N>
 __device__ __forceinline__ void wait_copies()  // at most N of this wave's copies still in flight
@@ -162,7 +157,9 @@ __device__ __forceinline__ void loads_landed(u32x2 &x, u32x4 (&w)[A][B])
 // HELP: some waves of a workgroup may have no query row at all (few query rows: decode); such a
 // wave takes no part in the attention, it copies its share of every tile and scores rows.
 constexpr int MAIN_WAVES = 8;
-template <int D, bool HELP>
+// EXACT: the scores of all rows are asked for (scores_out), so they are formed in double here; otherwise the
+// attention leaves approximate scores and the selection decides from exact ones of the few rows near its threshold.
+template <int D, bool HELP, bool EXACT>
 __device__ __forceinline__ void step_main_body(const StepParams &p, const int block_id)
 {
     constexpr int NW = MAIN_WAVES;   // waves per workgroup
@@ -184,11 +181,15 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [STAGES][K tile | V tile]
     __shared__ double red[NW][4];       // |mu|^2 in pieces: one per 16-lane row of every wave
     __shared__ double bs_part[NW][D];   // per-wave column sums of the block's keys
-    __shared__ double mu_s[D];          // the anchor: (key sum incl. this block) / n
+    __shared__ double mu_s[EXACT ? D : 1];   // the anchor: (key sum incl. this block) / n
+    // ... as the sum of two bf16 vectors, and |mu|^2 in pieces (approximate scores)
+    __shared__ __attribute__((aligned(16))) __bf16 mu_hi[D], mu_lo[D];
+    __shared__ float mu2_f[D / 16];
     // (mu.k, |k|^2, row) of scored rows, staged per wave until 64 are there: the square root and the
     // division that finish a score are long instruction sequences, run once per 64 rows this way
-    __shared__ double st_dot[NW][64], st_k2[NW][64];
-    __shared__ int st_row[NW][64];
+    constexpr int STAGED = EXACT ? 64 : 1;
+    __shared__ double st_dot[NW][STAGED], st_k2[NW][STAGED];
+    __shared__ int st_row[NW][STAGED];
     KD_TL_DECL
     KD_TL(0);
 
@@ -465,11 +466,19 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 
     KD_TL(4);   // queries in registers, block sum folded
     f32x16 oacc[NQ][NDB];
-    float mref[NQ], lrun[NQ][2];  // the row sum runs in two independent chains
+    // Row sums on the matrix pipe: a 16x16x32 product of the weights with ones.  (The dot instruction that
+    // added two weights at a time, v_dot2_f32_bf16, does not run beside an MFMA: it held the SIMD for 16.5 cycles
+    // each, 264 a tile and wave, where the four products take 64.)
+    // Read as a 16-column operand, the weights of lanes 0-15 and 32-47 are the two halves of queries 0-15, those
+    // of lanes 16-31 and 48-63 of queries 16-31: even rows of the other operand take the former, odd rows the
+    // latter, so element 0 of lsum in every lane is the sum of query lane % 16, element 1 that of 16 + lane % 16.
+    float mref[NQ];
+    f32x4 lsum[NQ];
+    const uint32_t sel_word = ((lane ^ (lane >> 4)) & 1) == 0 ? 0x3F803F80u : 0u;   // two bf16 ones or zeros
 #pragma unroll
     for (int a = 0; a < NQ; ++a) {
         mref[a] = -INFINITY;
-        lrun[a][0] = lrun[a][1] = 0.f;
+        lsum[a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -534,8 +543,9 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
             for (int a = 0; a < NQ; ++a) {
                 const float alpha = need[a] ? __builtin_amdgcn_exp2f(mref[a] - mtile[a]) : 1.f;
                 mref[a] = need[a] ? mtile[a] : mref[a];
-                lrun[a][0] *= alpha;
-                lrun[a][1] *= alpha;
+                const auto ar = __builtin_amdgcn_permlane16_swap(__float_as_uint(alpha), __float_as_uint(alpha), false, false);
+                lsum[a][0] *= __uint_as_float(ar[0]);
+                lsum[a][1] *= __uint_as_float(ar[1]);
 #pragma unroll
                 for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -571,8 +581,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     // block (i / (8 / SL)) % NQ, 16-key chunk kc = i / (8 NQ / SL), accumulator elements
     // 8 (kc % 2) + SL (i % (8 / SL)) .. + SL - 1 of key group kc / 2.  A slice goes through three steps
     // one pipeline step apart, so that no instruction waits for the one before it: F scale and shift,
-    // E exponential, C round to bf16 (the B operand of the second MFMA) and add the rounded weights to
-    // the row sum.  Small slices spread the vector work evenly between the MFMAs: a wave gets the
+    // E exponential, C round to bf16 (the B operand of the second MFMA).  Small slices spread the vector work evenly between the MFMAs: a wave gets the
     // matrix pipe every other MFMA slot, and what does not fit between two of its MFMAs delays the next.
     constexpr int SL = 2;              // exponentials per slice (2 or 4)
     constexpr int SPC = 8 / SL;        // slices per 16-key chunk and query block
@@ -597,15 +606,8 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 #pragma unroll
         for (int r = 0; r < SL / 2; ++r) {
             const int e0 = SL * part + 2 * r;   // element pair inside the 8 of this lane's chunk
-            bf16x2 pr;
-            pr[0] = (__bf16)ex[2 * r];
-            pr[1] = (__bf16)ex[2 * r + 1];
-            pk[a][kc][e0] = pr[0];
-            pk[a][kc][e0 + 1] = pr[1];
-            const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
-            const int chain = (e0 >> 1) & 1;    // the row sum runs in two chains
-            lrun[a][chain] = __builtin_amdgcn_fdot2_f32_bf16(pr, one, lrun[a][chain], false);
-            asm volatile("" : "+v"(lrun[a][chain]));
+            pk[a][kc][e0] = (__bf16)ex[2 * r];
+            pk[a][kc][e0 + 1] = (__bf16)ex[2 * r + 1];
         }
     };
 
@@ -614,22 +616,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     // the bf16 values, rounded once to float.  The query-row tiles of a head share the K tiles, so
     // tile t is scored by the workgroup with mt == t % mtiles.  UPR lanes share a row.
     int staged = 0;   // rows this wave has staged (wave uniform)
-    // Generation phase (p.argmax_rec): the row to evict is the arg-max of the scores, so every lane keeps
-    // the best of the rows it finishes as (orderable score bits << 32 | row), and whether it met the
-    // same score bits on another row (then the token position has to decide, which the selection does
-    // from all scores as before); the workgroup leaves one such record for the selection.
-    unsigned long long am_best = 0;
-    bool am_tie = false;
-    auto am_merge = [](unsigned long long &best, bool &tie, unsigned long long ob, bool ot) {
-        const uint32_t hb = (uint32_t)(best >> 32), ho = (uint32_t)(ob >> 32);
-        if (ho > hb) {
-            best = ob;
-            tie = ot;
-        } else if (ho == hb && ob != 0) {
-            tie = tie || ot || ob != best;
-            best = ob > best ? ob : best;
-        }
-    };
     auto flush_scores = [&]() {
         // same wave wrote and reads: the LDS accesses of one wave complete in order; the fences only
         // keep the compiler from moving the reads above the writes, and later writes above the reads
@@ -643,7 +629,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                 const float sc = finish_score(st_dot[wave][lane], st_k2[wave][lane], sqrt(nmu2), p.eps);
                 p.scores[(size_t)bh * p.cap + row] = sc;
                 if (p.scores_out) p.scores_out[(size_t)bh * p.n + row] = sc;
-                if constexpr (HELP) am_merge(am_best, am_tie, ((unsigned long long)orderable(sc) << 32) | (uint32_t)row, false);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -770,11 +755,63 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         // room for the next tile's rows of this wave?
         if (staged + ((TPASS + nscore - 1) / nscore) * RPP > 64) flush_scores();
     };
-    auto score_tile = [&](int t) {
-        if constexpr (HELP) score_tile_shared(t);
-        else score_tile_fixed(t);
+    // Approximate score of 16 keys of a tile (rows 16 gi .. of it), on the matrix pipe: 16x16x32 products of the key
+    // rows with the anchor (two bf16 vectors that add up to it within 2^-18, in every column) and with themselves; row r's
+    // two numbers are then in the lane of column r that holds row r.  What bounds it is the exact form it replaces: double
+    // multiply-adds and conversions (9 cycles each) on all eight waves of the step, 0.37 us per scored tile and another
+    // 1.5 us for the square roots and divisions (attention launch at 8192 keys, 32 / 8 heads, with and without scoring:
+    // 26.3 and 22.3 us), against 12 products and 12 LDS reads of four waves.
+    // The error against the exact score is below SCORE_SLACK (kd_kernels.h); a row whose numbers leave the range in
+    // which that holds gets a NaN, which sends the selection to the exact scores of all rows.
+    auto score_group = [&](int t, int gi) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // (the lane's addresses are worked out here, not kept in registers through the loop)
+        const int c16 = ln & 15, g = ln >> 4;
+        const unsigned char *tK = smem + (size_t)(t % STAGES) * 2 * TILE_B + (16 * gi + c16) * ROWB;
+        f32x4 dh = {0.f, 0.f, 0.f, 0.f}, dl = dh, kk = dh;
+#pragma unroll
+        for (int c = 0; c < D / 32; ++c) {
+            const bf16x8 ka = as_bf16x8(*reinterpret_cast<const u32x4 *>(tK + (((4 * c + g) ^ (c16 & (UPR - 1))) * 16)));
+            const bf16x8 mh = as_bf16x8(*reinterpret_cast<const u32x4 *>(&mu_hi[32 * c + 8 * g]));
+            const bf16x8 ml = as_bf16x8(*reinterpret_cast<const u32x4 *>(&mu_lo[32 * c + 8 * g]));
+            dh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, mh, dh, 0, 0, 0);
+            kk = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, ka, kk, 0, 0, 0);
+            dl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, ml, dl, 0, 0, 0);
+            if (HELP || (c & 1)) __builtin_amdgcn_sched_barrier(0);   // (the fragments of all chunks at once would spill)
+        }
+        float mu2 = 0.f;
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) mu2 += mu2_f[i];
+        const int e = c16 & 3;
+        const float dot = (e & 2) ? ((e & 1) ? dh[3] + dl[3] : dh[2] + dl[2]) : ((e & 1) ? dh[1] + dl[1] : dh[0] + dl[0]);
+        const float k2 = (e & 2) ? ((e & 1) ? kk[3] : kk[2]) : ((e & 1) ? kk[1] : kk[0]);
+        const float nmu = __builtin_amdgcn_sqrtf(mu2), eps = (float)p.eps;
+        float sc = dot * __builtin_amdgcn_rcpf(fmaxf(nmu * __builtin_amdgcn_sqrtf(k2), eps));
+        const bool fine = mu2 > 1e-24f && mu2 < 1e24f && eps < 1e30f && k2 > 1e-24f && k2 < 1e24f;
+        // a zero key (or one of no more than 3e-19 that the products flush to zero): its score is 0 within the slack
+        const bool zero = k2 < 1e-37f && mu2 < 1e24f && nmu * 1e-17f < 1e-6f * eps;
+        sc = fine ? sc : zero ? 0.f : __builtin_nanf("");
+        const int row = t * TILE_KEYS + 16 * gi + c16;
+        if ((c16 >> 2) == g && row < p.n) p.scores[(size_t)bh * p.cap + row] = sc;
     };
+    // The query-row tiles of a head share the key tiles: workgroup mt scores the tiles t == mt (mod mtiles).  Where
+    // every wave carries query rows the tile's four groups go to four waves, one per SIMD, the other four the next time;
+    // else to the waves without any.
     const bool scoring = p.do_score != 0;
+    int next_score = scoring ? t0 + (mt - t0 % p.mtiles + p.mtiles) % p.mtiles : 0x7fffffff;
+    int score_half = 0;
+    auto score_tile = [&](int t) {
+        if constexpr (EXACT) {
+            if constexpr (HELP) score_tile_shared(t);
+            else score_tile_fixed(t);
+        } else if (HELP && nactive < NW) {
+            for (int gi = sidx; gi < 4 && sidx >= 0; gi += nscore) score_group(t, gi);
+        } else {
+            if ((wave >> 2) == score_half) score_group(t, wave & 3);
+            score_half ^= 1;
+        }
+        next_score += p.mtiles;
+    };
 
     const int tint = min(t1, max(t0, p.len / TILE_KEYS));  // tiles before it: every key cached, no mask
     f32x16 s[NQ][2];
@@ -794,11 +831,25 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                 for (int w = 0; w < NW; ++w) tot += bs_part[w][tid];
                 ksum_after = ksum_before + tot;
                 const double m = ksum_after / (double)p.n;
-                mu_s[tid] = m;
+                if constexpr (EXACT) mu_s[tid] = m;
+                else {
+                    const __bf16 hi = (__bf16)(float)m;
+                    mu_hi[tid] = hi;
+                    mu_lo[tid] = (__bf16)(float)(m - (double)(float)hi);
+                }
                 sq = m * m;
             }
             sq = row_allreduce_f64<16>(sq);
-            if ((lane & 15) == 0) red[wave][lane >> 4] = sq;
+            if constexpr (EXACT) {
+                if ((lane & 15) == 0) red[wave][lane >> 4] = sq;
+            } else if (tid < D) {
+                if ((lane & 15) == 0) mu2_f[tid / 16] = (float)sq;
+                if (writer) {   // for the selection, which scores the rows near its threshold exactly
+                    double *anchor = p.anchor + (size_t)bh * (D + D / 16);
+                    anchor[tid] = ksum_after / (double)p.n;
+                    if ((lane & 15) == 0) anchor[D + tid / 16] = sq;
+                }
+            }
         }
         KD_TL(6);   // anchor formed
         if (active) {
@@ -877,7 +928,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                     if (COPY == 2 && t + STAGES - 1 < t1) issue_copy(t + STAGES - 1, c);
                 }
             }
-            if (scoring && t % p.mtiles == mt) score_tile(t);
+            if (t == next_score) score_tile(t);
             return;
         }
         if (NEXT) {
@@ -918,6 +969,12 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (t == t0 + 3) KD_TL(21);
 #endif
         if (NEXT && MASKED) mask_tile(sn, (t + 1) * TILE_KEYS);
+        bf16x8 sel_ones;   // (built here for every tile: four registers fewer through stage A)
+        {
+            uint32_t w = sel_word;
+            asm volatile("" : "+v"(w));
+            sel_ones = as_bf16x8(u32x4{w, w, w, w});
+        }
         float mch[NQ][2];  // max scan of tile t + 1 in two chains per block
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
@@ -930,6 +987,11 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 #pragma unroll
             for (int a = 0; a < NQ; ++a)
                 oacc[a][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[j % (VAHEAD + 1)], pk[a][kc], oacc[a][db], 0, 0, 0);
+            if (db == NDB - 1) {
+#pragma unroll
+                for (int a = 0; a < NQ; ++a)
+                    lsum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel_ones, pk[a][kc], lsum[a], 0, 0, 0);
+            }
             if (NEXT) {
                 constexpr int PER = 16 / NB;  // accumulator elements per step (both key groups at once)
 #pragma unroll
@@ -948,7 +1010,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (t == t0 + 3) KD_TL(22);
 #endif
         // tile t is still in its buffer (recycled in the next iteration): score its rows
-        if (scoring && t % p.mtiles == mt) score_tile(t);
+        if (t == next_score) score_tile(t);
 #ifdef KD_TIMELINE
         if (t == t0 + 2) KD_TL(19);   // tile scored (if this workgroup owns it)
         if (t == t0 + 3) KD_TL(23);
@@ -1019,8 +1081,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         const int nblk = (Mtot + 31) / 32;
 #pragma unroll
         for (int a = 0; a < NQ; ++a) {
-            const float lsum = lrun[a][0] + lrun[a][1];
-            const float ltot = sum_halves(lsum);
+            const float ltot = (lane & 16) ? lsum[a][1] : lsum[a][0];
             const float inv = ltot > 0.f ? 1.f / ltot : 0.f;   // a row of a split may see no key at all
             const int blk = (mt * TM + wave * (32 * NQ)) / 32 + a;
             _Float16 *base = p.part_o + ((((size_t)sp * BH + bh) * nblk + blk) * SLABS * 64 + lane) * 4;
@@ -1052,8 +1113,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         };
 #pragma unroll
         for (int a = 0; a < NQ; ++a) {
-            const float lsum = lrun[a][0] + lrun[a][1];
-            const float ltot = sum_halves(lsum);
+            const float ltot = (lane & 16) ? lsum[a][1] : lsum[a][0];
             const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
             const int row = 32 * a + l32;
 #pragma unroll
@@ -1098,32 +1158,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     // the key sum after this step, for step_post and for the next step
     if (writer && tid < D) p.ksum_next[(size_t)bh * D + tid] = ksum_after;
 
-    if (scoring) flush_scores();   // last: the square roots and divisions run while the stores above complete
-    if constexpr (HELP) {
-        if (scoring && p.argmax_rec) {   // uniform
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t lo = __shfl_xor((uint32_t)am_best, off), hi = __shfl_xor((uint32_t)(am_best >> 32), off);
-                const bool ot = __shfl_xor((int)am_tie, off) != 0;
-                am_merge(am_best, am_tie, ((unsigned long long)hi << 32) | lo, ot);
-            }
-            unsigned long long *wrec = reinterpret_cast<unsigned long long *>(&st_dot[0][0]);   // staging is over
-            __syncthreads();
-            if (lane == 0) {
-                wrec[2 * wave] = am_best;
-                wrec[2 * wave + 1] = am_tie ? 1ull : 0ull;
-            }
-            __syncthreads();
-            if (tid == 0) {
-                unsigned long long b0 = 0;
-                bool t0_ = false;
-                for (int w = 0; w < NW; ++w) am_merge(b0, t0_, wrec[2 * w], wrec[2 * w + 1] != 0);
-                unsigned long long *rec = p.argmax_rec + ((size_t)bh * p.splits + sp) * 2;
-                rec[0] = b0;
-                rec[1] = t0_ ? 1ull : 0ull;
-            }
-        }
-    }
+    if constexpr (EXACT) flush_scores();   // last: the square roots and divisions run while the stores above complete
     KD_TL(11);  // append stored, scores flushed
 #ifdef KD_TIMELINE
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the stores of this wave have been acknowledged
@@ -1136,11 +1171,11 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 #endif
 }
 
-template <int D, bool HELP>
+template <int D, bool HELP, bool EXACT>
 __global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_kernel(StepParams p)
 {
     warm_arguments<sizeof(StepParams)>();
-    step_main_body<D, HELP>(p, (int)blockIdx.x);
+    step_main_body<D, HELP, EXACT>(p, (int)blockIdx.x);
 }
 
 // step_main with passengers (with or without helper waves): the first `ncarry` workgroups run the pending selection and
@@ -1159,11 +1194,11 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepPara
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         PostShared &sh = *reinterpret_cast<PostShared *>(smem);
         unsigned char *dyn = smem + carry_shared_bytes();
-        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
-        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
+        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
+        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
-    step_main_body<D, HELP>(p, (int)blockIdx.x - ncarry);
+    step_main_body<D, HELP, false>(p, (int)blockIdx.x - ncarry);
 }
 
 // The same with a third kind of workgroup behind the selection's: `ride.nshift` workgroups that shift
@@ -1186,8 +1221,8 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         PostShared &sh = *reinterpret_cast<PostShared *>(smem);
         unsigned char *dyn = smem + carry_shared_bytes();
-        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
-        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS>(cy, sh, dyn, (int)blockIdx.x);
+        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
+        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
     if ((int)blockIdx.x < ncarry + nshift) {
@@ -1195,7 +1230,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
         shift_range<D, CARRY_THREADS>(ride.p, ride.flags, ride.nchunks, ride.epoch, i % heads, i / heads, ride.parts);
         return;
     }
-    step_main_body<D, false>(p, (int)blockIdx.x - ncarry - nshift);
+    step_main_body<D, false, false>(p, (int)blockIdx.x - ncarry - nshift);
 }
 
 static size_t main_lds_bytes(int D) { return (size_t)STAGES * 2 * TILE_KEYS * D * 2; }
@@ -1214,10 +1249,14 @@ hipError_t configure_main_kernels()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
                             (int)main_lds_bytes(D));                                               \
     if (e != hipSuccess) return e;
-    KD_SET((step_main_kernel<128, false>), 128)
-    KD_SET((step_main_kernel<128, true>), 128)
-    KD_SET((step_main_kernel<64, false>), 64)
-    KD_SET((step_main_kernel<64, true>), 64)
+    KD_SET((step_main_kernel<128, false, false>), 128)
+    KD_SET((step_main_kernel<128, false, true>), 128)
+    KD_SET((step_main_kernel<128, true, false>), 128)
+    KD_SET((step_main_kernel<128, true, true>), 128)
+    KD_SET((step_main_kernel<64, false, false>), 64)
+    KD_SET((step_main_kernel<64, false, true>), 64)
+    KD_SET((step_main_kernel<64, true, false>), 64)
+    KD_SET((step_main_kernel<64, true, true>), 64)
 #undef KD_SET
 #define KD_SET(fn)                                                                                  \
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -1242,9 +1281,12 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
     const size_t lds = main_lds_bytes(p.D);
     const bool help = main_runs_help(p);
     if (p.few) return hipErrorInvalidValue;
-#define KD_GO(DD)                                                                                          \
-    if (help) hipLaunchKernelGGL((step_main_kernel<DD, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);  \
-    else hipLaunchKernelGGL((step_main_kernel<DD, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);
+    const bool exact = p.do_score && !p.score_approx;
+#define KD_GO(DD)                                                                                                             \
+    if (help && exact) hipLaunchKernelGGL((step_main_kernel<DD, true, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);       \
+    else if (help) hipLaunchKernelGGL((step_main_kernel<DD, true, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);          \
+    else if (exact) hipLaunchKernelGGL((step_main_kernel<DD, false, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);         \
+    else hipLaunchKernelGGL((step_main_kernel<DD, false, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);
     if (p.D == 128 && p.NW == MAIN_WAVES) { KD_GO(128) }
     else if (p.D == 64 && p.NW == MAIN_WAVES) { KD_GO(64) }
 #undef KD_GO
@@ -1255,7 +1297,7 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
 bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
-    return p.NW == 8 && !p.few && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
+    return p.NW == 8 && !p.few && !(p.do_score && !p.score_approx) && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
            carry_need(cy, false) <= CARRY_DYN_MAX && ncarry > 0;
 }
 
@@ -1285,7 +1327,7 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
 bool can_host_shift(const StepParams &p, const StepParams &shifted)
 {
     const int E = shifted.n - shifted.N;
-    return p.NW == 8 && !p.few && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
+    return p.NW == 8 && !p.few && !(p.do_score && !p.score_approx) && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
 }
 
 hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, const ShiftRide &ride, hipStream_t s)

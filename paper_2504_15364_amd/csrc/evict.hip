@@ -308,7 +308,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void step_score_kernel(StepParams p)
 // step_post: workgroups [0, BH) select and compact one head each (when this step evicts); the
 // rest merge the attention partials.  SRC: 16-byte loads of scores (and of positions) a thread of the
 // selection holds in registers; 0: it reads them from memory where it needs them at all.
-template <int D, int SRC>
+template <int D, int SRC, bool APPROX>
 __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
 {
     warm_arguments<sizeof(StepParams)>();
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
 #endif
         return;
     }
-    select_and_compact<D, SRC, POST_THREADS>(p, sh, smem_raw, (int)blockIdx.x);
+    select_and_compact<D, SRC, POST_THREADS, APPROX>(p, sh, smem_raw, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------- ordered compaction
@@ -585,12 +585,10 @@ hipError_t configure_kernels()
     e = configure_few_kernels();
     if (e != hipSuccess) return e;
     static_assert(MAX_CAP / 8 + LISTS_LDS_MAX + 16 <= POST_DYN_MAX, "the non-resident selection always fits");
-    const void *post_fns[] = {reinterpret_cast<const void *>(step_post_kernel<128, 3>),
-                              reinterpret_cast<const void *>(step_post_kernel<128, 0>),
-                              reinterpret_cast<const void *>(step_post_kernel<64, 3>),
-                              reinterpret_cast<const void *>(step_post_kernel<64, 0>),
-                              reinterpret_cast<const void *>(step_post_kernel<128, 5>),
-                              reinterpret_cast<const void *>(step_post_kernel<64, 5>)};
+    const void *post_fns[] = {
+#define KD_FN(DD, SRC) reinterpret_cast<const void *>(step_post_kernel<DD, SRC, false>), reinterpret_cast<const void *>(step_post_kernel<DD, SRC, true>)
+        KD_FN(128, 0), KD_FN(128, 3), KD_FN(128, 5), KD_FN(64, 0), KD_FN(64, 3), KD_FN(64, 5)};
+#undef KD_FN
     for (const void *fn : post_fns) {
         e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)POST_DYN_MAX);
         if (e != hipSuccess) return e;
@@ -612,8 +610,8 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
     const int grid = (p.do_evict ? p.batch * p.hkv : 0) + p.merge_wgs;
     if (grid == 0) return hipSuccess;
     if (!p.do_evict && p.few) {
-        if (p.D == 128) hipLaunchKernelGGL((step_post_kernel<128, 0>), dim3(grid), dim3(POST_THREADS), 0, s, p);
-        else if (p.D == 64) hipLaunchKernelGGL((step_post_kernel<64, 0>), dim3(grid), dim3(POST_THREADS), 0, s, p);
+        if (p.D == 128) hipLaunchKernelGGL((step_post_kernel<128, 0, false>), dim3(grid), dim3(POST_THREADS), 0, s, p);
+        else if (p.D == 64) hipLaunchKernelGGL((step_post_kernel<64, 0, false>), dim3(grid), dim3(POST_THREADS), 0, s, p);
         else return hipErrorInvalidValue;
         return hipGetLastError();
     }
@@ -629,15 +627,21 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
     // Three 16-byte loads of scores (and of positions) a thread up to 12288 rows, five up to 20480; the registers hold no
     // more beside the rows that may move, so larger caches are read from memory in every pass.  With the arg-max
     // records of the attention launch the scores are hardly ever looked at.
-    const int src = p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
+    // (Five loads leave no room for the positions: not where every row's is needed.)
+    const bool positions = p.window_W > 0 || (p.n - p.N == 1 && !p.score_approx);
+    const int src = p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : positions ? 0 : 5;
     const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
-#define KD_GO(DD)                                                                                                      \
-    if (src == 0) hipLaunchKernelGGL((step_post_kernel<DD, 0>), dim3(grid), dim3(POST_THREADS), lds, s, p);             \
-    else if (src == 3) hipLaunchKernelGGL((step_post_kernel<DD, 3>), dim3(grid), dim3(POST_THREADS), lds, s, p);        \
-    else hipLaunchKernelGGL((step_post_kernel<DD, 5>), dim3(grid), dim3(POST_THREADS), lds, s, p);
+#define KD_GO2(DD, SRC)                                                                                                    \
+    if (p.score_approx) hipLaunchKernelGGL((step_post_kernel<DD, SRC, true>), dim3(grid), dim3(POST_THREADS), lds, s, p);   \
+    else hipLaunchKernelGGL((step_post_kernel<DD, SRC, false>), dim3(grid), dim3(POST_THREADS), lds, s, p);
+#define KD_GO(DD)                       \
+    if (src == 0) { KD_GO2(DD, 0) }      \
+    else if (src == 3) { KD_GO2(DD, 3) } \
+    else { KD_GO2(DD, 5) }
     if (p.D == 128) { KD_GO(128) }
     else if (p.D == 64) { KD_GO(64) }
 #undef KD_GO
+#undef KD_GO2
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -23,6 +23,11 @@ constexpr int POST_THREADS = 1024;  // workgroup size of step_post
 constexpr int SCORE_THREADS = 256;  // workgroup size of step_score
 constexpr int SCORE_ROWS = 128;     // rows per step_score workgroup: 32 per wave
 constexpr int HIST_BINS = 4096;     // score histogram resolution in step_post (bins over [-1, 1])
+// Bound of |approximate score - exact score| (step_main without scores_out).  With |k| and |mu| the norms and the sums of
+// the matrix pipe off by at most 2^-23 of the running magnitude per term: 128 terms of mu.k 1.6e-5 |mu||k| (the second
+// bf16 vector of the anchor adds a 256th of that), the anchor as two bf16 vectors 2^-18, |k| 128 / 2 terms 7.7e-6, square
+// roots, reciprocal and products 1e-6: 2.9e-5 in all, as |score| <= 1.
+constexpr float SCORE_SLACK = 3e-5f;
 constexpr int CHUNK_ROWS = 128;     // rows per workgroup in the from-scratch key-sum pass
 constexpr int ORD_ROWS = 128;       // rows per workgroup of the ordered compaction
 constexpr int ORD_THREADS = 1024;   // ... and its threads: 4 16-byte units each
@@ -50,7 +55,8 @@ struct StepParams {
     _Float16 *part_o;                // [psplits][BH][blocks of 32 rows][D/8 slabs][64 lanes][4] partial outputs in the
                                      // MFMA accumulator layout, each normalised by its row sum
     float2 *part_ml;                 // [psplits][BH * G * Bt]    (reference max in log2 units, row sum)
-    float *scores;                   // [BH][cap]
+    float *scores;                   // [BH][cap]; approximate if score_approx
+    double *anchor;                  // [BH][D + D / 16] the step's anchor and |mu|^2 in pieces of 16 columns (score_approx)
     int32_t *dstmap;                 // [BH][cap] ORDERED layout: destination row or -1
     int32_t *lists;                  // [BH][4 * B] evicted rows | holes | movers | mover rank of each tail row
     unsigned long long *argmax_rec;  // nullable [BH][splits][2]: the generation phase (one row to evict, no window):
@@ -68,6 +74,7 @@ struct StepParams {
     int lists_in_lds;                // selection lists live in LDS (else in `lists`)
     int merge_wgs;                   // merge workgroups in step_post (0 when psplits == 1)
     int do_score, do_evict;
+    int score_approx;                // the step's scores are within SCORE_SLACK of the exact ones (or NaN: not known)
     int anchor_mode, layout, window_W;
     int32_t pos0, window_pos_min;
     float scale_log2e;

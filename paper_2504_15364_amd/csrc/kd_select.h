@@ -55,12 +55,13 @@ struct PostShared {
     uint32_t radix_hist[256];
     uint32_t sel_bin, sel_rank, sel_cnt;
     int tb;           // threshold bin
-    uint32_t need;    // rows to evict from the threshold bin
     uint32_t ncand, nev;
     uint32_t cand_slot[CAND_MAX];
     uint32_t cand_key[CAND_MAX];
     int32_t cand_pos[CAND_MAX];
     double colsum[MAX_SELECT_WAVES][128];
+    double mu[128], mu2[8];   // the anchor and |mu|^2 in pieces (approximate scores: exact ones of the rows near the threshold)
+    int bad;                  // a row's score is not known even approximately
 };
 
 // bytes of dynamic LDS a carried selection places PostShared in, ahead of its bitmap and lists
@@ -207,16 +208,21 @@ __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool l
 // E row indices (evicted rows | evicted rows below N in ascending order): in LDS when they fit, else in the
 // scratch buffer.
 // The caller keeps n <= 32 * THREADS (a thread owns one word of the eviction bitmap) and, with SRC > 0,
-// n <= 4 * SRC * THREADS.
+// n <= 4 * SRC * THREADS; with SRC > 3 also no window, and approximate scores if a single row is evicted.
 // (inlined: outlined, the parameter block would be passed through scratch memory)
-template <int D, int SRC, int THREADS>
+// APPROX: the scores may be approximate (p.score_approx says).
+template <int D, int SRC, int THREADS, bool APPROX>
 __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh)
 {
     constexpr int UPR = D / 8;
-    constexpr int TAILU = SRC > 3 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (the registers the rows' scores leave)
+    constexpr int TAILU = SRC > 3 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (the registers the scores leave)
+    // The rows [N, n), the only ones that can move (FILL layout), are requested with the scores; scoring rows exactly takes
+    // the registers they would wait in, and they are then requested with the evicted keys.
+    constexpr bool EARLY_TAIL = !APPROX;
     constexpr int NWAVES = THREADS / 64;
     constexpr bool RES = SRC == SRC_LDS;
     constexpr int NQ4 = SRC > 0 ? SRC : 1;
+    constexpr bool PREG = SRC > 0 && SRC <= 3;   // positions in registers too (else read where they are needed)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int E = p.n - p.N;
@@ -240,7 +246,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     lds_cf32 *sc_s = (lds_cf32 *)sc_l;
     lds_ci32 *pos_s = (lds_ci32 *)pos_l;
     f32x4 sreg[NQ4];
-    i32x4 preg[NQ4];
+    i32x4 preg[PREG ? NQ4 : 1];
     // visit(row, score, position, k) for every row this thread owns, the k-th of at most 32
     auto row_of = [&](int k) { return SRC > 0 ? 4 * ((k >> 2) * THREADS + tid) + (k & 3) : tid + k * THREADS; };
     auto for_rows = [&](auto &&visit) {
@@ -251,7 +257,11 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int i = 4 * (q * THREADS + tid) + e;
-                    if (i < p.n) visit(i, sreg[q][e], preg[q][e], 4 * q + e);
+                    if (i < p.n) {
+                        int32_t pi = 0;   // (not asked for: see the caller's part below)
+                        if constexpr (PREG) pi = preg[q][e];
+                        visit(i, sreg[q][e], pi, 4 * q + e);
+                    }
                 }
             }
         } else {
@@ -275,17 +285,16 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     // ---- 0. every load that does not depend on the selection is issued here, so that the chain
     // below costs one memory round trip now and one for the evicted rows later: the scores and
     // positions of all rows (into registers, or by asynchronous copies into LDS, 1 KB per wave and
-    // instruction; the buffers hold a multiple of four rows), the running key sum, and (FILL layout) the
-    // K/V rows [N, n), the only ones that can move, into registers.
+    // instruction; the buffers hold a multiple of four rows) and the running key sum.
     if constexpr (SRC > 0) {
 #pragma unroll
         for (int q = 0; q < NQ4; ++q) {
             const int i = 4 * (q * THREADS + tid);
             sreg[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-            preg[q] = i32x4{0, 0, 0, 0};
-            if (i < p.n) {
-                sreg[q] = *reinterpret_cast<const f32x4 *>(sc_g + i);
-                preg[q] = *reinterpret_cast<const i32x4 *>(pos + i);
+            if (i < p.n) sreg[q] = *reinterpret_cast<const f32x4 *>(sc_g + i);
+            if constexpr (PREG) {
+                preg[q] = i32x4{0, 0, 0, 0};
+                if (i < p.n) preg[q] = *reinterpret_cast<const i32x4 *>(pos + i);
             }
         }
     }
@@ -301,17 +310,20 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     const double ksum_old = tid < D ? p.ksum_next[(size_t)bh * D + tid] : 0.0;  // the sum step_main just wrote
     const bool tail_regs = p.layout == 1 && 2 * E * UPR <= TAILU * THREADS;
     u32x4 tailv[TAILU];
-    if (tail_regs) {
+    auto request_tail = [&]() {
+        if (tail_regs) {
 #pragma unroll
-        for (int q = 0; q < TAILU; ++q) {
-            const int w = q * THREADS + tid;
-            tailv[q] = u32x4{0u, 0u, 0u, 0u};
-            if (q * THREADS < 2 * E * UPR && w < 2 * E * UPR) {
-                const int which = w >= E * UPR, rem = w - which * E * UPR;
-                tailv[q] = *reinterpret_cast<const u32x4 *>((which ? vb : kb) + (size_t)(p.N + rem / UPR) * D + (rem % UPR) * 8);
+            for (int q = 0; q < TAILU; ++q) {
+                const int w = q * THREADS + tid;
+                tailv[q] = u32x4{0u, 0u, 0u, 0u};
+                if (q * THREADS < 2 * E * UPR && w < 2 * E * UPR) {
+                    const int which = w >= E * UPR, rem = w - which * E * UPR;
+                    tailv[q] = *reinterpret_cast<const u32x4 *>((which ? vb : kb) + (size_t)(p.N + rem / UPR) * D + (rem % UPR) * 8);
+                }
             }
         }
-    }
+    };
+    if constexpr (EARLY_TAIL) request_tail();
     for (int i = tid; i < nwords; i += THREADS) evbits[i] = 0;
     const bool use_rec = E == 1 && p.argmax_rec != nullptr && p.window_W == 0 && 4 * p.splits <= HIST_BINS;   // uniform
     if (use_rec) {
@@ -322,18 +334,21 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     } else {
         for (int i = tid; i < HIST_BINS; i += THREADS) sh.hist[i] = 0;
     }
+    bool approx = APPROX && p.score_approx != 0;   // uniform
+    double mu = 0.0;   // the anchor, and |mu|^2 in pieces, as the attention left them (first used behind a later barrier)
+    if (approx && tid < D + D / 16) mu = p.anchor[(size_t)bh * (D + D / 16) + tid];
     if (tid == 0) {
         sh.ncand = 0;
         sh.nev = 0;
         sh.tb = 0;
-        sh.need = 0;
+        sh.bad = 0;
     }
     KD_TL(1);   // loads issued
     if (RES) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies have landed
     __syncthreads();   // every wave's part of the copies; the cleared histogram and bitmap
     KD_TL(2);   // scores and positions in LDS
 
-    if (E == 1) {
+    if (E == 1 && !approx) {
         // ---- 1'. a single row to evict (the generation phase): the arg-max by (score bits, position)
         // replaces histogram, threshold and ranking
         // The attention launch may have left the arg-max by (score bits, row) of every workgroup's rows
@@ -405,12 +420,15 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         __syncthreads();
         }   // !known
         if (p.layout == 1 && tail_regs && gbest != 0) {
-            // FILL with the one tail row (row N, this step's token) in registers: the rest of the work
+            // FILL: the one tail row (row N, this step's token) travels with the evicted key: the rest of the work
             // is one row read and at most one row moved, done here without lists
             const int e = sh.tb;
             double x[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[i] = 0.0;
+            u32x4 tail = {0u, 0u, 0u, 0u};
+            if constexpr (EARLY_TAIL) tail = tailv[0];
+            else if (tid < 2 * UPR) tail = *reinterpret_cast<const u32x4 *>((tid >= UPR ? vb : kb) + (size_t)p.N * D + (tid % UPR) * 8);
             if (tid < UPR) {
                 const u32x4 w = *reinterpret_cast<const u32x4 *>(kb + (size_t)e * D + tid * 8);
 #pragma unroll
@@ -437,7 +455,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             // unit u of K is the one that writes unit u of K)
             if (e != p.N && tid < 2 * UPR) {
                 const int which = tid >= UPR, unit = tid - which * UPR;
-                *reinterpret_cast<u32x4 *>((which ? vb : kb) + (size_t)e * D + unit * 8) = tailv[0];
+                *reinterpret_cast<u32x4 *>((which ? vb : kb) + (size_t)e * D + unit * 8) = tail;
                 if (tid == 0) pos[e] = p.pos0 + (p.N - p.len);
             }
             __syncthreads();
@@ -452,11 +470,36 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         }
         __syncthreads();
     } else {
+    // Exact score of row i: the UPR lanes that share it call this together, each with its 16-byte unit.
+    auto exact_score = [&](int i) {
+        const int u = tid % UPR;
+        const u32x4 w = *reinterpret_cast<const u32x4 *>(kb + (size_t)i * D + u * 8);
+        double dot = 0.0, k2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double x0 = bf16_lo(w[j]), x1 = bf16_hi(w[j]);
+            dot = __builtin_fma(sh.mu[u * 8 + 2 * j], x0, dot);
+            k2 = __builtin_fma(x0, x0, k2);
+            dot = __builtin_fma(sh.mu[u * 8 + 2 * j + 1], x1, dot);
+            k2 = __builtin_fma(x1, x1, k2);
+        }
+        dot = row_allreduce_f64<UPR>(dot);
+        k2 = row_allreduce_f64<UPR>(k2);
+        double mu2 = 0.0;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) mu2 += sh.mu2[j];
+        return finish_score(dot, k2, sqrt(mu2), p.eps);
+    };
+    for (;;) {   // (a second time, with exact scores of all rows, where approximate ones do not do)
     // ---- 1. histogram of the non-exempt scores in LDS
     for_rows([&](int, float s, int32_t pi, int) {
-        if (!exempt(pi)) atomicAdd(&sh.hist[score_bin(s)], 1u);
+        if (!exempt(pi)) {
+            atomicAdd(&sh.hist[score_bin(s)], 1u);
+            if (APPROX && s != s) sh.bad = 1;
+        }
     });
     __syncthreads();
+    if (approx && tid < D + D / 16) (tid < D ? sh.mu[tid] : sh.mu2[tid - D]) = mu;
     KD_TL(3);   // scores binned
 
     // ---- 2. threshold bin: thread t owns the HIST_BINS / THREADS bins below its top one, highest first
@@ -475,7 +518,6 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         for (int j = 0; j < HIST_BINS / THREADS; ++j) {
             if (above + cnt[j] >= (uint32_t)E) {
                 sh.tb = top - j;
-                sh.need = (uint32_t)E - above;
                 break;
             }
             above += cnt[j];
@@ -484,10 +526,13 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     if (tid == 0 && total < (uint32_t)E) atomicOr(p.status, STATUS_SELECT_COUNT);  // cannot happen: E <= candidates
     __syncthreads();
     const int tb = sh.tb;
-    const uint32_t need = sh.need;
     KD_TL(4);   // threshold bin known
 
-    // above the bin -> evicted, inside it -> candidate for the exact ranking
+    // Above the bin -> evicted, inside it -> candidate for the exact ranking.  The E-th largest approximate score lies in the
+    // bin and the E-th largest exact one within the slack of it: a row more than twice the slack above the bin is evicted
+    // whatever its exact score, one as far below it stays, and those between are candidates (the last term covers the
+    // rounding of the bin edges).
+    const float reach = approx ? 2.f * SCORE_SLACK + 1e-6f : 0.f;
     auto evict = [&](int i) {   // marks row i and appends it to the (unordered) list
         atomicOr(&evbits[i >> 5], 1u << (i & 31));
         const uint32_t at = atomicAdd(&sh.nev, 1u);
@@ -495,10 +540,18 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     };
     uint32_t mine_above = 0;   // the thread's rows above the bin: listed after the pass, so that the pass itself waits for nothing
     for_rows([&](int i, float s, int32_t pi, int k) {
-        // bin of the row, -1 if it cannot be evicted (exempt)
-        const int sb = !exempt(pi) ? score_bin(s) : -1;
-        if (sb > tb) mine_above |= 1u << k;
-        else if (sb == tb) {
+        if (exempt(pi)) return;
+        bool above_bin, in_bin;
+        if constexpr (APPROX) {
+            above_bin = score_bin(s - reach) > tb;
+            in_bin = score_bin(s + reach) >= tb;
+        } else {
+            const int sb = score_bin(s);
+            above_bin = sb > tb;
+            in_bin = sb == tb;
+        }
+        if (above_bin) mine_above |= 1u << k;
+        else if (in_bin) {
             const uint32_t c = atomicAdd(&sh.ncand, 1u);
             if (c < CAND_MAX) {
                 sh.cand_slot[c] = (uint32_t)i;
@@ -509,7 +562,46 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     });
     for (; mine_above; mine_above &= mine_above - 1) evict(row_of(__ffs(mine_above) - 1));
     __syncthreads();
-    const uint32_t ncand = sh.ncand;
+    const uint32_t ncand = sh.ncand, need = (uint32_t)E - sh.nev;
+    if constexpr (APPROX) {
+    if (approx && (sh.bad || ncand > CAND_MAX)) {   // uniform
+        // rare: nearly identical keys, or keys out of the range of the approximation
+        for (int r0 = 0; r0 < p.n; r0 += THREADS / UPR) {   // uniform
+            const int i = r0 + tid / UPR;
+            const float s = exact_score(min(i, p.n - 1));
+            if (i < p.n && tid % UPR == 0) {
+                if constexpr (RES) sc_l[i] = s;
+                else p.scores[(size_t)bh * p.cap + i] = s;
+            }
+        }
+        for (int i = tid; i < HIST_BINS; i += THREADS) sh.hist[i] = 0;
+        for (int i = tid; i < nwords; i += THREADS) evbits[i] = 0;
+        __syncthreads();
+        if (tid == 0) sh.ncand = sh.nev = 0;
+        if constexpr (SRC > 0) {
+#pragma unroll
+            for (int q = 0; q < NQ4; ++q) {
+                const int i = 4 * (q * THREADS + tid);
+                if (i < p.n) sreg[q] = *reinterpret_cast<const f32x4 *>(sc_g + i);
+            }
+        }
+        approx = false;
+        __syncthreads();
+        continue;
+    }
+    if (approx) {
+        for (uint32_t c0 = 0; c0 < ncand; c0 += THREADS / UPR) {   // uniform
+            const uint32_t c = c0 + tid / UPR;
+            const float s = exact_score((int)sh.cand_slot[min(c, ncand - 1)]);
+            if (c < ncand && tid % UPR == 0) sh.cand_key[c] = orderable(s);
+        }
+        __syncthreads();
+    }
+    }   // APPROX
+    if constexpr (SRC > 0 && !PREG) {
+        for (uint32_t c = tid; c < min(ncand, (uint32_t)CAND_MAX); c += THREADS) sh.cand_pos[c] = pos[sh.cand_slot[c]];
+        __syncthreads();
+    }
     KD_TL(5);   // candidates collected
 
     // ---- 3. exact ranking inside the bin by (score bits, position), largest first: a wave takes a
@@ -532,7 +624,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         }
         __syncthreads();
     } else {
-        radix_select_in_bin<THREADS>(p, sh, RES ? sc_l : sc_g, RES ? pos_l : pos, evbits, tb, need);
+        radix_select_in_bin<THREADS>(p, sh, RES ? sc_l : sc_g, RES ? pos_l : pos, evbits, tb, need);   // (exact scores here)
         for_rows([&](int i, float s, int32_t, int) {   // (it marks rows of the bin; they join the list here)
             if (score_bin(s) == tb && ((evbits[i >> 5] >> (i & 31)) & 1u)) {
                 const uint32_t at = atomicAdd(&sh.nev, 1u);
@@ -541,7 +633,9 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         });
         __syncthreads();
     }
-    }   // E > 1
+    break;
+    }   // for (;;)
+    }   // E > 1, or approximate scores
     KD_TL(6);   // ranking done: the eviction bitmap and the list of evicted rows are final
 
     int32_t *evlist = lists, *holes = lists + E;
@@ -559,7 +653,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     constexpr int RPW = 64 / UPR;
     const int eu = lane % UPR, erl = lane / UPR;
     // the rows of up to EV_BATCH rounds are requested together: one memory round trip, not one per round
-    constexpr int EV_BATCH = 4;
+    constexpr int EV_BATCH = SRC > 3 ? 2 : 4;
     u32x4 wv[EV_BATCH];
     auto request = [&](int rb0) {
 #pragma unroll
@@ -571,6 +665,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     };
     const bool sorted = p.anchor_mode == 1;   // uniform
     if (!sorted) request(wave * RPW);
+    if constexpr (!EARLY_TAIL) request_tail();
     uint32_t *word_base = sh.cand_slot;   // the candidate arrays are free by now
     static_assert(MAX_CAP / 32 <= CAND_MAX, "one count per bitmap word");
     {
@@ -682,7 +777,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         // the LDS copy nothing can be overwritten before it is read; reading from memory, the rows are taken in
         // ascending chunks, each read, then (barrier) written.
         int32_t *dst = p.dstmap + (size_t)bh * p.cap;
-        if constexpr (SRC > 0) {
+        if constexpr (PREG) {
 #pragma unroll
             for (int q = 0; q < NQ4; ++q) {
                 const int i = 4 * (q * THREADS + tid);

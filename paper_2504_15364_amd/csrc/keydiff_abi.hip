@@ -29,7 +29,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Layout {
     size_t k_bytes, meta_bytes, scratch_bytes;
     size_t off_pos, off_ksum, off_status, off_oflags;                                 // in meta
-    size_t off_part_o, off_part_ml, off_scores, off_dstmap, off_lists, off_ksum_part, off_q_rot, off_k_rot, off_argmax;  // in scratch
+    size_t off_part_o, off_part_ml, off_scores, off_dstmap, off_lists, off_ksum_part, off_anchor, off_q_rot, off_k_rot, off_argmax;  // in scratch
     int cap, max_part_rows;
     int target_wgs;   // bound used to size the partial buffers: twice the compute units of the chip
 };
@@ -134,7 +134,9 @@ Layout make_layout(const keydiff_config_t *c)
     L.off_scores = off;     off += align256(BH * L.cap * 4);
     L.off_dstmap = off;     off += align256(BH * L.cap * 4);
     L.off_lists = off;      off += align256(BH * 4 * (size_t)c->block_B * 4);
-    L.off_ksum_part = off;  off += align256(BH * chunks * D * 8);
+    L.off_ksum_part = off;  off += align256(BH * (chunks > 1 ? chunks : 2) * D * 8);   // (at least the step anchor below)
+    // the anchor of a step for its selection: shares the region of the key-sum partials, which only a cache load uses
+    L.off_anchor = L.off_ksum_part;
     L.off_q_rot = off;      off += align256((size_t)c->batch * c->n_q_heads * c->block_B * D * 2);   // rotated block (rope entry points)
     L.off_k_rot = off;      off += align256(BH * c->block_B * D * 2);
     L.off_argmax = off;     off += align256((size_t)(kTargetWorkgroups + BH) * 16);   // one arg-max record per step_main workgroup
@@ -238,6 +240,7 @@ kd::StepParams base_params(const keydiff_cache *c, int n, unsigned char *scratch
     p.part_ml = reinterpret_cast<float2 *>(scratch + c->L.off_part_ml);
     p.scores = reinterpret_cast<float *>(scratch + c->L.off_scores);
     p.dstmap = reinterpret_cast<int32_t *>(scratch + c->L.off_dstmap);
+    p.anchor = reinterpret_cast<double *>(scratch + c->L.off_anchor);
     p.lists = reinterpret_cast<int32_t *>(scratch + c->L.off_lists);
     p.batch = cf.batch;
     p.hq = cf.n_q_heads;
@@ -435,6 +438,12 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     p.pos0 = (int32_t)pos0;
     p.do_evict = evict;
     p.do_score = evict || scores_out != nullptr;
+    // Approximate scores where the selection can ride in another launch: they take 4 us off the attention at 8192 keys and
+    // add 4 us to the selection, which then scores the rows near its threshold exactly.  As a passenger it hides
+    // that; as the launch the caller waits for it does not (attention + selection, 32 / 8 heads: 30.0 and 32.6 us at
+    // 4096 keys with exact and approximate scores, 39.8 and 42.0 at 8192, 48.1 and 49.9 at 12000).  Scores
+    // the caller asks for are exact; so are those of step_few, see below.
+    p.score_approx = defer && carry != nullptr && evict;
     if (cf.window_W > 0) p.window_pos_min = (int32_t)(pos0 + Bt - cf.window_W);
 
     // a passenger rides only if the attention still fits the chip in one pass beside it
@@ -457,10 +466,11 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     }
     if (shift_parts == 0 && !riding) plan_attention(c, p);
     const int shift_wgs = shift_parts > 0 ? shift_parts * shifted->shift_p.batch * shifted->shift_p.hkv : 0;
-    // Generation phase: the attention launch's scoring waves (the kernels with helper waves) leave the
+    if (p.few) p.score_approx = 0;
+    // Generation phase: step_few leaves the
     // arg-max of the scores per workgroup, and the selection reads the row to evict off those records.
     if (evict && n - N == 1 && cf.window_W == 0 && cf.layout == KEYDIFF_LAYOUT_FILL &&
-        (p.few || p.mtiles * 32 * p.NW - p.G * p.Bt >= 32) && (size_t)p.batch * p.hkv * p.splits <= (size_t)c->L.target_wgs + p.batch * p.hkv)
+        p.few && (size_t)p.batch * p.hkv * p.splits <= (size_t)c->L.target_wgs + p.batch * p.hkv)
         p.argmax_rec = reinterpret_cast<unsigned long long *>(work + c->L.off_argmax);
 
     // ---- launches from here on

@@ -833,3 +833,32 @@ def test_steps_with_few_query_rows(hq, hkv, d, N, sizes, anchor):
         t += Bt
     assert cache.status() == 0
     cache.close()
+
+
+@pytest.mark.parametrize("kind", ["zero", "tiny", "huge", "all-small", "one-by-one"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_deferred_scores_outside_the_range_of_the_matrix_pipe(kind, d):
+    # With the eviction deferred the attention leaves approximate scores (float sums on the matrix pipe) and the
+    # selection scores the rows near its threshold exactly; rows whose norms leave the range of the approximation send it
+    # to the exact scores of every row.  Zero keys (which stay in range), keys of 2^-50 and 2^45 among ordinary ones, all
+    # keys of 2^-30, and a first eviction of a single row.  Queries are zero: only the
+    # eviction is at stake, and keys of 2^45 would otherwise decide the softmax by rounding.
+    N, B = (320, 64) if kind != "one-by-one" else (255, 64)
+    w = get_config("llama31_8b").small(n_q_heads=8, n_kv_heads=2, head_dim=d, prompt_T=N + 6 * B)
+    rng = np.random.default_rng(5)
+    datas = []
+    for seed in (81, 82):
+        data = make_layer(w, seed=seed)
+        k = bf16_bits_to_f32(data["k"]).copy()
+        rows = rng.random(k.shape[:2]) < 0.05
+        if kind == "zero":
+            k[rows] = 0.0
+        elif kind == "tiny":
+            k[rows] *= np.float32(2.0 ** -50)
+        elif kind == "huge":
+            k[rows] *= np.float32(2.0 ** 45)
+        elif kind == "all-small":
+            k *= np.float32(2.0 ** -30)
+        datas.append(dict(data, k=f32_to_bf16_bits(k), q=np.zeros_like(data["q"])))
+    run_layers_deferred(w, N, B, 2, seeds=None, check_every=1, expect_ride=None, datas=datas, layout=kd.LAYOUT_FILL)
+    run_layers_deferred(w, N, B, 2, seeds=None, check_every=0, expect_ride=True, datas=datas, layout=kd.LAYOUT_ORDERED)
