@@ -496,11 +496,14 @@ __global__ void ksum_final_kernel(const double *partials, double *ksum, int nchu
 // sum rounded to float on its own, then one rounding to bf16.
 // rows: all (sequence, head) rows of q followed by those of k_new, Bt tokens each; a thread takes the
 // 8 + 8 paired elements of one 16-byte unit of the first half.
+// blockIdx.y: the layer (a call through several layers rotates the blocks of all of them in one launch: with one launch a
+// layer the rotation of a 128-token block, 24 / 8 heads, took 3.7 us of kernel and a launch of its own in every layer).
 template <int D>
-__global__ __launch_bounds__(256) void rope_kernel(const uint16_t *q, const uint16_t *k, uint16_t *q_rot, uint16_t *k_rot,
-                                                   const float *cos_t, const float *sin_t, int q_rows, int k_rows, int Bt,
-                                                   int32_t pos0)
+__global__ __launch_bounds__(256) void rope_kernel(RopeBatch in, const float *cos_t, const float *sin_t, int q_rows, int k_rows,
+                                                   int Bt, int32_t pos0)
 {
+    const uint16_t *q = in.q[blockIdx.y], *k = in.k[blockIdx.y];
+    uint16_t *q_rot = in.q_rot[blockIdx.y], *k_rot = in.k_rot[blockIdx.y];
     constexpr int UPH = D / 16;   // 16-byte units per half row
     const size_t gid = (size_t)blockIdx.x * 256 + threadIdx.x;
     const size_t row = gid / UPH;
@@ -686,13 +689,14 @@ hipError_t launch_ksum_rebuild(const StepParams &p, double *partials, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_rope(const uint16_t *q, const uint16_t *k, uint16_t *q_rot, uint16_t *k_rot, const float *cos_t,
-                       const float *sin_t, int q_rows, int k_rows, int Bt, int D, int32_t pos0, hipStream_t s)
+hipError_t launch_rope(const RopeBatch &b, const float *cos_t, const float *sin_t, int q_rows, int k_rows, int Bt, int D,
+                       int32_t pos0, hipStream_t s)
 {
+    if (b.layers < 1 || b.layers > ROPE_LAYERS) return hipErrorInvalidValue;
     const size_t threads = ((size_t)q_rows + k_rows) * (D / 16);
-    const unsigned grid = (unsigned)((threads + 255) / 256);
-    if (D == 128) hipLaunchKernelGGL((rope_kernel<128>), dim3(grid), dim3(256), 0, s, q, k, q_rot, k_rot, cos_t, sin_t, q_rows, k_rows, Bt, pos0);
-    else if (D == 64) hipLaunchKernelGGL((rope_kernel<64>), dim3(grid), dim3(256), 0, s, q, k, q_rot, k_rot, cos_t, sin_t, q_rows, k_rows, Bt, pos0);
+    const dim3 grid((unsigned)((threads + 255) / 256), (unsigned)b.layers);
+    if (D == 128) hipLaunchKernelGGL((rope_kernel<128>), grid, dim3(256), 0, s, b, cos_t, sin_t, q_rows, k_rows, Bt, pos0);
+    else if (D == 64) hipLaunchKernelGGL((rope_kernel<64>), grid, dim3(256), 0, s, b, cos_t, sin_t, q_rows, k_rows, Bt, pos0);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -112,10 +112,16 @@ hipError_t launch_compact_ordered(const StepParams &p, int32_t *flags, int32_t e
 // the merge of pm's partials and the ordered shift of ps's cache in one launch (same head_dim)
 hipError_t launch_merge_shift(const StepParams &pm, const StepParams &ps, int32_t *flags, int32_t epoch, hipStream_t s);
 hipError_t launch_ksum_rebuild(const StepParams &p, double *partials, hipStream_t s);
-// rotary embedding of the block's queries (q_rows rows) and keys (k_rows rows), Bt tokens per (sequence,
+// rotary embedding of the blocks' queries (q_rows rows each) and keys (k_rows rows), Bt tokens per (sequence,
 // head) at positions pos0 + j, by the caller's float tables [position][D / 2]
-hipError_t launch_rope(const uint16_t *q, const uint16_t *k, uint16_t *q_rot, uint16_t *k_rot, const float *cos_t,
-                       const float *sin_t, int q_rows, int k_rows, int Bt, int D, int32_t pos0, hipStream_t s);
+constexpr int ROPE_LAYERS = 32;      // blocks one launch rotates
+struct RopeBatch {
+    const uint16_t *q[ROPE_LAYERS], *k[ROPE_LAYERS];
+    uint16_t *q_rot[ROPE_LAYERS], *k_rot[ROPE_LAYERS];
+    int layers;
+};
+hipError_t launch_rope(const RopeBatch &b, const float *cos_t, const float *sin_t, int q_rows, int k_rows, int Bt, int D,
+                       int32_t pos0, hipStream_t s);
 hipError_t launch_zero_words(int32_t *p, size_t nwords, hipStream_t s);
 hipError_t launch_load_rows(const uint16_t *src, uint16_t *dst, int BH, int cap, int D, int len,
                             hipStream_t s);

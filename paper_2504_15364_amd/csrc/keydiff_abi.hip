@@ -479,8 +479,14 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
         uint16_t *q_rot = reinterpret_cast<uint16_t *>(work + c->L.off_q_rot);
         uint16_t *k_rot = reinterpret_cast<uint16_t *>(work + c->L.off_k_rot);
         ProfScope ps(c, KEYDIFF_K_AUX, s);
-        KD_LAUNCH(kd::launch_rope(p.q, p.k_new, q_rot, k_rot, rope->cos_t, rope->sin_t, cf.batch * cf.n_q_heads * Bt,
-                                  cf.batch * cf.n_kv_heads * Bt, Bt, cf.head_dim, (int32_t)pos0, s),
+        kd::RopeBatch b{};
+        b.layers = 1;
+        b.q[0] = p.q;
+        b.k[0] = p.k_new;
+        b.q_rot[0] = q_rot;
+        b.k_rot[0] = k_rot;
+        KD_LAUNCH(kd::launch_rope(b, rope->cos_t, rope->sin_t, cf.batch * cf.n_q_heads * Bt, cf.batch * cf.n_kv_heads * Bt,
+                                  Bt, cf.head_dim, (int32_t)pos0, s),
                   "rotary embedding kernel");
         p.q = q_rot;
         p.k_new = k_rot;
@@ -721,14 +727,44 @@ static int block_layers(keydiff_cache_t *const *caches, int32_t n_layers, const 
             if (caches[m] == caches[l]) return fail(KEYDIFF_EINVAL, "layers %d and %d share a cache", m, l);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // The blocks of all layers rotated ahead, up to 32 layers a launch, into the layers' own scratch regions (which nothing
+    // but the step of the same layer reads).  Only where every layer would pass the checks of its step that the
+    // rotation depends on and the layers are shaped alike; else each step rotates its own block, so that what
+    // is enqueued before an error is found is the same as ever.
+    bool rotated = rope && n_layers > 1 && rope->cos_t && rope->sin_t && !misaligned(rope->cos_t) && !misaligned(rope->sin_t) &&
+                   Bt >= 1 && pos0 >= 0 && pos0 + Bt <= 0x7fffffffLL && pos0 + Bt <= rope->rows;
+    for (int l = 0; l < n_layers && rotated; ++l) {
+        const keydiff_config_t &cf = caches[l]->cfg, &c0 = caches[0]->cfg;
+        rotated = cf.batch == c0.batch && cf.n_q_heads == c0.n_q_heads && cf.n_kv_heads == c0.n_kv_heads &&
+                  cf.head_dim == c0.head_dim && Bt <= cf.block_B && !misaligned(q[l]) && !misaligned(k_new[l]) &&
+                  !misaligned(v_new[l]) && !misaligned(out[l]);
+    }
+    for (int l0 = 0; rotated && l0 < n_layers; l0 += kd::ROPE_LAYERS) {
+        const keydiff_config_t &cf = caches[l0]->cfg;
+        kd::RopeBatch b{};
+        b.layers = n_layers - l0 < kd::ROPE_LAYERS ? n_layers - l0 : kd::ROPE_LAYERS;
+        for (int i = 0; i < b.layers; ++i) {
+            keydiff_cache *c = caches[l0 + i];
+            b.q[i] = static_cast<const uint16_t *>(q[l0 + i]);
+            b.k[i] = static_cast<const uint16_t *>(k_new[l0 + i]);
+            b.q_rot[i] = reinterpret_cast<uint16_t *>(c->scratch + c->L.off_q_rot);
+            b.k_rot[i] = reinterpret_cast<uint16_t *>(c->scratch + c->L.off_k_rot);
+        }
+        ProfScope ps(caches[l0], KEYDIFF_K_AUX, s);
+        KD_LAUNCH(kd::launch_rope(b, rope->cos_t, rope->sin_t, cf.batch * cf.n_q_heads * Bt, cf.batch * cf.n_kv_heads * Bt,
+                                  Bt, cf.head_dim, (int32_t)pos0, s),
+                  "rotary embedding kernel");
+    }
     for (int l = 0; l < n_layers; ++l) {
+        const void *ql = rotated ? caches[l]->scratch + caches[l]->L.off_q_rot : q[l];
+        const void *kl = rotated ? caches[l]->scratch + caches[l]->L.off_k_rot : k_new[l];
         // layer 0 takes along what the last layer left pending at the previous block
         keydiff_cache *carry = n_layers > 1 ? caches[(l + n_layers - 1) % n_layers] : nullptr;
         // ... and, ORDERED layout, the row shift of the layer before that one, whose selection rode in the
         // launch of the layer between them
         keydiff_cache *shifted = n_layers > 2 ? caches[(l + n_layers - 2) % n_layers] : nullptr;
-        if (int rc = block_step(caches[l], q[l], k_new[l], v_new[l], Bt, pos0, out[l], nullptr, true, carry,
-                                caches[l]->scratch, s, rope, shifted, n_layers > 2))
+        if (int rc = block_step(caches[l], ql, kl, v_new[l], Bt, pos0, out[l], nullptr, true, carry,
+                                caches[l]->scratch, s, rotated ? nullptr : rope, shifted, n_layers > 2))
             return rc;
     }
     return KEYDIFF_OK;

@@ -862,3 +862,32 @@ def test_deferred_scores_outside_the_range_of_the_matrix_pipe(kind, d):
         datas.append(dict(data, k=f32_to_bf16_bits(k), q=np.zeros_like(data["q"])))
     run_layers_deferred(w, N, B, 2, seeds=None, check_every=1, expect_ride=None, datas=datas, layout=kd.LAYOUT_FILL)
     run_layers_deferred(w, N, B, 2, seeds=None, check_every=0, expect_ride=True, datas=datas, layout=kd.LAYOUT_ORDERED)
+
+
+@pytest.mark.parametrize("heads", [[(4, 2)] * 33, [(4, 2), (8, 2), (4, 2)]], ids=["33-layers", "layers-shaped-differently"])
+def test_rope_of_all_layers_is_the_rotation_of_each(heads):
+    # prefill_block_layers rotates the blocks of up to 32 layers in one launch where the layers are shaped alike, layer by
+    # layer otherwise: outputs, rows and positions are those of the call on blocks rotated beforehand, bit for bit
+    d, N, B, T = 64, 48, 16, 96
+    rng = np.random.default_rng(3)
+    cos, sin = rope_tables(0, T, d, 1e4)
+    tabs = (torch.from_numpy(cos).cuda(), torch.from_numpy(sin).cuda())
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, B, layout=kd.LAYOUT_FILL)) for hq, hkv in heads] for _ in range(2))
+    for t in range(0, T, B):
+        raw, rot, vs = [], [], []
+        for hq, hkv in heads:
+            q, k, v = (f32_to_bf16_bits(rng.standard_normal((1, h, B, d), dtype=np.float32)) for h in (hq, hkv, hkv))
+            turn = lambda x: f32_to_bf16_bits(apply_rope(bf16_bits_to_f32(x)[0].transpose(1, 0, 2), cos[t:t + B], sin[t:t + B])
+                                              .transpose(1, 0, 2)[None])
+            raw.append((to_dev(q), to_dev(k)))
+            rot.append((to_dev(turn(q)), to_dev(turn(k))))
+            vs.append(to_dev(v))
+        oa = kd.prefill_block_layers(a, [x[0] for x in raw], [x[1] for x in raw], vs, t, rope=tabs)
+        ob = kd.prefill_block_layers(b, [x[0] for x in rot], [x[1] for x in rot], vs, t)
+        assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(oa, ob)), t
+    for x, y in zip(a, b):
+        px, kx, vx = rows_by_position(x)
+        py, ky, vy = rows_by_position(y)
+        assert np.array_equal(px, py) and np.array_equal(kx, ky) and np.array_equal(vx, vy)
+        x.close()
+        y.close()
