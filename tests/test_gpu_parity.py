@@ -891,3 +891,19 @@ def test_rope_of_all_layers_is_the_rotation_of_each(heads):
         assert np.array_equal(px, py) and np.array_equal(kx, ky) and np.array_equal(vx, vy)
         x.close()
         y.close()
+
+
+@pytest.mark.parametrize("n", [1, 127, 129, 1030, 1153])
+@pytest.mark.parametrize("d", [64, 128])
+def test_key_sum_of_a_loaded_cache(n, d):
+    # the chunks of 128 rows whose sums a load adds up: one, a ragged one, more than the eight shares they are dealt to
+    w = get_config("llama32_3b").small(n_q_heads=4, n_kv_heads=2, head_dim=d, prompt_T=n)
+    data = make_layer(w, seed=600 + n)
+    for anchor in (kd.ANCHOR_MEAN_KEY, kd.ANCHOR_MEAN_UNIT_KEY):
+        cache, oc = make_pair(w, n, 8, anchor_mode=anchor)
+        k, v = (block_of(data[x], 0, n)[None] for x in ("k", "v"))
+        pos = np.broadcast_to(np.arange(n, dtype=np.int32), (1, 2, n)).copy()
+        cache.load(to_dev(k), to_dev(v), torch.from_numpy(pos).cuda())
+        oc.load(k, v, pos)
+        assert np.allclose(cache.scores().cpu().numpy(), oc.scores(), rtol=SCORE_RTOL, atol=SCORE_ATOL)
+        cache.close()
