@@ -625,7 +625,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
             if (row < p.n) {
                 double nmu2 = 0.0;
 #pragma unroll
-                for (int w = 0; w < NW; ++w) nmu2 += (red[w][0] + red[w][1]) + (red[w][2] + red[w][3]);
+                for (int w = 0; w < D / 64; ++w) nmu2 += (red[w][0] + red[w][1]) + (red[w][2] + red[w][3]);   // (the waves that formed it; all eight: 0.4 us a flush more)
                 const float sc = finish_score(st_dot[wave][lane], st_k2[wave][lane], sqrt(nmu2), p.eps);
                 p.scores[(size_t)bh * p.cap + row] = sc;
                 if (p.scores_out) p.scores_out[(size_t)bh * p.n + row] = sc;
