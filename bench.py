@@ -130,7 +130,7 @@ def bench_decode(args, w):
     if "step_main" in kernels:
         t_main = kernels["step_main"]["avg_us"] * 1e-6
         achieved = kv_bytes / t_main / 1e9
-        roofline = {"bound": "hbm", "kernel": "step_main_kernel (helper waves, alternating tiles)", "achieved": achieved,
+        roofline = {"bound": "hbm", "kernel": "step_few_kernel", "achieved": achieved,
                     "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": achieved / PEAK_HBM_GBPS,
                     "traffic": measured_traffic(w.name, "fill"), "bytes_per_launch": kv_bytes,
                     "avg_launch_us": kernels["step_main"]["avg_us"]}

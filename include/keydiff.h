@@ -37,8 +37,8 @@
  *     gives a thread-local message.  No exception crosses this boundary.
  *   - Inputs must be finite, and values (v_new, and what keydiff_cache_load brings in) must not exceed
  *     65504 in magnitude: where the keys of a step are cut into several ranges, the attention output
- *     of each range travels as fp16, normalised by its own weight sum (so it is bounded by the largest
- *     |v| it covers), before the ranges are merged; a larger value would become infinite there.  The
+ *     of each range travels as fp16 (float where a KV head has at most 32 query rows), normalised by its
+ *     own weight sum (so it is bounded by the largest |v| it covers), before the ranges are merged; a larger value would become infinite there.  The
  *     library does not check this.  Queries and keys have no such limit.
  *   - Scores are IEEE double arithmetic on the bf16
  *     data rounded once to float; the eviction decision is taken on that float
@@ -161,8 +161,8 @@ KEYDIFF_API int keydiff_prefill_block_static(keydiff_cache_t *cache, const void 
  * `cache` are the n = len + Bt rows before compaction and its scratch buffer is in use: a
  * cache used this way needs a scratch buffer of its own.  In the ORDERED layout only the
  * selection rides; the stable row shift of `carry` follows in the same call, inside this step's
- * merge launch (or in a launch of its own where the step has none).  The scores and the retained set are those
- * of keydiff_prefill_block bit for bit; `out` may differ in the last bf16 bit, because the
+ * merge launch (or in a launch of its own where the step has none).  The retained set is that
+ * of keydiff_prefill_block bit for bit (the scores behind it are exact only for the rows near the threshold); `out` may differ in the last bf16 bit, because the
  * keys are cut into a different number of ranges when passengers take part of the chip.    */
 KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const void *q, const void *k_new,
                                    const void *v_new, int32_t Bt, int64_t pos0, void *out,
@@ -194,7 +194,7 @@ KEYDIFF_API int keydiff_prefill_block_layers(keydiff_cache_t *const *caches, int
  * can live behind this boundary; the paper's method takes the keys as the cache holds them, i.e.
  * rotated).  q and k_new arrive as the projections produced them; they are rotated at the positions
  * pos0 + j (row j of the block) into buffers inside the scratch buffer, by one more launch ahead of
- * the step's own, and everything after that is keydiff_prefill_block / _layers on the rotated block.
+ * the step's own (_layers: one for up to 32 layers of the same shape, ahead of the first step), and everything after that is keydiff_prefill_block / _layers on the rotated block.
  *   cos_table, sin_table  device, float [table_rows][head_dim / 2], 16-byte aligned: cosine and sine of
  *                         the angle of position p (row p) and frequency i (column i)
  *   pairing               element i of a row is rotated with element i + head_dim / 2:

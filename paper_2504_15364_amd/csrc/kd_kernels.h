@@ -4,6 +4,7 @@
 //   step_main  append (Eq. 5) + split-KV flash attention partials (Eq. 1-2)
 //              + running key sum S' = S + sum of the block's keys (the anchor is S' / n)
 //              + cosine score of every row, taken from the K tiles while they sit in LDS
+//              (step_few instead where a KV head has at most FEW_ROWS query rows)
 //   step_post  merge of the attention partials  ||  selection of the rows to evict
 //              and compaction, one workgroup per head (Eq. 6-7)
 // plus, for the ORDERED layout only, one more launch that shifts rows in place.
