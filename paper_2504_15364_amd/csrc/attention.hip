@@ -86,13 +86,9 @@ __device__ __forceinline__ void async_copy16(uint32_t lds_base, const void *gbas
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(base), "v"(byte_off), "s"(gu) : "memory");
 }
 
-// max(a, b, c) without the NaN canonicalisation fmaxf carries (logits are finite or -inf)
-__device__ __forceinline__ float max3_raw(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
+// max(a, b, c), one v_max3_f32.  Left to the compiler, not written as an instruction: it reads results of the matrix
+// pipe, and only an instruction the compiler knows gets the wait states such a read needs (a 32x32x16 product: 12).
+__device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
 // Lane i and lane i ^ 32 hold the two halves of a query's keys (accumulator rows 4 h + ...).  One
 // v_permlane32_swap hands each the other's value without a trip through LDS: of the pair it
@@ -101,7 +97,7 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c)
 __device__ __forceinline__ float max_halves(float x)
 {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return max3_raw(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[0]));
+    return __builtin_elementwise_maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));   // (fmaxf would quiet both first)
 }
 
 template <int N>
@@ -556,9 +552,9 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     auto tile_max = [&](const f32x16 (&s)[NQ][2], float (&mloc)[NQ]) {
 #pragma unroll
         for (int a = 0; a < NQ; ++a) {
-            mloc[a] = max3_raw(s[a][0][0], s[a][1][0], s[a][0][0]);
+            mloc[a] = max3(s[a][0][0], s[a][1][0], s[a][0][0]);
 #pragma unroll
-            for (int e = 1; e < 16; ++e) mloc[a] = max3_raw(mloc[a], s[a][0][e], s[a][1][e]);
+            for (int e = 1; e < 16; ++e) mloc[a] = max3(mloc[a], s[a][0][e], s[a][1][e]);
         }
     };
     // LDS fragment reads
@@ -999,8 +995,8 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 #pragma unroll
                     for (int r = 0; r < PER; ++r) {
                         const int e = PER * j + r;
-                        mch[a][e & 1] = e < 2 ? max3_raw(sn[a][0][e], sn[a][1][e], sn[a][0][e])
-                                              : max3_raw(mch[a][e & 1], sn[a][0][e], sn[a][1][e]);
+                        mch[a][e & 1] = e < 2 ? max3(sn[a][0][e], sn[a][1][e], sn[a][0][e])
+                                              : max3(mch[a][e & 1], sn[a][0][e], sn[a][1][e]);
                     }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1017,7 +1013,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 #endif
         float mloc[NQ];
 #pragma unroll
-        for (int a = 0; a < NQ; ++a) mloc[a] = NEXT ? max3_raw(mch[a][0], mch[a][1], mch[a][0]) : 0.f;
+        for (int a = 0; a < NQ; ++a) mloc[a] = NEXT ? max3(mch[a][0], mch[a][1], mch[a][0]) : 0.f;
         if (NEXT) {
             new_reference(mloc);
         }

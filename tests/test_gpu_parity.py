@@ -907,3 +907,33 @@ def test_key_sum_of_a_loaded_cache(n, d):
         oc.load(k, v, pos)
         assert np.allclose(cache.scores().cpu().numpy(), oc.scores(), rtol=SCORE_RTOL, atol=SCORE_ATOL)
         cache.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hq,B", [(8, 128), (8, 16)], ids=["full-row-tiles", "helper-waves"])
+def test_first_reference_covers_the_last_dimensions(hq, B, d):
+    # The first running maximum of a query row is taken from the first key tile's logits right behind the product that
+    # completes them.  Here the last 16 dimensions, whose product is the last to be added, lift logits by far more than
+    # 2^127: a maximum taken a product too early would leave weights that overflow.  And a step is repeatable bit for bit.
+    w = get_config("llama31_8b").small(n_q_heads=hq, n_kv_heads=2, head_dim=d, prompt_T=512 + 2 * B)
+    data = dict(make_layer(w, seed=91 + d))
+    for x in ("q", "k"):
+        a = bf16_bits_to_f32(data[x]).copy()
+        a[..., -16:] = 9.0 * np.sign(a[..., -16:])   # q.k / sqrt(d): up to 16 * 81 / sqrt(d) from them
+        data[x] = f32_to_bf16_bits(a)
+    data["v"] = f32_to_bf16_bits(0.25 * bf16_bits_to_f32(data["v"]))   # (one key decides a row: its output is as large as v)
+    outs = []
+    for _ in range(2):
+        cache, oc = make_pair(w, 512, max(B, 64), layout=kd.LAYOUT_FILL)
+        got = []
+        for t, Bt in [(s, 64) for s in range(0, 512, 64)] + [(512, B), (512 + B, B)]:
+            q, k, v = (block_of(data[x], t, Bt)[None] for x in ("q", "k", "v"))
+            out = cache.prefill_block(to_dev(q), to_dev(k), to_dev(v), t)
+            ref, _, _ = oc.prefill_block(q, k, v, t)
+            assert np.abs(bf16_out_to_f32(out) - ref).max() <= ATTN_ATOL, (t, Bt)
+            got.append(out)
+        outs.append(got)
+        check_state(cache, oc, "at the end")
+        assert cache.status() == 0
+        cache.close()
+    assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(*outs))
