@@ -68,11 +68,12 @@ constexpr int STAGES = 4;             // LDS ring: tiles t - 1 and t in use, STA
 // Asynchronous 16-byte-per-lane copy global -> LDS.  `lds_base` is wave uniform; lane i writes
 // bytes [16 i, 16 i + 16) above it.  Issued through asm so that the compiler does not force
 // every outstanding copy to complete before the next LDS read; completion is awaited with
-// explicit s_waitcnt vmcnt(N) (copies complete in issue order).
+// explicit s_waitcnt vmcnt(N) (copies complete in issue order).  The instruction set asks for one wait state between a write
+// of m0, the LDS address, and the copy that uses it.
 __device__ __forceinline__ void async_copy16(uint32_t lds_base, const void *gaddr)
 {
     const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_base);
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(base), "v"(gaddr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(base), "v"(gaddr) : "memory");
 }
 __device__ __forceinline__ void async_copy16(uint32_t lds_base, const void *gbase, uint32_t byte_off)
 {
@@ -83,7 +84,7 @@ __device__ __forceinline__ void async_copy16(uint32_t lds_base, const void *gbas
     const uint32_t g_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)g);
     const uint32_t g_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(g >> 32));
     const uint64_t gu = ((uint64_t)g_hi << 32) | (uint64_t)g_lo;
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(base), "v"(byte_off), "s"(gu) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(base), "v"(byte_off), "s"(gu) : "memory");
 }
 
 // max(a, b, c), one v_max3_f32.  Left to the compiler, not written as an instruction: it reads results of the matrix

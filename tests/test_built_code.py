@@ -109,3 +109,21 @@ def test_matrix_results_are_not_touched_before_they_are_ready(listings):
             code.after(i, stop)
     assert products > 1000
     assert not found, "\n".join(map(str, sorted(found)[:20]))
+
+
+def test_copies_into_lds_wait_for_their_address(listings):
+    # m0 holds the LDS address of a copy: one wait state between the instruction that writes it and the copy
+    found, writes = set(), 0
+    for src, code in listings.items():
+        for i, n in enumerate(code.name):
+            if not (n.startswith("s_") and re.match(r"m0\b", code.args[i])):
+                continue
+            writes += 1
+
+            def stop(j, states):
+                if states == 0 and "_load_lds_" in code.name[j]:
+                    found.add((code.func[i], f"{n} {code.args[i]}", f"{code.name[j]} {code.args[j]}"))
+                return True
+            code.after(i, stop)
+    assert writes > 100
+    assert not found, f"{len(found)}: " + "\n".join(map(str, sorted(found)[:5]))
