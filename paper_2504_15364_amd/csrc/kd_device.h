@@ -34,18 +34,29 @@ namespace kd {
 // the fields of a parameter structure where they are needed, one such trip after another (measured on
 // the attention launch: 1 us).  warm_arguments<BYTES>() requests one word of each cache line of the
 // first BYTES bytes at once, ahead of everything else, and waits for them: later reads find the lines
-// in the scalar cache.  (At most 8 lines; the words themselves are not used.)
+// in the scalar cache.  (At most 8 lines; the words themselves are not used.)  Loads and wait are one block of assembly:
+// nothing the compiler places can come between a load and its arrival.
 template <size_t BYTES>
 __device__ __forceinline__ void warm_arguments()
 {
-    constexpr int LINES = (int)((BYTES + 63) / 64) < 8 ? (int)((BYTES + 63) / 64) : 8;
+    constexpr int LAST = (int)((BYTES + 63) / 64) - 1;   // the last line; where there are fewer lines than loads it is requested again
+    constexpr auto at = [](int line) { return 64 * (line < LAST ? line : LAST); };
     const char *ka = (const char *)__builtin_amdgcn_kernarg_segment_ptr();
-    uint32_t d[LINES];
-#pragma unroll
-    for (int i = 0; i < LINES; ++i) asm volatile("s_load_dword %0, %1, %2" : "=s"(d[i]) : "s"(ka), "n"(64 * i));
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < LINES; ++i) asm volatile("" : : "s"(d[i]));   // the destination registers stay reserved until here
+    uint32_t d0, d1, d2, d3, d4, d5, d6, d7;
+    if constexpr (LAST < 5) {
+        asm volatile("s_load_dword %0, %5, %6\n\ts_load_dword %1, %5, %7\n\ts_load_dword %2, %5, %8\n\t"
+                     "s_load_dword %3, %5, %9\n\ts_load_dword %4, %5, %10\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3), "=&s"(d4)
+                     : "s"(ka), "n"(at(0)), "n"(at(1)), "n"(at(2)), "n"(at(3)), "n"(at(4))
+                     : "memory");
+    } else {
+        asm volatile("s_load_dword %0, %8, %9\n\ts_load_dword %1, %8, %10\n\ts_load_dword %2, %8, %11\n\t"
+                     "s_load_dword %3, %8, %12\n\ts_load_dword %4, %8, %13\n\ts_load_dword %5, %8, %14\n\t"
+                     "s_load_dword %6, %8, %15\n\ts_load_dword %7, %8, %16\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3), "=&s"(d4), "=&s"(d5), "=&s"(d6), "=&s"(d7)
+                     : "s"(ka), "n"(at(0)), "n"(at(1)), "n"(at(2)), "n"(at(3)), "n"(at(4)), "n"(at(5)), "n"(at(6)), "n"(at(7))
+                     : "memory");
+    }
 }
 
 // Asynchronous 16-byte-per-lane copy global -> LDS (no registers).  `lds_base` is uniform over the

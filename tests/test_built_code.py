@@ -127,3 +127,16 @@ def test_copies_into_lds_wait_for_their_address(listings):
             code.after(i, stop)
     assert writes > 100
     assert not found, f"{len(found)}: " + "\n".join(map(str, sorted(found)[:5]))
+
+
+def test_scalar_loads_written_by_hand_wait_in_their_block():
+    # to the compiler the destination of such a load holds the data at once: it may copy or reuse the register while the
+    # load is on its way, unless the wait is part of the same block of assembly
+    blocks = 0
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".hip", ".h")):
+            for asm in re.findall(r"\basm\b(?:\s*volatile)?\s*\((.*?)\);", open(os.path.join(CSRC, name)).read(), re.S):
+                if "s_load" in asm:
+                    blocks += 1
+                    assert "s_waitcnt" in asm, (name, asm)
+    assert blocks > 0
