@@ -108,24 +108,11 @@ __device__ __forceinline__ void wait_copies()  // at most N of this wave's copie
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// the same for a count known only at run time (wave uniform, at most 24)
-__device__ __forceinline__ void wait_copies_upto(int n)
-{
-    switch (n) {
-#define KD_WAIT_CASE(N) case N: wait_copies<N>(); break;
-        KD_WAIT_CASE(1) KD_WAIT_CASE(2) KD_WAIT_CASE(3) KD_WAIT_CASE(4) KD_WAIT_CASE(5) KD_WAIT_CASE(6)
-        KD_WAIT_CASE(7) KD_WAIT_CASE(8) KD_WAIT_CASE(9) KD_WAIT_CASE(10) KD_WAIT_CASE(11) KD_WAIT_CASE(12)
-        KD_WAIT_CASE(13) KD_WAIT_CASE(14) KD_WAIT_CASE(15) KD_WAIT_CASE(16) KD_WAIT_CASE(17) KD_WAIT_CASE(18)
-        KD_WAIT_CASE(19) KD_WAIT_CASE(20) KD_WAIT_CASE(21) KD_WAIT_CASE(22) KD_WAIT_CASE(23) KD_WAIT_CASE(24)
-#undef KD_WAIT_CASE
-        default: wait_copies<0>(); break;
-    }
-}
-
 // Loads into registers that the compiler is not told are loads: it neither counts them nor waits
 // for them.  The registers hold the data only after an explicit wait (wait_copies: these loads and
 // the copies complete in issue order) followed by loads_landed() on them, which is where the code
-// that reads them takes them from.
+// that reads them takes them from.  Until then nothing may touch the registers: the code between has to leave the compiler no
+// reason to (no value that is a load on one path and something else on another); tests/test_built_code.py walks the listing.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u32x4 load16_async(const void *g)
 {
@@ -307,27 +294,17 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     constexpr int BPASS = 4;           // passes loaded together (one batch)
     constexpr int BBATCH = 2;          // batches requested up front
     const int bu = tid % UPR, brl = tid / UPR;
-    const int nbatch = !need_sum ? 0 : min(BBATCH, (p.Bt + BPASS * BROWS - 1) / (BPASS * BROWS));   // uniform
+    // They are requested and waited for whether or not this workgroup sums them and however many there are (rows past the
+    // block repeat its last one; all of them do where nothing is summed): on one path, without a merge of values in
+    // between, the compiler has no reason to move a register whose load is on its way.
     u32x4 kw[BBATCH][BPASS];
-    u32x2 ksum_raw = {0u, 0u};
+    u32x2 ksum_raw = load8_async(p.ksum + (size_t)bh * D + (tid & (D - 1)));
+    const int last_row = p.Bt - 1, first_row = need_sum ? brl : last_row;
 #pragma unroll
     for (int bt = 0; bt < BBATCH; ++bt)
 #pragma unroll
-        for (int ps = 0; ps < BPASS; ++ps) kw[bt][ps] = u32x4{0u, 0u, 0u, 0u};
-    auto request_rows = [&]() {
-        ksum_raw = load8_async(p.ksum + (size_t)bh * D + (tid & (D - 1)));
-#pragma unroll
-        for (int bt = 0; bt < BBATCH; ++bt) {
-            if (bt < nbatch) {
-#pragma unroll
-                for (int ps = 0; ps < BPASS; ++ps) {
-                    const int j = min((bt * BPASS + ps) * BROWS + brl, p.Bt - 1);   // rows past the block: masked below
-                    kw[bt][ps] = load16_async(knew + (size_t)j * D + bu * 8);
-                }
-            }
-        }
-    };
-    if (need_sum) request_rows();
+        for (int ps = 0; ps < BPASS; ++ps)
+            kw[bt][ps] = load16_async(knew + (size_t)min((bt * BPASS + ps) * BROWS + first_row, last_row) * D + bu * 8);
     // then the K half of tile t0 and the queries (what the first S^T reads), then the V half and tile
     // t0 + 1: one memory round trip covers all of it, and the order of arrival is the order of use
     if (ntl > 0) issue_half(t0, false);
@@ -384,7 +361,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 
     // ---- anchor, part 2: the block's rows have landed when only the copies issued behind them remain
     constexpr int QCOPIES = 32 * NQ * ROWB / 1024;   // copies of a wave's query rows
-    const int behind_rows = (ntl > 0 ? LPW : 0) + QCOPIES + (ntl > 1 ? LPW : 0);   // uniform
     double bacc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) bacc[i] = 0.0;
@@ -413,13 +389,14 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         }
     };
     double ksum_before = 0.0;
+    wait_copies<2 * LPW + QCOPIES>();
+    if (ntl < 2) wait_copies<QCOPIES>();   // fewer copies behind them (a range of one tile waits for everything below anyway)
+    loads_landed(ksum_raw, kw);
     if (need_sum) {
-        wait_copies_upto(behind_rows);
-        loads_landed(ksum_raw, kw);
         ksum_before = __hiloint2double((int)ksum_raw[1], (int)ksum_raw[0]);
 #pragma unroll
         for (int bt = 0; bt < BBATCH; ++bt)
-            if (bt < nbatch) add_rows(kw[bt], bt * BPASS * BROWS);
+            if (bt * BPASS * BROWS < p.Bt) add_rows(kw[bt], bt * BPASS * BROWS);
         // a block of more rows than were requested up front (rare): batch by batch, each waiting for
         // everything in flight
         for (int j0 = BBATCH * BPASS * BROWS; j0 < p.Bt; j0 += BPASS * BROWS) {   // uniform

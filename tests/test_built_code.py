@@ -140,3 +140,29 @@ def test_scalar_loads_written_by_hand_wait_in_their_block():
                     blocks += 1
                     assert "s_waitcnt" in asm, (name, asm)
     assert blocks > 0
+
+
+def test_loads_are_waited_for(listings):
+    # ... and where the wait is apart, because copies are to be requested in between, nothing may read or overwrite the
+    # destination of a load on any path from it to a wait for its kind
+    found, loads = set(), 0
+    for src, code in listings.items():
+        for i, n in enumerate(code.name):
+            vector = n.startswith("global_load_dword")
+            if not (vector or n.startswith("s_load_dword")):
+                continue
+            loads += 1
+            dst, counter = registers(code.args[i].split(",")[0]), "vmcnt" if vector else "lgkmcnt"
+
+            def stop(j, states):
+                if code.name[j] == "s_waitcnt" and counter in code.args[j]:
+                    return True
+                first, _, rest = code.args[j].partition(",")
+                in_order = vector and code.name[j].startswith("global_load_dword")   # loads land in the order of issue
+                if dst & (registers(rest) if in_order else registers(code.args[j])):
+                    found.add((code.func[i], f"{n} {code.args[i]}", f"{code.name[j]} {code.args[j]}"))
+                    return True
+                return False
+            code.after(i, stop)
+    assert loads > 500
+    assert not found, f"{len(found)}: " + "\n".join(map(str, sorted(found)[:20]))
