@@ -194,7 +194,9 @@ KEYDIFF_API int keydiff_prefill_block_layers(keydiff_cache_t *const *caches, int
  * can live behind this boundary; the paper's method takes the keys as the cache holds them, i.e.
  * rotated).  q and k_new arrive as the projections produced them; they are rotated at the positions
  * pos0 + j (row j of the block) into buffers inside the scratch buffer, by one more launch ahead of
- * the step's own (_layers: one for up to 32 layers of the same shape, ahead of the first step), and everything after that is keydiff_prefill_block / _layers on the rotated block.
+ * the step's own (_layers: one for up to 32 layers of the same shape, ahead of the first step, unless a layer's
+ * output overlaps the q or k_new of a later layer), and everything after that is keydiff_prefill_block / _layers on
+ * the rotated block.
  *   cos_table, sin_table  device, float [table_rows][head_dim / 2], 16-byte aligned: cosine and sine of
  *                         the angle of position p (row p) and frequency i (column i)
  *   pairing               element i of a row is rotated with element i + head_dim / 2:

@@ -360,6 +360,12 @@ int plan_with_shift(const keydiff_cache *c, kd::StepParams &p, const kd::StepPar
 
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) != 0; }
 
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + b_bytes && y < x + a_bytes;
+}
+
 // ORDERED layout: the stable row shift that follows a selection, by the destination map it wrote
 int compact_ordered(keydiff_cache *c, const kd::StepParams &p, hipStream_t s)
 {
@@ -738,6 +744,11 @@ static int block_layers(keydiff_cache_t *const *caches, int32_t n_layers, const 
         rotated = cf.batch == c0.batch && cf.n_q_heads == c0.n_q_heads && cf.n_kv_heads == c0.n_kv_heads &&
                   cf.head_dim == c0.head_dim && Bt <= cf.block_B && !misaligned(q[l]) && !misaligned(k_new[l]) &&
                   !misaligned(v_new[l]) && !misaligned(out[l]);
+        // ... and where no layer's output is (part of) what a later layer rotates: that layer's block is there only after the
+        // step before it
+        const size_t token = (size_t)cf.batch * Bt * cf.head_dim * 2, q_bytes = token * cf.n_q_heads, k_bytes = token * cf.n_kv_heads;
+        for (int m = 0; m < l && rotated; ++m)
+            rotated = !overlap(out[m], q_bytes, q[l], q_bytes) && !overlap(out[m], q_bytes, k_new[l], k_bytes);
     }
     for (int l0 = 0; rotated && l0 < n_layers; l0 += kd::ROPE_LAYERS) {
         const keydiff_config_t &cf = caches[l0]->cfg;

@@ -937,3 +937,33 @@ def test_first_reference_covers_the_last_dimensions(hq, B, d):
         assert cache.status() == 0
         cache.close()
     assert all(torch.equal(x.view(torch.int16), y.view(torch.int16)) for x, y in zip(*outs))
+
+
+@pytest.mark.parametrize("kind", ["queries", "keys"])
+def test_rope_of_all_layers_sees_what_an_earlier_layer_wrote(kind):
+    # a layer's block may lie in (part of) an earlier layer's output: it is rotated after that layer's step
+    hq, hkv, d, N, B = (4, 2, 64, 48, 16) if kind == "queries" else (4, 4, 64, 48, 16)
+    rng = np.random.default_rng(4)
+    cos, sin = rope_tables(0, 5 * B, d, 1e4)
+    tabs = (torch.from_numpy(cos).cuda(), torch.from_numpy(sin).cuda())
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, B, layout=kd.LAYOUT_FILL)) for _ in range(3)] for _ in range(2))
+    for t in range(0, 5 * B, B):
+        first = [f32_to_bf16_bits(rng.standard_normal((1, h, B, d), dtype=np.float32)) for h in (hq, hkv, hkv)]
+        got = []
+        for caches in (a, b):
+            q, k, v = (to_dev(x) for x in first)
+            # every layer's output is the next layer's block of queries (or of keys)
+            chain = [torch.zeros_like(q) for _ in caches]
+            qs, ks = ([q] + chain[:-1], [k] * 3) if kind == "queries" else ([q] * 3, [k] + chain[:-1])
+            if caches is a:
+                kd.prefill_block_layers(caches, qs, ks, [v] * 3, t, out=chain, rope=tabs)
+            else:
+                for c, x, y, o in zip(caches, qs, ks, chain):
+                    c.prefill_block_rope(x, y, v, t, *tabs, out=o)
+            got.append(chain)
+        for x, y in zip(*got):
+            assert float((x.float() - y.float()).abs().max()) <= ATTN_ATOL, t
+    for x, y in zip(a, b):
+        assert np.array_equal(rows_by_position(x)[0], rows_by_position(y)[0])
+        x.close()
+        y.close()
