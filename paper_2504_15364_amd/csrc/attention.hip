@@ -597,9 +597,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (lane < staged) {
             const int row = st_row[wave][lane];
             if (row < p.n) {
-                double nmu2 = 0.0;
-#pragma unroll
-                for (int w = 0; w < D / 64; ++w) nmu2 += (red[w][0] + red[w][1]) + (red[w][2] + red[w][3]);   // (the waves that formed it; all eight: 0.4 us a flush more)
+                const double nmu2 = sum_of_pieces<D>(&red[0][0]);   // (of the waves that formed it; all eight: 0.4 us a flush more)
                 const float sc = finish_score(st_dot[wave][lane], st_k2[wave][lane], sqrt(nmu2), p.eps);
                 p.scores[(size_t)bh * p.cap + row] = sc;
                 if (p.scores_out) p.scores_out[(size_t)bh * p.n + row] = sc;
@@ -652,7 +650,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         } else {
 #pragma unroll
             for (int ps = 0; ps < PASSES; ++ps) {
-                const double dot = row_allreduce_f64<UPR>(dotp[ps]), k2 = row_allreduce_f64<UPR>(k2p[ps]);
+                const double dot = row_score_sum_f64<UPR>(dotp[ps]), k2 = row_score_sum_f64<UPR>(k2p[ps]);
                 if (u == 0) {
                     const int slot = staged + ps * RPP + rl;
                     st_dot[wave][slot] = dot;
@@ -716,8 +714,8 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         for (; ps < TPASS; ps += nscore) {
             double dot, k2;
             partial(ps, dot, k2);
-            dot = row_allreduce_f64<UPR>(dot);
-            k2 = row_allreduce_f64<UPR>(k2);
+            dot = row_score_sum_f64<UPR>(dot);
+            k2 = row_score_sum_f64<UPR>(k2);
             if (u == 0) {
                 const int slot = staged + rl;
                 st_dot[wave][slot] = dot;

@@ -151,6 +151,28 @@ __device__ __forceinline__ double row_reduce_scatter4_f64(double q0, double q1, 
     return k;
 }
 
+// Sum over the lanes that share one key row in the order of row_reduce_scatter4_f64, every lane with the total.  A score's two
+// sums are formed in this order wherever an eviction may be decided by them, so that the paths to it agree in the last bit.
+template <int LANES>
+__device__ __forceinline__ double row_score_sum_f64(double x)
+{
+    if constexpr (LANES == 8) return row_allreduce_f64<8>(x);
+    x = dpp_add_f64<0x128>(x);   // row_ror:8
+    x = dpp_add_f64<0x141>(x);   // row_half_mirror
+    x = dpp_add_f64<0xB1>(x);    // quad_perm [1,0,3,2]
+    return dpp_add_f64<0x4E>(x); // quad_perm [2,3,0,1]
+}
+
+// |mu|^2 from its pieces of 16 columns, in one order for the same reason
+template <int D>
+__device__ __forceinline__ double sum_of_pieces(const double *piece)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < D / 16; i += 4) s += (piece[i] + piece[i + 1]) + (piece[i + 2] + piece[i + 3]);
+    return s;
+}
+
 // The canonical score of one key (appendix "FLOP count of KeyDiff"): mu.k / max(|mu| |k|, eps) in
 // IEEE double, rounded once to float; + 0 folds -0 into +0.  Every kernel that scores calls this.
 __device__ __forceinline__ float finish_score(double dot, double k2, double nmu, double eps)

@@ -470,7 +470,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         }
         __syncthreads();
     } else {
-    // Exact score of row i: the UPR lanes that share it call this together, each with its 16-byte unit.
+    // Exact score of row i, in the arithmetic of the attention's exact scores: the UPR lanes that share it call this together, each with its 16-byte unit.
     auto exact_score = [&](int i) {
         const int u = tid % UPR;
         const u32x4 w = *reinterpret_cast<const u32x4 *>(kb + (size_t)i * D + u * 8);
@@ -483,12 +483,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             dot = __builtin_fma(sh.mu[u * 8 + 2 * j + 1], x1, dot);
             k2 = __builtin_fma(x1, x1, k2);
         }
-        dot = row_allreduce_f64<UPR>(dot);
-        k2 = row_allreduce_f64<UPR>(k2);
-        double mu2 = 0.0;
-#pragma unroll
-        for (int j = 0; j < D / 16; ++j) mu2 += sh.mu2[j];
-        return finish_score(dot, k2, sqrt(mu2), p.eps);
+        return finish_score(row_score_sum_f64<UPR>(dot), row_score_sum_f64<UPR>(k2), sqrt(sum_of_pieces<D>(sh.mu2)), p.eps);
     };
     for (;;) {   // (a second time, with exact scores of all rows, where approximate ones do not do)
     // ---- 1. histogram of the non-exempt scores in LDS

@@ -967,3 +967,39 @@ def test_rope_of_all_layers_sees_what_an_earlier_layer_wrote(kind):
         assert np.array_equal(rows_by_position(x)[0], rows_by_position(y)[0])
         x.close()
         y.close()
+
+
+@pytest.mark.parametrize("hq,B", [(32, 128), (32, 88)], ids=["all-waves-score", "helper-waves-score"])
+def test_deferred_eviction_decides_by_the_same_bits(hq, B):
+    # The anchor is a multiple of (1, ..., 1) that no short binary fraction holds, and all but a few keys have components
+    # that sum to zero: their scores are the rounding of their double sums and nothing else.  The deferred eviction, whose
+    # selection forms the scores it decides by itself, has to evict what prefill_block evicts by the scores of the attention.
+    hkv, d, N = 8, 128, 8250
+    rng = np.random.default_rng(B)
+    n = N + B
+    half = f32_to_bf16_bits(rng.standard_normal((hkv, n // 2, d // 2), dtype=np.float32))
+    z = np.concatenate([bf16_bits_to_f32(half), -bf16_bits_to_f32(half)], axis=-1)
+    z = np.take_along_axis(z, rng.permuted(np.broadcast_to(np.arange(d), z.shape), axis=-1), axis=-1)
+    keys = np.concatenate([z, -z, np.zeros((hkv, n - 2 * (n // 2), d), np.float32)], axis=1)   # in pairs that cancel in the anchor
+    keys[:, :B // 4] = 1.0
+    keys[:, n // 2:n // 2 + B // 4] = 1.0
+    keys = np.stack([k[rng.permutation(n)] for k in keys])[None]
+    kept = []
+    for deferred in (False, True):
+        cache = kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, 128, layout=kd.LAYOUT_FILL))
+        other = kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, 128, layout=kd.LAYOUT_FILL))
+        bits = f32_to_bf16_bits(keys)
+        pos = np.broadcast_to(np.arange(N, dtype=np.int32), (1, hkv, N)).copy()
+        cache.load(to_dev(bits[:, :, :N]), to_dev(bits[:, :, :N]), torch.from_numpy(pos).cuda())
+        q = torch.zeros((1, hq, B, d), dtype=torch.bfloat16, device="cuda")
+        k = to_dev(bits[:, :, N:])
+        if deferred:
+            cache.prefill_block_deferred(q, k, k, N, carry=other)
+            cache.finish()
+        else:
+            cache.prefill_block(q, k, k, N)
+        kept.append(rows_by_position(cache)[0])
+        assert cache.status() == 0
+        cache.close()
+        other.close()
+    assert np.array_equal(*kept)
