@@ -28,6 +28,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int CAND_MAX = 1024;  // rows of the threshold bin ranked in LDS; more fall back to a radix select
 constexpr int MAX_SELECT_WAVES = POST_THREADS / 64;   // PostShared is laid out for the largest workgroup
@@ -62,6 +63,7 @@ struct PostShared {
     double colsum[MAX_SELECT_WAVES][128];
     double mu[128], mu2[8];   // the anchor and |mu|^2 in pieces (approximate scores: exact ones of the rows near the threshold)
     int bad;                  // a row's score is not known even approximately
+    uint32_t range[MAX_SELECT_WAVES];   // largest magnitude among a wave's evicted keys | complement of the smallest (less one)
 };
 
 // bytes of dynamic LDS a carried selection places PostShared in, ahead of its bitmap and lists
@@ -87,6 +89,23 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x)
     x += dpp_fetch<0x143, 0xC>(x);
     return x;
 }
+// the larger of every 16-bit half over the 64 lanes of a wave, on the vector ALU alone (no lane's value is below 0, what
+// dpp_fetch returns outside the row)
+__device__ __forceinline__ uint32_t wave_max_u16x2(uint32_t x)
+{
+    auto larger = [](uint32_t a, uint32_t b) {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+    };
+    x = larger(x, dpp_fetch<0x128, 0xF>(x));   // row_ror 8, 4, 2, 1
+    x = larger(x, dpp_fetch<0x124, 0xF>(x));
+    x = larger(x, dpp_fetch<0x122, 0xF>(x));
+    x = larger(x, dpp_fetch<0x121, 0xF>(x));
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = larger(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return larger(b[0], b[1]);
+}
+
 // exclusive prefix sum over the workgroup; `wave_tot`: LDS words of the waves that no thread still reads
 template <int THREADS, typename T>
 __device__ __forceinline__ T block_exclusive_scan_t(T v, T *wave_tot, T *total)
@@ -642,9 +661,11 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
 
     // ---- 4. evicted rows before each row: thread t owns bitmap word t = rows [32 t, 32 t + 32).  From that
     // count follow the destinations of the ORDERED layout, and of the FILL layout the rank of a hole (all evicted
-    // rows below it are holes) and of a mover.  The evicted keys are requested before the scan, so that their
-    // trip to memory runs under it; the sum of unit keys depends on the order of its terms in the last bit of
-    // a double, so there the list is put in order first.
+    // rows below it are holes) and of a mover.  The evicted keys are requested before the scan, in the order in which threads
+    // happened to list them, so that their trip to memory runs under it (putting the list in order first: 1 us of 10.6).
+    // A sum of doubles depends in its last bit on the order of its terms unless it is exact, which one of raw keys
+    // is in any order as long as their exponents lie close enough; that is looked at below, and the sum taken
+    // again in ascending order of the rows where they don't.  Unit keys are listed in order to begin with.
     constexpr int RPW = 64 / UPR;
     const int eu = lane % UPR, erl = lane / UPR;
     // the rows of up to EV_BATCH rounds are requested together: one memory round trip, not one per round
@@ -672,13 +693,15 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     auto before = [&](int i) { return (int)(word_base[i >> 5] + (uint32_t)__popc(evbits[i >> 5] & ((1u << (i & 31)) - 1u))); };
     auto evicted = [&](int i) { return ((evbits[i >> 5] >> (i & 31)) & 1u) != 0; };
     const int nholes = before(p.N);   // (row N exists: n > N)
-    if (sorted) {
-        // (the list is rewritten from the bitmap, thread by word)
+    auto put_in_order = [&]() {   // the list is rewritten from the bitmap, thread by word
         if (tid < nwords) {
             int at = (int)word_base[tid];
             for (uint32_t w = evbits[tid]; w; w &= w - 1) evlist[at++] = 32 * tid + __ffs(w) - 1;
         }
         __syncthreads();
+    };
+    if (sorted) {
+        put_in_order();
         request(wave * RPW);
     }
     if (p.layout == 1)
@@ -692,35 +715,30 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
 
     // ---- 5. take the evicted keys out of the running key sum (before rows are overwritten).
     // UPR lanes share an evicted row (16 bytes each); a wave holds 64/UPR rows at a time.
-    {
-        double acc[8];
+    // In order, there are sixteen partial sums whatever the number of waves (a wave of a smaller workgroup takes turns with its
+    // rounds), so that the passenger leaves the very sum step_post does.
+    constexpr int TURNS = MAX_SELECT_WAVES / NWAVES;
+    static_assert(TURNS * NWAVES == MAX_SELECT_WAVES && EV_BATCH % TURNS == 0, "a round's turn follows from its place in a batch");
+    auto add_key = [&](const u32x4 &w, double (&acc)[8]) {
+        double x[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-        for (int rb0 = wave * RPW; rb0 < E; rb0 += EV_BATCH * NWAVES * RPW) {  // uniform per wave
-            if (rb0 != wave * RPW) request(rb0);
-#pragma unroll
-            for (int b = 0; b < EV_BATCH; ++b) {
-                if (rb0 + b * NWAVES * RPW >= E) break;   // uniform
-                double x[8];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    x[2 * i] = bf16_lo(wv[b][i]);
-                    x[2 * i + 1] = bf16_hi(wv[b][i]);
-                }
-                double inv = 1.0;
-                if (p.anchor_mode == 1) {  // unit key: x / |k|
-                    double k2 = 0.0;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) k2 += x[i] * x[i];
-                    k2 = row_allreduce_f64<UPR>(k2);
-                    const double nk = sqrt(k2);
-                    inv = nk > 0.0 ? 1.0 / nk : 0.0;
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] += (p.anchor_mode == 1) ? x[i] * inv : x[i];
-            }
+        for (int i = 0; i < 4; ++i) {
+            x[2 * i] = bf16_lo(w[i]);
+            x[2 * i + 1] = bf16_hi(w[i]);
         }
-        // fold the rows of the wave (lanes with equal eu), then the waves
+        double inv = 1.0;
+        if (p.anchor_mode == 1) {  // unit key: x / |k|
+            double k2 = 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) k2 += x[i] * x[i];
+            k2 = row_allreduce_f64<UPR>(k2);
+            const double nk = sqrt(k2);
+            inv = nk > 0.0 ? 1.0 / nk : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += (p.anchor_mode == 1) ? x[i] * inv : x[i];
+    };
+    auto fold = [&](double (&acc)[8], int part) {   // the rows of the wave (lanes with equal eu)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             if constexpr (UPR == 16) acc[i] = sum_over_rows_f64(acc[i]);
@@ -731,9 +749,72 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         }
         if (erl == 0) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sh.colsum[wave][eu * 8 + i] = acc[i];
+            for (int i = 0; i < 8; ++i) sh.colsum[part][eu * 8 + i] = acc[i];
         }
+    };
+    {
+        double acc[TURNS][8];
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[t][i] = 0.0;
+        u16x2 largest = {0, 0}, smallest = {0xFFFF, 0xFFFF};   // magnitudes as bf16 bits; smallest: less one, so that zeros wrap
+        for (int rb0 = wave * RPW; rb0 < E; rb0 += EV_BATCH * NWAVES * RPW) {  // uniform per wave
+            if (rb0 != wave * RPW) request(rb0);
+#pragma unroll
+            for (int b = 0; b < EV_BATCH; ++b) {
+                if (rb0 + b * NWAVES * RPW >= E) break;   // uniform
+                add_key(wv[b], acc[b % TURNS]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const u16x2 m = __builtin_bit_cast(u16x2, wv[b][i] & 0x7FFF7FFFu);
+                    largest = __builtin_elementwise_max(largest, m);
+                    smallest = __builtin_elementwise_min(smallest, (u16x2)(m - (unsigned short)1));
+                }
+            }
+        }
+        if (TURNS == 1 || sorted) {
+#pragma unroll
+            for (int t = 0; t < TURNS; ++t) fold(acc[t], t * NWAVES + wave);
+        } else {
+#pragma unroll
+            for (int t = 1; t < TURNS; ++t)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[0][i] += acc[t][i];
+            fold(acc[0], wave);
+        }
+        const uint32_t range = wave_max_u16x2(max(largest[0], largest[1]) | ((uint32_t)(0xFFFF ^ min(smallest[0], smallest[1])) << 16));
+        if (lane == 0) sh.range[wave] = range;
         __syncthreads();   // also: every evicted row has been read before the compaction overwrites it
+    }
+    bool in_order = sorted;
+    if (!sorted) {
+        u16x2 range = {0, 0};
+#pragma unroll
+        for (int w = 0; w < NWAVES; ++w) range = __builtin_elementwise_max(range, __builtin_bit_cast(u16x2, sh.range[w]));
+        const uint32_t hi = range[0], lo = 0xFFFFu ^ range[1];
+        // Every term is a multiple of 2^-7 times the power of the smallest exponent, and any sum of them below 2 E times that of
+        // the largest: with the exponents no further apart than this it fits the 53 bits of a double.  (Exponent field 0 has the
+        // steps of field 1; among zeros alone lo is beyond hi.)
+        if ((hi >> 7) > max((lo + 1) >> 7, 1u) + (uint32_t)(45 - (32 - __clz(E)))) {   // uniform; rare
+            in_order = true;
+            put_in_order();
+#pragma unroll 1
+            for (int part = wave; part < MAX_SELECT_WAVES; part += NWAVES) {
+                double acc[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+#pragma unroll 1
+                for (int rb0 = part * RPW; rb0 < E; rb0 += MAX_SELECT_WAVES * RPW) {
+                    const int r = rb0 + erl;
+                    u32x4 w = {0u, 0u, 0u, 0u};
+                    if (r < E) w = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + eu * 8);
+                    add_key(w, acc);
+                }
+                fold(acc, part);
+            }
+            __syncthreads();
+        }
     }
     KD_TL(8);   // evicted rows read
 
@@ -814,6 +895,10 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < NWAVES; ++w) s += sh.colsum[w][tid];
+        if (TURNS > 1 && in_order) {
+#pragma unroll
+            for (int w = NWAVES; w < MAX_SELECT_WAVES; ++w) s += sh.colsum[w][tid];
+        }
         p.ksum_next[(size_t)bh * D + tid] = ksum_old - s;
     }
     KD_TL(9);   // moves issued

@@ -1003,3 +1003,38 @@ def test_deferred_eviction_decides_by_the_same_bits(hq, B):
         cache.close()
         other.close()
     assert np.array_equal(*kept)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("anchor", [kd.ANCHOR_MEAN_KEY, kd.ANCHOR_MEAN_UNIT_KEY], ids=["wide-exponents", "unit"])
+def test_key_sum_is_the_same_on_every_path_and_in_every_run(anchor, d):
+    # The keys that are evicted share a direction and have exponents up to 80 apart (their sum is not exact in double, nor
+    # is one of unit keys); the others come in pairs that cancel.  So what the eviction leaves of the key sum, and with it
+    # every score, is the rounding of the sum of the evicted keys.  Evicting inside the call, evicting inside another
+    # cache's launch and doing it again leave the same scores, bit for bit.
+    hq, hkv, N, B = 8, 2, 640, 128
+    rng = np.random.default_rng(17 + d)
+    z = rng.standard_normal((hkv, N // 2, d)).astype(np.float32)
+    common = 1.0 + 0.2 * rng.standard_normal((hkv, B, d))
+    out = common * np.exp2(rng.integers(-40, 41, size=(hkv, B, 1)))
+    keys = np.concatenate([z, -z, out.astype(np.float32)], axis=1)
+    keys = f32_to_bf16_bits(np.stack([k[rng.permutation(N + B)] for k in keys])[None])
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(1, hkv, N).contiguous()
+    q = torch.zeros((1, hq, B, d), dtype=torch.bfloat16, device="cuda")
+    first, k = to_dev(keys[:, :, :N]), to_dev(keys[:, :, N:])
+    scores = []
+    for path in ("inside", "carried", "inside", "carried"):
+        cache, other = (kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, B, layout=kd.LAYOUT_FILL, anchor_mode=anchor)) for _ in range(2))
+        cache.load(first, first, pos)
+        if path == "carried":
+            cache.prefill_block_deferred(q, k, k, N, carry=other)
+            other.prefill_block_deferred(q, k, k, 0, carry=cache)
+            assert other.plan()[3] & 1
+        else:
+            cache.prefill_block(q, k, k, N)
+        order = cache.positions().long().argsort(-1)
+        scores.append((cache.positions().gather(-1, order).cpu(), cache.scores().gather(-1, order).view(torch.int32).cpu()))
+        assert cache.status() == 0
+        cache.close()
+        other.close()
+    assert all(torch.equal(a, b) for x in scores[1:] for a, b in zip(scores[0], x))
