@@ -816,11 +816,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                 if ((lane & 15) == 0) red[wave][lane >> 4] = sq;
             } else if (tid < D) {
                 if ((lane & 15) == 0) mu2_f[tid / 16] = (float)sq;
-                if (writer) {   // for the selection, which scores the rows near its threshold exactly
-                    double *anchor = p.anchor + (size_t)bh * (D + D / 16);
-                    anchor[tid] = ksum_after / (double)p.n;
-                    if ((lane & 15) == 0) anchor[D + tid / 16] = sq;
-                }
+                if (writer) p.anchor[(size_t)bh * D + tid] = ksum_after / (double)p.n;   // for the selection's exact scores
             }
         }
         KD_TL(6);   // anchor formed

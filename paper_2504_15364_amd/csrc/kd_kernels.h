@@ -57,7 +57,7 @@ struct StepParams {
                                      // MFMA accumulator layout, each normalised by its row sum
     float2 *part_ml;                 // [psplits][BH * G * Bt]    (reference max in log2 units, row sum)
     float *scores;                   // [BH][cap]; approximate if score_approx
-    double *anchor;                  // [BH][D + D / 16] the step's anchor and |mu|^2 in pieces of 16 columns (score_approx)
+    double *anchor;                  // [BH][D] the step's anchor (score_approx)
     int32_t *dstmap;                 // [BH][cap] ORDERED layout: destination row or -1
     int32_t *lists;                  // [BH][4 * B] evicted rows | holes | movers | mover rank of each tail row
     unsigned long long *argmax_rec;  // nullable [BH][splits][2]: the generation phase (one row to evict, no window):

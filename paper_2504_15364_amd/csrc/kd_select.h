@@ -354,8 +354,8 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         for (int i = tid; i < HIST_BINS; i += THREADS) sh.hist[i] = 0;
     }
     bool approx = APPROX && p.score_approx != 0;   // uniform
-    double mu = 0.0;   // the anchor, and |mu|^2 in pieces, as the attention left them (first used behind a later barrier)
-    if (approx && tid < D + D / 16) mu = p.anchor[(size_t)bh * (D + D / 16) + tid];
+    double mu = 0.0;   // the anchor as the attention left it (first used behind a later barrier)
+    if (approx && tid < D) mu = p.anchor[(size_t)bh * D + tid];
     if (tid == 0) {
         sh.ncand = 0;
         sh.nev = 0;
@@ -513,7 +513,11 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         }
     });
     __syncthreads();
-    if (approx && tid < D + D / 16) (tid < D ? sh.mu[tid] : sh.mu2[tid - D]) = mu;
+    if (approx && tid < D) {   // (whole waves)
+        sh.mu[tid] = mu;
+        const double sq = row_allreduce_f64<16>(mu * mu);
+        if ((lane & 15) == 0) sh.mu2[tid / 16] = sq;
+    }
     KD_TL(3);   // scores binned
 
     // ---- 2. threshold bin: thread t owns the HIST_BINS / THREADS bins below its top one, highest first

@@ -134,7 +134,7 @@ Layout make_layout(const keydiff_config_t *c)
     L.off_scores = off;     off += align256(BH * L.cap * 4);
     L.off_dstmap = off;     off += align256(BH * L.cap * 4);
     L.off_lists = off;      off += align256(BH * 4 * (size_t)c->block_B * 4);
-    L.off_ksum_part = off;  off += align256(BH * (chunks > 1 ? chunks : 2) * D * 8);   // (at least the step anchor below)
+    L.off_ksum_part = off;  off += align256(BH * chunks * D * 8);
     // the anchor of a step for its selection: shares the region of the key-sum partials, which only a cache load uses
     L.off_anchor = L.off_ksum_part;
     L.off_q_rot = off;      off += align256((size_t)c->batch * c->n_q_heads * c->block_B * D * 2);   // rotated block (rope entry points)

@@ -28,6 +28,14 @@ def test_workspace_sizes():
     assert scratch > 8 * (8192 + 128) * 4
 
 
+@pytest.mark.parametrize("batch,hq,hkv,d,N,B", [(59, 8, 8, 128, 64, 64), (73, 32, 8, 128, 96, 16), (89, 32, 8, 128, 96, 8)])
+def test_small_caches_of_many_sequences_fit_the_static_array(batch, hq, hkv, d, N, B):
+    # configurations of at most 128 rows a head that fill the 40 MiB of keydiff_prefill_block_static's array to the last
+    # percent: a chunk of scratch more per head would leave them out
+    scratch = kd.workspace_bytes(kd.KeyDiffConfig(batch, hq, hkv, d, N, B))[3]
+    assert 39.2 * 2 ** 20 < scratch <= 40 * 2 ** 20
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(n_q_heads=5), kd.ESHAPE),            # not a multiple of the KV heads
     (dict(head_dim=96), kd.ESHAPE),
