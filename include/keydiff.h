@@ -37,9 +37,9 @@
  *     gives a thread-local message.  No exception crosses this boundary.
  *   - Inputs must be finite, and values (v_new, and what keydiff_cache_load brings in) must not exceed
  *     65504 in magnitude: where the keys of a step are cut into several ranges, the attention output
- *     of each range travels as fp16 (float where a KV head has at most 32 query rows), normalised by its
- *     own weight sum (so it is bounded by the largest |v| it covers), before the ranges are merged; a larger value would become infinite there.  The
- *     library does not check this.  Queries and keys have no such limit.
+ *     of each range travels as fp16 (as float in some steps of at most 32 query rows per KV head),
+ *     normalised by its own weight sum (so it is bounded by the largest |v| it covers), before the ranges
+ *     are merged; a larger value would become infinite there.  The library does not check this.  Queries and keys have no such limit.
  *   - Scores are IEEE double arithmetic on the bf16
  *     data rounded once to float; the eviction decision is taken on that float
  *     and ties keep the lower token position.

@@ -11,7 +11,7 @@
 // log-sum-exp in step_post (or the merge kernel).  Workgroup ids map KV heads
 // round-robin so that the workgroups of one head share an XCD and its L2.
 // Variants: HELP (workgroups whose last waves have no query row: those copy tiles and score
-// rows; with at most 32 rows per head another kernel runs, few.hip), and the
+// rows; few rows and many keys: another kernel runs, few.hip), and the
 // carrying kernel whose first workgroups run another cache's pending selection.
 //
 // Data path.  K and V tiles stream global -> LDS asynchronously

@@ -1,5 +1,5 @@
 // step_few: the attention launch of a block step whose KV heads have few query rows (G * Bt <= 32: the
-// generation phase above all).  Same work as step_main -- append (Eq. 5), block attention over cache ||
+// generation phase above all) and enough keys for it to pay (the plan has the rule and both sides' times).  Same work as step_main -- append (Eq. 5), block attention over cache ||
 // block (Eq. 1-2), anchor and cosine score of every key -- cut for a step that is bound by reading the
 // cache once, not by the matrix cores.
 //

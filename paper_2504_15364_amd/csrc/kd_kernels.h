@@ -4,7 +4,7 @@
 //   step_main  append (Eq. 5) + split-KV flash attention partials (Eq. 1-2)
 //              + running key sum S' = S + sum of the block's keys (the anchor is S' / n)
 //              + cosine score of every row, taken from the K tiles while they sit in LDS
-//              (step_few instead where a KV head has at most FEW_ROWS query rows)
+//              (step_few instead where a KV head has few query rows and many keys)
 //   step_post  merge of the attention partials  ||  selection of the rows to evict
 //              and compaction, one workgroup per head (Eq. 6-7)
 // plus, for the ORDERED layout only, one more launch that shifts rows in place.
@@ -19,7 +19,7 @@ namespace kd {
 
 constexpr int TILE_KEYS = 64;       // keys per attention K/V tile
 constexpr int FEW_KEYS = 32;        // keys per wave and tile in step_few
-constexpr int FEW_ROWS = 32;        // query rows per KV head up to which a step runs step_few instead of step_main
+constexpr int FEW_ROWS = 32;        // query rows per KV head up to which a step may run step_few instead of step_main (the plan decides)
 constexpr int POST_THREADS = 1024;  // workgroup size of step_post
 constexpr int SCORE_THREADS = 256;  // workgroup size of step_score
 constexpr int SCORE_ROWS = 128;     // rows per step_score workgroup: 32 per wave
@@ -67,7 +67,7 @@ struct StepParams {
     int batch, hq, hkv, G, D, Bt, len, n, N, B, cap;
     int splits, mtiles, ntiles, NW;      // NW: waves (of 32 query rows) per step_main workgroup
     int psplits;                     // partials per output row the merge adds up (1: none, the attention writes `out`)
-    int few;                         // the step runs step_few (at most FEW_ROWS query rows per KV head): its partials are
+    int few;                         // the step runs step_few (at most FEW_ROWS query rows per KV head, see the plan): its partials are
                                      // float [psplits][BH][G * Bt][D] in part_o
     int edge_cost;                   // weight (in plain tiles: 1 or 2) of a tile holding rows of the block when
                                      // the key tiles are divided over the splits

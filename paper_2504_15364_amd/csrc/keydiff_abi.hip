@@ -2,6 +2,7 @@
 // the Eq. 5 state machine (len, positions) and the per-step kernel sequence.
 #include "../../include/keydiff.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -292,10 +293,23 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     p.mtiles = (Mtot + TM - 1) / TM;
     p.ntiles = (p.n + kd::TILE_KEYS - 1) / kd::TILE_KEYS;
     const int target = c->L.target_wgs / 2;   // the compute units of the chip
-    p.few = Mtot <= kd::FEW_ROWS;
+    {
+        // Few query rows: step_few, whose waves each read keys of their own, or step_main, whose fixed costs are 3 us lower but
+        // where one or two waves then do all the attention and the merge goes through whole blocks of 32 rows of every range.
+        // Up to 16 rows step_few takes the steps with many ranges to merge or several tiles in a range, and those that evict
+        // a single row on 8 heads or more; with 17 to 32 rows, of which it reads every key twice, those whose ranges are
+        // many for their length.  Measured, step_main / step_few, us a step with its selection (D = 128):
+        //   1 token, 4 or 8 rows:  1 KV head, 300 keys 13.1 / 15.4, 1025 16.0 / 16.0, 4097 28.4 / 16.5;
+        //                          8 KV heads, 300 keys 16.7 / 15.4;  16 x 8 heads, 513 keys 20.1 / 17.8
+        //   4 to 16 rows:          8 KV heads, 516 keys 15.8 / 19.9, 2052 19.5 / 20.2;  1 KV head, 4098 keys 27.9 / 20.2
+        //   24 to 32 rows:         1 KV head, 8196 keys 43.0 / 22.7;  4 KV heads, 8196 keys 28.8 / 22.9, 16388 30.5 / 31.4;
+        //                          8 KV heads, 2056 keys 20.4 / 20.4, 8200 24.1 / 26.5;  16 x 8 heads, 8200 keys 117.8 / 152.6
+        const int ranges = std::max(1, std::min(target / BH, p.ntiles)), range_tiles = (p.ntiles + ranges - 1) / ranges;
+        p.few = Mtot <= 16 ? (p.n - p.N == 1 ? BH >= 8 || ranges > 16 : ranges > 31 || range_tiles >= 5)
+                           : Mtot <= kd::FEW_ROWS && ranges >= 32 && 16 * range_tiles <= ranges;
+    }
     if (p.few) {
-        // Few query rows (the generation phase): every wave of a workgroup takes 32-key tiles of its own, so
-        // a range needs eight tiles to keep its waves busy; never more workgroups than compute units.
+        // Every wave of a workgroup takes 32-key tiles of its own, so a range needs eight tiles to keep its waves busy; never more workgroups than compute units.
         const int nt = (p.n + kd::FEW_KEYS - 1) / kd::FEW_KEYS;
         p.mtiles = (Mtot + 15) / 16;
         int splits = target / (BH * p.mtiles);

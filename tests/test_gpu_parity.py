@@ -807,7 +807,10 @@ def test_argument_errors_enqueue_nothing():
     (32, 2, 64, 515, (1, 2, 1)),               # 16 and 32 rows
     (3, 3, 64, 1031, (32, 17, 16, 31, 1)),     # blocks of many rows, masked inside
     (5, 1, 128, 31, (1, 2, 3, 6)),             # fewer keys than a tile
-], ids=["g4", "g7", "g16", "g1", "short"])
+    (8, 2, 64, 2100, (1, 2, 4, 8, 7)),         # enough keys that none of the steps runs the other kernel
+    (3, 3, 128, 2113, (32, 17, 16, 31, 1)),
+    (32, 1, 128, 2050, (1, 1)),                # one token, two row tiles
+], ids=["g4", "g7", "g16", "g1", "short", "long-d64", "long-blocks", "long-g32"])
 @pytest.mark.parametrize("anchor", [kd.ANCHOR_MEAN_KEY, kd.ANCHOR_MEAN_UNIT_KEY], ids=["mean", "unit"])
 def test_steps_with_few_query_rows(hq, hkv, d, N, sizes, anchor):
     # at most 32 query rows per KV head take a kernel of their own: edges of its row tiles, of its 32-key tiles and of
