@@ -1265,7 +1265,8 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
 bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
-    return p.NW == 8 && !p.few && !(p.do_score && !p.score_approx) && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
+    // (a step of few query rows takes no passenger whichever kernel runs it: it is shorter than a selection)
+    return p.NW == 8 && p.G * p.Bt > FEW_ROWS && !(p.do_score && !p.score_approx) && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
            carry_need(cy, false) <= CARRY_DYN_MAX && ncarry > 0;
 }
 

@@ -462,7 +462,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     // add 4 us to the selection, which then scores the rows near its threshold exactly.  As a passenger it hides
     // that; as the launch the caller waits for it does not (attention + selection, 32 / 8 heads: 30.0 and 32.6 us at
     // 4096 keys with exact and approximate scores, 39.8 and 42.0 at 8192, 48.1 and 49.9 at 12000).  Scores
-    // the caller asks for are exact; so are those of step_few, see below.
+    // the caller asks for are exact; so are those of a step of few query rows.
     p.score_approx = defer && carry != nullptr && evict;
     if (cf.window_W > 0) p.window_pos_min = (int32_t)(pos0 + Bt - cf.window_W);
 
@@ -486,7 +486,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     }
     if (shift_parts == 0 && !riding) plan_attention(c, p);
     const int shift_wgs = shift_parts > 0 ? shift_parts * shifted->shift_p.batch * shifted->shift_p.hkv : 0;
-    if (p.few) p.score_approx = 0;
+    if (p.G * p.Bt <= kd::FEW_ROWS) p.score_approx = 0;
     // Generation phase: step_few leaves the
     // arg-max of the scores per workgroup, and the selection reads the row to evict off those records.
     if (evict && n - N == 1 && cf.window_W == 0 && cf.layout == KEYDIFF_LAYOUT_FILL &&
