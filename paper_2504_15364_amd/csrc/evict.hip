@@ -636,12 +636,11 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
         return hipGetLastError();
     }
     if (p.n > 32 * POST_THREADS) return hipErrorInvalidValue;   // a thread owns one word of the eviction bitmap
-    // Three 16-byte loads of scores (and of positions) a thread up to 12288 rows, five up to 20480; the registers hold no
-    // more beside the rows that may move, so larger caches are read from memory in every pass.  With the arg-max
-    // records of the attention launch the scores are hardly ever looked at.
-    // (Five loads leave no room for the positions: not where every row's is needed.)
-    const bool positions = p.window_W > 0 || (p.n - p.N == 1 && !p.score_approx);
-    const int src = p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : positions ? 0 : 5;
+    // Three 16-byte loads of scores and of positions a thread up to 12288 rows, five of scores alone up to 20480 (a pass that
+    // needs every row's position reads those from memory); the registers hold no more beside the rows that may move, so
+    // larger caches are read from memory in every pass.  With the arg-max records of the attention launch the scores are hardly
+    // ever looked at.
+    const int src = p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
     const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
 #define KD_GO2(DD, SRC)                                                                                                    \
     if (p.score_approx) hipLaunchKernelGGL((step_post_kernel<DD, SRC, true>), dim3(grid), dim3(POST_THREADS), lds, s, p);   \

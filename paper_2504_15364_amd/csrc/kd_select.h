@@ -227,7 +227,7 @@ __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool l
 // E row indices (evicted rows | evicted rows below N in ascending order): in LDS when they fit, else in the
 // scratch buffer.
 // The caller keeps n <= 32 * THREADS (a thread owns one word of the eviction bitmap) and, with SRC > 0,
-// n <= 4 * SRC * THREADS; with SRC > 3 also no window, and approximate scores if a single row is evicted.
+// n <= 4 * SRC * THREADS.
 // (inlined: outlined, the parameter block would be passed through scratch memory)
 // APPROX: the scores may be approximate (p.score_approx says).
 template <int D, int SRC, int THREADS, bool APPROX>
@@ -266,28 +266,32 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     lds_ci32 *pos_s = (lds_ci32 *)pos_l;
     f32x4 sreg[NQ4];
     i32x4 preg[PREG ? NQ4 : 1];
-    // visit(row, score, position, k) for every row this thread owns, the k-th of at most 32
+    // visit(row, score, position, k) for every row this thread owns, the k-th of at most 32.  Positions that lie in neither
+    // registers nor LDS are read (and handed to visit) only where a pass asks for them: with a window, or to choose by them.
     auto row_of = [&](int k) { return SRC > 0 ? 4 * ((k >> 2) * THREADS + tid) + (k & 3) : tid + k * THREADS; };
-    auto for_rows = [&](auto &&visit) {
+    auto for_rows = [&](bool positions, auto &&visit) {
         if constexpr (SRC > 0) {
 #pragma unroll
             for (int q = 0; q < NQ4; ++q) {
                 if (q * 4 * THREADS >= p.n) break;   // uniform
+                const int i0 = 4 * (q * THREADS + tid);
+                i32x4 pq = {0, 0, 0, 0};
+                if constexpr (PREG) pq = preg[q];
+                else if (positions && i0 < p.n) pq = *reinterpret_cast<const i32x4 *>(pos + i0);   // (a multiple of four rows)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int i = 4 * (q * THREADS + tid) + e;
-                    if (i < p.n) {
-                        int32_t pi = 0;   // (not asked for: see the caller's part below)
-                        if constexpr (PREG) pi = preg[q][e];
-                        visit(i, sreg[q][e], pi, 4 * q + e);
-                    }
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (i0 + e < p.n) visit(i0 + e, sreg[q][e], (int32_t)pq[e], 4 * q + e);
             }
         } else {
+            if constexpr (RES) {
 #pragma unroll 2
-            for (int i = tid, k = 0; i < p.n; i += THREADS, ++k) {
-                if constexpr (RES) visit(i, (float)sc_s[i], (int32_t)pos_s[i], k);
-                else visit(i, sc_g[i], pos[i], k);
+                for (int i = tid, k = 0; i < p.n; i += THREADS, ++k) visit(i, (float)sc_s[i], (int32_t)pos_s[i], k);
+            } else if (positions) {
+#pragma unroll 2
+                for (int i = tid, k = 0; i < p.n; i += THREADS, ++k) visit(i, sc_g[i], pos[i], k);
+            } else {
+#pragma unroll 4
+                for (int i = tid, k = 0; i < p.n; i += THREADS, ++k) visit(i, sc_g[i], 0, k);
             }
         }
     };
@@ -411,7 +415,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         if (!known) {
         uint64_t best = 0;   // 0: no row (every real key is larger: orderable() of a finite score is > 0)
         int besti = -1;
-        for_rows([&](int i, float s, int32_t pi, int) {
+        for_rows(true, [&](int i, float s, int32_t pi, int) {
             if (!exempt(pi)) {
                 const uint64_t key = ((uint64_t)orderable(s) << 32) | (uint32_t)pi;
                 if (key > best) {
@@ -506,7 +510,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     };
     for (;;) {   // (a second time, with exact scores of all rows, where approximate ones do not do)
     // ---- 1. histogram of the non-exempt scores in LDS
-    for_rows([&](int, float s, int32_t pi, int) {
+    for_rows(p.window_W > 0, [&](int, float s, int32_t pi, int) {
         if (!exempt(pi)) {
             atomicAdd(&sh.hist[score_bin(s)], 1u);
             if (APPROX && s != s) sh.bad = 1;
@@ -557,7 +561,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         if (at < (uint32_t)E) lists[at] = i;
     };
     uint32_t mine_above = 0;   // the thread's rows above the bin: listed after the pass, so that the pass itself waits for nothing
-    for_rows([&](int i, float s, int32_t pi, int k) {
+    for_rows(p.window_W > 0, [&](int i, float s, int32_t pi, int k) {
         if (exempt(pi)) return;
         bool above_bin, in_bin;
         if constexpr (APPROX) {
@@ -616,7 +620,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         __syncthreads();
     }
     }   // APPROX
-    if constexpr (SRC > 0 && !PREG) {
+    if constexpr (!RES && !PREG) {
         for (uint32_t c = tid; c < min(ncand, (uint32_t)CAND_MAX); c += THREADS) sh.cand_pos[c] = pos[sh.cand_slot[c]];
         __syncthreads();
     }
@@ -643,7 +647,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         __syncthreads();
     } else {
         radix_select_in_bin<THREADS>(p, sh, RES ? sc_l : sc_g, RES ? pos_l : pos, evbits, tb, need);   // (exact scores here)
-        for_rows([&](int i, float s, int32_t, int) {   // (it marks rows of the bin; they join the list here)
+        for_rows(false, [&](int i, float s, int32_t, int) {   // (it marks rows of the bin; they join the list here)
             if (score_bin(s) == tb && ((evbits[i >> 5] >> (i & 31)) & 1u)) {
                 const uint32_t at = atomicAdd(&sh.nev, 1u);
                 if (at < (uint32_t)E) lists[at] = i;

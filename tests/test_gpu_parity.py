@@ -1041,3 +1041,59 @@ def test_key_sum_is_the_same_on_every_path_and_in_every_run(anchor, d):
         cache.close()
         other.close()
     assert all(torch.equal(a, b) for x in scores[1:] for a, b in zip(scores[0], x))
+
+
+def keys_with_ties(rng, hkv, n, d, kind):
+    """bf16 bits [hkv][n][d]: "plain"; "pairs": every key twice; "few": five keys over and over (more equal scores than
+    the selection ranks in LDS)."""
+    k = rng.standard_normal((hkv, n, d), dtype=np.float32) + 1.0
+    if kind == "pairs":
+        k[:, n // 2:2 * (n // 2)] = k[:, :n // 2]
+    elif kind == "few":
+        k = k[:, :5][:, rng.integers(0, 5, size=n)]
+    return f32_to_bf16_bits(np.stack([x[rng.permutation(n)] for x in k]))
+
+
+@pytest.mark.parametrize("kind", ["plain", "pairs", "few"])
+@pytest.mark.parametrize("n,E,d,layout,window", [
+    (12288, 96, 64, kd.LAYOUT_FILL, 0),        # scores and positions in the registers of step_post, to the last row
+    (12289, 96, 128, kd.LAYOUT_FILL, 0),       # scores alone
+    (12301, 96, 64, kd.LAYOUT_ORDERED, 0),
+    (16385, 300, 64, kd.LAYOUT_FILL, 0),       # more tail rows than registers hold
+    (16390, 1, 64, kd.LAYOUT_ORDERED, 0),      # one row, chosen by every row's position
+    (20480, 96, 128, kd.LAYOUT_ORDERED, 0),
+    (20481, 96, 64, kd.LAYOUT_FILL, 0),        # read from memory in every pass
+    (20490, 1, 64, kd.LAYOUT_ORDERED, 0),
+    (12500, 96, 64, kd.LAYOUT_FILL, 900),      # a window: every row's position decides whether it counts
+    (20500, 64, 64, kd.LAYOUT_ORDERED, 900),
+])
+def test_selection_of_long_caches(n, E, d, layout, window, kind):
+    hq, hkv, N = 2, 1, n - E
+    w = get_config("llama31_8b").small(n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prompt_T=n)
+    rng = np.random.default_rng(n + E)
+    k = keys_with_ties(rng, hkv, n, d, kind)[None]
+    v = f32_to_bf16_bits(rng.standard_normal((1, hkv, n, d), dtype=np.float32))
+    q = torch.zeros((1, hq, 512, d), dtype=torch.bfloat16, device="cuda")
+    for path in ("inside", "alone"):
+        cache, oc = make_pair(w, N, 512, layout=layout, window_W=window)
+        other = kd.KeyDiffCache(cache.cfg)
+        if window:   # needs consecutive positions from the start
+            for t in range(0, N, 512):
+                Bt = min(512, N - t)
+                cache.prefill_block(q[:, :, :Bt].contiguous(), to_dev(k[:, :, t:t + Bt]), to_dev(v[:, :, t:t + Bt]), t)
+                oc.prefill_block(None, k[:, :, t:t + Bt].copy(), v[:, :, t:t + Bt].copy(), t)
+        else:
+            pos = np.broadcast_to(np.arange(N, dtype=np.int32), (1, hkv, N)).copy()
+            cache.load(to_dev(k[:, :, :N]), to_dev(v[:, :, :N]), torch.from_numpy(pos).cuda())
+            oc.load(k[:, :, :N].copy(), v[:, :, :N].copy(), pos)
+        block = q[:, :, :E].contiguous(), to_dev(k[:, :, N:]), to_dev(v[:, :, N:])
+        if path == "inside":
+            cache.prefill_block(*block, N)
+        else:
+            cache.prefill_block_deferred(*block, N, carry=other)
+            cache.finish()
+        assert oc.prefill_block(None, k[:, :, N:].copy(), v[:, :, N:].copy(), N)[2] == E
+        check_state(cache, oc, path)
+        assert cache.status() == 0
+        cache.close()
+        other.close()
