@@ -138,11 +138,12 @@ __device__ __forceinline__ void loads_landed(u32x2 &x, u32x4 (&w)[A][B])
 
 // A workgroup is NW = 8 waves of NQ = 1 block of 32 query rows each (two waves per SIMD: with one wave
 // of 64 rows per SIMD every vector, LDS and copy-issue latency lay open and the kernel was slower).
-// HELP: some waves of a workgroup may have no query row at all (few query rows: decode); such a
+// HELP: some waves of a workgroup may have no query row at all (rows that end inside a tile of 256); such a
 // wave takes no part in the attention, it copies its share of every tile and scores rows.
 constexpr int MAIN_WAVES = 8;
-// EXACT: the scores of all rows are asked for (scores_out), so they are formed in double here; otherwise the
-// attention leaves approximate scores and the selection decides from exact ones of the few rows near its threshold.
+// EXACT: the scores of all rows are formed in double here (where the caller asks for them, where the call evicts by
+// itself, and where a deferred selection would not hide the work of scoring); otherwise the attention leaves approximate
+// scores, or none, and the selection decides from exact ones of the few rows near its threshold.
 template <int D, bool HELP, bool EXACT>
 __device__ __forceinline__ void step_main_body(const StepParams &p, const int block_id)
 {
@@ -1154,7 +1155,8 @@ __global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_kernel(StepParams p
 // kinds of workgroup is needed.
 // cy_res: the passengers work on LDS copies of their head's scores and positions (the launch then
 // asks for the dynamic LDS that takes)
-template <int D, bool HELP>
+// (EXACT: neither the step's own scores nor the carried ones are approximate)
+template <int D, bool HELP, bool EXACT>
 __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepParams p, StepParams cy, int ncarry, int cy_res)
 {
     warm_arguments<2 * sizeof(StepParams) + 8>();   // both parameter blocks: the role is not known yet
@@ -1162,11 +1164,11 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepPara
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         PostShared &sh = *reinterpret_cast<PostShared *>(smem);
         unsigned char *dyn = smem + carry_shared_bytes();
-        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
-        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
+        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS, !EXACT>(cy, sh, dyn, (int)blockIdx.x);
+        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS, !EXACT>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
-    step_main_body<D, HELP, false>(p, (int)blockIdx.x - ncarry);
+    step_main_body<D, HELP, EXACT>(p, (int)blockIdx.x - ncarry);
 }
 
 // The same with a third kind of workgroup behind the selection's: `ride.nshift` workgroups that shift
@@ -1180,7 +1182,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepPara
 struct RideCounts {
     int ncarry, cy_res, nshift;
 };
-template <int D>
+template <int D, bool EXACT>
 __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCounts cnt, StepParams p, StepParams cy, ShiftRide ride)
 {
     warm_arguments<sizeof(RideCounts) + 2 * sizeof(StepParams)>();
@@ -1189,8 +1191,8 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
         PostShared &sh = *reinterpret_cast<PostShared *>(smem);
         unsigned char *dyn = smem + carry_shared_bytes();
-        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
-        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS, true>(cy, sh, dyn, (int)blockIdx.x);
+        if (cy_res) select_and_compact<D, SRC_LDS, CARRY_THREADS, !EXACT>(cy, sh, dyn, (int)blockIdx.x);
+        else select_and_compact<D, SRC_MEMORY, CARRY_THREADS, !EXACT>(cy, sh, dyn, (int)blockIdx.x);
         return;
     }
     if ((int)blockIdx.x < ncarry + nshift) {
@@ -1198,7 +1200,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
         shift_range<D, CARRY_THREADS>(ride.p, ride.flags, ride.nchunks, ride.epoch, i % heads, i / heads, ride.parts);
         return;
     }
-    step_main_body<D, false, false>(p, (int)blockIdx.x - ncarry - nshift);
+    step_main_body<D, false, EXACT>(p, (int)blockIdx.x - ncarry - nshift);
 }
 
 static size_t main_lds_bytes(int D) { return (size_t)STAGES * 2 * TILE_KEYS * D * 2; }
@@ -1230,12 +1232,16 @@ hipError_t configure_main_kernels()
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
                             (int)CARRY_DYN_MAX);                                                    \
     if (e != hipSuccess) return e;
-    KD_SET((step_main_carry_kernel<128, false>))
-    KD_SET((step_main_carry_kernel<128, true>))
-    KD_SET((step_main_carry_kernel<64, false>))
-    KD_SET((step_main_carry_kernel<64, true>))
-    KD_SET((step_main_ride_kernel<128>))
-    KD_SET((step_main_ride_kernel<64>))
+#define KD_SETS(DD)                                     \
+    KD_SET((step_main_carry_kernel<DD, false, false>)) \
+    KD_SET((step_main_carry_kernel<DD, false, true>))  \
+    KD_SET((step_main_carry_kernel<DD, true, false>))  \
+    KD_SET((step_main_carry_kernel<DD, true, true>))   \
+    KD_SET((step_main_ride_kernel<DD, false>))         \
+    KD_SET((step_main_ride_kernel<DD, true>))
+    KD_SETS(128)
+    KD_SETS(64)
+#undef KD_SETS
 #undef KD_SET
     return hipSuccess;
 }
@@ -1243,13 +1249,15 @@ hipError_t configure_main_kernels()
 // workgroups whose last waves have no query row at all run the variant in which those waves help
 static bool main_runs_help(const StepParams &p) { return p.mtiles * 32 * p.NW - p.G * p.Bt >= 32; }
 
+static bool scores_exactly(const StepParams &p) { return p.do_score && !p.score_approx; }
+
 hipError_t launch_step_main(const StepParams &p, hipStream_t s)
 {
     const int grid = p.batch * p.hkv * p.mtiles * p.splits;
     const size_t lds = main_lds_bytes(p.D);
     const bool help = main_runs_help(p);
     if (p.few) return hipErrorInvalidValue;
-    const bool exact = p.do_score && !p.score_approx;
+    const bool exact = scores_exactly(p);
 #define KD_GO(DD)                                                                                                             \
     if (help && exact) hipLaunchKernelGGL((step_main_kernel<DD, true, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);       \
     else if (help) hipLaunchKernelGGL((step_main_kernel<DD, true, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);          \
@@ -1262,12 +1270,18 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
+Ride ride_of(const StepParams &cy)
+{
+    if (cy.n > 32 * CARRY_THREADS || carry_need(cy, false) > CARRY_DYN_MAX) return Ride::none;
+    return carry_need(cy, true) <= CARRY_DYN_MAX && !cy.argmax_rec ? Ride::lds : Ride::memory;
+}
+
 bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
     // (a step of few query rows takes no passenger whichever kernel runs it: it is shorter than a selection)
-    return p.NW == 8 && p.G * p.Bt > FEW_ROWS && !(p.do_score && !p.score_approx) && p.D == cy.D && cy.do_evict && cy.n <= 32 * CARRY_THREADS &&
-           carry_need(cy, false) <= CARRY_DYN_MAX && ncarry > 0;
+    return p.NW == 8 && p.G * p.Bt > FEW_ROWS && !(scores_exactly(p) && cy.score_approx) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
+           ride_of(cy) != Ride::none;
 }
 
 hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hipStream_t s)
@@ -1279,13 +1293,15 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
 #ifdef KD_TIMELINE
     cyl.timeline = p.timeline;   // one record per workgroup of the launch, passengers first
 #endif
-    const int res = carry_need(cy, true) <= CARRY_DYN_MAX && !cy.argmax_rec ? 1 : 0;
+    const int res = ride_of(cy) == Ride::lds ? 1 : 0;
     const size_t need = carry_need(cy, res != 0);
     const size_t lds = need > main_lds_bytes(p.D) ? need : main_lds_bytes(p.D);
-    const bool help = main_runs_help(p);
-#define KD_GO(DD)                                                                                                   \
-    if (help) hipLaunchKernelGGL((step_main_carry_kernel<DD, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
-    else hipLaunchKernelGGL((step_main_carry_kernel<DD, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res);
+    const bool help = main_runs_help(p), exact = scores_exactly(p);
+#define KD_GO(DD)                                                                                                                             \
+    if (help && exact) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    else if (help) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    else if (exact) hipLaunchKernelGGL((step_main_carry_kernel<DD, false, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    else hipLaunchKernelGGL((step_main_carry_kernel<DD, false, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res);
     if (p.D == 128) { KD_GO(128) }
     else if (p.D == 64) { KD_GO(64) }
 #undef KD_GO
@@ -1296,7 +1312,7 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
 bool can_host_shift(const StepParams &p, const StepParams &shifted)
 {
     const int E = shifted.n - shifted.N;
-    return p.NW == 8 && !p.few && !(p.do_score && !p.score_approx) && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
+    return p.NW == 8 && !p.few && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
 }
 
 hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, const ShiftRide &ride, hipStream_t s)
@@ -1309,12 +1325,17 @@ hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, cons
 #ifdef KD_TIMELINE
     cyl.timeline = p.timeline;   // one record per workgroup of the launch that stamps (the shifting ones do not)
 #endif
-    const int res = cy && carry_need(*cy, true) <= CARRY_DYN_MAX && !cy->argmax_rec ? 1 : 0;
+    const int res = cy && ride_of(*cy) == Ride::lds ? 1 : 0;
     const size_t need = cy ? carry_need(*cy, res != 0) : 0;
     const size_t lds = need > main_lds_bytes(p.D) ? need : main_lds_bytes(p.D);
     const RideCounts cnt{ncarry, res, ride.nshift};
-    if (p.D == 128) hipLaunchKernelGGL((step_main_ride_kernel<128>), dim3(grid), dim3(CARRY_THREADS), lds, s, cnt, p, cyl, ride);
-    else if (p.D == 64) hipLaunchKernelGGL((step_main_ride_kernel<64>), dim3(grid), dim3(CARRY_THREADS), lds, s, cnt, p, cyl, ride);
+    const bool exact = scores_exactly(p);
+#define KD_GO(DD)                                                                                                                     \
+    if (exact) hipLaunchKernelGGL((step_main_ride_kernel<DD, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, cnt, p, cyl, ride); \
+    else hipLaunchKernelGGL((step_main_ride_kernel<DD, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, cnt, p, cyl, ride);
+    if (p.D == 128) { KD_GO(128) }
+    else if (p.D == 64) { KD_GO(64) }
+#undef KD_GO
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

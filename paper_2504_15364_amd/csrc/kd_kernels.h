@@ -24,7 +24,7 @@ constexpr int POST_THREADS = 1024;  // workgroup size of step_post
 constexpr int SCORE_THREADS = 256;  // workgroup size of step_score
 constexpr int SCORE_ROWS = 128;     // rows per step_score workgroup: 32 per wave
 constexpr int HIST_BINS = 4096;     // score histogram resolution in step_post (bins over [-1, 1])
-// Bound of |approximate score - exact score| (step_main without scores_out).  With |k| and |mu| the norms and the sums of
+// Bound of |approximate score - exact score| (step_main with score_approx).  With |k| and |mu| the norms and the sums of
 // the matrix pipe off by at most 2^-23 of the running magnitude per term: 128 terms of mu.k 1.6e-5 |mu||k| (the second
 // bf16 vector of the anchor adds a 256th of that), the anchor as two bf16 vectors 2^-18, |k| 128 / 2 terms 7.7e-6, square
 // roots, reciprocal and products 1e-6: 2.9e-5 in all, as |score| <= 1.
@@ -89,6 +89,10 @@ hipError_t configure_kernels();      // one-time function attributes (dynamic LD
 hipError_t launch_step_main(const StepParams &p, hipStream_t s);
 // the same step where a KV head has at most FEW_ROWS query rows (p.few set by the plan)
 hipError_t launch_step_few(const StepParams &p, hipStream_t s);
+// How the selection of step `cy` would ride in another launch: not at all, reading its scores and positions from memory in
+// every pass, or from copies in LDS.
+enum class Ride { none, memory, lds };
+Ride ride_of(const StepParams &cy);
 // step_main of `p` whose first workgroups run the selection and compaction `cy` describes (the
 // parameters of an earlier step of another cache; for the ORDERED layout the caller still launches
 // the row shift afterwards); can_carry says whether the pair fits

@@ -343,6 +343,27 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     p.merge_wgs = p.psplits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
 }
 
+// Whether a step whose selection is to ride in a later launch shaped like this one leaves approximate scores.  They take up
+// to 4 us off the attention (at 8192 keys) and add up to 4 us to the selection, which then scores the rows near its threshold
+// exactly: they pay where the attention is the longer of the two, that is where its ranges are long for the number of keys
+// the selection goes through.  With one row tile per head they never are.  The ORDERED layout's selection moves no rows
+// and is the shorter for it, but it reads the positions of all: not from memory.  Measured, us a layer with exact and with
+// approximate scores, tiles a range in brackets:
+//   FILL, 32 / 8 heads:   8192 keys, blocks of 128 [9] 31.0 / 30.1, of 256 [19] 48.9 / 47.5, of 64 [5, one row tile] 25.5 / 26.7;
+//                         4096 keys, blocks of 128 [5] 23.1 / 23.3, of 256 [10] 33.4 / 32.0;  2048 keys, blocks of 256 [6] 25.4 / 24.9
+//   FILL, 28 / 4 heads:   8192 keys, blocks of 64 [5] 24.5 / 25.8;  4096 keys, blocks of 256 [8] 29.7 / 29.4
+//   ORDERED, 24 / 8:      4096 keys, blocks of 128 [5] 28.7 / 27.7;  32 / 8: 2048 keys, blocks of 128 [3] 20.5 / 19.7,
+//                         12288 keys, blocks of 128 (positions from memory) 45.9 / 49.5
+bool approximate_scores_pay(const keydiff_cache *c, const kd::StepParams &p)
+{
+    const int BH = p.batch * p.hkv, mtiles = (p.G * p.Bt + 255) / 256, target = c->L.target_wgs / 2;
+    const kd::Ride ride = kd::ride_of(p);
+    if (mtiles < 2 || ride == kd::Ride::none || BH + BH * mtiles > target) return false;
+    const int ntiles = (p.n + kd::TILE_KEYS - 1) / kd::TILE_KEYS;
+    const int ranges = std::min((target - BH) / (BH * mtiles), ntiles), tiles = (ntiles + ranges - 1) / ranges;
+    return p.layout == KEYDIFF_LAYOUT_FILL ? 2048 * (tiles - 4) >= p.n : ride == kd::Ride::lds && 1024 * tiles >= p.n;
+}
+
 // Whether an attention launch shaped like `p` (of cache c) should take along the row shift `sp` describes,
 // next to `seats_sel` workgroups of a carried selection: returns the workgroups per head to give the
 // shift (0: do not), and leaves in p the plan of the attention that goes with the answer.
@@ -458,12 +479,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     p.pos0 = (int32_t)pos0;
     p.do_evict = evict;
     p.do_score = evict || scores_out != nullptr;
-    // Approximate scores where the selection can ride in another launch: they take 4 us off the attention at 8192 keys and
-    // add 4 us to the selection, which then scores the rows near its threshold exactly.  As a passenger it hides
-    // that; as the launch the caller waits for it does not (attention + selection, 32 / 8 heads: 30.0 and 32.6 us at
-    // 4096 keys with exact and approximate scores, 39.8 and 42.0 at 8192, 48.1 and 49.9 at 12000).  Scores
-    // the caller asks for are exact; so are those of a step of few query rows.
-    p.score_approx = defer && carry != nullptr && evict;
+    p.score_approx = defer && carry != nullptr && evict && approximate_scores_pay(c, p);
     if (cf.window_W > 0) p.window_pos_min = (int32_t)(pos0 + Bt - cf.window_W);
 
     // a passenger rides only if the attention still fits the chip in one pass beside it
@@ -486,7 +502,6 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     }
     if (shift_parts == 0 && !riding) plan_attention(c, p);
     const int shift_wgs = shift_parts > 0 ? shift_parts * shifted->shift_p.batch * shifted->shift_p.hkv : 0;
-    if (p.G * p.Bt <= kd::FEW_ROWS) p.score_approx = 0;
     // Generation phase: step_few leaves the
     // arg-max of the scores per workgroup, and the selection reads the row to evict off those records.
     if (evict && n - N == 1 && cf.window_W == 0 && cf.layout == KEYDIFF_LAYOUT_FILL &&

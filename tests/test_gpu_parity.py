@@ -1097,3 +1097,48 @@ def test_selection_of_long_caches(n, E, d, layout, window, kind):
         assert cache.status() == 0
         cache.close()
         other.close()
+
+
+@pytest.mark.parametrize("kind", ["plain", "zero", "tiny", "huge", "all-small", "alike", "window"])
+@pytest.mark.parametrize("layout", [kd.LAYOUT_FILL, kd.LAYOUT_ORDERED], ids=["fill", "ordered"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_approximate_scores_decide_like_exact_ones(d, layout, kind):
+    # 64 KV heads of 320 query rows: one range of keys a workgroup, long enough that the deferred steps leave approximate
+    # scores.  Keys in and out of the range of the approximation, keys that differ by the last bits of a score, a window; the
+    # evictions ride in the launch of the other layer, or (every third block) are finished alone.  Queries are zero, so that
+    # the oracle needs no attention.
+    hq, hkv, N, B, blocks_ = 320, 64, 448, 64, 13
+    T = B * blocks_
+    rng = np.random.default_rng(23)
+    layers, data = [], []
+    for _ in range(2):
+        k = rng.standard_normal((hkv, T, d), dtype=np.float32) + 1.0
+        rows = rng.random(k.shape[:2]) < 0.05
+        if kind == "zero":
+            k[rows] = 0.0
+        elif kind in ("tiny", "huge"):
+            k[rows] *= np.float32(2.0 ** (-50 if kind == "tiny" else 45))
+        elif kind == "all-small":
+            k *= np.float32(2.0 ** -30)
+        elif kind == "alike":
+            k = np.tile(np.linspace(-1.0, 2.0, d, dtype=np.float32), (hkv, T, 1))
+            np.put_along_axis(k, rng.integers(0, d, size=(hkv, T, 1)), np.float32(1.5), axis=-1)
+        data.append((f32_to_bf16_bits(k)[None], f32_to_bf16_bits(rng.standard_normal((1, hkv, T, d), dtype=np.float32))))
+        w = get_config("llama31_8b").small(n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prompt_T=T)
+        layers.append(make_pair(w, N, B, layout=layout, window_W=40 if kind == "window" else 0))
+    q = torch.zeros((1, hq, B, d), dtype=torch.bfloat16, device="cuda")
+    rode = 0
+    for i in range(blocks_):
+        for l, ((cache, oc), (k, v)) in enumerate(zip(layers, data)):
+            kb, vb = (x[:, :, i * B:(i + 1) * B].copy() for x in (k, v))
+            cache.prefill_block_deferred(q, to_dev(kb), to_dev(vb), i * B, carry=layers[1 - l][0])
+            rode += cache.plan()[3] & 1
+            oc.prefill_block(None, kb, vb, i * B)
+        if i % 3 == 2:
+            for l, (cache, oc) in enumerate(layers):
+                check_state(cache, oc, f"layer {l} after block {i}")
+    assert rode >= 6
+    for l, (cache, oc) in enumerate(layers):
+        check_state(cache, oc, f"layer {l} at the end")
+        assert cache.status() == 0
+        cache.close()
