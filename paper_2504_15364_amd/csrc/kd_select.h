@@ -62,8 +62,7 @@ struct PostShared {
     int32_t cand_pos[CAND_MAX];
     double colsum[MAX_SELECT_WAVES][128];
     double mu[128], mu2[8];   // the anchor and |mu|^2 in pieces (approximate scores: exact ones of the rows near the threshold)
-    int bad;                  // a row's score is not known even approximately
-    uint32_t range[MAX_SELECT_WAVES];   // largest magnitude among a wave's evicted keys | complement of the smallest (less one)
+    int bad;                  // 1: a row's score is not known even approximately; 2: the evicted keys' sum may depend on their order
 };
 
 // bytes of dynamic LDS a carried selection places PostShared in, ahead of its bitmap and lists
@@ -89,23 +88,6 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x)
     x += dpp_fetch<0x143, 0xC>(x);
     return x;
 }
-// the larger of every 16-bit half over the 64 lanes of a wave, on the vector ALU alone (no lane's value is below 0, what
-// dpp_fetch returns outside the row)
-__device__ __forceinline__ uint32_t wave_max_u16x2(uint32_t x)
-{
-    auto larger = [](uint32_t a, uint32_t b) {
-        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
-    };
-    x = larger(x, dpp_fetch<0x128, 0xF>(x));   // row_ror 8, 4, 2, 1
-    x = larger(x, dpp_fetch<0x124, 0xF>(x));
-    x = larger(x, dpp_fetch<0x122, 0xF>(x));
-    x = larger(x, dpp_fetch<0x121, 0xF>(x));
-    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    x = larger(a[0], a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    return larger(b[0], b[1]);
-}
-
 // exclusive prefix sum over the workgroup; `wave_tot`: LDS words of the waves that no thread still reads
 template <int THREADS, typename T>
 __device__ __forceinline__ T block_exclusive_scan_t(T v, T *wave_tot, T *total)
@@ -766,6 +748,11 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         for (int t = 0; t < TURNS; ++t)
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[t][i] = 0.0;
+        // A sum of the keys is exact in any order where every term is a multiple of 2^-7 times the power of one exponent and any sum of
+        // them stays below 2^53 times that, that is where the exponents lie within 45 - log2(E) of one another.  Looked for: no
+        // element of 2^10 or more, none but zeros as far below.
+        constexpr uint32_t below = (127 + 10) << 7;   // (bf16 bits)
+        const uint32_t least = below - ((uint32_t)(45 - (32 - __clz(E))) << 7);
         u16x2 largest = {0, 0}, smallest = {0xFFFF, 0xFFFF};   // magnitudes as bf16 bits; smallest: less one, so that zeros wrap
         for (int rb0 = wave * RPW; rb0 < E; rb0 += EV_BATCH * NWAVES * RPW) {  // uniform per wave
             if (rb0 != wave * RPW) request(rb0);
@@ -791,38 +778,28 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                 for (int i = 0; i < 8; ++i) acc[0][i] += acc[t][i];
             fold(acc[0], wave);
         }
-        const uint32_t range = wave_max_u16x2(max(largest[0], largest[1]) | ((uint32_t)(0xFFFF ^ min(smallest[0], smallest[1])) << 16));
-        if (lane == 0) sh.range[wave] = range;
+        const bool out_of_range = (uint32_t)max(largest[0], largest[1]) >= below || (uint32_t)min(smallest[0], smallest[1]) + 1 < least;
+        if (__ballot(out_of_range) != 0 && lane == 0) sh.bad = 2;
         __syncthreads();   // also: every evicted row has been read before the compaction overwrites it
     }
-    bool in_order = sorted;
-    if (!sorted) {
-        u16x2 range = {0, 0};
-#pragma unroll
-        for (int w = 0; w < NWAVES; ++w) range = __builtin_elementwise_max(range, __builtin_bit_cast(u16x2, sh.range[w]));
-        const uint32_t hi = range[0], lo = 0xFFFFu ^ range[1];
-        // Every term is a multiple of 2^-7 times the power of the smallest exponent, and any sum of them below 2 E times that of
-        // the largest: with the exponents no further apart than this it fits the 53 bits of a double.  (Exponent field 0 has the
-        // steps of field 1; among zeros alone lo is beyond hi.)
-        if ((hi >> 7) > max((lo + 1) >> 7, 1u) + (uint32_t)(45 - (32 - __clz(E)))) {   // uniform; rare
-            in_order = true;
-            put_in_order();
+    const bool in_order = sorted || sh.bad == 2;   // uniform
+    if (in_order && !sorted) {   // rare
+        put_in_order();
 #pragma unroll 1
-            for (int part = wave; part < MAX_SELECT_WAVES; part += NWAVES) {
-                double acc[8];
+        for (int part = wave; part < MAX_SELECT_WAVES; part += NWAVES) {
+            double acc[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+            for (int i = 0; i < 8; ++i) acc[i] = 0.0;
 #pragma unroll 1
-                for (int rb0 = part * RPW; rb0 < E; rb0 += MAX_SELECT_WAVES * RPW) {
-                    const int r = rb0 + erl;
-                    u32x4 w = {0u, 0u, 0u, 0u};
-                    if (r < E) w = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + eu * 8);
-                    add_key(w, acc);
-                }
-                fold(acc, part);
+            for (int rb0 = part * RPW; rb0 < E; rb0 += MAX_SELECT_WAVES * RPW) {
+                const int r = rb0 + erl;
+                u32x4 w = {0u, 0u, 0u, 0u};
+                if (r < E) w = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + eu * 8);
+                add_key(w, acc);
             }
-            __syncthreads();
+            fold(acc, part);
         }
+        __syncthreads();
     }
     KD_TL(8);   // evicted rows read
 
