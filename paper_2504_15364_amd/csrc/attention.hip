@@ -140,7 +140,6 @@ __device__ __forceinline__ void loads_landed(u32x2 &x, u32x4 (&w)[A][B])
 // of 64 rows per SIMD every vector, LDS and copy-issue latency lay open and the kernel was slower).
 // HELP: some waves of a workgroup may have no query row at all (rows that end inside a tile of 256); such a
 // wave takes no part in the attention, it copies its share of every tile and scores rows.
-constexpr int MAIN_WAVES = 8;
 // EXACT: the scores of all rows are formed in double here (where the caller asks for them, where the call evicts by
 // itself, and where a deferred selection would not hide the work of scoring); otherwise the attention leaves approximate
 // scores, or none, and the selection decides from exact ones of the few rows near its threshold.
@@ -189,7 +188,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     id /= BH;
     const int mt = id % p.mtiles;
     const int sp = id / p.mtiles;
-    const int b = bh / p.hkv, kvh = bh % p.hkv;
     const int Mtot = p.G * p.Bt;
     // Key range of this split.  A tile that takes rows of the block (causal mask, a second source,
     // decisions per copy) costs more than a plain tile of cached keys -- about 1.4 times by the
@@ -334,7 +332,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     const int qoff = wave * QBYTES, qhalf = qoff / (2 * TILE_B);
     unsigned char *qwave = smem + (size_t)((t0 + 2 + qhalf) % STAGES) * 2 * TILE_B + (qoff - qhalf * 2 * TILE_B);
     {
-        const char *qhead = reinterpret_cast<const char *>(p.q + (size_t)(b * p.hq + kvh * p.G) * p.Bt * D);
+        const char *qhead = reinterpret_cast<const char *>(p.q + (size_t)bh * p.G * p.Bt * D);
         const int m0 = mt * TM + wave * QROWS;   // first row of the wave
         if (m0 + QROWS <= Mtot) {
             // every row exists: one base address for the wave, a 32-bit offset per lane and copy
@@ -1039,7 +1037,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     KD_TL(9);   // last tile done
 
     // ---- output: stored first, so that the write latency runs under the score flush and the append
-    if (active && p.psplits > 1) {
+    if (active && p.splits > 1) {
         // Partials leave in the accumulator's own layout, as whole 512-byte slabs with no detour
         // through LDS: slab (db, jj) of a 32-row block holds, for lane (h, l32), the four values
         // d = 32 db + 8 jj + 4 h .. + 3 of row l32.  Only the merge reads them, in the same order, in
@@ -1099,7 +1097,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         }
         // rows of this wave: m = mbase .. mbase + WROWS - 1, contiguous in `out`
         const int mbase = mt * TM + wave * WROWS;
-        unsigned char *gbase = reinterpret_cast<unsigned char *>(p.out + ((size_t)(b * p.hq + kvh * p.G) * p.Bt + mbase) * D);
+        unsigned char *gbase = reinterpret_cast<unsigned char *>(p.out + ((size_t)bh * p.G * p.Bt + mbase) * D);
         constexpr int RPI = 1024 / ROWB;   // rows one wave-wide 16-byte-per-lane store covers
 #pragma unroll
         for (int i = 0; i < WBYTES / 1024; ++i) {
@@ -1247,7 +1245,7 @@ hipError_t configure_main_kernels()
 }
 
 // workgroups whose last waves have no query row at all run the variant in which those waves help
-static bool main_runs_help(const StepParams &p) { return p.mtiles * 32 * p.NW - p.G * p.Bt >= 32; }
+static bool main_runs_help(const StepParams &p) { return p.mtiles * 32 * MAIN_WAVES - p.G * p.Bt >= 32; }
 
 static bool scores_exactly(const StepParams &p) { return p.do_score && !p.score_approx; }
 
@@ -1263,8 +1261,8 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
     else if (help) hipLaunchKernelGGL((step_main_kernel<DD, true, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);          \
     else if (exact) hipLaunchKernelGGL((step_main_kernel<DD, false, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);         \
     else hipLaunchKernelGGL((step_main_kernel<DD, false, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);
-    if (p.D == 128 && p.NW == MAIN_WAVES) { KD_GO(128) }
-    else if (p.D == 64 && p.NW == MAIN_WAVES) { KD_GO(64) }
+    if (p.D == 128) { KD_GO(128) }
+    else if (p.D == 64) { KD_GO(64) }
 #undef KD_GO
     else return hipErrorInvalidValue;
     return hipGetLastError();
@@ -1280,7 +1278,7 @@ bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
     // (a step of few query rows takes no passenger whichever kernel runs it: it is shorter than a selection)
-    return p.NW == 8 && p.G * p.Bt > FEW_ROWS && !(scores_exactly(p) && cy.score_approx) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
+    return p.G * p.Bt > FEW_ROWS && !(scores_exactly(p) && cy.score_approx) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
            ride_of(cy) != Ride::none;
 }
 
@@ -1312,7 +1310,7 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
 bool can_host_shift(const StepParams &p, const StepParams &shifted)
 {
     const int E = shifted.n - shifted.N;
-    return p.NW == 8 && !p.few && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
+    return !p.few && !main_runs_help(p) && p.D == shifted.D && E > 0 && E <= ORD_ROWS;
 }
 
 hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, const ShiftRide &ride, hipStream_t s)

@@ -157,12 +157,12 @@ __device__ __forceinline__ void merge_rows(const StepParams &p, size_t gid)
     float mx = -INFINITY;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float Lsum = 0.f;
-    for (int s0 = 0; s0 < p.psplits; s0 += MB) {
+    for (int s0 = 0; s0 < p.splits; s0 += MB) {
         float2 ml[MB];
         f16x4 o[MB];
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            const bool live = s0 + i < p.psplits;
+            const bool live = s0 + i < p.splits;
             const f16x4 zero = {(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
             ml[i] = live ? p.part_ml[(size_t)(s0 + i) * rows + row] : make_float2(-INFINITY, 0.f);
             o[i] = live ? *reinterpret_cast<const f16x4 *>(pbase + (size_t)(s0 + i) * pstride) : zero;
@@ -191,7 +191,6 @@ __device__ __forceinline__ void merge_rows(const StepParams &p, size_t gid)
         }
     }
     const float inv = 1.f / Lsum;
-    const int b = bh / p.hkv, kvh = bh % p.hkv;
     const int g = m / p.Bt, j = m % p.Bt;
     const int d0 = 8 * slab + 4 * (L >> 5);
     bf16x4 o;
@@ -199,7 +198,7 @@ __device__ __forceinline__ void merge_rows(const StepParams &p, size_t gid)
     o[1] = (__bf16)(acc.y * inv);
     o[2] = (__bf16)(acc.z * inv);
     o[3] = (__bf16)(acc.w * inv);
-    *reinterpret_cast<bf16x4 *>(p.out + ((size_t)(b * p.hq + kvh * p.G + g) * p.Bt + j) * D + d0) = o;
+    *reinterpret_cast<bf16x4 *>(p.out + (((size_t)bh * p.G + g) * p.Bt + j) * D + d0) = o;
 }
 
 // The merge of step_few's partials (float, [psplits][BH][G * Bt][D], each normalised by its row sum): one
@@ -212,7 +211,7 @@ __device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int b
     constexpr int MB = 8;                       // splits requested together
     const int BH = p.batch * p.hkv, Mtot = p.G * p.Bt;
     const int items = Mtot * (D / 4);           // at most POST_THREADS (32 rows of 128)
-    const int shares = min(POST_THREADS / items, p.psplits);
+    const int shares = min(POST_THREADS / items, p.splits);
     const int it = (int)threadIdx.x % items, share = (int)threadIdx.x / items;
     const float *part = reinterpret_cast<const float *>(p.part_o) + (size_t)bh * Mtot * D + (size_t)it * 4;
     const float2 *mls = p.part_ml + (size_t)bh * Mtot + it / (D / 4);
@@ -220,13 +219,13 @@ __device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int b
     float mx = -INFINITY, Lsum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     if (share < shares) {
-        for (int s0 = share; s0 < p.psplits; s0 += MB * shares) {
+        for (int s0 = share; s0 < p.splits; s0 += MB * shares) {
             float2 ml[MB];
             f32x4 o[MB];
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 const int s_ = s0 + i * shares;
-                const bool live = s_ < p.psplits;
+                const bool live = s_ < p.splits;
                 ml[i] = live ? mls[(size_t)s_ * mstride] : make_float2(-INFINITY, 0.f);
                 o[i] = live ? *reinterpret_cast<const f32x4 *>(part + (size_t)s_ * pstride) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
@@ -272,11 +271,10 @@ __device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int b
         return;
     }
     const float inv = 1.f / Lsum;
-    const int b = bh / p.hkv, kvh = bh % p.hkv;
     bf16x4 o;
 #pragma unroll
     for (int r = 0; r < 4; ++r) o[r] = (__bf16)(acc[r] * inv);
-    *reinterpret_cast<bf16x4 *>(p.out + (size_t)(b * p.hq + kvh * p.G) * p.Bt * D + (size_t)it * 4) = o;
+    *reinterpret_cast<bf16x4 *>(p.out + (size_t)bh * p.G * p.Bt * D + (size_t)it * 4) = o;
 }
 
 // The merge as a kernel of its own (a step whose eviction is deferred has nothing else to run
@@ -610,7 +608,7 @@ hipError_t configure_kernels()
 
 hipError_t launch_step_score(const StepParams &p, hipStream_t s)
 {
-    const int grid = p.batch * p.hkv * p.score_chunks;
+    const int grid = p.batch * p.hkv * ((p.n + SCORE_ROWS - 1) / SCORE_ROWS);
     if (p.D == 128) hipLaunchKernelGGL((step_score_kernel<128>), dim3(grid), dim3(SCORE_THREADS), 0, s, p);
     else if (p.D == 64) hipLaunchKernelGGL((step_score_kernel<64>), dim3(grid), dim3(SCORE_THREADS), 0, s, p);
     else return hipErrorInvalidValue;
@@ -675,7 +673,7 @@ hipError_t launch_merge_shift(const StepParams &pm, const StepParams &ps, int32_
     const size_t merge_threads = (size_t)pm.batch * pm.hkv * ((pm.G * pm.Bt + 31) / 32) * (pm.D / 8) * 64;
     const int mw = (int)((merge_threads + ORD_THREADS - 1) / ORD_THREADS);
     const int grid = mw + ps.batch * ps.hkv * nchunks;
-    if (ps.n - ps.N > ORD_THREADS * ORD_ROWS || pm.D != ps.D || pm.psplits < 2 || pm.few) return hipErrorInvalidValue;
+    if (ps.n - ps.N > ORD_THREADS * ORD_ROWS || pm.D != ps.D || pm.splits < 2 || pm.few) return hipErrorInvalidValue;
     if (pm.D == 128) hipLaunchKernelGGL((merge_shift_kernel<128>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, ps, flags, nchunks, epoch, mw);
     else if (pm.D == 64) hipLaunchKernelGGL((merge_shift_kernel<64>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, ps, flags, nchunks, epoch, mw);
     else return hipErrorInvalidValue;

@@ -92,7 +92,6 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     const int c16 = lane & 15, g = lane >> 4;
     const int BH = p.batch * p.hkv;
     const int bh = (int)blockIdx.x % BH, mt = (int)blockIdx.x / BH % p.mtiles, sp = (int)blockIdx.x / BH / p.mtiles;
-    const int b = bh / p.hkv, kvh = bh % p.hkv;
     const int Mtot = p.G * p.Bt;
     const int m0 = 16 * mt, mrows = min(16, Mtot - m0);   // this workgroup's query rows
     const int nt = (p.n + FEW_KEYS - 1) / FEW_KEYS;
@@ -182,7 +181,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     bf16x8 qreg[NC];
     int vis;   // rows [0, vis) are visible to the lane's query: all cached rows, block rows 0 .. j
     {
-        const uint16_t *qhead = p.q + (size_t)(b * p.hq + kvh * p.G) * p.Bt * D;
+        const uint16_t *qhead = p.q + (size_t)bh * p.G * p.Bt * D;
         const int m = min(m0 + c16, Mtot - 1);
         vis = p.len + m % p.Bt + 1;
 #pragma unroll
@@ -439,14 +438,14 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         const float inv = L > 0.f ? 1.f / L : 0.f;   // a row may see no key of this workgroup's range
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] *= inv;
-        if (p.psplits > 1) {
+        if (p.splits > 1) {
             *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.part_o) + (((size_t)sp * BH + bh) * Mtot + m0 + m) * D + d0) = acc;
             if (d0 == 0) p.part_ml[((size_t)sp * BH + bh) * Mtot + m0 + m] = make_float2(mx, L);
         } else {
             bf16x4 o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = (__bf16)acc[i];
-            *reinterpret_cast<bf16x4 *>(p.out + ((size_t)(b * p.hq + kvh * p.G) * p.Bt + m0 + m) * D + d0) = o;
+            *reinterpret_cast<bf16x4 *>(p.out + ((size_t)bh * p.G * p.Bt + m0 + m) * D + d0) = o;
         }
     }
     if (scoring && p.argmax_rec && tid == 0) {

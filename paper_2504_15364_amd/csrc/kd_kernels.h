@@ -18,6 +18,7 @@
 namespace kd {
 
 constexpr int TILE_KEYS = 64;       // keys per attention K/V tile
+constexpr int MAIN_WAVES = 8;       // waves (of 32 query rows) per step_main workgroup
 constexpr int FEW_KEYS = 32;        // keys per wave and tile in step_few
 constexpr int FEW_ROWS = 32;        // query rows per KV head up to which a step may run step_few instead of step_main (the plan decides)
 constexpr int POST_THREADS = 1024;  // workgroup size of step_post
@@ -39,6 +40,7 @@ constexpr int MAX_CAP = 32768;      // budget_N + block_B limit (selection bitma
 constexpr int STATUS_SELECT_COUNT = 1;  // selection evicted a number of rows other than n - N
 constexpr int STATUS_ORDER_TIMEOUT = 2; // ordered compaction: a workgroup gave up waiting for its predecessors
 
+// (256 bytes: four lines of argument memory, which is cold in every launch)
 struct StepParams {
     // tensors of the call
     const uint16_t *q;               // [batch][hq][Bt][D]
@@ -53,9 +55,9 @@ struct StepParams {
                                      // step_main (+ the block's keys), then by step_post (- the evicted keys)
     int32_t *status;
     // scratch
-    _Float16 *part_o;                // [psplits][BH][blocks of 32 rows][D/8 slabs][64 lanes][4] partial outputs in the
+    _Float16 *part_o;                // [splits][BH][blocks of 32 rows][D/8 slabs][64 lanes][4] partial outputs in the
                                      // MFMA accumulator layout, each normalised by its row sum
-    float2 *part_ml;                 // [psplits][BH * G * Bt]    (reference max in log2 units, row sum)
+    float2 *part_ml;                 // [splits][BH * G * Bt]     (reference max in log2 units, row sum)
     float *scores;                   // [BH][cap]; approximate if score_approx
     double *anchor;                  // [BH][D] the step's anchor (score_approx)
     int32_t *dstmap;                 // [BH][cap] ORDERED layout: destination row or -1
@@ -64,16 +66,14 @@ struct StepParams {
                                      // per step_main workgroup the largest (orderable score bits << 32 | row) among the
                                      // rows it scored, and whether another of its rows has the same score bits
     // sizes
-    int batch, hq, hkv, G, D, Bt, len, n, N, B, cap;
-    int splits, mtiles, ntiles, NW;      // NW: waves (of 32 query rows) per step_main workgroup
-    int psplits;                     // partials per output row the merge adds up (1: none, the attention writes `out`)
+    int batch, hkv, G, D, Bt, len, n, N, B, cap;
+    int splits, mtiles, ntiles;      // splits: ranges of keys per head, one partial per output row each (1: the attention writes `out`)
     int few;                         // the step runs step_few (at most FEW_ROWS query rows per KV head, see the plan): its partials are
-                                     // float [psplits][BH][G * Bt][D] in part_o
+                                     // float [splits][BH][G * Bt][D] in part_o
     int edge_cost;                   // weight (in plain tiles: 1 or 2) of a tile holding rows of the block when
                                      // the key tiles are divided over the splits
-    int score_chunks;                // step_score workgroups per head
     int lists_in_lds;                // selection lists live in LDS (else in `lists`)
-    int merge_wgs;                   // merge workgroups in step_post (0 when psplits == 1)
+    int merge_wgs;                   // merge workgroups in step_post (0 when splits == 1)
     int do_score, do_evict;
     int score_approx;                // the step's scores are within SCORE_SLACK of the exact ones (or NaN: not known)
     int anchor_mode, layout, window_W;
@@ -84,6 +84,9 @@ struct StepParams {
     unsigned long long *timeline;    // [workgroup][32] wall-clock stamps of this launch (profiling build only)
 #endif
 };
+#ifndef KD_TIMELINE
+static_assert(sizeof(StepParams) == 256, "a field that crosses into a fifth line costs every launch that reads it a trip to memory");
+#endif
 
 hipError_t configure_kernels();      // one-time function attributes (dynamic LDS sizes)
 hipError_t launch_step_main(const StepParams &p, hipStream_t s);

@@ -244,7 +244,6 @@ kd::StepParams base_params(const keydiff_cache *c, int n, unsigned char *scratch
     p.anchor = reinterpret_cast<double *>(scratch + c->L.off_anchor);
     p.lists = reinterpret_cast<int32_t *>(scratch + c->L.off_lists);
     p.batch = cf.batch;
-    p.hq = cf.n_q_heads;
     p.hkv = cf.n_kv_heads;
     p.G = cf.n_q_heads / cf.n_kv_heads;
     p.D = cf.head_dim;
@@ -253,10 +252,7 @@ kd::StepParams base_params(const keydiff_cache *c, int n, unsigned char *scratch
     p.B = cf.block_B;
     p.cap = c->L.cap;
     p.splits = 1;
-    p.psplits = 1;
     p.edge_cost = 1;
-    p.score_chunks = (n + kd::SCORE_ROWS - 1) / kd::SCORE_ROWS;
-    if (p.score_chunks < 1) p.score_chunks = 1;
     p.lists_in_lds = kd::lists_fit_lds(n, cf.budget_N) ? 1 : 0;
     p.anchor_mode = cf.anchor_mode;
     p.layout = cf.layout;
@@ -288,8 +284,7 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     // Workgroups of eight waves x 32 query rows, one per compute unit.  Where the rows of a head do
     // not fill the last workgroup its idle waves help (copy tiles, score rows); measured against
     // 4-wave workgroups at 64 and 128 rows per head: 29.6 vs 44.3 and 31.4 vs 47.2 us per step.
-    p.NW = 8;
-    const int TM = 32 * p.NW;
+    const int TM = 32 * kd::MAIN_WAVES;
     p.mtiles = (Mtot + TM - 1) / TM;
     p.ntiles = (p.n + kd::TILE_KEYS - 1) / kd::TILE_KEYS;
     const int target = c->L.target_wgs / 2;   // the compute units of the chip
@@ -317,7 +312,7 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
         if (splits < 1) splits = 1;
         // the float partials take two of the scratch buffer's fp16 rows each
         while (splits > 1 && 2l * splits * BH * Mtot > c->L.max_part_rows) --splits;
-        p.splits = p.psplits = splits;
+        p.splits = splits;
         p.merge_wgs = splits > 1 ? BH : 0;
         return;
     }
@@ -333,14 +328,14 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     // partial rows must fit the scratch sized at init
     const int Mpad = (Mtot + 31) / 32 * 32;   // partials are stored in blocks of 32 rows
     while (splits > 1 && (long)splits * BH * Mpad > c->L.max_part_rows) --splits;
-    p.splits = p.psplits = splits;
+    p.splits = splits;
     // a tile with rows of the block counts as two plain ones when the tiles are dealt out (it takes
     // about 1.4 times as long, and an equal share would make its split the last to end); every split
     // must still span at least one tile, which a span of 2 * edge_cost cost units guarantees
     const int tplain = p.len / kd::TILE_KEYS < p.ntiles ? p.len / kd::TILE_KEYS : p.ntiles;
     p.edge_cost = (tplain + 2 * (p.ntiles - tplain)) / splits >= 4 ? 2 : 1;
     const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64;
-    p.merge_wgs = p.psplits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
+    p.merge_wgs = p.splits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
 }
 
 // Whether a step whose selection is to ride in a later launch shaped like this one leaves approximate scores.  They take up
@@ -601,7 +596,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     if (shift_owed)   // ... else in a launch of its own
         if (int rc = compact_ordered(carry, carry->pend, s)) return rc;
     if (c->profiling) ProfScope ps(c, KEYDIFF_K_EVENT_PAIR, s);
-    c->plan[0] = p.psplits;
+    c->plan[0] = p.splits;
     c->plan[1] = p.mtiles;
     c->plan[2] = p.ntiles;
     c->plan[3] = (riding ? 1 : 0) | (shift_parts > 0 ? 2 : 0);
