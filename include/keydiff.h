@@ -162,8 +162,10 @@ KEYDIFF_API int keydiff_prefill_block_static(keydiff_cache_t *cache, const void 
  * cache used this way needs a scratch buffer of its own.  In the ORDERED layout only the
  * selection rides; the stable row shift of `carry` follows in the same call, inside this step's
  * merge launch (or in a launch of its own where the step has none).  The retained set is that
- * of keydiff_prefill_block bit for bit (the scores behind it are exact only for the rows near the threshold); `out` may differ in the last bf16 bit, because the
- * keys are cut into a different number of ranges when passengers take part of the chip.    */
+ * of keydiff_prefill_block bit for bit (where the step leaves approximate scores, the selection forms
+ * the exact ones of the rows near its threshold in the same arithmetic); `out` may differ in the last
+ * bf16 bit, because the keys are cut into a different number of ranges when passengers take part of
+ * the chip.                                                                                  */
 KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const void *q, const void *k_new,
                                    const void *v_new, int32_t Bt, int64_t pos0, void *out,
                                    keydiff_cache_t *carry, void *stream);
@@ -231,7 +233,7 @@ KEYDIFF_API int keydiff_cache_len(const keydiff_cache_t *cache, int32_t *len);
 
 /* How the last block step on `cache` was cut up for the chip (host values, no sync): plan_out[0] the
  * number of key ranges (split-KV partials per output row the merge adds up; 1 = no merge launch),
- * [1] workgroups of 256 query rows per KV head, [2] 64-key tiles of the step, [3] bit 0: the step's
+ * [1] row tiles per KV head (of 256 query rows, or of 16 in some steps of at most 32), [2] 64-key tiles of the step, [3] bit 0: the step's
  * launch carried another cache's pending eviction, bit 1: it carried another cache's pending row
  * shift (ORDERED layout).  For byte and launch accounting by a benchmark.  */
 KEYDIFF_API int keydiff_cache_plan(const keydiff_cache_t *cache, int32_t plan_out[4]);
@@ -256,7 +258,7 @@ KEYDIFF_API int keydiff_cache_status(const keydiff_cache_t *cache, int32_t *stat
  * keydiff_profile_read synchronises, writes the summed milliseconds and launch
  * counts of each kernel class (arrays of KEYDIFF_NKERNELS, host) and resets.    */
 enum {
-    KEYDIFF_K_MAIN = 0,    /* step_main: append + attention partials + key sum + cosine scores
+    KEYDIFF_K_MAIN = 0,    /* step_main or step_few: append + attention partials + key sum + cosine scores
                               (+ the carried selection of another cache, if any)               */
     KEYDIFF_K_SCORE = 1,   /* step_score: cosine scores outside a block step (keydiff_scores)  */
     KEYDIFF_K_POST = 2,    /* step_post: partial merge || selection and compaction of the step (the

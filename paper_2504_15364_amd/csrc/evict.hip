@@ -45,7 +45,7 @@ __device__ __forceinline__ void score_rows(const StepParams &p, ScoreShared &sh,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int u = lane % UPR, rl = lane / UPR;
     const uint16_t *kb = p.k + (size_t)bh * p.cap * D;
-    // the rows are requested before the anchor is formed: the two memory round trips (key sum, rows) overlap
+    // the rows are requested ahead of the key sum
     const int base = row0 + wave * WROWS;
     u32x4 w[NP];
 #pragma unroll

@@ -61,9 +61,9 @@ struct StepParams {
     float *scores;                   // [BH][cap]; approximate if score_approx
     double *anchor;                  // [BH][D] the step's anchor (score_approx)
     int32_t *dstmap;                 // [BH][cap] ORDERED layout: destination row or -1
-    int32_t *lists;                  // [BH][4 * B] evicted rows | holes | movers | mover rank of each tail row
+    int32_t *lists;                  // [BH][4 * B]: of E rows each, evicted rows | those below N in ascending order (the rest is not used)
     unsigned long long *argmax_rec;  // nullable [BH][splits][2]: the generation phase (one row to evict, no window):
-                                     // per step_main workgroup the largest (orderable score bits << 32 | row) among the
+                                     // per step_few workgroup the largest (orderable score bits << 32 | row) among the
                                      // rows it scored, and whether another of its rows has the same score bits
     // sizes
     int batch, hkv, G, D, Bt, len, n, N, B, cap;
@@ -90,7 +90,7 @@ static_assert(sizeof(StepParams) == 256, "a field that crosses into a fifth line
 
 hipError_t configure_kernels();      // one-time function attributes (dynamic LDS sizes)
 hipError_t launch_step_main(const StepParams &p, hipStream_t s);
-// the same step where a KV head has at most FEW_ROWS query rows (p.few set by the plan)
+// the same step where the plan chose step_few (p.few)
 hipError_t launch_step_few(const StepParams &p, hipStream_t s);
 // How the selection of step `cy` would ride in another launch: not at all, reading its scores and positions from memory in
 // every pass, or from copies in LDS.

@@ -385,9 +385,9 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                     fold(((uint64_t)hi << 32) | lo, ot);
                 }
                 if (lane == 0) {
-                sh.sel_cnt = (b0 != 0 && !tie) ? 1u : 0u;
-                sh.tb = (int)(uint32_t)b0;
-                if (b0 != 0 && !tie) evbits[(uint32_t)b0 >> 5] |= 1u << ((uint32_t)b0 & 31);
+                    sh.sel_cnt = (b0 != 0 && !tie) ? 1u : 0u;
+                    sh.tb = (int)(uint32_t)b0;
+                    if (b0 != 0 && !tie) evbits[(uint32_t)b0 >> 5] |= 1u << ((uint32_t)b0 & 31);
                 }
             }
             __syncthreads();
@@ -395,35 +395,35 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             gbest = known ? 1 : 0;
         }
         if (!known) {
-        uint64_t best = 0;   // 0: no row (every real key is larger: orderable() of a finite score is > 0)
-        int besti = -1;
-        for_rows(true, [&](int i, float s, int32_t pi, int) {
-            if (!exempt(pi)) {
-                const uint64_t key = ((uint64_t)orderable(s) << 32) | (uint32_t)pi;
-                if (key > best) {
-                    best = key;
-                    besti = i;
+            uint64_t best = 0;   // 0: no row (every real key is larger: orderable() of a finite score is > 0)
+            int besti = -1;
+            for_rows(true, [&](int i, float s, int32_t pi, int) {
+                if (!exempt(pi)) {
+                    const uint64_t key = ((uint64_t)orderable(s) << 32) | (uint32_t)pi;
+                    if (key > best) {
+                        best = key;
+                        besti = i;
+                    }
                 }
+            });
+            uint64_t wbest = best;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t lo = __shfl_xor((uint32_t)wbest, off), hi = __shfl_xor((uint32_t)(wbest >> 32), off);
+                const uint64_t o = ((uint64_t)hi << 32) | lo;
+                wbest = o > wbest ? o : wbest;
             }
-        });
-        uint64_t wbest = best;
+            if (lane == 0) sh.wave_tot64[wave] = wbest;
+            __syncthreads();
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t lo = __shfl_xor((uint32_t)wbest, off), hi = __shfl_xor((uint32_t)(wbest >> 32), off);
-            const uint64_t o = ((uint64_t)hi << 32) | lo;
-            wbest = o > wbest ? o : wbest;
+            for (int w = 0; w < NWAVES; ++w) gbest = sh.wave_tot64[w] > gbest ? sh.wave_tot64[w] : gbest;
+            // positions are unique within a head, so exactly one thread holds the winning key
+            if (besti >= 0 && best == gbest) {
+                atomicOr(&evbits[besti >> 5], 1u << (besti & 31));
+                sh.tb = besti;
+            }
+            __syncthreads();
         }
-        if (lane == 0) sh.wave_tot64[wave] = wbest;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NWAVES; ++w) gbest = sh.wave_tot64[w] > gbest ? sh.wave_tot64[w] : gbest;
-        // positions are unique within a head, so exactly one thread holds the winning key
-        if (besti >= 0 && best == gbest) {
-            atomicOr(&evbits[besti >> 5], 1u << (besti & 31));
-            sh.tb = besti;
-        }
-        __syncthreads();
-        }   // !known
         if (p.layout == 1 && tail_regs && gbest != 0) {
             // FILL: the one tail row (row N, this step's token) travels with the evicted key: the rest of the work
             // is one row read and at most one row moved, done here without lists
