@@ -426,9 +426,8 @@ def test_deferred_eviction_with_states_read_in_between():
 
 
 def test_deferred_eviction_where_nothing_can_ride():
-    # with a single wave's worth of query rows per head the attention runs its alternating-waves mode,
-    # which has no carrying variant: every eviction is finished in a launch of its own, in both
-    # layouts, with the plain call's results
+    # a step of at most 32 query rows per head carries nothing: every eviction is finished in a launch of its
+    # own, in both layouts, with the plain call's results
     w = get_config("llama32_3b").small(n_q_heads=4, n_kv_heads=2, head_dim=128, prompt_T=240)
     run_layers_deferred(w, 80, 8, 2, seeds=(46, 47), check_every=0, expect_ride=False, layout=kd.LAYOUT_FILL)
     run_layers_deferred(w, 80, 8, 2, seeds=(48, 49), check_every=0, expect_ride=False, layout=kd.LAYOUT_ORDERED)
@@ -841,10 +840,9 @@ def test_steps_with_few_query_rows(hq, hkv, d, N, sizes, anchor):
 @pytest.mark.parametrize("kind", ["zero", "tiny", "huge", "all-small", "one-by-one"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_deferred_scores_outside_the_range_of_the_matrix_pipe(kind, d):
-    # With the eviction deferred the attention leaves approximate scores (float sums on the matrix pipe) and the
-    # selection scores the rows near its threshold exactly; rows whose norms leave the range of the approximation send it
-    # to the exact scores of every row.  Zero keys (which stay in range), keys of 2^-50 and 2^45 among ordinary ones, all
-    # keys of 2^-30, and a first eviction of a single row.  Queries are zero: only the
+    # Zero keys, keys of 2^-50 and 2^45 among ordinary ones, all keys of 2^-30, and a first eviction of a single row, with the
+    # eviction deferred.  These steps have one row tile per head, so their scores are exact; where they are approximate, and
+    # out of range for some of these keys: test_approximate_scores_decide_like_exact_ones.  Queries are zero: only the
     # eviction is at stake, and keys of 2^45 would otherwise decide the softmax by rounding.
     N, B = (320, 64) if kind != "one-by-one" else (255, 64)
     w = get_config("llama31_8b").small(n_q_heads=8, n_kv_heads=2, head_dim=d, prompt_T=N + 6 * B)
@@ -1142,3 +1140,34 @@ def test_approximate_scores_decide_like_exact_ones(d, layout, kind):
         check_state(cache, oc, f"layer {l} at the end")
         assert cache.status() == 0
         cache.close()
+
+
+@pytest.mark.parametrize("kind", ["plain", "pairs", "few"])
+@pytest.mark.parametrize("n,d,layout", [(12305, 64, kd.LAYOUT_FILL), (16384, 128, kd.LAYOUT_FILL), (11000, 64, kd.LAYOUT_ORDERED)])
+def test_selection_of_long_caches_from_approximate_scores(n, d, layout, kind):
+    # steps long enough that a deferred one leaves approximate scores, finished alone and inside another cache's launch; with
+    # five keys over and over more rows come near the threshold than are scored one by one
+    hq, hkv, E = 32, 8, 128
+    N = n - E
+    w = get_config("llama31_8b").small(n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prompt_T=n)
+    rng = np.random.default_rng(n)
+    k = keys_with_ties(rng, hkv, n, d, kind)[None]
+    q = torch.zeros((1, hq, E, d), dtype=torch.bfloat16, device="cuda")
+    first, block = to_dev(k[:, :, :N]), to_dev(k[:, :, N:])
+    pos = np.broadcast_to(np.arange(N, dtype=np.int32), (1, hkv, N)).copy()
+    for alone in (True, False):
+        cache, oc = make_pair(w, N, E, layout=layout)
+        other = kd.KeyDiffCache(cache.cfg)
+        cache.load(first, first, torch.from_numpy(pos).cuda())
+        oc.load(k[:, :, :N].copy(), k[:, :, :N].copy(), pos)
+        cache.prefill_block_deferred(q, block, block, N, carry=other)
+        if alone:
+            cache.finish()
+        else:
+            other.prefill_block_deferred(q, block, block, 0, carry=cache)
+            assert other.plan()[3] & 1
+        oc.prefill_block(None, k[:, :, N:].copy(), k[:, :, N:].copy(), N)
+        check_state(cache, oc, "alone" if alone else "carried")
+        assert cache.status() == 0
+        cache.close()
+        other.close()
