@@ -173,15 +173,20 @@ KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const voi
 /* One block through every layer of a model (Eq. 5 applied per layer, Fig. 1's four steps in each):
  * caches, q, k_new, v_new and out are host arrays of n_layers pointers, the tensors of layer l
  * shaped as for keydiff_prefill_block; Bt and pos0 are the block's, the same in every layer.
- * Equivalent to keydiff_prefill_block_deferred on layer 0, 1, ... in turn with the layer before it
+ * The layers' retained sets, rows and outputs are those of keydiff_prefill_block on layer 0, 1, ... in turn (`out` up to
+ * the last bf16 bit, as the keys may be cut into other ranges).  Layers that are shaped alike and as long, and of which
+ * none writes (output, cache, scratch buffer) what another one touches, share their launches: up to 16 layers' attention
+ * in one, their merges and evictions in the next, the row shifts of the ORDERED layout in a third; nothing is left pending.
+ * Else, or while one of the handles is being profiled (its kernels are then its own), the call is
+ * keydiff_prefill_block_deferred on layer 0, 1, ... in turn with the layer before it
  * as `carry` (for layer 0 the last layer, whose eviction from the previous block is still
  * pending): every layer's selection and compaction runs inside the next layer's attention
  * launch, and the last layer's stays pending until the next block (or keydiff_finish, or any
- * other call on that cache).  With n_layers == 1 nothing can be carried and the eviction is
- * enqueued at the start of the next call on the cache.  ORDERED layout with three layers or more:
- * the stable row shift of layer l, whose selection rode in the launch of layer l + 1, rides in the
- * attention launch of layer l + 2 where the shapes allow it (a block that evicts at most 128 rows,
- * 256-row query tiles that are full, the same head_dim), so after the call the shifts of the last
+ * other call on that cache).  With n_layers == 1 the call is keydiff_prefill_block.
+ * ORDERED layout with three layers or more goes the second way wherever
+ * the stable row shift of layer l, whose selection rode in the launch of layer l + 1, can ride in the
+ * attention launch of layer l + 2 (a block that evicts at most 128 rows,
+ * 256-row query tiles that are full, the same head_dim), so that after the call the shifts of the last
  * two layers may still be pending as well; like a pending eviction, a pending shift is enqueued
  * first by any other call on its cache, and the rows of such a cache are not in position order
  * until then.  All pointers are checked before

@@ -167,7 +167,8 @@ def check_rope_tables(cfg, cos, sin):
 
 def prefill_block_layers(caches, q, k_new, v_new, pos0: int, out=None, stream=None, rope=None):
     """One block through the layers of a model: `caches`, `q`, `k_new`, `v_new` (and `out`) are
-    sequences with one entry per layer; every layer's eviction rides in the next layer's launch.
+    sequences with one entry per layer.  Layers shaped alike share their launches; else every layer's eviction
+    rides in the next layer's launch.
     rope = (cos, sin): float32 device tables [positions][head_dim / 2]; q and k_new are then rotated
     inside the call (keydiff_prefill_block_layers_rope)."""
     import torch

@@ -1145,6 +1145,16 @@ __global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_kernel(StepParams p
     step_main_body<D, HELP, EXACT>(p, (int)blockIdx.x);
 }
 
+// The steps of several layers in one launch, layer blockIdx.y each: what a step costs besides its tiles (5 us before the loop,
+// 2 after it, the merge of as many partials as it takes to fill the chip with one layer) is paid once for all of them.
+template <int D, bool HELP, bool EXACT>
+__global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_layers_kernel(LayerSteps steps)
+{
+    const int layer = (int)blockIdx.y;
+    warm_arguments<sizeof(StepParams)>(layer * (uint32_t)sizeof(StepParams));
+    step_main_body<D, HELP, EXACT>(steps.p[layer], (int)blockIdx.x);
+}
+
 // step_main with passengers (with or without helper waves): the first `ncarry` workgroups run the pending selection and
 // compaction of another cache (one head each, parameters `cy`), the rest are the workgroups of
 // step_main proper.  A selection is a chain of short dependent stages that keeps one compute unit
@@ -1213,18 +1223,20 @@ static size_t carry_need(const StepParams &cy, bool resident)
 hipError_t configure_main_kernels()
 {
     hipError_t e;
-#define KD_SET(fn, D)                                                                              \
+#define KD_SET(fn, DD)                                                                              \
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
-                            (int)main_lds_bytes(D));                                               \
+                            (int)main_lds_bytes(DD));                                               \
     if (e != hipSuccess) return e;
-    KD_SET((step_main_kernel<128, false, false>), 128)
-    KD_SET((step_main_kernel<128, false, true>), 128)
-    KD_SET((step_main_kernel<128, true, false>), 128)
-    KD_SET((step_main_kernel<128, true, true>), 128)
-    KD_SET((step_main_kernel<64, false, false>), 64)
-    KD_SET((step_main_kernel<64, false, true>), 64)
-    KD_SET((step_main_kernel<64, true, false>), 64)
-    KD_SET((step_main_kernel<64, true, true>), 64)
+#define KD_SETS(DD, HELP)                                   \
+    KD_SET((step_main_kernel<DD, HELP, false>), DD)        \
+    KD_SET((step_main_kernel<DD, HELP, true>), DD)         \
+    KD_SET((step_main_layers_kernel<DD, HELP, false>), DD) \
+    KD_SET((step_main_layers_kernel<DD, HELP, true>), DD)
+    KD_SETS(128, false)
+    KD_SETS(128, true)
+    KD_SETS(64, false)
+    KD_SETS(64, true)
+#undef KD_SETS
 #undef KD_SET
 #define KD_SET(fn)                                                                                  \
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -1261,6 +1273,25 @@ hipError_t launch_step_main(const StepParams &p, hipStream_t s)
     else if (help) hipLaunchKernelGGL((step_main_kernel<DD, true, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);          \
     else if (exact) hipLaunchKernelGGL((step_main_kernel<DD, false, true>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);         \
     else hipLaunchKernelGGL((step_main_kernel<DD, false, false>), dim3(grid), dim3(64 * MAIN_WAVES), lds, s, p);
+    if (p.D == 128) { KD_GO(128) }
+    else if (p.D == 64) { KD_GO(64) }
+#undef KD_GO
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_step_main_layers(const LayerSteps &steps, int layers, hipStream_t s)
+{
+    const StepParams &p = steps.p[0];
+    if (layers < 2 || layers > GROUP_LAYERS || p.few) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(p.batch * p.hkv * p.mtiles * p.splits), (unsigned)layers);
+    const size_t lds = main_lds_bytes(p.D);
+    const bool help = main_runs_help(p), exact = scores_exactly(p);
+#define KD_GO(DD)                                                                                                           \
+    if (help && exact) hipLaunchKernelGGL((step_main_layers_kernel<DD, true, true>), grid, dim3(64 * MAIN_WAVES), lds, s, steps); \
+    else if (help) hipLaunchKernelGGL((step_main_layers_kernel<DD, true, false>), grid, dim3(64 * MAIN_WAVES), lds, s, steps);    \
+    else if (exact) hipLaunchKernelGGL((step_main_layers_kernel<DD, false, true>), grid, dim3(64 * MAIN_WAVES), lds, s, steps);   \
+    else hipLaunchKernelGGL((step_main_layers_kernel<DD, false, false>), grid, dim3(64 * MAIN_WAVES), lds, s, steps);
     if (p.D == 128) { KD_GO(128) }
     else if (p.D == 64) { KD_GO(64) }
 #undef KD_GO

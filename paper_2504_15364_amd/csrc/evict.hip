@@ -281,14 +281,26 @@ __device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int b
 // here): small workgroups, so that the rows spread over every compute unit.
 // Workgroup i takes head i % BH, like the workgroups of step_main: on a chip whose workgroups go
 // round-robin over the XCDs the partials of a head are then read on the XCD that wrote them.
-template <int D>
-__global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(StepParams p)
+template <int D, int MB = 16>
+__device__ __forceinline__ void merge_body(const StepParams &p)
 {
     const int BH = p.batch * p.hkv;
     const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (D / 8) * 64;
     const int bh = blockIdx.x % BH;
     const size_t local = (size_t)(blockIdx.x / BH) * MERGE_THREADS + threadIdx.x;
-    if (local < per_head) merge_rows<D>(p, (size_t)bh * per_head + local);
+    if (local < per_head) merge_rows<D, MB>(p, (size_t)bh * per_head + local);
+}
+template <int D>
+__global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(StepParams p)
+{
+    merge_body<D>(p);
+}
+// ... of several layers, blockIdx.y each (few splits: the layers fill the chip)
+template <int D>
+__global__ __launch_bounds__(MERGE_THREADS) void merge_layers_kernel(LayerSteps steps)
+{
+    warm_arguments<sizeof(StepParams)>(blockIdx.y * (uint32_t)sizeof(StepParams));
+    merge_body<D, 8>(steps.p[blockIdx.y]);
 }
 
 // step_score: every workgroup scores SCORE_ROWS rows of one head.  The launch boundary after it
@@ -307,13 +319,12 @@ __global__ __launch_bounds__(SCORE_THREADS) void step_score_kernel(StepParams p)
 // rest merge the attention partials.  SRC: 16-byte loads of scores (and of positions) a thread of the
 // selection holds in registers; 0: it reads them from memory where it needs them at all.
 template <int D, int SRC, bool APPROX>
-__global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
+__device__ __forceinline__ void post_body(const StepParams &p, int block)
 {
-    warm_arguments<sizeof(StepParams)>();
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     __shared__ PostShared sh;
     const int n_select = p.do_evict ? p.batch * p.hkv : 0;
-    if ((int)blockIdx.x >= n_select) {
+    if (block >= n_select) {
 #ifdef KD_TIMELINE
         unsigned long long *tl = reinterpret_cast<unsigned long long *>(&sh);   // (the selection's tables are not in use here)
         if (threadIdx.x < 32) tl[threadIdx.x] = 0;
@@ -321,8 +332,8 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
         if (threadIdx.x == 0) tl[0] = wall_clock64();
 #endif
         static_assert(sizeof(PostShared) >= POST_THREADS * 6 * sizeof(float), "the merge of step_few's partials uses the selection's tables");
-        if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), (int)blockIdx.x - n_select);
-        else merge_rows<D>(p, (size_t)(blockIdx.x - n_select) * POST_THREADS + threadIdx.x);
+        if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), block - n_select);
+        else merge_rows<D>(p, (size_t)(block - n_select) * POST_THREADS + threadIdx.x);
 #ifdef KD_TIMELINE
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
@@ -331,11 +342,24 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
             tl[31] = 4;   // record kind: merging workgroup
         }
         __syncthreads();
-        if (p.timeline && threadIdx.x < 32) p.timeline[(size_t)blockIdx.x * 32 + threadIdx.x] = tl[threadIdx.x];
+        if (p.timeline && threadIdx.x < 32) p.timeline[(size_t)block * 32 + threadIdx.x] = tl[threadIdx.x];
 #endif
         return;
     }
-    select_and_compact<D, SRC, POST_THREADS, APPROX>(p, sh, smem_raw, (int)blockIdx.x);
+    select_and_compact<D, SRC, POST_THREADS, APPROX>(p, sh, smem_raw, block);
+}
+template <int D, int SRC, bool APPROX>
+__global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
+{
+    warm_arguments<sizeof(StepParams)>();
+    post_body<D, SRC, APPROX>(p, (int)blockIdx.x);
+}
+// ... of several layers: blockIdx.x is the layer, so that the selections, which take longest, are dispatched first
+template <int D, int SRC>
+__global__ __launch_bounds__(POST_THREADS) void step_post_layers_kernel(LayerSteps steps)
+{
+    warm_arguments<sizeof(StepParams)>(blockIdx.x * (uint32_t)sizeof(StepParams));
+    post_body<D, SRC, false>(steps.p[blockIdx.x], (int)blockIdx.y);
 }
 
 // ------------------------------------------------------------- ordered compaction
@@ -346,13 +370,12 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_kernel(StepParams p)
 // stores.  Workgroups are numbered chunk-major, so a workgroup only ever waits for lower-numbered
 // ones; the wait is bounded and reports a timeout in the status word instead of hanging.
 template <int D>
-__device__ __forceinline__ void shift_chunk(const StepParams &p, int32_t *flags, int nchunks, int32_t epoch, int block)
+__device__ __forceinline__ void shift_chunk(const ShiftStep &p, int block)
 {
     constexpr int UPR = D / 8;
     constexpr int UPT = ORD_ROWS * UPR * 2 / ORD_THREADS;   // 16-byte units (K and V) per thread
     static_assert(UPT * ORD_THREADS == ORD_ROWS * UPR * 2, "the chunk must divide over the threads");
-    const int BH = p.batch * p.hkv;
-    const int bh = block % BH, chunk = block / BH, tid = threadIdx.x;
+    const int bh = block % p.BH, chunk = block / p.BH, tid = threadIdx.x;
     uint16_t *kb = p.k + (size_t)bh * p.cap * D;
     uint16_t *vb = p.v + (size_t)bh * p.cap * D;
     const int32_t *dst = p.dstmap + (size_t)bh * p.cap;
@@ -377,12 +400,12 @@ __device__ __forceinline__ void shift_chunk(const StepParams &p, int32_t *flags,
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every row of this chunk is in registers
     __syncthreads();
-    int32_t *myflags = flags + (size_t)bh * nchunks;
-    if (tid == 0) __hip_atomic_store(&myflags[chunk], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int32_t *myflags = p.flags + (size_t)bh * ((p.n + ORD_ROWS - 1) / ORD_ROWS);
+    if (tid == 0) __hip_atomic_store(&myflags[chunk], p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int reach = (p.n - p.N + ORD_ROWS - 1) / ORD_ROWS;   // chunks below this one its rows can land in
     if (tid < reach && chunk - 1 - tid >= 0) {
         int spins = 0;
-        while (__hip_atomic_load(&myflags[chunk - 1 - tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
+        while (__hip_atomic_load(&myflags[chunk - 1 - tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != p.epoch) {
             if (++spins > ORD_SPIN_LIMIT) {
                 atomicOr(p.status, STATUS_ORDER_TIMEOUT);
                 break;
@@ -401,9 +424,9 @@ __device__ __forceinline__ void shift_chunk(const StepParams &p, int32_t *flags,
 }
 
 template <int D>
-__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_ordered_kernel(StepParams p, int32_t *flags, int nchunks, int32_t epoch)
+__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_ordered_kernel(ShiftSteps steps)
 {
-    shift_chunk<D>(p, flags, nchunks, epoch, (int)blockIdx.x);
+    shift_chunk<D>(steps.s[blockIdx.y], (int)blockIdx.x);   // (blockIdx.y: the cache)
 }
 
 // The merge of one cache's attention partials and the ordered shift of another cache in one launch
@@ -414,8 +437,7 @@ __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 
 // the caller waits for their output -- the others shift one chunk each, numbered chunk-major
 // behind them, so a shifting workgroup still only ever waits for lower-numbered ones.
 template <int D>
-__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void merge_shift_kernel(StepParams pm, StepParams ps, int32_t *flags, int nchunks,
-                                                                  int32_t epoch, int merge_wgs)
+__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void merge_shift_kernel(StepParams pm, ShiftStep shift, int merge_wgs)
 {
     if ((int)blockIdx.x < merge_wgs) {
         // (few splits per round trip: the launch lasts as long as the shift does, and the registers
@@ -423,7 +445,7 @@ __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 
         merge_rows<D, 4>(pm, (size_t)blockIdx.x * ORD_THREADS + threadIdx.x);
         return;
     }
-    shift_chunk<D>(ps, flags, nchunks, epoch, (int)blockIdx.x - merge_wgs);
+    shift_chunk<D>(shift, (int)blockIdx.x - merge_wgs);
 }
 
 // --------------------------------------------------- key sum from scratch (cache load)
@@ -596,7 +618,9 @@ hipError_t configure_kernels()
     if (e != hipSuccess) return e;
     static_assert(MAX_CAP / 8 + LISTS_LDS_MAX + 16 <= POST_DYN_MAX, "the non-resident selection always fits");
     const void *post_fns[] = {
-#define KD_FN(DD, SRC) reinterpret_cast<const void *>(step_post_kernel<DD, SRC, false>), reinterpret_cast<const void *>(step_post_kernel<DD, SRC, true>)
+#define KD_FN(DD, SRC)                                                                                                          \
+    reinterpret_cast<const void *>(step_post_kernel<DD, SRC, false>), reinterpret_cast<const void *>(step_post_kernel<DD, SRC, true>), \
+        reinterpret_cast<const void *>(step_post_layers_kernel<DD, SRC>)
         KD_FN(128, 0), KD_FN(128, 3), KD_FN(128, 5), KD_FN(64, 0), KD_FN(64, 3), KD_FN(64, 5)};
 #undef KD_FN
     for (const void *fn : post_fns) {
@@ -613,6 +637,15 @@ hipError_t launch_step_score(const StepParams &p, hipStream_t s)
     else if (p.D == 64) hipLaunchKernelGGL((step_score_kernel<64>), dim3(grid), dim3(SCORE_THREADS), 0, s, p);
     else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+// Three 16-byte loads of scores and of positions a thread up to 12288 rows, five of scores alone up to 20480 (a pass that
+// needs every row's position reads those from memory); the registers hold no more beside the rows that may move, so
+// larger caches are read from memory in every pass.  With the arg-max records of the attention launch the scores are hardly
+// ever looked at.
+static int post_source(const StepParams &p)
+{
+    return p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
 }
 
 hipError_t launch_step_post(const StepParams &p, hipStream_t s)
@@ -634,11 +667,7 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
         return hipGetLastError();
     }
     if (p.n > 32 * POST_THREADS) return hipErrorInvalidValue;   // a thread owns one word of the eviction bitmap
-    // Three 16-byte loads of scores and of positions a thread up to 12288 rows, five of scores alone up to 20480 (a pass that
-    // needs every row's position reads those from memory); the registers hold no more beside the rows that may move, so
-    // larger caches are read from memory in every pass.  With the arg-max records of the attention launch the scores are hardly
-    // ever looked at.
-    const int src = p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
+    const int src = post_source(p);
     const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
 #define KD_GO2(DD, SRC)                                                                                                    \
     if (p.score_approx) hipLaunchKernelGGL((step_post_kernel<DD, SRC, true>), dim3(grid), dim3(POST_THREADS), lds, s, p);   \
@@ -655,27 +684,58 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_compact_ordered(const StepParams &p, int32_t *flags, int32_t epoch, hipStream_t s)
+hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStream_t s)
 {
-    const int nchunks = (p.n + ORD_ROWS - 1) / ORD_ROWS;
-    const int grid = p.batch * p.hkv * nchunks;
-    if (p.n - p.N > ORD_THREADS * ORD_ROWS) return hipErrorInvalidValue;   // one waiting thread per chunk in reach
-    if (p.D == 128) hipLaunchKernelGGL((compact_ordered_kernel<128>), dim3(grid), dim3(ORD_THREADS), 0, s, p, flags, nchunks, epoch);
-    else if (p.D == 64) hipLaunchKernelGGL((compact_ordered_kernel<64>), dim3(grid), dim3(ORD_THREADS), 0, s, p, flags, nchunks, epoch);
+    const StepParams &p = steps.p[0];
+    if (layers < 2 || layers > GROUP_LAYERS || p.few || p.argmax_rec || p.score_approx) return hipErrorInvalidValue;
+    const int per_layer = (p.do_evict ? p.batch * p.hkv : 0) + p.merge_wgs;
+    if (per_layer == 0) return hipSuccess;
+    if (!p.do_evict) {
+        const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (p.D / 8) * 64;
+        const dim3 grid((unsigned)(p.batch * p.hkv * ((per_head + MERGE_THREADS - 1) / MERGE_THREADS)), (unsigned)layers);
+        if (p.D == 128) hipLaunchKernelGGL((merge_layers_kernel<128>), grid, dim3(MERGE_THREADS), 0, s, steps);
+        else if (p.D == 64) hipLaunchKernelGGL((merge_layers_kernel<64>), grid, dim3(MERGE_THREADS), 0, s, steps);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
+    if (p.n > 32 * POST_THREADS) return hipErrorInvalidValue;
+    const int src = post_source(p);
+    const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
+    const dim3 grid((unsigned)layers, (unsigned)per_layer);
+#define KD_GO(DD)                                                                                                          \
+    if (src == 0) hipLaunchKernelGGL((step_post_layers_kernel<DD, 0>), grid, dim3(POST_THREADS), lds, s, steps);             \
+    else if (src == 3) hipLaunchKernelGGL((step_post_layers_kernel<DD, 3>), grid, dim3(POST_THREADS), lds, s, steps);        \
+    else hipLaunchKernelGGL((step_post_layers_kernel<DD, 5>), grid, dim3(POST_THREADS), lds, s, steps);
+    if (p.D == 128) { KD_GO(128) }
+    else if (p.D == 64) { KD_GO(64) }
+#undef KD_GO
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-// pm: the step whose partials are merged; ps: the step of the other cache whose destination map is applied
-hipError_t launch_merge_shift(const StepParams &pm, const StepParams &ps, int32_t *flags, int32_t epoch, hipStream_t s)
+static int shift_chunks(const ShiftStep &sh) { return (sh.n + ORD_ROWS - 1) / ORD_ROWS; }
+// one waiting thread per chunk in reach
+static bool shift_fits(const ShiftStep &sh) { return sh.n - sh.N <= ORD_THREADS * ORD_ROWS; }
+
+hipError_t launch_compact_ordered(const ShiftSteps &steps, int layers, int D, hipStream_t s)
 {
-    const int nchunks = (ps.n + ORD_ROWS - 1) / ORD_ROWS;
+    if (layers < 1 || layers > GROUP_LAYERS || !shift_fits(steps.s[0])) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(steps.s[0].BH * shift_chunks(steps.s[0])), (unsigned)layers);
+    if (D == 128) hipLaunchKernelGGL((compact_ordered_kernel<128>), grid, dim3(ORD_THREADS), 0, s, steps);
+    else if (D == 64) hipLaunchKernelGGL((compact_ordered_kernel<64>), grid, dim3(ORD_THREADS), 0, s, steps);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+// pm: the step whose partials are merged; shift: the other cache's
+hipError_t launch_merge_shift(const StepParams &pm, const ShiftStep &shift, hipStream_t s)
+{
     const size_t merge_threads = (size_t)pm.batch * pm.hkv * ((pm.G * pm.Bt + 31) / 32) * (pm.D / 8) * 64;
     const int mw = (int)((merge_threads + ORD_THREADS - 1) / ORD_THREADS);
-    const int grid = mw + ps.batch * ps.hkv * nchunks;
-    if (ps.n - ps.N > ORD_THREADS * ORD_ROWS || pm.D != ps.D || pm.splits < 2 || pm.few) return hipErrorInvalidValue;
-    if (pm.D == 128) hipLaunchKernelGGL((merge_shift_kernel<128>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, ps, flags, nchunks, epoch, mw);
-    else if (pm.D == 64) hipLaunchKernelGGL((merge_shift_kernel<64>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, ps, flags, nchunks, epoch, mw);
+    const int grid = mw + shift.BH * shift_chunks(shift);
+    if (!shift_fits(shift) || pm.splits < 2 || pm.few) return hipErrorInvalidValue;
+    if (pm.D == 128) hipLaunchKernelGGL((merge_shift_kernel<128>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, shift, mw);
+    else if (pm.D == 64) hipLaunchKernelGGL((merge_shift_kernel<64>), dim3(grid), dim3(ORD_THREADS), 0, s, pm, shift, mw);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -36,12 +36,13 @@ namespace kd {
 // first BYTES bytes at once, ahead of everything else, and waits for them: later reads find the lines
 // in the scalar cache.  (At most 8 lines; the words themselves are not used.)  Loads and wait are one block of assembly:
 // nothing the compiler places can come between a load and its arrival.
+// offset: where in the argument block they start (uniform, a multiple of 64).
 template <size_t BYTES>
-__device__ __forceinline__ void warm_arguments()
+__device__ __forceinline__ void warm_arguments(uint32_t offset = 0)
 {
     constexpr int LAST = (int)((BYTES + 63) / 64) - 1;   // the last line; where there are fewer lines than loads it is requested again
     constexpr auto at = [](int line) { return 64 * (line < LAST ? line : LAST); };
-    const char *ka = (const char *)__builtin_amdgcn_kernarg_segment_ptr();
+    const char *ka = (const char *)__builtin_amdgcn_kernarg_segment_ptr() + offset;
     uint32_t d0, d1, d2, d3, d4, d5, d6, d7;
     if constexpr (LAST < 5) {
         asm volatile("s_load_dword %0, %5, %6\n\ts_load_dword %1, %5, %7\n\ts_load_dword %2, %5, %8\n\t"

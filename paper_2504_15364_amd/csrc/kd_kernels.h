@@ -88,8 +88,29 @@ struct StepParams {
 static_assert(sizeof(StepParams) == 256, "a field that crosses into a fifth line costs every launch that reads it a trip to memory");
 #endif
 
+// The same block step of several layers at once (keydiff_prefill_block_layers): one launch whose grid's second dimension is
+// the layer.  All have the same sizes; pointers, and what follows from them, are each layer's own.
+constexpr int GROUP_LAYERS = 16;     // (4 KB of arguments)
+struct LayerSteps {
+    StepParams p[GROUP_LAYERS];
+};
+// The row shift of one ORDERED cache by the destination map its selection wrote (flags: [BH][chunks of ORD_ROWS rows] int32 in
+// zero-initialised device memory; epoch: a value no earlier shift of this cache used)
+struct ShiftStep {
+    uint16_t *k, *v;
+    const int32_t *dstmap;
+    int32_t *status, *flags;
+    int BH, n, N, cap;
+    int32_t epoch;
+};
+struct ShiftSteps {
+    ShiftStep s[GROUP_LAYERS];
+};
+
 hipError_t configure_kernels();      // one-time function attributes (dynamic LDS sizes)
 hipError_t launch_step_main(const StepParams &p, hipStream_t s);
+// ... of `layers` layers in one launch (2 .. GROUP_LAYERS of them, none with step_few)
+hipError_t launch_step_main_layers(const LayerSteps &steps, int layers, hipStream_t s);
 // the same step where the plan chose step_few (p.few)
 hipError_t launch_step_few(const StepParams &p, hipStream_t s);
 // How the selection of step `cy` would ride in another launch: not at all, reading its scores and positions from memory in
@@ -115,10 +136,11 @@ bool can_host_shift(const StepParams &p, const StepParams &shifted);
 hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, const ShiftRide &ride, hipStream_t s);
 hipError_t launch_step_score(const StepParams &p, hipStream_t s);
 hipError_t launch_step_post(const StepParams &p, hipStream_t s);
-// flags: [BH][ceil(cap / ORD_ROWS)] int32 in zero-initialised device memory; epoch: a value no earlier launch used
-hipError_t launch_compact_ordered(const StepParams &p, int32_t *flags, int32_t epoch, hipStream_t s);
-// the merge of pm's partials and the ordered shift of ps's cache in one launch (same head_dim)
-hipError_t launch_merge_shift(const StepParams &pm, const StepParams &ps, int32_t *flags, int32_t epoch, hipStream_t s);
+hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStream_t s);
+// the ordered shift of `layers` caches of the same sizes
+hipError_t launch_compact_ordered(const ShiftSteps &steps, int layers, int D, hipStream_t s);
+// the merge of pm's partials and the ordered shift of another cache in one launch (same head_dim)
+hipError_t launch_merge_shift(const StepParams &pm, const ShiftStep &shift, hipStream_t s);
 hipError_t launch_ksum_rebuild(const StepParams &p, double *partials, hipStream_t s);
 // rotary embedding of the blocks' queries (q_rows rows each) and keys (k_rows rows), Bt tokens per (sequence,
 // head) at positions pos0 + j, by the caller's float tables [position][D / 2]

@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -397,12 +398,19 @@ bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
 }
 
 // ORDERED layout: the stable row shift that follows a selection, by the destination map it wrote
+kd::ShiftStep shift_step(keydiff_cache *c, const kd::StepParams &p)
+{
+    c->epoch = c->epoch == 0x7fffffff ? 1 : c->epoch + 1;
+    return kd::ShiftStep{p.k, p.v, p.dstmap, p.status, reinterpret_cast<int32_t *>(c->meta + c->L.off_oflags), p.batch * p.hkv, p.n,
+                         p.N, p.cap, c->epoch};
+}
+
 int compact_ordered(keydiff_cache *c, const kd::StepParams &p, hipStream_t s)
 {
     ProfScope ps(c, KEYDIFF_K_COMPACT, s);
-    c->epoch = c->epoch == 0x7fffffff ? 1 : c->epoch + 1;
-    KD_LAUNCH(kd::launch_compact_ordered(p, reinterpret_cast<int32_t *>(c->meta + c->L.off_oflags), c->epoch, s),
-              "ordered compaction kernel");
+    kd::ShiftSteps steps;
+    steps.s[0] = shift_step(c, p);
+    KD_LAUNCH(kd::launch_compact_ordered(steps, 1, p.D, s), "ordered compaction kernel");
     return KEYDIFF_OK;
 }
 
@@ -426,6 +434,43 @@ int finish_pending(keydiff_cache *c, hipStream_t s)
     c->pending = false;
     if (c->cfg.layout == KEYDIFF_LAYOUT_ORDERED) return compact_ordered(c, p, s);
     return KEYDIFF_OK;
+}
+
+// The parameters of one block step but for its plan (plan_attention).
+kd::StepParams step_params(const keydiff_cache *c, const void *q, const void *k_new, const void *v_new, int32_t Bt, int64_t pos0,
+                           void *out, float *scores_out, unsigned char *work)
+{
+    const keydiff_config_t &cf = c->cfg;
+    const int n = c->len + Bt;
+    kd::StepParams p = base_params(c, n, work);
+    p.q = static_cast<const uint16_t *>(q);
+    p.k_new = static_cast<const uint16_t *>(k_new);
+    p.v_new = static_cast<const uint16_t *>(v_new);
+    p.out = static_cast<uint16_t *>(out);
+    p.scores_out = scores_out;
+    p.Bt = Bt;
+    p.len = c->len;
+    p.pos0 = (int32_t)pos0;
+    p.do_evict = n > cf.budget_N;
+    p.do_score = p.do_evict || scores_out != nullptr;
+    if (cf.window_W > 0) p.window_pos_min = (int32_t)(pos0 + Bt - cf.window_W);
+    return p;
+}
+
+// Whether the block at pos0 continues the positions of the blocks before it (a sliding window needs that).
+bool continues(const keydiff_cache *c, int64_t pos0) { return c->contiguous && (c->next_pos < 0 || c->next_pos == pos0); }
+
+// What a step leaves in the handle once its launches are enqueued (carried: keydiff_cache_plan's fourth value).
+void step_enqueued(keydiff_cache *c, const kd::StepParams &p, int64_t pos0, bool contiguous, int carried)
+{
+    c->plan[0] = p.splits;
+    c->plan[1] = p.mtiles;
+    c->plan[2] = p.ntiles;
+    c->plan[3] = carried;
+    c->kpar ^= 1;   // step_main wrote the new key sum into the other half
+    c->len = p.do_evict ? p.N : p.n;
+    c->contiguous = contiguous;
+    c->next_pos = pos0 + p.Bt;
 }
 
 // `work`: the buffer for the step's temporaries -- the handle's scratch buffer, or the static array.
@@ -457,25 +502,14 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
                                                 (long long)rope->rows, (long long)(pos0 + Bt));
     }
     const keydiff_config_t &cf = c->cfg;
-    const int len = c->len, n = len + Bt, N = cf.budget_N;
-    const bool contiguous = c->contiguous && (c->next_pos < 0 || c->next_pos == pos0);
+    const int n = c->len + Bt, N = cf.budget_N;
+    const bool contiguous = continues(c, pos0);
     if (cf.window_W > 0 && n > N && !contiguous)
         return fail(KEYDIFF_ESTATE, "the sliding window needs consecutive token positions across calls");
 
     const bool evict = n > N;
-    kd::StepParams p = base_params(c, n, work);
-    p.q = static_cast<const uint16_t *>(q);
-    p.k_new = static_cast<const uint16_t *>(k_new);
-    p.v_new = static_cast<const uint16_t *>(v_new);
-    p.out = static_cast<uint16_t *>(out);
-    p.scores_out = scores_out;
-    p.Bt = Bt;
-    p.len = len;
-    p.pos0 = (int32_t)pos0;
-    p.do_evict = evict;
-    p.do_score = evict || scores_out != nullptr;
+    kd::StepParams p = step_params(c, q, k_new, v_new, Bt, pos0, out, scores_out, work);
     p.score_approx = defer && carry != nullptr && evict && approximate_scores_pay(c, p);
-    if (cf.window_W > 0) p.window_pos_min = (int32_t)(pos0 + Bt - cf.window_W);
 
     // a passenger rides only if the attention still fits the chip in one pass beside it
     bool riding = false;
@@ -572,10 +606,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
             pm.do_evict = 0;   // the merge half of step_post only
             ProfScope ps(c, KEYDIFF_K_POST, s);
             if (shift_owed && carry->pend.D == p.D) {
-                carry->epoch = carry->epoch == 0x7fffffff ? 1 : carry->epoch + 1;
-                KD_LAUNCH(kd::launch_merge_shift(pm, carry->pend, reinterpret_cast<int32_t *>(carry->meta + carry->L.off_oflags),
-                                                 carry->epoch, s),
-                          "merge + ordered compaction kernel");
+                KD_LAUNCH(kd::launch_merge_shift(pm, shift_step(carry, carry->pend), s), "merge + ordered compaction kernel");
                 shift_owed = false;
             } else {
                 KD_LAUNCH(kd::launch_step_post(pm, s), "step_post kernel (merge)");
@@ -596,14 +627,159 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
     if (shift_owed)   // ... else in a launch of its own
         if (int rc = compact_ordered(carry, carry->pend, s)) return rc;
     if (c->profiling) ProfScope ps(c, KEYDIFF_K_EVENT_PAIR, s);
-    c->plan[0] = p.splits;
-    c->plan[1] = p.mtiles;
-    c->plan[2] = p.ntiles;
-    c->plan[3] = (riding ? 1 : 0) | (shift_parts > 0 ? 2 : 0);
-    c->kpar ^= 1;   // step_main wrote the new key sum into the other half
-    c->len = evict ? N : n;
-    c->contiguous = contiguous;
-    c->next_pos = pos0 + Bt;
+    step_enqueued(c, p, pos0, contiguous, (riding ? 1 : 0) | (shift_parts > 0 ? 2 : 0));
+    return KEYDIFF_OK;
+}
+
+// ---- The block step of several layers in the same launches.
+//
+// A workgroup of the attention spends 7 us around its loop over key tiles whatever the length of its range, and one layer
+// (16 row tiles of 256 query rows, 32 / 8 heads) has to be cut into 15 or 16 ranges to fill the chip: ranges of nine tiles at
+// 8192 keys, and as many partials to merge.  Layers of one call do not depend on one another (their blocks are all there
+// before the call), so their row tiles fill the chip together, with ranges as many times longer as there are layers.  The
+// evictions of all of them follow in one launch beside the merge.  Measured against every layer by itself with its eviction carried
+// by the next one's launch, us a layer and block: 32 / 8 heads, 8192 keys, blocks of 128, 4 layers 26.6 -> 19.7; 28 / 4 heads, blocks of 256,
+// 2 layers 37.7 -> 36.5; ORDERED, 24 / 8 heads, 4096 keys, 3 layers 25.2 -> 18.2.  Scores are exact here: approximate ones
+// (4 us off 75 of attention for four layers, 3 more for the selection) gained 1 % in the first case and cost 1 % in the other two.
+
+// The plan of `layers` layers in one launch, left in p (shared by all of them), and its estimated time in us (loosely: it only
+// ranks the plans of one call against one another).  More workgroups than compute units run in several rounds.
+double plan_layers(const keydiff_cache *c, kd::StepParams &p, int layers)
+{
+    plan_attention(c, p);
+    const int target = c->L.target_wgs / 2, BH = p.batch * p.hkv, tiles = layers * BH * p.mtiles;
+    const int Mpad = (p.G * p.Bt + 31) / 32 * 32;
+    const int tplain = std::min(p.len / kd::TILE_KEYS, p.ntiles), cost = tplain + 2 * (p.ntiles - tplain);
+    const double tile_us = p.D == 128 ? 1.75 : 1.0;
+    double best = 0.0;
+    int splits = 1;
+    for (int s = 1; s <= p.splits; ++s) {   // (never more ranges than for one layer alone: the scratch buffer holds those)
+        if (s > 1 && (long)s * BH * Mpad > c->L.max_part_rows) break;
+        const int rounds = (tiles * s + target - 1) / target;
+        const double us = rounds * (7.0 + tile_us * ((cost + s - 1) / s)) + (s > 1 ? 2.0 + 1e-6 * layers * s * BH * Mpad * p.D * 2 / 3.5 : 0.0);
+        if (s == 1 || us < best) {
+            best = us;
+            splits = s;
+        }
+    }
+    p.splits = splits;
+    p.edge_cost = cost / splits >= 4 ? 2 : 1;
+    const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64;
+    p.merge_wgs = splits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
+    return best;
+}
+
+// How many launches (of attention) the layers of one call are dealt to, evenly; 0: one by one, every eviction carried by the next
+// layer's launch.
+int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layers)
+{
+    kd::StepParams p = step;
+    plan_attention(c, p);
+    if (p.few) return 0;
+    // (ORDERED, three layers or more: where the row shifts can ride in the attention launches, which leave the memory system to them, they do)
+    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2) {
+        kd::StepParams probe = step;
+        if (plan_with_shift(c, probe, step, p.batch * p.hkv) > 0) return 0;
+    }
+    const double post_us = p.do_evict ? 12.0 : 3.0;
+    const int least = (n_layers + kd::GROUP_LAYERS - 1) / kd::GROUP_LAYERS;
+    int best_k = least;
+    double best = 0.0;
+    for (int k = least; k <= std::min(n_layers, least + 3); ++k) {
+        const int more = n_layers % k, layers = n_layers / k;
+        double us = k * post_us + (k - more) * plan_layers(c, p, layers);
+        if (more) us += more * plan_layers(c, p, layers + 1);
+        if (k == least || us < best) {
+            best = us;
+            best_k = k;
+        }
+    }
+    return best_k;
+}
+
+// Whether the steps of the layers of one call may share launches: everything a step checks holds for every layer (else the
+// layers run one by one, and an error is found where it always was), they are shaped alike and in the same state, and no layer writes
+// what another one touches (so that their order is of no consequence).
+// rotated: q and k_new have been rotated into the scratch buffers already.
+bool layers_alike(keydiff_cache *const *caches, int n_layers, const void *const *q, const void *const *k_new, const void *const *v_new,
+                  int32_t Bt, int64_t pos0, void *const *out, bool rotated)
+{
+    const keydiff_cache *c0 = caches[0];
+    const keydiff_config_t &cf = c0->cfg;
+    if (Bt < 1 || Bt > cf.block_B || pos0 < 0 || pos0 + Bt > 0x7fffffffLL) return false;
+    const bool windowed_eviction = cf.window_W > 0 && c0->len + Bt > cf.budget_N;
+    struct Span {
+        uintptr_t from, to;
+        bool write;
+    };
+    const std::unique_ptr<Span[]> spans(new (std::nothrow) Span[(size_t)n_layers * 8]);
+    if (!spans) return false;
+    size_t nspans = 0;
+    const size_t token = (size_t)cf.batch * Bt * cf.head_dim * 2, q_bytes = token * cf.n_q_heads, k_bytes = token * cf.n_kv_heads;
+    for (int l = 0; l < n_layers; ++l) {
+        const keydiff_cache *c = caches[l];
+        const keydiff_config_t &a = c->cfg;
+        if (a.batch != cf.batch || a.n_q_heads != cf.n_q_heads || a.n_kv_heads != cf.n_kv_heads || a.head_dim != cf.head_dim ||
+            a.budget_N != cf.budget_N || a.block_B != cf.block_B || a.anchor_mode != cf.anchor_mode || a.window_W != cf.window_W ||
+            a.layout != cf.layout || c->eps != c0->eps || c->scale_log2e != c0->scale_log2e || c->device != c0->device ||
+            c->len != c0->len || c->profiling)   // (the kernels of a profiled handle are its own)
+            return false;
+        if (misaligned(q[l]) || misaligned(k_new[l]) || misaligned(v_new[l]) || misaligned(out[l])) return false;
+        if (windowed_eviction && !continues(c, pos0)) return false;
+        auto add = [&](const void *x, size_t bytes, bool write) {
+            const uintptr_t from = reinterpret_cast<uintptr_t>(x);
+            spans[nspans++] = {from, from + bytes, write};
+        };
+        if (!rotated) {
+            add(q[l], q_bytes, false);
+            add(k_new[l], k_bytes, false);
+        }
+        add(v_new[l], k_bytes, false);
+        add(out[l], q_bytes, true);
+        add(c->k, c->L.k_bytes, true);
+        add(c->v, c->L.k_bytes, true);
+        add(c->meta, c->L.meta_bytes, true);
+        add(c->scratch, c->L.scratch_bytes, true);
+    }
+    std::sort(spans.get(), spans.get() + nspans, [](const Span &x, const Span &y) { return x.from < y.from; });
+    uintptr_t written = 0, touched = 0;   // ends of what lies before
+    for (size_t i = 0; i < nspans; ++i) {
+        const Span &x = spans[i];
+        if (x.from < written || (x.write && x.from < touched)) return false;
+        touched = std::max(touched, x.to);
+        if (x.write) written = std::max(written, x.to);
+    }
+    return true;
+}
+
+// The steps of `layers` layers, prepared up to their plan (`plan`'s, of plan_layers).
+int layers_step(keydiff_cache *const *caches, kd::LayerSteps &steps, int layers, const kd::StepParams &plan, int64_t pos0, hipStream_t s)
+{
+    for (int l = 0; l < layers; ++l) {
+        if (int rc = finish_pending(caches[l], s)) return rc;
+        kd::StepParams &p = steps.p[l];
+        p.mtiles = plan.mtiles;
+        p.ntiles = plan.ntiles;
+        p.splits = plan.splits;
+        p.edge_cost = plan.edge_cost;
+        p.merge_wgs = plan.merge_wgs;
+    }
+#ifdef KD_TIMELINE
+    const int wgs = plan.batch * plan.hkv * plan.mtiles * plan.splits;
+    unsigned long long *slot = timeline_slot((long)layers * wgs);
+    for (int l = 0; l < layers; ++l) steps.p[l].timeline = slot ? slot + (size_t)l * wgs * 32 : nullptr;
+#endif
+    KD_LAUNCH(kd::launch_step_main_layers(steps, layers, s), "step_main kernel (several layers)");
+#ifdef KD_TIMELINE
+    for (int l = 0; l < layers; ++l) steps.p[l].timeline = nullptr;
+#endif
+    KD_LAUNCH(kd::launch_step_post_layers(steps, layers, s), "step_post kernel (several layers)");
+    if (plan.do_evict && plan.layout == KEYDIFF_LAYOUT_ORDERED) {
+        kd::ShiftSteps shifts;
+        for (int l = 0; l < layers; ++l) shifts.s[l] = shift_step(caches[l], steps.p[l]);
+        KD_LAUNCH(kd::launch_compact_ordered(shifts, layers, plan.D, s), "ordered compaction kernel (several layers)");
+    }
+    for (int l = 0; l < layers; ++l) step_enqueued(caches[l], steps.p[l], pos0, continues(caches[l], pos0), 0);
     return KEYDIFF_OK;
 }
 
@@ -790,15 +966,38 @@ static int block_layers(keydiff_cache_t *const *caches, int32_t n_layers, const 
                                   Bt, cf.head_dim, (int32_t)pos0, s),
                   "rotary embedding kernel");
     }
+    auto q_of = [&](int l) { return rotated ? (const void *)(caches[l]->scratch + caches[l]->L.off_q_rot) : q[l]; };
+    auto k_of = [&](int l) { return rotated ? (const void *)(caches[l]->scratch + caches[l]->L.off_k_rot) : k_new[l]; };
+    if (n_layers == 1)   // nothing to share a launch with, and nothing that could carry the eviction
+        return block_step(caches[0], q[0], k_new[0], v_new[0], Bt, pos0, out[0], nullptr, false, nullptr, caches[0]->scratch, s, rope);
+    if ((!rope || rotated) && layers_alike(caches, n_layers, q, k_new, v_new, Bt, pos0, out, rotated)) {
+        kd::StepParams one = step_params(caches[0], q[0], k_new[0], v_new[0], Bt, pos0, out[0], nullptr, caches[0]->scratch);
+        const int groups = layer_groups(caches[0], one, n_layers);
+        for (int l = 0, i = 0; i < groups; ++i) {
+            const int layers = n_layers / groups + (i < n_layers % groups ? 1 : 0);
+            int rc;
+            if (layers == 1) {
+                rc = block_step(caches[l], q_of(l), k_of(l), v_new[l], Bt, pos0, out[l], nullptr, false, nullptr, caches[l]->scratch, s);
+            } else {
+                plan_layers(caches[0], one, layers);
+                kd::LayerSteps steps;
+                for (int m = 0; m < layers; ++m)
+                    steps.p[m] = step_params(caches[l + m], q_of(l + m), k_of(l + m), v_new[l + m], Bt, pos0, out[l + m], nullptr,
+                                             caches[l + m]->scratch);
+                rc = layers_step(caches + l, steps, layers, one, pos0, s);
+            }
+            if (rc) return rc;
+            l += layers;
+        }
+        if (groups > 0) return KEYDIFF_OK;
+    }
     for (int l = 0; l < n_layers; ++l) {
-        const void *ql = rotated ? caches[l]->scratch + caches[l]->L.off_q_rot : q[l];
-        const void *kl = rotated ? caches[l]->scratch + caches[l]->L.off_k_rot : k_new[l];
         // layer 0 takes along what the last layer left pending at the previous block
         keydiff_cache *carry = n_layers > 1 ? caches[(l + n_layers - 1) % n_layers] : nullptr;
         // ... and, ORDERED layout, the row shift of the layer before that one, whose selection rode in the
         // launch of the layer between them
         keydiff_cache *shifted = n_layers > 2 ? caches[(l + n_layers - 2) % n_layers] : nullptr;
-        if (int rc = block_step(caches[l], ql, kl, v_new[l], Bt, pos0, out[l], nullptr, true, carry,
+        if (int rc = block_step(caches[l], q_of(l), k_of(l), v_new[l], Bt, pos0, out[l], nullptr, true, carry,
                                 caches[l]->scratch, s, rotated ? nullptr : rope, shifted, n_layers > 2))
             return rc;
     }

@@ -1,0 +1,94 @@
+"""keydiff_prefill_block_layers where the steps of its layers share launches, against keydiff_prefill_block layer by
+layer (which the oracle checks elsewhere): positions, rows and scores bit for bit, outputs within the attention's bar
+(the keys are cut into fewer ranges)."""
+import numpy as np
+import pytest
+
+import paper_2504_15364_amd as kd
+from helpers import ATTN_ATOL
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _blocks(heads, T, B, seed):
+    hq, hkv, d = heads
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    shift = torch.randn((1, hkv, 1, d), generator=gen, device="cuda")
+    for t in range(0, T, B):
+        n = min(B, T - t)
+        q, k, v = (torch.randn((1, h, n, d), generator=gen, device="cuda") for h in (hq, hkv, hkv))
+        yield t, q.bfloat16(), (k + shift).bfloat16(), v.bfloat16()
+
+
+def _same_state(a, b, where):
+    assert a.len == b.len, where
+    n = a.len
+    pa, pb = a.positions(), b.positions()
+    assert torch.equal(pa, pb), f"positions differ {where}"
+    for x, y in ((a.key_rows(), b.key_rows()), (a.value_rows(), b.value_rows())):
+        assert torch.equal(x[:, :, :n].view(torch.int16), y[:, :, :n].view(torch.int16)), f"rows differ {where}"
+    assert torch.equal(a.scores().view(torch.int32), b.scores().view(torch.int32)), f"key sums differ {where}"
+    assert a.status() == 0 and b.status() == 0
+
+
+@pytest.mark.parametrize("heads,N,B,T,layers,kw", [
+    ((8, 2, 128), 512, 128, 1100, 2, {}),                                              # ragged last block
+    ((8, 2, 128), 512, 128, 900, 17, {}),                                              # more layers than a launch takes
+    ((6, 2, 128), 300, 48, 650, 5, {"anchor_mode": kd.ANCHOR_MEAN_UNIT_KEY}),           # waves without query rows
+    ((4, 1, 64), 256, 32, 480, 16, {"layout": kd.LAYOUT_ORDERED}),                      # the shifts of a full launch
+    ((8, 2, 64), 512, 64, 820, 2, {"layout": kd.LAYOUT_ORDERED}),
+    ((14, 2, 128), 384, 64, 640, 3, {"window_W": 64}),
+    ((8, 2, 128), 300, 256, 1000, 1, {}),                                              # one layer: the step of prefill_block
+], ids=["2", "17", "5-helper", "16-ordered", "2-ordered", "3-window", "1"])
+def test_layers_in_one_launch(heads, N, B, T, layers, kw):
+    kw = {"layout": kd.LAYOUT_FILL, **kw}
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, *heads, N, B, **kw)) for _ in range(layers)] for _ in range(2))
+    for i, blks in enumerate(zip(*(_blocks(heads, T, B, 100 + l) for l in range(layers)))):
+        t = blks[0][0]
+        if i == 5 and kw["layout"] == kd.LAYOUT_FILL and not kw.get("window_W"):
+            # a block on which the layers run one by one and leave evictions pending
+            outs = []
+            for l, (_, q, k, v) in enumerate(blks):
+                outs.append(a[l].prefill_block_deferred(q, k, v, t, carry=a[l - 1] if layers > 1 else None))
+        else:
+            outs = kd.prefill_block_layers(a, [x[1] for x in blks], [x[2] for x in blks], [x[3] for x in blks], t)
+        for l, (_, q, k, v) in enumerate(blks):
+            want = b[l].prefill_block(q, k, v, t)
+            assert float((outs[l].float() - want.float()).abs().max()) <= ATTN_ATOL, (t, l)
+        assert layers < 16 or a[0].plan()[0] <= b[0].plan()[0]
+    for l in range(layers):
+        _same_state(a[l], b[l], f"layer {l}")
+        a[l].close()
+        b[l].close()
+
+
+@pytest.mark.parametrize("kind", ["chain", "in-place", "common-inputs"])
+def test_layers_that_touch_one_anothers_memory_keep_their_order(kind):
+    heads, N, B, T, layers = (8, 2, 128), 64, 32, 160, 3
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, *heads, N, B, layout=kd.LAYOUT_FILL)) for _ in range(layers)] for _ in range(2))
+    for blks in zip(*(_blocks(heads, T, B, 300 + l) for l in range(layers))):
+        t = blks[0][0]
+        got = []
+        for caches in (a, b):
+            qs, ks, vs = ([x[i].clone() for x in blks] for i in (1, 2, 3))
+            if kind == "chain":          # a layer's output is the next layer's queries
+                outs = [torch.zeros_like(q) for q in qs]
+                qs = [qs[0]] + outs[:-1]
+            elif kind == "in-place":
+                outs = qs
+            else:                        # inputs in common: nothing is written that another layer reads
+                outs = [torch.zeros_like(q) for q in qs]
+                ks[1] = vs[0]
+            if caches is a:
+                kd.prefill_block_layers(caches, qs, ks, vs, t, out=outs)
+            else:
+                for c, q, k, v, o in zip(caches, qs, ks, vs, outs):
+                    c.prefill_block(q, k, v, t, out=o)
+            got.append(outs)
+        for x, y in zip(*got):
+            assert float((x.float() - y.float()).abs().max()) <= ATTN_ATOL, t
+    for l in range(layers):
+        _same_state(a[l], b[l], f"layer {l}")
+        a[l].close()
+        b[l].close()
