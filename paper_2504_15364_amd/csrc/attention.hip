@@ -1165,8 +1165,9 @@ __global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_layers_kernel(Layer
 // asks for the dynamic LDS that takes)
 // (EXACT: neither the step's own scores nor the carried ones are approximate)
 template <int D, bool HELP, bool EXACT>
-__global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepParams p, StepParams cy, int ncarry, int cy_res)
+__global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepParams, StepParams, int ncarry, int cy_res)
 {
+    const StepParams &p = argument_at<StepParams>(0), &cy = argument_at<StepParams>(sizeof(StepParams));
     warm_arguments<2 * sizeof(StepParams) + 8>();   // both parameter blocks: the role is not known yet
     if ((int)blockIdx.x < ncarry) {
         extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1245,7 +1246,6 @@ hipError_t configure_main_kernels()
 #define KD_SETS(DD)                                     \
     KD_SET((step_main_carry_kernel<DD, false, false>)) \
     KD_SET((step_main_carry_kernel<DD, false, true>))  \
-    KD_SET((step_main_carry_kernel<DD, true, false>))  \
     KD_SET((step_main_carry_kernel<DD, true, true>))   \
     KD_SET((step_main_ride_kernel<DD, false>))         \
     KD_SET((step_main_ride_kernel<DD, true>))
@@ -1257,7 +1257,7 @@ hipError_t configure_main_kernels()
 }
 
 // workgroups whose last waves have no query row at all run the variant in which those waves help
-static bool main_runs_help(const StepParams &p) { return p.mtiles * 32 * MAIN_WAVES - p.G * p.Bt >= 32; }
+bool main_runs_help(const StepParams &p) { return p.mtiles * 32 * MAIN_WAVES - p.G * p.Bt >= 32; }
 
 static bool scores_exactly(const StepParams &p) { return p.do_score && !p.score_approx; }
 
@@ -1309,7 +1309,8 @@ bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
     // (a step of few query rows takes no passenger whichever kernel runs it: it is shorter than a selection)
-    return p.G * p.Bt > FEW_ROWS && !(scores_exactly(p) && cy.score_approx) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
+    // (approximate scores ride, and are formed, only where every wave carries query rows: the kernel with helper waves has no registers left)
+    return p.G * p.Bt > FEW_ROWS && !(cy.score_approx && (scores_exactly(p) || main_runs_help(p))) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
            ride_of(cy) != Ride::none;
 }
 
@@ -1327,8 +1328,7 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
     const size_t lds = need > main_lds_bytes(p.D) ? need : main_lds_bytes(p.D);
     const bool help = main_runs_help(p), exact = scores_exactly(p);
 #define KD_GO(DD)                                                                                                                             \
-    if (help && exact) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
-    else if (help) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    if (help) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
     else if (exact) hipLaunchKernelGGL((step_main_carry_kernel<DD, false, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
     else hipLaunchKernelGGL((step_main_carry_kernel<DD, false, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res);
     if (p.D == 128) { KD_GO(128) }

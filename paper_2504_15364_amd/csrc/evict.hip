@@ -602,7 +602,7 @@ __global__ void load_pos_kernel(const int32_t *src, int32_t *dst, int cap, int l
 // ---------------------------------------------------------------------- launchers
 constexpr size_t LISTS_LDS_MAX = 48 * 1024;
 
-bool lists_fit_lds(int n, int N) { return n > N && (size_t)(n - N) * 8 <= LISTS_LDS_MAX; }
+bool lists_fit_lds(int n, int N) { return n > N && (size_t)(n - N) * 4 <= LISTS_LDS_MAX; }
 
 // dynamic LDS a step_post launch may ask for next to its static tables (160 KB per compute unit)
 constexpr size_t POST_DYN_MAX = 64 * 1024;

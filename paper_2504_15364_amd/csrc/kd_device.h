@@ -60,6 +60,15 @@ __device__ __forceinline__ void warm_arguments(uint32_t offset = 0)
     }
 }
 
+// The kernel's argument of type T at `offset` of the argument block, read where it is needed.  (Fields of an argument named in the
+// usual way are all loaded at the start of the kernel: more than the scalar registers hold of two parameter blocks, so that
+// dozens of them were kept in lanes of vector registers.)
+template <class T>
+__device__ __forceinline__ const T &argument_at(uint32_t offset)
+{
+    return *(const T *)((const char *)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+}
+
 // Asynchronous 16-byte-per-lane copy global -> LDS (no registers).  `lds_base` is uniform over the
 // active lanes; lane i writes bytes [16 i, 16 i + 16) above it.  Issued through asm, so the compiler
 // does not count it: completion is awaited with an explicit s_waitcnt vmcnt (copies complete in

@@ -61,7 +61,7 @@ struct StepParams {
     float *scores;                   // [BH][cap]; approximate if score_approx
     double *anchor;                  // [BH][D] the step's anchor (score_approx)
     int32_t *dstmap;                 // [BH][cap] ORDERED layout: destination row or -1
-    int32_t *lists;                  // [BH][4 * B]: of E rows each, evicted rows | those below N in ascending order (the rest is not used)
+    int32_t *lists;                  // [BH][4 * B]: the E evicted rows in ascending order (the rest is not used)
     unsigned long long *argmax_rec;  // nullable [BH][splits][2]: the generation phase (one row to evict, no window):
                                      // per step_few workgroup the largest (orderable score bits << 32 | row) among the
                                      // rows it scored, and whether another of its rows has the same score bits
@@ -117,6 +117,8 @@ hipError_t launch_step_few(const StepParams &p, hipStream_t s);
 // every pass, or from copies in LDS.
 enum class Ride { none, memory, lds };
 Ride ride_of(const StepParams &cy);
+// whether some waves of the step's row tiles have no query row (they copy tiles and score)
+bool main_runs_help(const StepParams &p);
 // step_main of `p` whose first workgroups run the selection and compaction `cy` describes (the
 // parameters of an earlier step of another cache; for the ORDERED layout the caller still launches
 // the row shift afterwards); can_carry says whether the pair fits

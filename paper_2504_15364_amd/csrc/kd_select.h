@@ -12,11 +12,17 @@
 // runs on one compute unit per head, whose instruction cache nothing has warmed, while the
 // attention saturates the memory system: with the rows in registers and every pass unrolled
 // (25 KB of straight-line code) it spent most of its time waiting for its own instructions.  In step_post,
-// where sixteen waves share the fetch and the caller waits for the end, the registers are the shorter way, and
-// the evicted keys are requested as soon as their list is known, ahead of the scan that ranks holes and movers
-// (measured, 8 heads, 4096 rows, 128 evicted: 12.9 -> 10.6 us a launch; 16896 rows, 512 evicted, where the
-// scores were read from memory in every pass before: 34 -> 24 us).  Not kept: the destinations of the tail rows
-// worked out ahead of the barrier (1 us slower), the kernel's own code requested into L2 at its start (slower).
+// where sixteen waves share the fetch and the caller waits for the end, the registers are the shorter way.
+//
+// What bounds it there is the issue of its instructions: sixteen waves on four SIMDs, 16 cycles for each instruction that all of
+// them execute (288 rows took 8.2 us of the 11.2 that 4224 take).  Hence: a row's place in the histogram is worked out once and
+// compared as a float afterwards; the eviction bitmap is put together from the rows a wave holds (no atomics but for the
+// few candidates) and gives the list of evicted rows in order; block-wide scans fold the totals of the waves across
+// lanes; half of the waves take K rows, the other half V rows, so that a wave's addresses differ by constants;
+// and a K row's piece is read by the thread that overwrites it, so that the moves wait for no barrier and the sum of the
+// evicted keys is formed behind them.  Launches of step_post before and after, us: 8 heads of 128, 128 rows evicted of 4224
+// 11.15 -> 9.0, of 8320 in the ORDERED layout 12.6 -> 11.0, 512 of 16896 26.6 -> 20.8; of 64, 32 of 288 ORDERED 8.2 -> 6.5, 64 of 576
+// (8 heads) 9.8 -> 7.6.  Not kept: 512 threads (4224 rows 2 us slower, 2112 rows 0.5 us faster), 256 (slower at all sizes).
 #pragma once
 #include "kd_kernels.h"
 #include "kd_device.h"
@@ -33,6 +39,7 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 constexpr int CAND_MAX = 1024;  // rows of the threshold bin ranked in LDS; more fall back to a radix select
 constexpr int MAX_SELECT_WAVES = POST_THREADS / 64;   // PostShared is laid out for the largest workgroup
 constexpr int CARRY_THREADS = 512;                  // workgroup size of the step_main variant that carries a selection
+constexpr int KEY_PARTS = 8;                        // partial sums of the evicted keys
 constexpr int SELECT_TAILU = 8;                     // 16-byte units of the tail rows [N, n) a thread keeps in registers
 
 // float -> unsigned key with the same order
@@ -42,12 +49,12 @@ __device__ __forceinline__ uint32_t orderable(float s)
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// monotone non-decreasing map of a score onto [0, HIST_BINS)
-__device__ __forceinline__ int score_bin(float s)
+// Monotone non-decreasing map of a score onto [0, HIST_BINS): the integer part of score_place, which is clamped (a NaN to 0).
+__device__ __forceinline__ float score_place(float s)
 {
-    const float f = floorf((s + 1.0f) * (float)(HIST_BINS / 2));
-    return (int)fminf(fmaxf(f, 0.f), (float)(HIST_BINS - 1));
+    return __builtin_amdgcn_fmed3f(__builtin_fmaf(s, (float)(HIST_BINS / 2), (float)(HIST_BINS / 2)), 0.f, (float)(HIST_BINS - 1));
 }
+__device__ __forceinline__ int score_bin(float s) { return (int)score_place(s); }
 
 struct PostShared {
     uint32_t hist[HIST_BINS];  // score histogram of the head (a monotone map of the float)
@@ -62,7 +69,7 @@ struct PostShared {
     int32_t cand_pos[CAND_MAX];
     double colsum[MAX_SELECT_WAVES][128];
     double mu[128], mu2[8];   // the anchor and |mu|^2 in pieces (approximate scores: exact ones of the rows near the threshold)
-    int bad;                  // 1: a row's score is not known even approximately; 2: the evicted keys' sum may depend on their order
+    int bad;                  // a row's score is not known even approximately
 };
 
 // bytes of dynamic LDS a carried selection places PostShared in, ahead of its bitmap and lists
@@ -97,14 +104,11 @@ __device__ __forceinline__ T block_exclusive_scan_t(T v, T *wave_tot, T *total)
     const T inc = wave_inclusive_scan(v);
     if (lane == 63) wave_tot[wave] = inc;
     __syncthreads();
-    T base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NWAVES; ++w) {
-        const T t = wave_tot[w];
-        if (w < wave) base += t;
-        tot += t;
-    }
-    *total = tot;
+    // the totals of the waves, one a lane, scanned the same way (every thread adding them up by itself: 0.4 us a scan of 16 waves)
+    static_assert(NWAVES <= 16, "the totals fit one row of lanes");
+    const T totals = wave_inclusive_scan(lane < NWAVES ? wave_tot[lane & (NWAVES - 1)] : (T)0);
+    *total = (T)__builtin_amdgcn_readlane((int)totals, NWAVES - 1);
+    const T base = wave == 0 ? (T)0 : (T)__builtin_amdgcn_readlane((int)totals, __builtin_amdgcn_readfirstlane(wave - 1));
     return base + inc - v;
 }
 
@@ -199,15 +203,14 @@ constexpr int SRC_MEMORY = 0, SRC_LDS = -1;
 __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool lists_in_lds, bool resident)
 {
     size_t b = ((size_t)((n + 31) / 32) * 4 + 15) & ~(size_t)15;
-    if (lists_in_lds) b += (size_t)(n - N) * 8;
+    if (lists_in_lds) b += ((size_t)(n - N) * 4 + 15) & ~(size_t)15;
     if (resident) b += (size_t)cap * 8;
     return b;
 }
 
 // ------------------------------------------------------------- select + compaction
-// `dyn`: dynamic LDS of select_dyn_bytes(...) bytes, 16-byte aligned.  The lists are two arrays of
-// E row indices (evicted rows | evicted rows below N in ascending order): in LDS when they fit, else in the
-// scratch buffer.
+// `dyn`: dynamic LDS of select_dyn_bytes(...) bytes, 16-byte aligned.  The list of evicted rows lies in LDS when it fits, else in
+// the scratch buffer.
 // The caller keeps n <= 32 * THREADS (a thread owns one word of the eviction bitmap) and, with SRC > 0,
 // n <= 4 * SRC * THREADS.
 // (inlined: outlined, the parameter block would be passed through scratch memory)
@@ -216,7 +219,7 @@ template <int D, int SRC, int THREADS, bool APPROX>
 __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh)
 {
     constexpr int UPR = D / 8;
-    constexpr int TAILU = SRC > 3 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (the registers the scores leave)
+    constexpr int TAILU = THREADS > 512 || D == 64 || SRC <= 0 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (128 rows a batch with 1024 threads, 256 of 64)
     // The rows [N, n), the only ones that can move (FILL layout), are requested with the scores; scoring rows exactly takes
     // the registers they would wait in, and they are then requested with the evicted keys.
     constexpr bool EARLY_TAIL = !APPROX;
@@ -237,7 +240,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     int32_t *lists = p.lists + (size_t)bh * 4 * p.B;
     if (p.lists_in_lds) {
         lists = reinterpret_cast<int32_t *>(dyn + dyn_off);
-        dyn_off += (size_t)E * 8;
+        dyn_off += ((size_t)E * 4 + 15) & ~(size_t)15;
     }
     float *sc_l = reinterpret_cast<float *>(dyn + dyn_off);
     int32_t *pos_l = reinterpret_cast<int32_t *>(dyn + dyn_off + (size_t)p.cap * 4);
@@ -247,10 +250,13 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     lds_cf32 *sc_s = (lds_cf32 *)sc_l;
     lds_ci32 *pos_s = (lds_ci32 *)pos_l;
     f32x4 sreg[NQ4];
+    // score_place of the rows in registers, -1: not there, or exempt (with approximate scores a bit of `live` for each row that is neither)
+    f32x4 place[APPROX ? 1 : NQ4];
+    uint32_t live = 0;
+    static_assert(4 * NQ4 <= 32, "one bit a row");
     i32x4 preg[PREG ? NQ4 : 1];
     // visit(row, score, position, k) for every row this thread owns, the k-th of at most 32.  Positions that lie in neither
     // registers nor LDS are read (and handed to visit) only where a pass asks for them: with a window, or to choose by them.
-    auto row_of = [&](int k) { return SRC > 0 ? 4 * ((k >> 2) * THREADS + tid) + (k & 3) : tid + k * THREADS; };
     auto for_rows = [&](bool positions, auto &&visit) {
         if constexpr (SRC > 0) {
 #pragma unroll
@@ -313,20 +319,24 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         }
     }
     const double ksum_old = tid < D ? p.ksum_next[(size_t)bh * D + tid] : 0.0;  // the sum step_main just wrote
-    const bool tail_regs = p.layout == 1 && 2 * E * UPR <= TAILU * THREADS;
+    // The first half of the waves takes the K rows of the tail, the second half the V rows: thread (tail_row0, unit) the rows
+    // tail_row0, tail_row0 + TROWS, ..
+    constexpr int TROWS = THREADS / 2 / UPR;
+    auto tail_row0 = [&]() { return (tid % (THREADS / 2)) / UPR; };
+    auto tail_rows = [&]() { return wave >= NWAVES / 2 ? vb : kb; };
+    const uint32_t unit_off = (uint32_t)(tid % UPR) * 8;
     u32x4 tailv[TAILU];
-    auto request_tail = [&]() {
-        if (tail_regs) {
+    auto request_rows = [&](int r0) {   // rows N + r0 + tail_row0, + TROWS, .. of the tail
 #pragma unroll
-            for (int q = 0; q < TAILU; ++q) {
-                const int w = q * THREADS + tid;
-                tailv[q] = u32x4{0u, 0u, 0u, 0u};
-                if (q * THREADS < 2 * E * UPR && w < 2 * E * UPR) {
-                    const int which = w >= E * UPR, rem = w - which * E * UPR;
-                    tailv[q] = *reinterpret_cast<const u32x4 *>((which ? vb : kb) + (size_t)(p.N + rem / UPR) * D + (rem % UPR) * 8);
-                }
-            }
+        for (int q = 0; q < TAILU; ++q) {
+            const int r = r0 + q * TROWS;   // uniform
+            tailv[q] = u32x4{0u, 0u, 0u, 0u};
+            if (r < E && r + tail_row0() < E)
+                tailv[q] = *reinterpret_cast<const u32x4 *>(tail_rows() + (size_t)(p.N + r) * D + (uint32_t)(tail_row0() * D) + unit_off);
         }
+    };
+    auto request_tail = [&]() {
+        if (p.layout == 1) request_rows(0);
     };
     if constexpr (EARLY_TAIL) request_tail();
     for (int i = tid; i < nwords; i += THREADS) evbits[i] = 0;
@@ -424,7 +434,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             }
             __syncthreads();
         }
-        if (p.layout == 1 && tail_regs && gbest != 0) {
+        if (p.layout == 1 && gbest != 0) {
             // FILL: the one tail row (row N, this step's token) travels with the evicted key: the rest of the work
             // is one row read and at most one row moved, done here without lists
             const int e = sh.tb;
@@ -433,7 +443,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             for (int i = 0; i < 8; ++i) x[i] = 0.0;
             u32x4 tail = {0u, 0u, 0u, 0u};
             if constexpr (EARLY_TAIL) tail = tailv[0];
-            else if (tid < 2 * UPR) tail = *reinterpret_cast<const u32x4 *>((tid >= UPR ? vb : kb) + (size_t)p.N * D + (tid % UPR) * 8);
+            else if (tail_row0() == 0) tail = *reinterpret_cast<const u32x4 *>(tail_rows() + (size_t)p.N * D + unit_off);
             if (tid < UPR) {
                 const u32x4 w = *reinterpret_cast<const u32x4 *>(kb + (size_t)e * D + tid * 8);
 #pragma unroll
@@ -458,22 +468,16 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             }
             // the evicted key has been read: its slot may take the tail row (the thread that read
             // unit u of K is the one that writes unit u of K)
-            if (e != p.N && tid < 2 * UPR) {
-                const int which = tid >= UPR, unit = tid - which * UPR;
-                *reinterpret_cast<u32x4 *>((which ? vb : kb) + (size_t)e * D + unit * 8) = tail;
+            if (e != p.N && tail_row0() == 0) {
+                *reinterpret_cast<u32x4 *>(tail_rows() + (size_t)e * D + unit_off) = tail;
                 if (tid == 0) pos[e] = p.pos0 + (p.N - p.len);
             }
             __syncthreads();
             if (tid < D) p.ksum_next[(size_t)bh * D + tid] = ksum_old - sh.colsum[0][tid];
             KD_SEL_RETURN;
         }
-        // (ORDERED, or no tail row in registers: the evicted row goes the way of the others below; where nothing
-        // could be evicted -- impossible -- the list stays empty and the count check reports it)
-        if (tid == 0 && gbest != 0) {
-            lists[0] = sh.tb;
-            sh.nev = 1;
-        }
-        __syncthreads();
+        // (ORDERED: the evicted row goes the way of the others below; where nothing
+        // could be evicted -- impossible -- the bitmap stays empty and the count check reports it)
     } else {
     // Exact score of row i, in the arithmetic of the attention's exact scores: the UPR lanes that share it call this together, each with its 16-byte unit.
     auto exact_score = [&](int i) {
@@ -492,12 +496,31 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     };
     for (;;) {   // (a second time, with exact scores of all rows, where approximate ones do not do)
     // ---- 1. histogram of the non-exempt scores in LDS
-    for_rows(p.window_W > 0, [&](int, float s, int32_t pi, int) {
-        if (!exempt(pi)) {
-            atomicAdd(&sh.hist[score_bin(s)], 1u);
-            if (APPROX && s != s) sh.bad = 1;
+    auto count = [&](float s, float at) {
+        atomicAdd(&sh.hist[(int)at], 1u);
+        if (APPROX && s != s) sh.bad = 1;
+    };
+    if constexpr (SRC > 0) {
+#pragma unroll
+        for (int q = 0; q < NQ4; ++q) {
+            if (q * 4 * THREADS >= p.n) break;   // uniform
+            const int i0 = 4 * (q * THREADS + tid);
+            i32x4 pq = {0, 0, 0, 0};
+            if constexpr (PREG) pq = preg[q];
+            else if (p.window_W > 0 && i0 < p.n) pq = *reinterpret_cast<const i32x4 *>(pos + i0);   // (a multiple of four rows)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float at = i0 + e >= p.n || exempt((int32_t)pq[e]) ? -1.f : score_place(sreg[q][e]);
+                if constexpr (APPROX) live |= at >= 0.f ? 1u << (4 * q + e) : 0u;
+                else place[q][e] = at;
+                if (at >= 0.f) count(sreg[q][e], at);
+            }
         }
-    });
+    } else {
+        for_rows(p.window_W > 0, [&](int, float s, int32_t pi, int) {
+            if (!exempt(pi)) count(s, score_place(s));
+        });
+    }
     __syncthreads();
     if (approx && tid < D) {   // (whole waves)
         sh.mu[tid] = mu;
@@ -536,26 +559,20 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     // bin and the E-th largest exact one within the slack of it: a row more than twice the slack above the bin is evicted
     // whatever its exact score, one as far below it stays, and those between are candidates (the last term covers the
     // rounding of the bin edges).
+    const float above_from = (float)(tb + 1);   // (no place of the top bin reaches it)
     const float reach = approx ? 2.f * SCORE_SLACK + 1e-6f : 0.f;
-    auto evict = [&](int i) {   // marks row i and appends it to the (unordered) list
-        atomicOr(&evbits[i >> 5], 1u << (i & 31));
-        const uint32_t at = atomicAdd(&sh.nev, 1u);
-        if (at < (uint32_t)E) lists[at] = i;
-    };
-    uint32_t mine_above = 0;   // the thread's rows above the bin: listed after the pass, so that the pass itself waits for nothing
-    for_rows(p.window_W > 0, [&](int i, float s, int32_t pi, int k) {
-        if (exempt(pi)) return;
+    uint32_t nabove = 0;   // of the rows this lane has looked at (or, on rows in LDS or memory, its wave)
+    // a row that may be chosen, with its place: true if it lies above the bin; in the bin, it joins the candidates
+    auto classify = [&](int i, float s, float at, int32_t pi) {
         bool above_bin, in_bin;
         if constexpr (APPROX) {
             above_bin = score_bin(s - reach) > tb;
             in_bin = score_bin(s + reach) >= tb;
         } else {
-            const int sb = score_bin(s);
-            above_bin = sb > tb;
-            in_bin = sb == tb;
+            above_bin = at >= above_from;
+            in_bin = at >= (float)tb;
         }
-        if (above_bin) mine_above |= 1u << k;
-        else if (in_bin) {
+        if (!above_bin && in_bin) {
             const uint32_t c = atomicAdd(&sh.ncand, 1u);
             if (c < CAND_MAX) {
                 sh.cand_slot[c] = (uint32_t)i;
@@ -563,8 +580,47 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                 sh.cand_pos[c] = pi;
             }
         }
-    });
-    for (; mine_above; mine_above &= mine_above - 1) evict(row_of(__ffs(mine_above) - 1));
+        return above_bin;
+    };
+    // The bitmap is written word by word, without atomics: a wave holds whole words of it.
+    if constexpr (SRC > 0) {
+#pragma unroll
+        for (int q = 0; q < NQ4; ++q) {
+            if (q * 4 * THREADS >= p.n) break;   // uniform
+            const int i0 = 4 * (q * THREADS + tid);
+            uint32_t four = 0;   // the thread's four rows; eight lanes make a word
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float at = APPROX ? 0.f : place[APPROX ? 0 : q][e];
+                if ((!APPROX || ((live >> (4 * q + e)) & 1u)) && classify(i0 + e, sreg[q][e], at, PREG ? (int32_t)preg[PREG ? q : 0][e] : 0))
+                    four |= 1u << e;
+            }
+            nabove += (uint32_t)__popc(four);
+            uint32_t word = four << (4 * (lane & 7));
+            word |= dpp_fetch<0xB1, 0xF>(word);    // quad_perm [1,0,3,2]
+            word |= dpp_fetch<0x4E, 0xF>(word);    // quad_perm [2,3,0,1]
+            word |= dpp_fetch<0x141, 0xF>(word);   // row_half_mirror
+            if ((lane & 7) == 0 && i0 < p.n) evbits[i0 >> 5] = word;
+        }
+        nabove = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(nabove), 63);
+    } else {
+        auto mark = [&](int i, bool above_bin) {   // (rows i of the wave's lanes: 64 in a row from a multiple of 64)
+            const uint64_t m = __ballot(above_bin);
+            if (lane == 0) *reinterpret_cast<uint64_t *>(evbits + (i >> 5)) = m;
+            nabove += (uint32_t)__popcll(m);
+        };
+        for (int i0 = 64 * wave; i0 < p.n; i0 += THREADS) {   // uniform per wave
+            const int i = i0 + lane;
+            bool above_bin = false;
+            if (i < p.n) {
+                const float s = RES ? (float)sc_s[i] : sc_g[i];
+                const int32_t pi = RES ? (int32_t)pos_s[i] : p.window_W > 0 ? pos[i] : 0;
+                if (!exempt(pi)) above_bin = classify(i, s, APPROX ? 0.f : score_place(s), pi);
+            }
+            mark(i0, above_bin);
+        }
+    }
+    if (lane == 0 && nabove != 0) atomicAdd(&sh.nev, nabove);
     __syncthreads();
     const uint32_t ncand = sh.ncand, need = (uint32_t)E - sh.nev;
     if constexpr (APPROX) {
@@ -582,6 +638,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         for (int i = tid; i < nwords; i += THREADS) evbits[i] = 0;
         __syncthreads();
         if (tid == 0) sh.ncand = sh.nev = 0;
+        live = 0;
         if constexpr (SRC > 0) {
 #pragma unroll
             for (int q = 0; q < NQ4; ++q) {
@@ -624,92 +681,55 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                 }
                 rank += (uint32_t)__popcll(__ballot(gt));
             }
-            if (lane == 0 && rank < need) evict((int)sh.cand_slot[c]);
+            if (lane == 0 && rank < need) atomicOr(&evbits[sh.cand_slot[c] >> 5], 1u << (sh.cand_slot[c] & 31));
         }
         __syncthreads();
     } else {
         radix_select_in_bin<THREADS>(p, sh, RES ? sc_l : sc_g, RES ? pos_l : pos, evbits, tb, need);   // (exact scores here)
-        for_rows(false, [&](int i, float s, int32_t, int) {   // (it marks rows of the bin; they join the list here)
-            if (score_bin(s) == tb && ((evbits[i >> 5] >> (i & 31)) & 1u)) {
-                const uint32_t at = atomicAdd(&sh.nev, 1u);
-                if (at < (uint32_t)E) lists[at] = i;
-            }
-        });
-        __syncthreads();
     }
     break;
     }   // for (;;)
     }   // E > 1, or approximate scores
     KD_TL(6);   // ranking done: the eviction bitmap and the list of evicted rows are final
 
-    int32_t *evlist = lists, *holes = lists + E;
-    // an impossible count is reported and nothing is moved (keeps every index in range)
-    if (sh.nev != (uint32_t)E) {   // uniform
-        if (tid == 0) atomicOr(p.status, STATUS_SELECT_COUNT);
-        KD_SEL_RETURN;
-    }
-
-    // ---- 4. evicted rows before each row: thread t owns bitmap word t = rows [32 t, 32 t + 32).  From that
-    // count follow the destinations of the ORDERED layout, and of the FILL layout the rank of a hole (all evicted
-    // rows below it are holes) and of a mover.  The evicted keys are requested before the scan, in the order in which threads
-    // happened to list them, so that their trip to memory runs under it (putting the list in order first: 1 us of 10.6).
-    // A sum of doubles depends in its last bit on the order of its terms unless it is exact, which one of raw keys
-    // is in any order as long as their exponents lie close enough; that is looked at below, and the sum taken
-    // again in ascending order of the rows where they don't.  Unit keys are listed in order to begin with.
-    constexpr int RPW = 64 / UPR;
-    const int eu = lane % UPR, erl = lane / UPR;
-    // the rows of up to EV_BATCH rounds are requested together: one memory round trip, not one per round
-    constexpr int EV_BATCH = SRC > 3 ? 2 : 4;
-    u32x4 wv[EV_BATCH];
-    auto request = [&](int rb0) {
-#pragma unroll
-        for (int b = 0; b < EV_BATCH; ++b) {
-            const int r = rb0 + b * NWAVES * RPW + erl;
-            wv[b] = u32x4{0u, 0u, 0u, 0u};
-            if (r < E) wv[b] = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + eu * 8);
-        }
-    };
-    const bool sorted = p.anchor_mode == 1;   // uniform
-    if (!sorted) request(wave * RPW);
+    // ---- 4. the evicted rows in ascending order, from the bitmap: thread t owns word t = rows [32 t, 32 t + 32).  The count of
+    // evicted rows before each word also gives the destinations of the ORDERED layout, and of the FILL layout the rank of a hole
+    // (the k-th evicted row below N is hole k) and of a mover.
+    int32_t *evlist = lists;
     if constexpr (!EARLY_TAIL) request_tail();
     uint32_t *word_base = sh.cand_slot;   // the candidate arrays are free by now
     static_assert(MAX_CAP / 32 <= CAND_MAX, "one count per bitmap word");
     {
-        uint32_t tot_ev;
-        const uint32_t eb = block_exclusive_scan_t<THREADS, uint32_t>(tid < nwords ? (uint32_t)__popc(evbits[tid]) : 0u, sh.wave_tot2, &tot_ev);
-        if (tid < nwords) word_base[tid] = eb;
+        uint32_t total;
+        uint32_t w = tid < nwords ? evbits[tid] : 0u;
+        uint32_t at = block_exclusive_scan_t<THREADS, uint32_t>((uint32_t)__popc(w), sh.wave_tot2, &total);
+        // an impossible count is reported and nothing is moved (keeps every index in range)
+        if (total != (uint32_t)E) {   // uniform
+            if (tid == 0) atomicOr(p.status, STATUS_SELECT_COUNT);
+            KD_SEL_RETURN;
+        }
+        if (tid < nwords) word_base[tid] = at;
+        for (; w; w &= w - 1) evlist[at++] = 32 * tid + __ffs(w) - 1;
     }
     __syncthreads();
     auto before = [&](int i) { return (int)(word_base[i >> 5] + (uint32_t)__popc(evbits[i >> 5] & ((1u << (i & 31)) - 1u))); };
     auto evicted = [&](int i) { return ((evbits[i >> 5] >> (i & 31)) & 1u) != 0; };
-    const int nholes = before(p.N);   // (row N exists: n > N)
-    auto put_in_order = [&]() {   // the list is rewritten from the bitmap, thread by word
-        if (tid < nwords) {
-            int at = (int)word_base[tid];
-            for (uint32_t w = evbits[tid]; w; w &= w - 1) evlist[at++] = 32 * tid + __ffs(w) - 1;
-        }
-        __syncthreads();
-    };
-    if (sorted) {
-        put_in_order();
-        request(wave * RPW);
-    }
-    if (p.layout == 1)
-        for (int r = tid; r < E; r += THREADS) {
-            const int i = evlist[r];
-            if (i < p.N) holes[before(i)] = i;
-        }
-    // rank of tail row N + r among the movers (rows from N on that stay), -1 if it is evicted: mover k goes to hole k
-    auto mover = [&](int r) { return evicted(p.N + r) ? -1 : r - (before(p.N + r) - nholes); };
-    KD_TL(7);   // holes listed
+    KD_TL(7);   // evicted rows listed
 
-    // ---- 5. take the evicted keys out of the running key sum (before rows are overwritten).
-    // UPR lanes share an evicted row (16 bytes each); a wave holds 64/UPR rows at a time.
-    // In order, there are sixteen partial sums whatever the number of waves (a wave of a smaller workgroup takes turns with its
-    // rounds), so that the passenger leaves the very sum step_post does.
-    constexpr int TURNS = MAX_SELECT_WAVES / NWAVES;
-    static_assert(TURNS * NWAVES == MAX_SELECT_WAVES && EV_BATCH % TURNS == 0, "a round's turn follows from its place in a batch");
-    auto add_key = [&](const u32x4 &w, double (&acc)[8]) {
+    // ---- 5. compaction, and the evicted keys taken out of the running key sum.  A sum of doubles depends in its last bit on the
+    // order of its terms: E terms are dealt to KEY_PARTS parts in rounds of 64 / UPR (the lanes of a wave that share no row), in the order of the
+    // tail rows they make room for (FILL) or of the rows themselves (ORDERED), whatever the number of threads, so that the
+    // passenger leaves the very sum step_post does.
+    constexpr int RPW = 64 / UPR, KWAVES = NWAVES / 2, TURNS = KEY_PARTS / KWAVES;
+    static_assert(TURNS >= 1 && TURNS * KWAVES == KEY_PARTS && TAILU % TURNS == 0, "a round's part follows from its place in a batch");
+    static_assert(TROWS == RPW * KWAVES, "a wave of the first half takes RPW rows a round");
+    const bool keys = wave < KWAVES;   // uniform per wave: takes K rows (the others V rows)
+    double acc[TURNS][8];
+#pragma unroll
+    for (int t = 0; t < TURNS; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[t][i] = 0.0;
+    auto add_key = [&](const u32x4 &w, double (&a)[8]) {
         double x[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -726,135 +746,59 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             inv = nk > 0.0 ? 1.0 / nk : 0.0;
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += (p.anchor_mode == 1) ? x[i] * inv : x[i];
+        for (int i = 0; i < 8; ++i) a[i] += (p.anchor_mode == 1) ? x[i] * inv : x[i];
     };
-    auto fold = [&](double (&acc)[8], int part) {   // the rows of the wave (lanes with equal eu)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if constexpr (UPR == 16) acc[i] = sum_over_rows_f64(acc[i]);
-            else {
-#pragma unroll
-                for (int off = UPR; off < 64; off <<= 1) acc[i] += shfl_xor_f64(acc[i], off);
-            }
-        }
-        if (erl == 0) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sh.colsum[part][eu * 8 + i] = acc[i];
-        }
-    };
-    {
-        double acc[TURNS][8];
-#pragma unroll
-        for (int t = 0; t < TURNS; ++t)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[t][i] = 0.0;
-        // A sum of the keys is exact in any order where every term is a multiple of 2^-7 times the power of one exponent and any sum of
-        // them stays below 2^53 times that, that is where the exponents lie within 45 - log2(E) of one another.  Looked for: no
-        // element of 2^10 or more, none but zeros as far below.
-        constexpr uint32_t below = (127 + 10) << 7;   // (bf16 bits)
-        const uint32_t least = below - ((uint32_t)(45 - (32 - __clz(E))) << 7);
-        u16x2 largest = {0, 0}, smallest = {0xFFFF, 0xFFFF};   // magnitudes as bf16 bits; smallest: less one, so that zeros wrap
-        for (int rb0 = wave * RPW; rb0 < E; rb0 += EV_BATCH * NWAVES * RPW) {  // uniform per wave
-            if (rb0 != wave * RPW) request(rb0);
-#pragma unroll
-            for (int b = 0; b < EV_BATCH; ++b) {
-                if (rb0 + b * NWAVES * RPW >= E) break;   // uniform
-                add_key(wv[b], acc[b % TURNS]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const u16x2 m = __builtin_bit_cast(u16x2, wv[b][i] & 0x7FFF7FFFu);
-                    largest = __builtin_elementwise_max(largest, m);
-                    smallest = __builtin_elementwise_min(smallest, (u16x2)(m - (unsigned short)1));
-                }
-            }
-        }
-        if (TURNS == 1 || sorted) {
-#pragma unroll
-            for (int t = 0; t < TURNS; ++t) fold(acc[t], t * NWAVES + wave);
-        } else {
-#pragma unroll
-            for (int t = 1; t < TURNS; ++t)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[0][i] += acc[t][i];
-            fold(acc[0], wave);
-        }
-        const bool out_of_range = (uint32_t)max(largest[0], largest[1]) >= below || (uint32_t)min(smallest[0], smallest[1]) + 1 < least;
-        if (__ballot(out_of_range) != 0 && lane == 0) sh.bad = 2;
-        __syncthreads();   // also: every evicted row has been read before the compaction overwrites it
-    }
-    const bool in_order = sorted || sh.bad == 2;   // uniform
-    // (rare; said so that the code lies out of the way: in line it cost the passenger, whose instructions come from cold
-    // memory, 1.3 % of the 24 / 8 head ORDERED prompt)
-    if (__builtin_expect(in_order && !sorted, 0)) {
-        put_in_order();
-#pragma unroll 1
-        for (int part = wave; part < MAX_SELECT_WAVES; part += NWAVES) {
-            double acc[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-#pragma unroll 1
-            for (int rb0 = part * RPW; rb0 < E; rb0 += MAX_SELECT_WAVES * RPW) {
-                const int r = rb0 + erl;
-                u32x4 w = {0u, 0u, 0u, 0u};
-                if (r < E) w = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + eu * 8);
-                add_key(w, acc);
-            }
-            fold(acc, part);
-        }
-        __syncthreads();
-    }
-    KD_TL(8);   // evicted rows read
-
-    // ---- 6. compaction
     if (p.layout == 1) {
-        // FILL: k-th surviving row of [N, n) moves into the k-th evicted slot of [0, N).  Rows from N
-        // on belong to this step's block: row i holds token pos0 + (i - len).
-        if (tail_regs) {
+        // FILL: the k-th surviving row of [N, n) moves into the k-th evicted slot of [0, N).  Rows from N on belong to this step's
+        // block: row i holds token pos0 + (i - len).  The thread that brings a piece of a K row takes the piece it overwrites
+        // along (a load ahead of a store of the same thread to the same place), and of a tail row that is itself evicted the
+        // piece it already holds: no wave waits for another.
+        const int nholes = before(p.N);   // (row N exists: n > N)
+        for (int r0 = 0; r0 < E; r0 += TAILU * TROWS) {   // uniform
+            if (r0 > 0) request_rows(r0);
+            int to[TAILU];
 #pragma unroll
             for (int q = 0; q < TAILU; ++q) {
-                const int w = q * THREADS + tid;
-                if (q * THREADS < 2 * E * UPR && w < 2 * E * UPR) {
-                    const int which = w >= E * UPR, rem = w - which * E * UPR;
-                    const int mr = mover(rem / UPR);
-                    if (mr >= 0)
-                        *reinterpret_cast<u32x4 *>((which ? vb : kb) + (size_t)holes[mr] * D + (rem % UPR) * 8) = tailv[q];
+                const int r = r0 + q * TROWS + tail_row0();
+                to[q] = -1;
+                if (r0 + q * TROWS < E && r < E && !evicted(p.N + r)) to[q] = evlist[r - (before(p.N + r) - nholes)];
+            }
+            u32x4 old[TAILU];
+            if (keys) {
+#pragma unroll
+                for (int q = 0; q < TAILU; ++q) {
+                    old[q] = tailv[q];   // (zeros past the last row)
+                    if (to[q] >= 0) old[q] = *reinterpret_cast<const u32x4 *>(kb + (size_t)to[q] * D + unit_off);
                 }
             }
-        } else {
-            // Rows leave [N, n) and arrive below N, so the loads of MOVES units stand before their stores: one trip to memory, not
-            // MOVES in a row (256 rows evicted, as a passenger: 4.5 us less).
-            constexpr int MOVES = 4;
-            const int rem = tid % (UPR * 2), u = rem % UPR;
-            uint16_t *base_ptr = rem < UPR ? kb : vb;
-            constexpr int RSTEP = THREADS / (UPR * 2);
-            for (int r0 = tid / (UPR * 2); r0 < E; r0 += MOVES * RSTEP) {
-                u32x4 val[MOVES];
-                int to[MOVES];
 #pragma unroll
-                for (int m = 0; m < MOVES; ++m) {
-                    const int r = r0 + m * RSTEP;
-                    to[m] = -1;
-                    val[m] = u32x4{0u, 0u, 0u, 0u};
-                    if (r < E) {
-                        val[m] = *reinterpret_cast<const u32x4 *>(base_ptr + (size_t)(p.N + r) * D + u * 8);
-                        const int mr = mover(r);
-                        if (mr >= 0) to[m] = holes[mr];
-                    }
-                }
+            for (int q = 0; q < TAILU; ++q)
+                if (to[q] >= 0) *reinterpret_cast<u32x4 *>(tail_rows() + (size_t)to[q] * D + unit_off) = tailv[q];
+            if (keys) {
 #pragma unroll
-                for (int m = 0; m < MOVES; ++m)
-                    if (to[m] >= 0) *reinterpret_cast<u32x4 *>(base_ptr + (size_t)to[m] * D + u * 8) = val[m];
+                for (int q = 0; q < TAILU; ++q)
+                    if (r0 + q * TROWS < E) add_key(old[q], acc[q % TURNS]);
+            } else if (unit_off == 0) {
+#pragma unroll
+                for (int q = 0; q < TAILU; ++q)
+                    if (to[q] >= 0) pos[to[q]] = p.pos0 + (p.N + r0 + q * TROWS + tail_row0() - p.len);
             }
-        }
-        for (int r = tid; r < E; r += THREADS) {
-            const int mr = mover(r);
-            if (mr >= 0) pos[holes[mr]] = p.pos0 + (p.N + r - p.len);
         }
     } else {
         // ORDERED: kept row i moves to i - (evicted rows before i); positions are compacted here, the
         // K/V rows by compact_ordered_kernel.  A position lands at or below the row it came from: from registers or
         // the LDS copy nothing can be overwritten before it is read; reading from memory, the rows are taken in
         // ascending chunks, each read, then (barrier) written.
+        u32x4 old[TAILU];
+        auto request_keys = [&](int r0) {
+#pragma unroll
+            for (int q = 0; q < TAILU; ++q) {
+                const int r = r0 + q * TROWS + tail_row0();
+                old[q] = u32x4{0u, 0u, 0u, 0u};
+                if (r < E) old[q] = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + unit_off);
+            }
+        };
+        if (keys) request_keys(0);
         int32_t *dst = p.dstmap + (size_t)bh * p.cap;
         if constexpr (PREG) {
 #pragma unroll
@@ -893,18 +837,41 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                 }
             }
         }
+        if (keys) {
+            for (int r0 = 0; r0 < E; r0 += TAILU * TROWS) {   // uniform
+                if (r0 > 0) request_keys(r0);
+#pragma unroll
+                for (int q = 0; q < TAILU; ++q)
+                    if (r0 + q * TROWS < E) add_key(old[q], acc[q % TURNS]);
+            }
+        }
     }
-    if (tid < D) {   // (the sums of the waves were published by the barrier above; stored last, off the moves' way)
+    KD_TL(8);   // moves issued
+    if (keys) {
+#pragma unroll
+        for (int t = 0; t < TURNS; ++t) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {   // the rows of the wave (lanes with the same unit)
+                if constexpr (UPR == 16) acc[t][i] = sum_over_rows_f64(acc[t][i]);
+                else {
+#pragma unroll
+                    for (int off = UPR; off < 64; off <<= 1) acc[t][i] += shfl_xor_f64(acc[t][i], off);
+                }
+            }
+            if (lane < UPR) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sh.colsum[t * KWAVES + wave][lane * 8 + i] = acc[t][i];
+            }
+        }
+    }
+    __syncthreads();
+    if (tid < D) {
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < NWAVES; ++w) s += sh.colsum[w][tid];
-        if (TURNS > 1 && in_order) {
-#pragma unroll
-            for (int w = NWAVES; w < MAX_SELECT_WAVES; ++w) s += sh.colsum[w][tid];
-        }
+        for (int w = 0; w < KEY_PARTS; ++w) s += sh.colsum[w][tid];
         p.ksum_next[(size_t)bh * D + tid] = ksum_old - s;
     }
-    KD_TL(9);   // moves issued
+    KD_TL(9);   // key sum stored
 #ifdef KD_TIMELINE
     __builtin_amdgcn_s_waitcnt(0x0F70);
     KD_SEL_RETURN;

@@ -354,7 +354,7 @@ bool approximate_scores_pay(const keydiff_cache *c, const kd::StepParams &p)
 {
     const int BH = p.batch * p.hkv, mtiles = (p.G * p.Bt + 255) / 256, target = c->L.target_wgs / 2;
     const kd::Ride ride = kd::ride_of(p);
-    if (mtiles < 2 || ride == kd::Ride::none || BH + BH * mtiles > target) return false;
+    if (mtiles < 2 || mtiles * 256 - p.G * p.Bt >= 32 || ride == kd::Ride::none || BH + BH * mtiles > target) return false;
     const int ntiles = (p.n + kd::TILE_KEYS - 1) / kd::TILE_KEYS;
     const int ranges = std::min((target - BH) / (BH * mtiles), ntiles), tiles = (ntiles + ranges - 1) / ranges;
     return p.layout == KEYDIFF_LAYOUT_FILL ? 2048 * (tiles - 4) >= p.n : ride == kd::Ride::lds && 1024 * tiles >= p.n;
@@ -665,7 +665,7 @@ double plan_layers(const keydiff_cache *c, kd::StepParams &p, int layers)
     p.splits = splits;
     p.edge_cost = cost / splits >= 4 ? 2 : 1;
     const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64;
-    p.merge_wgs = splits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
+    p.merge_wgs = p.splits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
     return best;
 }
 
