@@ -597,7 +597,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
             const int row = st_row[wave][lane];
             if (row < p.n) {
                 const double nmu2 = sum_of_pieces<D>(&red[0][0]);   // (of the waves that formed it; all eight: 0.4 us a flush more)
-                const float sc = finish_score(st_dot[wave][lane], st_k2[wave][lane], sqrt(nmu2), p.eps);
+                const float sc = finish_score(st_dot[wave][lane], st_k2[wave][lane], nmu2, p.eps);
                 p.scores[(size_t)bh * p.cap + row] = sc;
                 if (p.scores_out) p.scores_out[(size_t)bh * p.n + row] = sc;
             }

@@ -69,7 +69,6 @@ __device__ __forceinline__ void score_rows(const StepParams &p, ScoreShared &sh,
     double mu2 = 0.0;
 #pragma unroll
     for (int wv = 0; wv < SCORE_WAVES; ++wv) mu2 += sh.red[wv];
-    const double nmu = sqrt(mu2);
 
     double mreg[8];
 #pragma unroll
@@ -123,7 +122,7 @@ __device__ __forceinline__ void score_rows(const StepParams &p, ScoreShared &sh,
     const int row = base + lane;
     if (lane < WROWS && row < row1) {
         const double dot = sh.dot[wave][lane], k2 = sh.k2[wave][lane];
-        const float sc = finish_score(dot, k2, nmu, p.eps);
+        const float sc = finish_score(dot, k2, mu2, p.eps);
         p.scores[(size_t)bh * p.cap + row] = sc;
         if (p.scores_out) p.scores_out[(size_t)bh * p.n + row] = sc;
     }
@@ -618,10 +617,14 @@ hipError_t configure_kernels()
     if (e != hipSuccess) return e;
     static_assert(MAX_CAP / 8 + LISTS_LDS_MAX + 16 <= POST_DYN_MAX, "the non-resident selection always fits");
     const void *post_fns[] = {
-#define KD_FN(DD, SRC)                                                                                                          \
-    reinterpret_cast<const void *>(step_post_kernel<DD, SRC, false>), reinterpret_cast<const void *>(step_post_kernel<DD, SRC, true>), \
+#define KD_FN(DD, SRC)                                                           \
+    reinterpret_cast<const void *>(step_post_kernel<DD, SRC, false>),             \
         reinterpret_cast<const void *>(step_post_layers_kernel<DD, SRC>)
-        KD_FN(128, 0), KD_FN(128, 3), KD_FN(128, 5), KD_FN(64, 0), KD_FN(64, 3), KD_FN(64, 5)};
+#define KD_FNS(DD)                                                               \
+    KD_FN(DD, 0), KD_FN(DD, 3), KD_FN(DD, 5), reinterpret_cast<const void *>(step_post_kernel<DD, 0, true>), \
+        reinterpret_cast<const void *>(step_post_kernel<DD, 3, true>)
+        KD_FNS(128), KD_FNS(64)};
+#undef KD_FNS
 #undef KD_FN
     for (const void *fn : post_fns) {
         e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)POST_DYN_MAX);
@@ -641,11 +644,11 @@ hipError_t launch_step_score(const StepParams &p, hipStream_t s)
 
 // Three 16-byte loads of scores and of positions a thread up to 12288 rows, five of scores alone up to 20480 (a pass that
 // needs every row's position reads those from memory); the registers hold no more beside the rows that may move, so
-// larger caches are read from memory in every pass.  With the arg-max records of the attention launch the scores are hardly
+// larger caches are read from memory in every pass (with approximate scores, whose exact ones take registers, beyond 12288 rows).  With the arg-max records of the attention launch the scores are hardly
 // ever looked at.
 static int post_source(const StepParams &p)
 {
-    return p.argmax_rec || p.n > 5 * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
+    return p.argmax_rec || p.n > (p.score_approx ? 3 : 5) * 4 * POST_THREADS ? 0 : p.n <= 3 * 4 * POST_THREADS ? 3 : 5;
 }
 
 hipError_t launch_step_post(const StepParams &p, hipStream_t s)
@@ -675,7 +678,7 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
 #define KD_GO(DD)                       \
     if (src == 0) { KD_GO2(DD, 0) }      \
     else if (src == 3) { KD_GO2(DD, 3) } \
-    else { KD_GO2(DD, 5) }
+    else hipLaunchKernelGGL((step_post_kernel<DD, 5, false>), dim3(grid), dim3(POST_THREADS), lds, s, p);
     if (p.D == 128) { KD_GO(128) }
     else if (p.D == 64) { KD_GO(64) }
 #undef KD_GO

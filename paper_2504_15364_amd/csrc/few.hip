@@ -191,7 +191,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
 
     // ---- anchor: key sum after this step = key sum before it + the block's keys (at most 32 rows)
     double ksum_after = 0.0;
-    double nmu = 0.0;
+    double nmu2 = 0.0;   // |mu|^2
     if (need_sum) {
         double bacc[8];
 #pragma unroll
@@ -243,10 +243,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         sq = row_allreduce_f64<16>(sq);
         if (tid < D && (lane & 15) == 0) red[tid / 16] = sq;
         __syncthreads();
-        double nmu2 = 0.0;
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) nmu2 += red[i];
-        nmu = sqrt(nmu2);
     }
 
     // ---- state of the wave
@@ -284,7 +282,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     int held_row = 0x7fffffff;
     auto flush_scores = [&]() {   // sqrt and divide on full waves: 64 rows of two tiles
         if (held_row < p.n) {
-            const float sc = finish_score(held_dot, held_k2, nmu, p.eps);
+            const float sc = finish_score(held_dot, held_k2, nmu2, p.eps);
             p.scores[(size_t)bh * p.cap + held_row] = sc;
             if (p.scores_out) p.scores_out[(size_t)bh * p.n + held_row] = sc;
             am_merge(am_best, am_tie, ((unsigned long long)orderable(sc) << 32) | (uint32_t)held_row, false);

@@ -492,7 +492,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             dot = __builtin_fma(sh.mu[u * 8 + 2 * j + 1], x1, dot);
             k2 = __builtin_fma(x1, x1, k2);
         }
-        return finish_score(row_score_sum_f64<UPR>(dot), row_score_sum_f64<UPR>(k2), sqrt(sum_of_pieces<D>(sh.mu2)), p.eps);
+        return finish_score(row_score_sum_f64<UPR>(dot), row_score_sum_f64<UPR>(k2), sum_of_pieces<D>(sh.mu2), p.eps);
     };
     for (;;) {   // (a second time, with exact scores of all rows, where approximate ones do not do)
     // ---- 1. histogram of the non-exempt scores in LDS
