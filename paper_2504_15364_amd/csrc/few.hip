@@ -14,7 +14,9 @@
 // The eight results are merged through LDS once at the end, and the key ranges of different workgroups by
 // step_post from float partials.  Measured per step against step_main with two waves sharing the key tiles
 // (attention + merge and selection, 32 / 8 heads, N = 8192): one sequence 14.3 + 22.9 -> 15.0 + 4.0 us,
-// sixteen sequences 106.9 + 6.9 -> 98 + 4.8 us (537 MB: 5.5 TB/s).
+// sixteen sequences 106.9 + 6.9 -> 98 + 4.8 us (537 MB: 5.5 TB/s).  Of the 14.5 us of one sequence 5.8 bring the data in; the rest is the chain
+// behind it, of which the arg-max (six exchanges of 64-bit pairs through LDS, then one thread over eight records) took 2: on the
+// vector ALU, and the eight records by a wave that has nothing to merge, 13.7 us.
 //
 //   S^T = K Q^T  A = K rows, loaded straight from memory in operand layout (lane: row l % 16, 16 bytes at
 //                32 c + 8 (l / 16): 64 contiguous bytes per row and instruction); B = Q^T (registers)
@@ -66,6 +68,26 @@ __device__ __forceinline__ double pair_split_f64(double x, double y)
     return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
 
+// Arg-max over a wave of (orderable score bits << 32 | row) with a tie flag: every lane gets the record with the largest score bits
+// and whether another one has them too (or the winner's own flag is set).  0: no row.  On the vector ALU alone.
+__device__ __forceinline__ void wave_argmax(unsigned long long &best, bool &tie)
+{
+    const uint32_t hi = (uint32_t)(best >> 32);
+    uint32_t m = hi;   // maximum of the lanes below and this one, as in wave_inclusive_scan; lane 63: of all
+    m = max(m, dpp_fetch<0x111, 0xF>(m));
+    m = max(m, dpp_fetch<0x112, 0xF>(m));
+    m = max(m, dpp_fetch<0x114, 0xF>(m));
+    m = max(m, dpp_fetch<0x118, 0xF>(m));
+    m = max(m, dpp_fetch<0x142, 0xA>(m));
+    m = max(m, dpp_fetch<0x143, 0xC>(m));
+    m = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    const uint64_t with = __builtin_amdgcn_ballot_w64(hi == m);   // (of 64 lanes without a row: all, with m == 0)
+    const int first = __builtin_ctzll(with);
+    const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)best, first);
+    tie = m != 0 && (__popcll(with) > 1 || __builtin_amdgcn_ballot_w64(hi == m && tie) != 0);
+    best = ((unsigned long long)m << 32) | row;
+}
+
 // STREAM: the cached rows are read with the non-temporal hint (see launch_step_few)
 template <int D, bool STREAM>
 __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
@@ -87,6 +109,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     __shared__ float2 ml_s[NW][16];
     __shared__ unsigned long long rec_s[NW][2];
 
+    KD_TL_DECL
+    KD_TL(0);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, g = lane >> 4;
@@ -177,6 +201,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         if (t + NW < t1) load_k(t + NW, kb2);
     }
 
+    KD_TL(1);   // first tiles requested
     // ---- query rows: B operand of the first product, column c16; rows past the last repeat it
     bf16x8 qreg[NC];
     int vis;   // rows [0, vis) are visible to the lane's query: all cached rows, block rows 0 .. j
@@ -247,6 +272,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         for (int i = 0; i < D / 16; ++i) nmu2 += red[i];
     }
 
+    KD_TL(2);   // anchor formed
     // ---- state of the wave
     f32x4 oacc[NDB], lacc = {0.f, 0.f, 0.f, 0.f};
     float mref = -INFINITY;
@@ -268,16 +294,6 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     // best row this lane has finished as (orderable score bits << 32 | row), and whether it met the same bits twice
     unsigned long long am_best = 0;
     bool am_tie = false;
-    auto am_merge = [](unsigned long long &best, bool &tie, unsigned long long ob, bool ot) {
-        const uint32_t hb = (uint32_t)(best >> 32), ho = (uint32_t)(ob >> 32);
-        if (ho > hb) {
-            best = ob;
-            tie = ot;
-        } else if (ho == hb && ob != 0) {
-            tie = tie || ot || ob != best;
-            best = ob > best ? ob : best;
-        }
-    };
     double held_dot = 0.0, held_k2 = 0.0;   // (mu.k, |k|^2) of the lane's row of the two tiles scored last
     int held_row = 0x7fffffff;
     auto flush_scores = [&]() {   // sqrt and divide on full waves: 64 rows of two tiles
@@ -285,7 +301,9 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
             const float sc = finish_score(held_dot, held_k2, nmu2, p.eps);
             p.scores[(size_t)bh * p.cap + held_row] = sc;
             if (p.scores_out) p.scores_out[(size_t)bh * p.n + held_row] = sc;
-            am_merge(am_best, am_tie, ((unsigned long long)orderable(sc) << 32) | (uint32_t)held_row, false);
+            const uint32_t bits = orderable(sc), top = (uint32_t)(am_best >> 32);
+            am_tie = bits > top ? false : am_tie || bits == top;
+            if (bits > top) am_best = ((unsigned long long)bits << 32) | (uint32_t)held_row;
         }
         held_row = 0x7fffffff;
     };
@@ -301,6 +319,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         if (t + NW < t1) load_v(t + NW, vr);
         __builtin_amdgcn_sched_barrier(0);
 
+        KD_TL(3);   // V of the tile in LDS
         // logits: element i of s[kg] is key 32 t + 16 kg + 4 g + i of query column c16
         f32x4 s[2];
 #pragma unroll
@@ -347,6 +366,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         }
         if (t + 2 * NW < t1) load_k(t + 2 * NW, kc);   // kc is free
         __builtin_amdgcn_sched_barrier(0);
+        KD_TL(4);   // tile scored
 
         // weights
         if ((t + 1) * FEW_KEYS > p.len) {   // uniform: rows of the block or past the end
@@ -392,12 +412,15 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         tile(t, false, ka);
         if (t + NW < t1) tile(t + NW, true, kb2);
     }
+    KD_TL(5);   // tiles done
     if (scoring) flush_scores();   // (an odd number of tiles leaves half a wave's rows)
 
     if (writer && tid < D) p.ksum_next[(size_t)bh * D + tid] = ksum_after;
 
     // ---- the eight results become one
+    KD_TL(6);   // scores finished
     __syncthreads();   // every wave is done with its V tile
+    KD_TL(7);   // every wave done
     float *ow = reinterpret_cast<float *>(smem) + (size_t)wave * 16 * D;
     if (c16 < mrows) {
 #pragma unroll
@@ -405,18 +428,24 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         if (g == 0) ml_s[wave][c16] = make_float2(mref, lacc[0]);
     }
     if (scoring && p.argmax_rec) {   // uniform
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t lo = __shfl_xor((uint32_t)am_best, off), hi = __shfl_xor((uint32_t)(am_best >> 32), off);
-            const bool ot = __shfl_xor((int)am_tie, off) != 0;
-            am_merge(am_best, am_tie, ((unsigned long long)hi << 32) | lo, ot);
-        }
+        wave_argmax(am_best, am_tie);
         if (lane == 0) {
             rec_s[wave][0] = am_best;
             rec_s[wave][1] = am_tie ? 1ull : 0ull;
         }
     }
     __syncthreads();
+    KD_TL(8);   // results and arg-max records in LDS
+    if (scoring && p.argmax_rec && wave == NW - 1) {   // (the last wave: with few query rows it has nothing to merge)
+        unsigned long long best = lane < NW ? rec_s[lane & (NW - 1)][0] : 0;
+        bool tie = lane < NW && rec_s[lane & (NW - 1)][1] != 0;
+        wave_argmax(best, tie);
+        if (lane == 0) {
+            unsigned long long *rec = p.argmax_rec + ((size_t)bh * p.splits + sp) * 2;
+            rec[0] = best;
+            rec[1] = tie ? 1ull : 0ull;
+        }
+    }
     for (int it = tid; it < mrows * (D / 4); it += NT) {
         const int m = it / (D / 4), d0 = it % (D / 4) * 4;
         float mx = -INFINITY;
@@ -446,14 +475,13 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
             *reinterpret_cast<bf16x4 *>(p.out + ((size_t)bh * p.G * p.Bt + m0 + m) * D + d0) = o;
         }
     }
-    if (scoring && p.argmax_rec && tid == 0) {
-        unsigned long long best = 0;
-        bool tie = false;
-        for (int w = 0; w < NW; ++w) am_merge(best, tie, rec_s[w][0], rec_s[w][1] != 0);
-        unsigned long long *rec = p.argmax_rec + ((size_t)bh * p.splits + sp) * 2;
-        rec[0] = best;
-        rec[1] = tie ? 1ull : 0ull;
-    }
+    KD_TL(9);   // partial stored
+#ifdef KD_TIMELINE
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    KD_TL(12);
+    if (threadIdx.x == 0) kd_tl[31] = 5;   // record kind: step_few workgroup
+    KD_TL_DUMP(p.timeline, blockIdx.x);
+#endif
 }
 
 hipError_t configure_few_kernels()
