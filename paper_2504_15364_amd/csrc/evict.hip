@@ -601,6 +601,14 @@ __global__ void load_pos_kernel(const int32_t *src, int32_t *dst, int cap, int l
 // ---------------------------------------------------------------------- launchers
 constexpr size_t LISTS_LDS_MAX = 48 * 1024;
 
+// A compute unit shifts the rows of a head at some 100 GB/s; a launch of its own with the rows spread over the chip costs 3 us and
+// its gap.  Measured, us a step with the shift apart / inside the selection (4 / 1 heads of 64, 8 / 2 of 64 and 24 / 8 of 128):
+// 128 rows 16.0 / 14.6, 16.5 / 14.7, 17.4 / 15.4;  288 rows 16.4 / 14.7, 16.7 / 14.9, 18.3 / 16.7;  512 rows 16.5 / 15.3,
+// 17.1 / 15.5, 18.2 / 17.9;  544 rows 17.9 / 16.6, 18.1 / 16.9, 19.6 / 20.1;  1024 rows 17.1 / 17.5, 17.6 / 17.7, 19.2 / 22.8.
+constexpr int SHIFT_HERE_MAX = 48 * 1024;   // elements of a head's K
+bool shift_fits_selection(const StepParams &p) { return (long)p.n * p.D <= SHIFT_HERE_MAX; }
+static_assert(SHIFT_HERE_MAX / 64 <= 3 * 4 * POST_THREADS, "the selection holds the scores of such a cache in registers");
+
 bool lists_fit_lds(int n, int N) { return n > N && (size_t)(n - N) * 4 <= LISTS_LDS_MAX; }
 
 // dynamic LDS a step_post launch may ask for next to its static tables (160 KB per compute unit)

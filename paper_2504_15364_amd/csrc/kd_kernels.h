@@ -31,6 +31,7 @@ constexpr int HIST_BINS = 4096;     // score histogram resolution in step_post (
 // roots, reciprocal and products 1e-6: 2.9e-5 in all, as |score| <= 1.
 constexpr float SCORE_SLACK = 3e-5f;
 constexpr int CHUNK_ROWS = 128;     // rows per workgroup in the from-scratch key-sum pass
+constexpr int LAYOUT_SHIFT_HERE = 2;  // StepParams::layout: ORDERED, and the selection shifts the rows too (short caches, shift_fits_selection)
 constexpr int ORD_ROWS = 128;       // rows per workgroup of the ordered compaction
 constexpr int ORD_THREADS = 1024;   // ... and its threads: 4 16-byte units each
 constexpr int ORD_SPIN_LIMIT = 1 << 20;  // polls of a predecessor's flag before giving up
@@ -161,5 +162,7 @@ hipError_t launch_load_pos(const int32_t *src, int32_t *dst, int BH, int cap, in
                            hipStream_t s);
 
 bool lists_fit_lds(int n, int N);
+// whether the selection of an ORDERED step (a launch of its own) had better shift the rows itself
+bool shift_fits_selection(const StepParams &p);
 
 }  // namespace kd

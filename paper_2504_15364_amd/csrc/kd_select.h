@@ -815,7 +815,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                         if (!gone && i + e < p.n) pos[to] = preg[q][e];
                         to += gone ? 0 : 1;
                     }
-                    *reinterpret_cast<i32x4 *>(dst + i) = d;
+                    if (p.layout != LAYOUT_SHIFT_HERE) *reinterpret_cast<i32x4 *>(dst + i) = d;
                 }
             }
         } else {
@@ -846,6 +846,19 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             }
         }
     }
+    // ORDERED, a short cache: the rows behind the first evicted one are shifted here, pass by pass in ascending order (a row
+    // moves down, so no pass overwrites what a later one has to read); the first pass is requested ahead of the key sum.
+    constexpr int SHIFTU = 8;
+    const bool shift_here = SRC > 0 && p.layout == LAYOUT_SHIFT_HERE;   // uniform
+    u32x4 moved[SHIFTU];
+    auto request_shift = [&](int i0) {
+#pragma unroll
+        for (int q = 0; q < SHIFTU; ++q) {
+            const int i = i0 + q * TROWS + tail_row0();
+            if (i < p.n) moved[q] = *reinterpret_cast<const u32x4 *>(tail_rows() + (size_t)i * D + unit_off);
+        }
+    };
+    if (shift_here) request_shift(evlist[0]);
     KD_TL(8);   // moves issued
     if (keys) {
 #pragma unroll
@@ -864,7 +877,23 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             }
         }
     }
+    if (shift_here) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the rows of the first pass (and the evicted keys) are in registers
     __syncthreads();
+    if (shift_here) {
+        for (int i0 = evlist[0]; i0 < p.n; i0 += SHIFTU * TROWS) {   // uniform
+            if (i0 > evlist[0]) {
+                request_shift(i0);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+            }
+#pragma unroll
+            for (int q = 0; q < SHIFTU; ++q) {
+                const int i = i0 + q * TROWS + tail_row0();
+                if (i < p.n && !evicted(i))
+                    *reinterpret_cast<u32x4 *>(tail_rows() + (size_t)(i - before(i)) * D + unit_off) = moved[q];
+            }
+        }
+    }
     if (tid < D) {
         double s = 0.0;
 #pragma unroll

@@ -433,6 +433,8 @@ int finish_pending(keydiff_cache *c, hipStream_t s)
     if (!c->pending) return KEYDIFF_OK;
     kd::StepParams p = c->pend;
     p.merge_wgs = 0;
+    const bool ordered = c->cfg.layout == KEYDIFF_LAYOUT_ORDERED, shift_here = ordered && kd::shift_fits_selection(p);
+    if (shift_here) p.layout = kd::LAYOUT_SHIFT_HERE;
 #ifdef KD_TIMELINE
     p.timeline = nullptr;   // only launches of step_main are recorded
 #endif
@@ -441,7 +443,7 @@ int finish_pending(keydiff_cache *c, hipStream_t s)
         KD_LAUNCH(kd::launch_step_post(p, s), "step_post kernel (deferred selection)");
     }
     c->pending = false;
-    if (c->cfg.layout == KEYDIFF_LAYOUT_ORDERED) return compact_ordered(c, p, s);
+    if (ordered && !shift_here) return compact_ordered(c, p, s);
     return KEYDIFF_OK;
 }
 
@@ -595,6 +597,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
         }
     }
     const bool deferred = defer && evict;
+    const bool shift_here = evict && !deferred && cf.layout == KEYDIFF_LAYOUT_ORDERED && kd::shift_fits_selection(p);
     // a selection that rode in this step's attention launch wrote its destination map: the rows of an
     // ORDERED carrier's cache are shifted after that launch -- inside this step's merge launch where
     // there is one (the shift is bound by memory traffic, the merge leaves the memory system idle)
@@ -629,9 +632,10 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
         p.timeline = timeline_slot((long)(evict ? p.batch * p.hkv : 0) + p.merge_wgs);   // step_post records into the next slot
 #endif
         ProfScope ps(c, KEYDIFF_K_POST, s);
+        if (shift_here) p.layout = kd::LAYOUT_SHIFT_HERE;
         KD_LAUNCH(kd::launch_step_post(p, s), "step_post kernel");
     }
-    if (evict && !deferred && cf.layout == KEYDIFF_LAYOUT_ORDERED)
+    if (evict && !deferred && cf.layout == KEYDIFF_LAYOUT_ORDERED && !shift_here)
         if (int rc = compact_ordered(c, p, s)) return rc;
     if (shift_owed)   // ... else in a launch of its own
         if (int rc = compact_ordered(carry, carry->pend, s)) return rc;
@@ -781,8 +785,11 @@ int layers_step(keydiff_cache *const *caches, kd::LayerSteps &steps, int layers,
 #ifdef KD_TIMELINE
     for (int l = 0; l < layers; ++l) steps.p[l].timeline = nullptr;
 #endif
+    const bool ordered = plan.do_evict && plan.layout == KEYDIFF_LAYOUT_ORDERED, shift_here = ordered && kd::shift_fits_selection(plan);
+    if (shift_here)
+        for (int l = 0; l < layers; ++l) steps.p[l].layout = kd::LAYOUT_SHIFT_HERE;
     KD_LAUNCH(kd::launch_step_post_layers(steps, layers, s), "step_post kernel (several layers)");
-    if (plan.do_evict && plan.layout == KEYDIFF_LAYOUT_ORDERED) {
+    if (ordered && !shift_here) {
         kd::ShiftSteps shifts;
         for (int l = 0; l < layers; ++l) shifts.s[l] = shift_step(caches[l], steps.p[l]);
         KD_LAUNCH(kd::launch_compact_ordered(shifts, layers, plan.D, s), "ordered compaction kernel (several layers)");

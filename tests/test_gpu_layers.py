@@ -92,3 +92,38 @@ def test_layers_that_touch_one_anothers_memory_keep_their_order(kind):
         _same_state(a[l], b[l], f"layer {l}")
         a[l].close()
         b[l].close()
+
+
+@pytest.mark.parametrize("d,N,B", [(64, 736, 32), (64, 737, 32), (64, 500, 260), (128, 352, 32), (128, 353, 32), (128, 190, 190),
+                                   (64, 40, 1), (128, 60, 7)])
+@pytest.mark.parametrize("call", ["block", "layers", "deferred"])
+def test_short_ordered_caches_are_shifted_by_the_selection(d, N, B, call):
+    # up to 48 K elements of K a head (768 rows of 64, 384 of 128) the selection shifts the rows of an ORDERED cache, in
+    # passes of 512 or 256; beyond, a launch of its own does.  The retained rows are those of the FILL layout, in order.
+    heads, layers = (8, 2, d), 2 if call == "layers" else 1
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, *heads, N, B, layout=lay)) for _ in range(layers)]
+            for lay in (kd.LAYOUT_ORDERED, kd.LAYOUT_FILL))
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    x = [torch.randn((1, 2, N, d), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(1, 2, N).contiguous()
+    for c in a + b:
+        c.load(*x, pos)
+    for blks in zip(*(_blocks(heads, 4 * B + B // 2, B, 500 + l) for l in range(layers))):
+        t = N + blks[0][0]
+        for caches in (a, b):
+            if call == "layers":
+                kd.prefill_block_layers(caches, [y[1] for y in blks], [y[2] for y in blks], [y[3] for y in blks], t)
+            elif call == "deferred":
+                caches[0].prefill_block_deferred(*blks[0][1:], t)
+            else:
+                caches[0].prefill_block(*blks[0][1:], t)
+    for ca, cb in zip(a, b):
+        pa, pb = ca.positions(), cb.positions().sort(-1)
+        assert torch.equal(pa, pb.values)
+        for ra, rb in ((ca.key_rows(), cb.key_rows()), (ca.value_rows(), cb.value_rows())):
+            pick = pb.indices[..., None].expand(-1, -1, -1, d)
+            assert torch.equal(ra[:, :, :N].view(torch.int16), rb[:, :, :N].gather(2, pick).view(torch.int16))
+        assert torch.allclose(ca.scores(), cb.scores().gather(2, pb.indices), rtol=1e-6, atol=1e-7)
+        assert ca.status() == 0 and cb.status() == 0
+        ca.close()
+        cb.close()
