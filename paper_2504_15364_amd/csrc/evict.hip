@@ -200,6 +200,70 @@ __device__ __forceinline__ void merge_rows(const StepParams &p, size_t gid)
     *reinterpret_cast<bf16x4 *>(p.out + (((size_t)bh * p.G + g) * p.Bt + j) * D + d0) = o;
 }
 
+// The same for at most four splits, MERGE_PIECES pieces of four values a thread (gid0, gid0 + stride, ..), all of them requested
+// together: a piece is a few loads then, and what the merge takes is as many bytes in flight from fewer workgroups (merge of 4 splits of
+// 2048 rows a head, 8 heads: 9.4 -> 6.3 us; beside the selections of four layers 12.5 -> 11.9).  With five to eight splits, two pieces a thread
+// were slower (5 splits, three layers: 4.5 -> 5.4 us).
+template <int D>
+__device__ __forceinline__ void merge_rows_few_splits(const StepParams &p, size_t gid0, size_t stride)
+{
+    constexpr int SLABS = D / 8, MB = MERGE_FEW_SPLITS, ITEMS = MERGE_PIECES;
+    const int BH = p.batch * p.hkv, Mtot = p.G * p.Bt, nblk = (Mtot + 31) / 32;
+    const size_t rows = (size_t)BH * Mtot, pstride = (size_t)BH * nblk * SLABS * 64 * 4;
+    float2 ml[ITEMS][MB];
+    f16x4 o[ITEMS][MB];
+    size_t row[ITEMS];
+    int d0[ITEMS];
+    bool there[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const size_t gid = gid0 + it * stride;
+        const int L = (int)(gid % 64), slab = (int)((gid / 64) % SLABS);
+        const size_t blkid = gid / (64 * SLABS);
+        const int bh = (int)(blkid / nblk), m = (int)(blkid % nblk) * 32 + (L & 31);
+        there[it] = blkid < (size_t)BH * nblk && m < Mtot;
+        row[it] = (size_t)bh * Mtot + m;
+        d0[it] = 8 * slab + 4 * (L >> 5);
+        const _Float16 *pbase = p.part_o + gid * 4;   // ((block, slab, lane) in this order is what gid counts)
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            const bool live = there[it] && i < p.splits;
+            const f16x4 zero = {(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
+            ml[it][i] = live ? p.part_ml[(size_t)i * rows + row[it]] : make_float2(-INFINITY, 0.f);
+            o[it][i] = live ? *reinterpret_cast<const f16x4 *>(pbase + (size_t)i * pstride) : zero;
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        if (!there[it]) continue;
+        float mx = ml[it][0].x;
+#pragma unroll
+        for (int i = 1; i < MB; ++i) mx = fmaxf(mx, ml[it][i].x);
+        float acc[4] = {0.f, 0.f, 0.f, 0.f}, Lsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+            const float w = ml[it][i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[it][i].x - mx) * ml[it][i].y;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] += w * (float)o[it][i][r];
+            Lsum += w;
+        }
+        const float inv = 1.f / Lsum;
+        bf16x4 out;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[r] = (__bf16)(acc[r] * inv);
+        *reinterpret_cast<bf16x4 *>(p.out + row[it] * D + d0[it]) = out;
+    }
+}
+
+// `thread` of `threads` that merge, each merge_pieces pieces
+template <int D>
+__device__ __forceinline__ void merge_thread(const StepParams &p, size_t thread, size_t threads)
+{
+    if (p.splits <= MERGE_FEW_SPLITS) merge_rows_few_splits<D>(p, thread, threads);   // uniform
+    else if (p.splits <= 8) merge_rows<D, 8>(p, thread);
+    else merge_rows<D>(p, thread);
+}
+
 // The merge of step_few's partials (float, [psplits][BH][G * Bt][D], each normalised by its row sum): one
 // workgroup per head, a thread per four output values and share of the splits.  What bounds it is the
 // trip to memory: the splits are dealt over the threads that are left (with 4 rows of 128 eight ways), so
@@ -280,26 +344,26 @@ __device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int b
 // here): small workgroups, so that the rows spread over every compute unit.
 // Workgroup i takes head i % BH, like the workgroups of step_main: on a chip whose workgroups go
 // round-robin over the XCDs the partials of a head are then read on the XCD that wrote them.
-template <int D, int MB = 16>
+template <int D>
 __device__ __forceinline__ void merge_body(const StepParams &p)
 {
     const int BH = p.batch * p.hkv;
-    const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (D / 8) * 64;
+    const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (D / 8) * 64, threads = per_head / merge_pieces(p.splits);
     const int bh = blockIdx.x % BH;
     const size_t local = (size_t)(blockIdx.x / BH) * MERGE_THREADS + threadIdx.x;
-    if (local < per_head) merge_rows<D, MB>(p, (size_t)bh * per_head + local);
+    if (local < threads) merge_thread<D>(p, (size_t)bh * per_head + local, threads);
 }
 template <int D>
 __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(StepParams p)
 {
     merge_body<D>(p);
 }
-// ... of several layers, blockIdx.y each (few splits: the layers fill the chip)
+// ... of several layers, blockIdx.y each
 template <int D>
 __global__ __launch_bounds__(MERGE_THREADS) void merge_layers_kernel(LayerSteps steps)
 {
     warm_arguments<sizeof(StepParams)>(blockIdx.y * (uint32_t)sizeof(StepParams));
-    merge_body<D, 8>(steps.p[blockIdx.y]);
+    merge_body<D>(steps.p[blockIdx.y]);
 }
 
 // step_score: every workgroup scores SCORE_ROWS rows of one head.  The launch boundary after it
@@ -332,7 +396,7 @@ __device__ __forceinline__ void post_body(const StepParams &p, int block)
 #endif
         static_assert(sizeof(PostShared) >= POST_THREADS * 6 * sizeof(float), "the merge of step_few's partials uses the selection's tables");
         if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), block - n_select);
-        else merge_rows<D>(p, (size_t)(block - n_select) * POST_THREADS + threadIdx.x);
+        else merge_thread<D>(p, (size_t)(block - n_select) * POST_THREADS + threadIdx.x, (size_t)p.merge_wgs * POST_THREADS);
 #ifdef KD_TIMELINE
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
@@ -670,7 +734,7 @@ hipError_t launch_step_post(const StepParams &p, hipStream_t s)
         return hipGetLastError();
     }
     if (!p.do_evict) {   // merge only
-        const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (p.D / 8) * 64;
+        const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (p.D / 8) * 64 / merge_pieces(p.splits);
         const int mgrid = p.batch * p.hkv * (int)((per_head + MERGE_THREADS - 1) / MERGE_THREADS);
         if (p.D == 128) hipLaunchKernelGGL((merge_kernel<128>), dim3(mgrid), dim3(MERGE_THREADS), 0, s, p);
         else if (p.D == 64) hipLaunchKernelGGL((merge_kernel<64>), dim3(mgrid), dim3(MERGE_THREADS), 0, s, p);
@@ -702,7 +766,7 @@ hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStrea
     const int per_layer = (p.do_evict ? p.batch * p.hkv : 0) + p.merge_wgs;
     if (per_layer == 0) return hipSuccess;
     if (!p.do_evict) {
-        const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (p.D / 8) * 64;
+        const size_t per_head = (size_t)((p.G * p.Bt + 31) / 32) * (p.D / 8) * 64 / merge_pieces(p.splits);
         const dim3 grid((unsigned)(p.batch * p.hkv * ((per_head + MERGE_THREADS - 1) / MERGE_THREADS)), (unsigned)layers);
         if (p.D == 128) hipLaunchKernelGGL((merge_layers_kernel<128>), grid, dim3(MERGE_THREADS), 0, s, steps);
         else if (p.D == 64) hipLaunchKernelGGL((merge_layers_kernel<64>), grid, dim3(MERGE_THREADS), 0, s, steps);

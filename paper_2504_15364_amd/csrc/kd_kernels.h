@@ -108,6 +108,10 @@ struct ShiftSteps {
     ShiftStep s[GROUP_LAYERS];
 };
 
+// Pieces (of four output values) a thread of the merge takes: with few splits several
+constexpr int MERGE_FEW_SPLITS = 4, MERGE_PIECES = 4;
+__host__ __device__ constexpr int merge_pieces(int splits) { return splits <= MERGE_FEW_SPLITS ? MERGE_PIECES : 1; }
+
 hipError_t configure_kernels();      // one-time function attributes (dynamic LDS sizes)
 hipError_t launch_step_main(const StepParams &p, hipStream_t s);
 // ... of `layers` layers in one launch (2 .. GROUP_LAYERS of them, none with step_few)

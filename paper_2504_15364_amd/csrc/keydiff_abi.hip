@@ -344,7 +344,7 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
     const int Mpad = (Mtot + 31) / 32 * 32;   // partials are stored in blocks of 32 rows
     while (splits > 1 && (long)splits * BH * Mpad > c->L.max_part_rows) --splits;
     set_ranges(p, splits);
-    const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64;
+    const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64 / kd::merge_pieces(p.splits);
     p.merge_wgs = p.splits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
 }
 
@@ -676,7 +676,7 @@ double plan_layers(const keydiff_cache *c, kd::StepParams &p, int layers)
         }
     }
     set_ranges(p, splits);
-    const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64;
+    const size_t merge_threads = (size_t)BH * (Mpad / 32) * (p.D / 8) * 64 / kd::merge_pieces(p.splits);
     p.merge_wgs = p.splits > 1 ? (int)((merge_threads + kd::POST_THREADS - 1) / kd::POST_THREADS) : 0;
     return best;
 }
