@@ -232,8 +232,8 @@ def main():
                     help="cache budget N (a multiple of the block size); 0 = the workload's (the paper's budgets: 2K-8K)")
     ap.add_argument("--layout", choices=["fill", "ordered"], default="fill")
     ap.add_argument("--eviction", choices=["deferred", "immediate"], default="deferred",
-                    help="deferred: the selection and compaction of layer l runs inside the attention launch "
-                         "of layer l + 1 (keydiff_prefill_block_deferred); immediate: inside layer l's own step")
+                    help="deferred: every block through all layers in one call (keydiff_prefill_block_layers: the layers "
+                         "share their launches); immediate: layer by layer (keydiff_prefill_block)")
     ap.add_argument("--profile-steps", type=int, default=8, help="extra steps timed per kernel with HIP events")
     ap.add_argument("--seed", type=int, default=20250415)
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -263,10 +263,10 @@ def main():
     L = args.layers or w.n_layers
     B, N, D, Hq, Hkv = w.block_B, w.budget_N, w.head_dim, w.n_q_heads, w.n_kv_heads
     fill_blocks = N // B
-    n_steps = args.warmup + args.steps + args.profile_steps
+    n_steps = args.warmup + args.steps + 2 * args.profile_steps
     T_need = (fill_blocks + max(n_steps, 0 if args.no_extras else 7 + args.mode_steps)) * B
     if T_need > w.prompt_T:
-        sys.exit(f"--warmup + --steps + --profile-steps = {n_steps} exceeds the {w.prompt_T // B - fill_blocks} "
+        sys.exit(f"--warmup + --steps + 2 x --profile-steps = {n_steps} exceeds the {w.prompt_T // B - fill_blocks} "
                  f"evicting steps of a {w.prompt_T}-token prompt")
 
     # ---- seeded host data, one fresh seed per layer (threads: numpy releases the GIL)
@@ -293,15 +293,25 @@ def main():
     deferred = args.eviction == "deferred" and L > 1
 
     def run_block(i):
-        if deferred:   # one call: layer l takes along the eviction layer l - 1 left pending (layer 0: the last layer's)
+        if deferred:   # one call for all layers
             kd.prefill_block_layers(caches, [t[i] for t in dq], [t[i] for t in dk], [t[i] for t in dv], i * B, out=outs)
             return
         for l in range(L):
             caches[l].prefill_block(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l])
 
-    def finish_all():   # the one eviction still pending belongs to the timed work
+    def run_block_by_layer(i):
+        # What the call does with handles that are being profiled, whose kernels have to be their own: layer l takes along the
+        # eviction layer l - 1 left pending (layer 0: the last layer's)
+        for l in range(L):
+            if deferred:
+                caches[l].prefill_block_deferred(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l], carry=caches[l - 1])
+            else:
+                caches[l].prefill_block(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l])
+
+    def finish_all():   # what may still be pending belongs to the timed work
         if deferred:
-            caches[L - 1].finish()
+            for c in caches:
+                c.finish()
 
     def load_first_N(cache, l):
         # while n <= N nothing is evicted, so after the first N tokens the cache IS those tokens in
@@ -341,13 +351,21 @@ def main():
     us_per_layer_step = elapsed / (args.steps * L) * 1e6
     tokens_per_s_per_layer = B / (elapsed / (args.steps * L))
 
-    # ---- per-kernel durations, HIP events recorded by the library on its launch stream
+    # ---- per-kernel durations, HIP events recorded by the library on its launch stream, layer by layer (first without events:
+    # what the brackets are compared with)
     kernels = {}
     if args.profile_steps > 0:
+        t_start = time.perf_counter()
+        for _ in range(args.profile_steps):
+            run_block_by_layer(i)
+            i += 1
+        finish_all()
+        torch.cuda.synchronize()
+        us_by_layer = (time.perf_counter() - t_start) / (args.profile_steps * L) * 1e6
         for c in caches:
             c.profile_enable(True)
         for _ in range(args.profile_steps):
-            run_block(i)
+            run_block_by_layer(i)
             i += 1
         finish_all()
         torch.cuda.synchronize()
@@ -371,7 +389,7 @@ def main():
         layer_steps = args.profile_steps * L
         bracket_sum_us = sum(v[0] for v in tot.values()) * 1e3 / layer_steps    # per layer-step
         launches_per_layer_step = sum(v[1] for v in tot.values()) / layer_steps
-        overhead_us = min(pair_us, max(0.0, (bracket_sum_us - us_per_layer_step) / launches_per_layer_step))
+        overhead_us = min(pair_us, max(0.0, (bracket_sum_us - us_by_layer) / launches_per_layer_step))
         kernels = {k: {"avg_us": v[0] / v[1] * 1e3 - overhead_us, "launches": v[1],
                        "event_bracket_us": v[0] / v[1] * 1e3, "event_overhead_us": overhead_us,
                        "empty_event_pair_us": pair_us}
@@ -397,7 +415,8 @@ def main():
                         cs[l].prefill_block(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l])
             for i in range(fill_blocks, fill_blocks + 3):
                 blk(i)
-            cs[L - 1].finish()
+            for c in cs:
+                c.finish()
             torch.cuda.synchronize()
             t0_ = time.perf_counter()
             for i in range(fill_blocks + 3, fill_blocks + 3 + args.mode_steps):
@@ -463,8 +482,10 @@ def main():
     if "step_main" in kernels:
         t_attn = kernels["step_main"]["avg_us"] * 1e-6
         achieved = flops_attn / t_attn / 1e12
-        # with deferred eviction nearly every launch of the class is the carrying variant of the kernel
+        # (layer by layer; with deferred eviction nearly every launch of the class is the carrying variant of the kernel)
         roofline = {"bound": "mfma", "kernel": "step_main_carry_kernel" if deferred else "step_main_kernel",
+                    "launches": "one layer each (profiled handles); the timed steps share launches between layers, see step_roofline"
+                                if deferred else "one layer each",
                     "achieved": achieved,
                     "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_MFMA_TFLOPS,
                     "traffic": measured_traffic(w.name, args.layout), "flops_per_launch": flops_attn,
@@ -576,7 +597,8 @@ def main():
         "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": w.name, "n_q_heads": Hq, "n_kv_heads": Hkv, "head_dim": D, "budget_N": N,
                    "block_B": B, "layers": L, "layout": args.layout,
-                   "eviction": "deferred" if deferred else "immediate", "tokens_per_step": B,
+                   "eviction": "deferred" if deferred else "immediate", "call": "prefill_block_layers" if deferred else "prefill_block",
+                   "tokens_per_step": B,
                    "step": "one steady-state block step through every layer"},
         "us_per_layer_step": us_per_layer_step,
         "step_roofline": {"binding": "mfma" if flops_attn / 2.5e15 > bytes_step / 8e12 else "hbm",

@@ -2,7 +2,7 @@
 
 Needs the profiling build of the library (`python -m paper_2504_15364_amd.build --timeline`), which
 stamps the 100 MHz wall clock at named points of every workgroup; this script runs steady-state block
-steps of a workload through several layers with the eviction deferred (the launch bench.py times),
+steps of a workload through several layers (by default with every eviction carried by the next layer's launch),
 collects the stamps of every launch and prints, per phase, when it ends (microseconds after the
 launch's first workgroup started; mean / min / max over workgroups and launches).
 
@@ -52,9 +52,9 @@ SEL_PHASES = [
     (4, "threshold bin known"),
     (5, "candidates collected"),
     (6, "ranking done"),
-    (7, "lists written"),
-    (8, "evicted rows read, key sum stored"),
-    (9, "moves issued"),
+    (7, "evicted rows listed"),
+    (8, "moves issued"),
+    (9, "key sum stored"),
     (12, "stores acknowledged (workgroup ends)"),
 ]
 TICK_US = 0.01   # wall_clock64 counts a constant 100 MHz clock
@@ -67,8 +67,9 @@ def main():
     ap.add_argument("--steps", type=int, default=6)
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--seed", type=int, default=20250415)
-    ap.add_argument("--eviction", choices=["deferred", "immediate"], default="deferred",
-                    help="immediate: keydiff_prefill_block per layer; the selection then runs in step_post, after the attention")
+    ap.add_argument("--eviction", choices=["deferred", "immediate", "layers"], default="deferred",
+                    help="immediate: keydiff_prefill_block per layer; the selection then runs in step_post, after the attention; "
+                         "layers: keydiff_prefill_block_layers, the attention of several layers in one launch (recorded up to 512 workgroups)")
     args = ap.parse_args()
 
     import torch
@@ -111,6 +112,9 @@ def main():
 
     def run_block(i):
         if args.eviction == "deferred":
+            for l in range(L):
+                caches[l].prefill_block_deferred(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l], carry=caches[l - 1] if L > 1 else None)
+        elif args.eviction == "layers":
             kd.prefill_block_layers(caches, [t[i] for t in dq], [t[i] for t in dk], [t[i] for t in dv], i * B, out=outs)
         else:
             for l in range(L):
@@ -119,7 +123,7 @@ def main():
     for i in range(fill, fill + args.warmup):
         run_block(i)
     torch.cuda.synchronize()
-    slots = L * args.steps * (1 if args.eviction == "deferred" else 2)   # immediate: step_main, then step_post
+    slots = L * args.steps * (2 if args.eviction == "immediate" else 1)   # immediate: step_main, then step_post
     WGS = 512
     buf = torch.zeros(slots * WGS * 32, dtype=torch.int64, device="cuda")
     got = lib.keydiff_timeline_buffer(buf.data_ptr(), buf.numel() * 8)
@@ -168,7 +172,7 @@ def main():
                 prev = m
 
     print(f"# workload {w.name}: {L} layers, {args.steps} recorded block steps, eviction {args.eviction} "
-          f"({'step_main_carry_kernel' if args.eviction == 'deferred' else 'step_main_kernel, then step_post_kernel'})")
+          f"({dict(deferred='step_main_carry_kernel', immediate='step_main_kernel, then step_post_kernel', layers='step_main_layers_kernel')[args.eviction]})")
     print("# stamps: thread 0 of every workgroup, constant 100 MHz clock (0.01 us resolution)")
     summarise(1, ATTN_PHASES, "attention workgroups")
     summarise(2, SEL_PHASES, "carried selection workgroups" if args.eviction == "deferred"
@@ -192,7 +196,7 @@ def main():
             end = (r[i, 12] - t_launch) * TICK_US
             by_split.setdefault(wg // (BH * mtiles), []).append((end, r[i, 30], (r[i, 0] - t_launch) * TICK_US))
             by_head.setdefault(wg % BH, []).append(end)
-    if by_split:
+    if by_split and args.eviction != "layers":   # (several layers in a launch)
         print("\nattention workgroups by key split: tiles, start, end (us, mean over launches, heads and row tiles)")
         for sp in sorted(by_split):
             v = np.array(by_split[sp])
