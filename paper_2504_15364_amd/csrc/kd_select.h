@@ -219,7 +219,7 @@ template <int D, int SRC, int THREADS, bool APPROX>
 __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh)
 {
     constexpr int UPR = D / 8;
-    constexpr int TAILU = THREADS > 512 || D == 64 || SRC <= 0 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (128 rows a batch with 1024 threads, 256 of 64)
+    constexpr int TAILU = THREADS > 512 || D == 64 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (128 rows a batch, 256 of 64 with 1024 threads)
     // The rows [N, n), the only ones that can move (FILL layout), are requested with the scores; scoring rows exactly takes
     // the registers they would wait in, and they are then requested with the evicted keys.
     constexpr bool EARLY_TAIL = !APPROX;
@@ -609,6 +609,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             if (lane == 0) *reinterpret_cast<uint64_t *>(evbits + (i >> 5)) = m;
             nabove += (uint32_t)__popcll(m);
         };
+#pragma unroll 2
         for (int i0 = 64 * wave; i0 < p.n; i0 += THREADS) {   // uniform per wave
             const int i = i0 + lane;
             bool above_bin = false;
