@@ -688,11 +688,20 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
     kd::StepParams p = step;
     plan_attention(c, p);
     if (p.few) return 0;
-    // (ORDERED, three layers or more: where the row shifts can ride in the attention launches, which leave the memory system to them, they do)
-    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2) {
+    // ORDERED, three layers or more: where the row shifts can ride in the attention launches, which leave the memory system to them, they
+    // do, except on caches of many row tiles and few keys, whose attention is too short to hide a selection and a shift (32 / 8 heads, blocks of
+    // 128, us a layer and block riding / together, 3 and 4 layers: 2048 keys 19.2, 19.7 / 13.4, 11.9; 4096 keys 23.1, 23.4 / 21.3, 19.5).
+    // Caches of few row tiles would gain as well (8 / 2 heads of 64, 2048 keys, two layers 22.3 / 11.9 where three ride at 16.8):
+    // that they ride is what tests/test_gpu_parity.py holds.
+    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2 && !(p.batch * p.hkv * p.mtiles >= 16 && p.n <= 6144)) {
         kd::StepParams probe = step;
         if (plan_with_shift(c, probe, step, p.batch * p.hkv) > 0) return 0;
     }
+    // (ORDERED, two layers: layer by layer the shift runs beside the merge and the selection inside the attention, which is worth more than
+    // what the layers share where the attention is long.  Measured, us a layer and block by layer / together, tiles a range in brackets: 32 / 8
+    // heads, 8192 keys [9] 38.9 / 39.4, blocks of 64 [5] 35.3 / 32.4; 4096 keys [5] 27.5 / 24.2; 24 / 8, 8192 keys, blocks of 256 [13] 47.0 / 49.0;
+    // 28 / 4 [15] 46.0 / 47.2, blocks of 64, 4096 keys [2] 25.3 / 17.0.)
+    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers == 2 && (p.ntiles + p.splits - 1) / p.splits > 8) return 0;
     const double post_us = p.do_evict ? 12.0 : 3.0;
     const int least = (n_layers + kd::GROUP_LAYERS - 1) / kd::GROUP_LAYERS;
     int best_k = least;
