@@ -183,8 +183,8 @@ KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const voi
  * pending): every layer's selection and compaction runs inside the next layer's attention
  * launch, and the last layer's stays pending until the next block (or keydiff_finish, or any
  * other call on that cache).  With n_layers == 1 the call is keydiff_prefill_block.
- * ORDERED layout with three layers or more goes the second way (but for caches of at most 6144 rows and 16 row tiles or more, and with
- * two layers where the ranges of keys are longer than eight tiles) wherever
+ * In the ORDERED layout two layers go the second way where one alone would have key ranges of more than eight tiles; three
+ * or more, except on caches of at most 6144 rows with 16 row tiles or more, wherever
  * the stable row shift of layer l, whose selection rode in the launch of layer l + 1, can ride in the
  * attention launch of layer l + 2 (a block that evicts at most 128 rows,
  * 256-row query tiles that are full, the same head_dim), so that after the call the shifts of the last
