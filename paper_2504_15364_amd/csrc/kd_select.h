@@ -247,6 +247,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     // the LDS copies as LDS pointers, so that the loops use ds_read
     typedef __attribute__((address_space(3))) const float lds_cf32;
     typedef __attribute__((address_space(3))) const int32_t lds_ci32;
+    typedef __attribute__((address_space(3))) const i32x4 lds_ci32x4;
     lds_cf32 *sc_s = (lds_cf32 *)sc_l;
     lds_ci32 *pos_s = (lds_ci32 *)pos_l;
     f32x4 sreg[NQ4];
@@ -725,6 +726,9 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     static_assert(TURNS >= 1 && TURNS * KWAVES == KEY_PARTS && TAILU % TURNS == 0, "a round's part follows from its place in a batch");
     static_assert(TROWS == RPW * KWAVES, "a wave of the first half takes RPW rows a round");
     const bool keys = wave < KWAVES;   // uniform per wave: takes K rows (the others V rows)
+    constexpr int KEY_ROWS = KEY_PARTS * RPW;   // ORDERED: rows a round
+    const bool part_waves = wave < KEY_PARTS;   // uniform per wave
+    static_assert(NWAVES >= KEY_PARTS, "a wave for every part");
     double acc[TURNS][8];
 #pragma unroll
     for (int t = 0; t < TURNS; ++t)
@@ -790,44 +794,49 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         // K/V rows by compact_ordered_kernel.  A position lands at or below the row it came from: from registers or
         // the LDS copy nothing can be overwritten before it is read; reading from memory, the rows are taken in
         // ascending chunks, each read, then (barrier) written.
+        // Nothing moves here, so KEY_PARTS waves take keys, one part each (a passenger: all of its waves).  The keys are added ahead
+        // of the positions: behind their stores, the wait for the keys would be one for the stores too.
         u32x4 old[TAILU];
-        auto request_keys = [&](int r0) {
+        for (int r0 = 0; r0 < E && part_waves; r0 += TAILU * KEY_ROWS) {   // uniform per wave
 #pragma unroll
             for (int q = 0; q < TAILU; ++q) {
-                const int r = r0 + q * TROWS + tail_row0();
+                const int r = r0 + q * KEY_ROWS + tid / UPR;
                 old[q] = u32x4{0u, 0u, 0u, 0u};
                 if (r < E) old[q] = *reinterpret_cast<const u32x4 *>(kb + (size_t)evlist[r] * D + unit_off);
             }
-        };
-        if (keys) request_keys(0);
+#pragma unroll
+            for (int q = 0; q < TAILU; ++q)
+                if (r0 + q * KEY_ROWS < E) add_key(old[q], acc[0]);
+        }
         int32_t *dst = p.dstmap + (size_t)bh * p.cap;
+        // four rows, which share a bitmap word (the buffers hold a multiple of four rows)
+        auto place_rows = [&](int i, const i32x4 &at) {
+            const uint32_t word = evbits[i >> 5], bit = (uint32_t)i & 31u;
+            int to = i - (int)(word_base[i >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u)));
+            i32x4 d;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool gone = ((word >> (bit + e)) & 1u) != 0;
+                d[e] = gone ? -1 : to;
+                if (!gone && i + e < p.n) pos[to] = at[e];
+                to += gone ? 0 : 1;
+            }
+            if (p.layout != LAYOUT_SHIFT_HERE) *reinterpret_cast<i32x4 *>(dst + i) = d;
+        };
         if constexpr (PREG) {
 #pragma unroll
             for (int q = 0; q < NQ4; ++q) {
                 const int i = 4 * (q * THREADS + tid);
-                if (i < p.n) {   // (the four rows share a bitmap word; the buffers hold a multiple of four rows)
-                    const uint32_t word = evbits[i >> 5], bit = (uint32_t)i & 31u;
-                    int to = i - (int)(word_base[i >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u)));
-                    i32x4 d;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const bool gone = ((word >> (bit + e)) & 1u) != 0;
-                        d[e] = gone ? -1 : to;
-                        if (!gone && i + e < p.n) pos[to] = preg[q][e];
-                        to += gone ? 0 : 1;
-                    }
-                    if (p.layout != LAYOUT_SHIFT_HERE) *reinterpret_cast<i32x4 *>(dst + i) = d;
-                }
+                if (i < p.n) place_rows(i, preg[q]);
             }
+        } else if constexpr (RES) {
+            for (int i = 4 * tid; i < p.n; i += 4 * THREADS) place_rows(i, (i32x4)*(lds_ci32x4 *)(pos_s + i));
         } else {
             for (int i0 = 0; i0 < p.n; i0 += THREADS) {   // uniform
                 const int i = i0 + tid;
                 int32_t pi = 0;
-                if (i < p.n) {
-                    if constexpr (RES) pi = pos_s[i];
-                    else pi = pos[i];
-                }
-                if (!RES) __syncthreads();
+                if (i < p.n) pi = pos[i];
+                __syncthreads();
                 if (i < p.n) {
                     if (evicted(i)) dst[i] = -1;
                     else {
@@ -836,14 +845,6 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                         pos[to] = pi;
                     }
                 }
-            }
-        }
-        if (keys) {
-            for (int r0 = 0; r0 < E; r0 += TAILU * TROWS) {   // uniform
-                if (r0 > 0) request_keys(r0);
-#pragma unroll
-                for (int q = 0; q < TAILU; ++q)
-                    if (r0 + q * TROWS < E) add_key(old[q], acc[q % TURNS]);
             }
         }
     }
@@ -861,9 +862,10 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     };
     if (shift_here) request_shift(evlist[0]);
     KD_TL(8);   // moves issued
-    if (keys) {
+    if (p.layout == 1 ? keys : part_waves) {
 #pragma unroll
         for (int t = 0; t < TURNS; ++t) {
+            if (t > 0 && p.layout != 1) break;   // uniform
 #pragma unroll
             for (int i = 0; i < 8; ++i) {   // the rows of the wave (lanes with the same unit)
                 if constexpr (UPR == 16) acc[t][i] = sum_over_rows_f64(acc[t][i]);

@@ -127,3 +127,33 @@ def test_short_ordered_caches_are_shifted_by_the_selection(d, N, B, call):
         assert ca.status() == 0 and cb.status() == 0
         ca.close()
         cb.close()
+
+
+@pytest.mark.parametrize("anchor", [kd.ANCHOR_MEAN_KEY, kd.ANCHOR_MEAN_UNIT_KEY], ids=["mean", "unit"])
+@pytest.mark.parametrize("d,N,E", [(128, 2900, 100), (128, 2816, 256), (128, 1500, 300), (64, 2900, 100), (64, 2560, 512), (64, 700, 520)])
+def test_ordered_eviction_carried_leaves_what_one_inside_the_step_leaves(d, N, E, anchor):
+    # The keys an ORDERED eviction takes out of the key sum are read by all waves of a passenger and by half of those of
+    # step_post, in batches of 256 rows (or 128, 256 of 64): positions, rows and scores are the same bits either way.  The evicted keys
+    # have exponents up to 40 apart, so that every score shows the order in which they were summed.
+    hq, hkv, T = 8, 2, N + E
+    rng = np.random.default_rng(N + E + d)
+    keys = 1.0 + 0.3 * rng.standard_normal((1, hkv, T, d))
+    far = np.stack([rng.permutation(T)[:E] for _ in range(hkv)])
+    for h in range(hkv):
+        keys[0, h, far[h]] = np.exp2(rng.integers(-20, 21, size=(E, 1))) * (1.0 + 0.05 * rng.standard_normal((E, d)))
+    keys = torch.from_numpy(keys.astype(np.float32)).cuda().bfloat16()
+    values = torch.randn(keys.shape, generator=torch.Generator(device="cuda").manual_seed(E), device="cuda").bfloat16()
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(1, hkv, N).contiguous()
+    q = torch.zeros((1, hq, E, d), dtype=torch.bfloat16, device="cuda")
+    block = (q, keys[:, :, N:].contiguous(), values[:, :, N:].contiguous())
+    a, b, other = (kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, E, layout=kd.LAYOUT_ORDERED, anchor_mode=anchor)) for _ in range(3))
+    for c in (a, b):
+        c.load(keys[:, :, :N].contiguous(), values[:, :, :N].contiguous(), pos)
+    a.prefill_block(*block, N)
+    b.prefill_block_deferred(*block, N, carry=other)
+    other.prefill_block_deferred(*block, 0, carry=b)
+    assert other.plan()[3] & 1
+    _same_state(a, b, "carried")
+    assert torch.all(a.positions().diff(dim=-1) > 0)
+    for c in (a, b, other):
+        c.close()
