@@ -1163,10 +1163,12 @@ __global__ __launch_bounds__(64 * MAIN_WAVES) void step_main_layers_kernel(Layer
 // kinds of workgroup is needed.
 // cy_res: the passengers work on LDS copies of their head's scores and positions (the launch then
 // asks for the dynamic LDS that takes)
-// (EXACT: neither the step's own scores nor the carried ones are approximate)
-template <int D, bool HELP, bool EXACT>
+// (EXACT: neither the step's own scores nor the carried ones are approximate.  RES: cy_res, where it is known beforehand: with helper
+// waves and approximate scores the registers do not hold what both kinds of selection keep of the parameters, and a kernel each spills nothing)
+template <int D, bool HELP, bool EXACT, int RES = -1>
 __global__ __launch_bounds__(CARRY_THREADS) void step_main_carry_kernel(StepParams, StepParams, int ncarry, int cy_res)
 {
+    if constexpr (RES >= 0) cy_res = RES;
     const StepParams &p = argument_at<StepParams>(0), &cy = argument_at<StepParams>(sizeof(StepParams));
     warm_arguments<2 * sizeof(StepParams) + 8>();   // both parameter blocks: the role is not known yet
     if ((int)blockIdx.x < ncarry) {
@@ -1246,6 +1248,8 @@ hipError_t configure_main_kernels()
 #define KD_SETS(DD)                                     \
     KD_SET((step_main_carry_kernel<DD, false, false>)) \
     KD_SET((step_main_carry_kernel<DD, false, true>))  \
+    KD_SET((step_main_carry_kernel<DD, true, false, 0>)) \
+    KD_SET((step_main_carry_kernel<DD, true, false, 1>)) \
     KD_SET((step_main_carry_kernel<DD, true, true>))   \
     KD_SET((step_main_ride_kernel<DD, false>))         \
     KD_SET((step_main_ride_kernel<DD, true>))
@@ -1309,8 +1313,7 @@ bool can_carry(const StepParams &p, const StepParams &cy)
 {
     const int ncarry = cy.batch * cy.hkv;
     // (a step of few query rows takes no passenger whichever kernel runs it: it is shorter than a selection)
-    // (approximate scores ride, and are formed, only where every wave carries query rows: the kernel with helper waves has no registers left)
-    return p.G * p.Bt > FEW_ROWS && !(cy.score_approx && (scores_exactly(p) || main_runs_help(p))) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
+    return p.G * p.Bt > FEW_ROWS && !(cy.score_approx && scores_exactly(p)) && p.D == cy.D && cy.do_evict && ncarry > 0 &&
            ride_of(cy) != Ride::none;
 }
 
@@ -1328,7 +1331,9 @@ hipError_t launch_step_main_carry(const StepParams &p, const StepParams &cy, hip
     const size_t lds = need > main_lds_bytes(p.D) ? need : main_lds_bytes(p.D);
     const bool help = main_runs_help(p), exact = scores_exactly(p);
 #define KD_GO(DD)                                                                                                                             \
-    if (help) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    if (help && exact) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    else if (help && res) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, false, 1>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
+    else if (help) hipLaunchKernelGGL((step_main_carry_kernel<DD, true, false, 0>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
     else if (exact) hipLaunchKernelGGL((step_main_carry_kernel<DD, false, true>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res); \
     else hipLaunchKernelGGL((step_main_carry_kernel<DD, false, false>), dim3(grid), dim3(CARRY_THREADS), lds, s, p, cyl, ncarry, res);
     if (p.D == 128) { KD_GO(128) }

@@ -357,15 +357,22 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
 //   FILL, 32 / 8 heads:   8192 keys, blocks of 128 [9] 31.0 / 30.1, of 256 [19] 48.9 / 47.5, of 64 [5, one row tile] 25.5 / 26.7;
 //                         4096 keys, blocks of 128 [5] 23.1 / 23.3, of 256 [10] 33.4 / 32.0;  2048 keys, blocks of 256 [6] 25.4 / 24.9
 //   FILL, 28 / 4 heads:   8192 keys, blocks of 64 [5] 24.5 / 25.8;  4096 keys, blocks of 256 [8] 29.7 / 29.4
-//   ORDERED, 24 / 8:      4096 keys, blocks of 128 [5] 28.7 / 27.7;  32 / 8: 2048 keys, blocks of 128 [3] 20.5 / 19.7,
-//                         12288 keys, blocks of 128 (positions from memory) 45.9 / 49.5
+//   ORDERED, 32 / 8:      2048 keys, blocks of 128 [3] 20.5 / 19.7, 12288 keys, blocks of 128 (positions from memory) 45.9 / 49.5
+// Where waves without query rows score (the others then wait for nothing they would do themselves) exact scores cost the attention less, and
+// approximate ones pay from 450 rows a tile down.  Measured on keys that are not rotated, whose scores lie close together, blocks of 128,
+// rows a tile in brackets:
+//   FILL, 24 / 8:         8192 keys [924] 32.2 / 41.0;  two sequences, 4096 keys [422] 32.2 / 30.9, 8192 [438] 49.7 / 47.7;
+//                         four, 2048 [181] 36.5 / 33.6;  eight, 2048 [64] 69.5 / 61.9;  28 / 4, blocks of 200, 4096 keys [614] 28.7 / 34.6
+//   ORDERED, 24 / 8:      2048 keys [725] 21.0 / 23.9, 4096 [845] 29.1 / 34.3;  two sequences, 2048 keys [435] 30.0 / 28.3;
+//                         four, 4096 keys [192] 75.0 / 70.8
 bool approximate_scores_pay(const keydiff_cache *c, const kd::StepParams &p)
 {
     const int BH = p.batch * p.hkv, mtiles = (p.G * p.Bt + 255) / 256, target = c->L.target_wgs / 2;
     const kd::Ride ride = kd::ride_of(p);
-    if (mtiles < 2 || mtiles * 256 - p.G * p.Bt >= 32 || ride == kd::Ride::none || BH + BH * mtiles > target) return false;
+    if (mtiles < 2 || ride == kd::Ride::none || BH + BH * mtiles > target) return false;
     const int ntiles = (p.n + kd::TILE_KEYS - 1) / kd::TILE_KEYS;
     const int ranges = std::min((target - BH) / (BH * mtiles), ntiles), tiles = (ntiles + ranges - 1) / ranges;
+    if (mtiles * 256 - p.G * p.Bt >= 32 && 450 * tiles < p.n) return false;
     return p.layout == KEYDIFF_LAYOUT_FILL ? 2048 * (tiles - 4) >= p.n : ride == kd::Ride::lds && 1024 * tiles >= p.n;
 }
 
