@@ -241,7 +241,8 @@ KEYDIFF_API int keydiff_cache_len(const keydiff_cache_t *cache, int32_t *len);
  * number of key ranges (split-KV partials per output row the merge adds up; 1 = no merge launch),
  * [1] row tiles per KV head (of 256 query rows, or of 16 in some steps of at most 32), [2] 64-key tiles of the step, [3] bit 0: the step's
  * launch carried another cache's pending eviction, bit 1: it carried another cache's pending row
- * shift (ORDERED layout).  For byte and launch accounting by a benchmark.  */
+ * shift (ORDERED layout), bit 2: the step shared its launches with those of other layers of one call.
+ * For byte and launch accounting by a benchmark.  */
 KEYDIFF_API int keydiff_cache_plan(const keydiff_cache_t *cache, int32_t plan_out[4]);
 
 /* Token position of every cached row: pos_out int32 [batch][n_kv_heads][len] (device). */

@@ -318,7 +318,8 @@ class KeyDiffCache:
         return n.value
 
     def plan(self):
-        """(key ranges, row tiles per head, key tiles, passengers: bit 0 a selection, bit 1 a row shift) of the last block step."""
+        """(key ranges, row tiles per head, key tiles, passengers: bit 0 a selection, bit 1 a row shift; bit 2: the step
+        shared its launches with those of other layers) of the last block step."""
         out = (C.c_int32 * 4)()
         _check(self._L.keydiff_cache_plan(self._h, out))
         return tuple(out)

@@ -810,7 +810,7 @@ int layers_step(keydiff_cache *const *caches, kd::LayerSteps &steps, int layers,
         for (int l = 0; l < layers; ++l) shifts.s[l] = shift_step(caches[l], steps.p[l]);
         KD_LAUNCH(kd::launch_compact_ordered(shifts, layers, plan.D, s), "ordered compaction kernel (several layers)");
     }
-    for (int l = 0; l < layers; ++l) step_enqueued(caches[l], steps.p[l], pos0, continues(caches[l], pos0), 0);
+    for (int l = 0; l < layers; ++l) step_enqueued(caches[l], steps.p[l], pos0, continues(caches[l], pos0), 4);
     return KEYDIFF_OK;
 }
 

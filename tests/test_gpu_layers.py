@@ -36,17 +36,20 @@ def _same_state(a, b, where):
     ((8, 2, 128), 512, 128, 1100, 2, {}),                                              # ragged last block
     ((8, 2, 128), 512, 128, 900, 17, {}),                                              # more layers than a launch takes
     ((6, 2, 128), 300, 48, 650, 5, {"anchor_mode": kd.ANCHOR_MEAN_UNIT_KEY}),           # waves without query rows
-    ((4, 1, 64), 256, 32, 480, 16, {"layout": kd.LAYOUT_ORDERED}),                      # the shifts of a full launch
-    ((8, 2, 64), 512, 64, 820, 2, {"layout": kd.LAYOUT_ORDERED}),
+    ((4, 1, 64), 256, 32, 480, 16, {"layout": kd.LAYOUT_ORDERED}),                      # (shifted by the selection)
+    ((8, 2, 64), 512, 64, 820, 2, {"layout": kd.LAYOUT_ORDERED}),                       # (likewise)
+    ((4, 1, 128), 640, 160, 1480, 16, {"layout": kd.LAYOUT_ORDERED}),                   # the shifts of a full launch, two chunks to wait for
+    ((8, 2, 128), 900, 128, 1600, 2, {"layout": kd.LAYOUT_ORDERED}),
     ((14, 2, 128), 384, 64, 640, 3, {"window_W": 64}),
     ((8, 2, 128), 300, 256, 1000, 1, {}),                                              # one layer: the step of prefill_block
-], ids=["2", "17", "5-helper", "16-ordered", "2-ordered", "3-window", "1"])
+], ids=["2", "17", "5-helper", "16-ordered-short", "2-ordered-short", "16-ordered", "2-ordered", "3-window", "1"])
 def test_layers_in_one_launch(heads, N, B, T, layers, kw):
     kw = {"layout": kd.LAYOUT_FILL, **kw}
     a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, *heads, N, B, **kw)) for _ in range(layers)] for _ in range(2))
     for i, blks in enumerate(zip(*(_blocks(heads, T, B, 100 + l) for l in range(layers)))):
         t = blks[0][0]
-        if i == 5 and kw["layout"] == kd.LAYOUT_FILL and not kw.get("window_W"):
+        by_layer = i == 5 and kw["layout"] == kd.LAYOUT_FILL and not kw.get("window_W")
+        if by_layer:
             # a block on which the layers run one by one and leave evictions pending
             outs = []
             for l, (_, q, k, v) in enumerate(blks):
@@ -56,6 +59,8 @@ def test_layers_in_one_launch(heads, N, B, T, layers, kw):
         for l, (_, q, k, v) in enumerate(blks):
             want = b[l].prefill_block(q, k, v, t)
             assert float((outs[l].float() - want.float()).abs().max()) <= ATTN_ATOL, (t, l)
+        assert all(bool(c.plan()[3] & 4) == (layers > 1 and not by_layer) for c in a), (t, a[0].plan())   # launches were shared
+        assert all(c.plan()[3] == 0 for c in b)
         assert layers < 16 or a[0].plan()[0] <= b[0].plan()[0]
     for l in range(layers):
         _same_state(a[l], b[l], f"layer {l}")
@@ -82,6 +87,7 @@ def test_layers_that_touch_one_anothers_memory_keep_their_order(kind):
                 ks[1] = vs[0]
             if caches is a:
                 kd.prefill_block_layers(caches, qs, ks, vs, t, out=outs)
+                assert all(bool(c.plan()[3] & 4) == (kind == "common-inputs") for c in a)
             else:
                 for c, q, k, v, o in zip(caches, qs, ks, vs, outs):
                     c.prefill_block(q, k, v, t, out=o)
@@ -89,6 +95,35 @@ def test_layers_that_touch_one_anothers_memory_keep_their_order(kind):
         for x, y in zip(*got):
             assert float((x.float() - y.float()).abs().max()) <= ATTN_ATOL, t
     for l in range(layers):
+        _same_state(a[l], b[l], f"layer {l}")
+        a[l].close()
+        b[l].close()
+
+
+@pytest.mark.parametrize("heads,N,B,kw", [
+    ((8, 2, 128), 12300, 128, {}),                                   # scores alone in the registers of the selection
+    ((4, 1, 64), 12288 - 64, 64, {}),                                # the last length with positions there too
+    ((4, 1, 64), 20500, 64, {}),                                     # read from memory in every pass
+    ((4, 1, 64), 20480 - 64, 64, {"layout": kd.LAYOUT_ORDERED}),     # the last length in registers
+    ((8, 2, 128), 20600, 128, {"layout": kd.LAYOUT_ORDERED}),
+], ids=["12428", "12288", "20564", "20480-ordered", "20728-ordered"])
+def test_layers_with_long_caches_in_one_launch(heads, N, B, kw):
+    hq, hkv, d = heads
+    kw = {"layout": kd.LAYOUT_FILL, **kw}
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, *heads, N, B, **kw)) for _ in range(2)] for _ in range(2))
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(1, hkv, N).contiguous()
+    for l, pair in enumerate(zip(a, b)):
+        (_, _, k, v), = _blocks(heads, N, N, 700 + l)
+        for c in pair:
+            c.load(k, v, pos)
+    for blks in zip(*(_blocks(heads, 3 * B, B, 800 + l) for l in range(2))):
+        t = N + blks[0][0]
+        outs = kd.prefill_block_layers(a, [x[1] for x in blks], [x[2] for x in blks], [x[3] for x in blks], t)
+        assert all(c.plan()[3] & 4 for c in a), a[0].plan()
+        for l, (_, q, k, v) in enumerate(blks):
+            want = b[l].prefill_block(q, k, v, t)
+            assert float((outs[l].float() - want.float()).abs().max()) <= ATTN_ATOL, (t, l)
+    for l in range(2):
         _same_state(a[l], b[l], f"layer {l}")
         a[l].close()
         b[l].close()
