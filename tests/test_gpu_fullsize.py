@@ -140,11 +140,13 @@ def test_decode_8b_shape_batch16_all_steps():
 BENCH_SEED = 20250415 + 100 * 3     # bench.py: --seed + 100 * (config number) + layer
 
 
-def test_llama31_8b_shape_whole_prompt_through_the_layers_call_with_the_bench_seeds():
+@pytest.mark.parametrize("profiled", [False, True], ids=["shared-launches", "layer-by-layer"])
+def test_llama31_8b_shape_whole_prompt_through_the_layers_call_with_the_bench_seeds(profiled):
     # What bench.py times, from empty caches over the whole prompt: keydiff_prefill_block_layers on
-    # the first four layers with the benchmark's own seeds, every layer's eviction carried by the
-    # next layer's attention launch.  Retained sets of layers 0-2 are compared with the oracle after
-    # every block (reading them forces nothing: their evictions have ridden already); the last
+    # the first four layers with the benchmark's own seeds, whose steps share their launches.  Handles that are
+    # being profiled have launches of their own: the same call then goes layer by layer, every layer's eviction carried by
+    # the next layer's attention launch.  Retained sets of layers 0-2 are compared with the oracle after
+    # every block (reading them forces nothing: nothing is pending, or their evictions have ridden already); layer by layer the last
     # layer's eviction is still pending after a call, and reading its positions would run it in a
     # launch of its own, so it is read every 16th block and at the end -- both ways of finishing an
     # eviction then occur.  Attention on sampled (block, layer) pairs.
@@ -159,10 +161,12 @@ def test_llama31_8b_shape_whole_prompt_through_the_layers_call_with_the_bench_se
         ocs = [oracle.OracleCache(1, w.n_q_heads, w.n_kv_heads, w.head_dim, N, B) for _ in range(L)]
         dq, dk, dv = ([dev_blocks(d[x], B) for d in layers] for x in ("q", "k", "v"))
         for c in caches:
-            c.profile_enable(True)
+            c.profile_enable(profiled)
         sampled = {(5, 0), (64, 1), (65, 3), (150, 2), (255, 0), (255, 3)}
         for i in range(nb):
             outs = kd.prefill_block_layers(caches, [t[i] for t in dq], [t[i] for t in dk], [t[i] for t in dv], i * B)
+
+            assert all(bool(c.plan()[3] & 4) != profiled for c in caches)
 
             def one(l):
                 q = block_of(layers[l]["q"], i * B, B)[None] if (i, l) in sampled else None
@@ -174,7 +178,7 @@ def test_llama31_8b_shape_whole_prompt_through_the_layers_call_with_the_bench_se
                 if refs[l] is not None:
                     err = float(np.abs(bf16_out_to_f32(outs[l]) - refs[l]).max())
                     assert err <= ATTN_ATOL, f"attention error {err}, block {i}, layer {l}"
-                if l < L - 1 or i % 16 == 15 or i == nb - 1:
+                if not profiled or l < L - 1 or i % 16 == 15 or i == nb - 1:
                     pos = np.sort(caches[l].positions().cpu().numpy(), axis=-1)
                     assert np.array_equal(pos, ocs[l].positions()), f"retained set differs: block {i}, layer {l}"
     rode = alone = 0
@@ -186,7 +190,45 @@ def test_llama31_8b_shape_whole_prompt_through_the_layers_call_with_the_bench_se
         alone += caches[l].profile_read()["select_alone"][1]
         caches[l].close()
     evicting = nb - N // B
-    assert alone == evicting // 16, f"{alone} evictions ran alone; expected the {evicting // 16} the test forced"
+    assert alone == (evicting // 16 if profiled else 0), f"{alone} evictions ran alone; expected the {evicting // 16} the test forced"
+
+
+def test_llama31_8b_shape_sixteen_layers_in_one_launch():
+    # as many layers as a launch takes, from caches at the budget; attention on sampled (block, layer) pairs
+    from concurrent.futures import ThreadPoolExecutor
+    w = get_config("llama31_8b")
+    B, N, L, steps = w.block_B, w.budget_N, 16, 4
+    caches, ocs, dev = [], [], []
+    with ThreadPoolExecutor(8) as ex:
+        datas = list(ex.map(lambda l: make_layer(w, seed=BENCH_SEED + l, layer=l, t1=N + steps * B), range(L)))
+        for data in datas:
+            cache = kd.KeyDiffCache(kd.KeyDiffConfig(1, w.n_q_heads, w.n_kv_heads, w.head_dim, N, B, layout=kd.LAYOUT_FILL))
+            oc = oracle.OracleCache(1, w.n_q_heads, w.n_kv_heads, w.head_dim, N, B)
+            K0, V0 = (data[x][:N].transpose(1, 0, 2)[None].copy() for x in ("k", "v"))
+            P0 = np.broadcast_to(np.arange(N, dtype=np.int32), (1, w.n_kv_heads, N)).copy()
+            cache.load(to_dev(K0), to_dev(V0), torch.from_numpy(P0).cuda())
+            oc.load(K0, V0, P0)
+            caches.append(cache), ocs.append(oc)
+            dev.append(tuple(dev_blocks(data[x][N:], B) for x in ("q", "k", "v")))
+        sampled = {(0, 0), (1, 7), (2, 8), (steps - 1, L - 1)}
+        for i in range(steps):
+            t = N + i * B
+            outs = kd.prefill_block_layers(caches, [d[0][i] for d in dev], [d[1][i] for d in dev], [d[2][i] for d in dev], t)
+            assert all(c.plan()[3] & 4 for c in caches)
+
+            def one(l):
+                q = block_of(datas[l]["q"], t, B)[None] if (i, l) in sampled else None
+                return ocs[l].prefill_block(q, block_of(datas[l]["k"], t, B)[None], block_of(datas[l]["v"], t, B)[None], t)[0]
+            for l, ref in enumerate(ex.map(one, range(L))):
+                if ref is not None:
+                    err = float(np.abs(bf16_out_to_f32(outs[l]) - ref).max())
+                    assert err <= ATTN_ATOL, f"attention error {err}, step {i}, layer {l}"
+    for l in range(L):
+        pos, K, V = rows_by_position(caches[l])
+        assert np.array_equal(pos, ocs[l].positions()), f"retained set of layer {l} differs"
+        assert np.array_equal(K, ocs[l].keys()) and np.array_equal(V, ocs[l].values())
+        assert caches[l].status() == 0
+        caches[l].close()
 
 
 def test_llama31_8b_shape_ordered_layout_through_the_layers_call():

@@ -445,8 +445,8 @@ def test_deferred_eviction_ordered_layout_rides_and_shifts_afterwards():
 
 
 def test_block_through_all_layers_in_one_call():
-    # keydiff_prefill_block_layers: one call per block enqueues every layer, each carrying the one
-    # before it; layer 0 carries the last layer's eviction of the previous block
+    # keydiff_prefill_block_layers on handles that are being profiled (others share launches, tests/test_gpu_layers.py): one call
+    # per block enqueues every layer, each carrying the one before it; layer 0 carries the last layer's eviction of the previous block
     w = get_config("llama31_8b").small(n_q_heads=8, n_kv_heads=2, prompt_T=1408)
     N, B, nl = 640, 128, 4
     layers = [make_pair(w, N, B, layout=kd.LAYOUT_FILL) for _ in range(nl)]
@@ -490,8 +490,8 @@ def test_ordered_layers_call_shifts_inside_later_attention_launches(check_every)
     # l rides in the attention launch of layer l + 1 and the stable row shift by its destination map in
     # that of layer l + 2 (workgroups that own a range of 128-row chunks each).  Reading a cache's state
     # in between runs whatever is still pending for it in launches of its own.
-    # (the last block is ragged: its launches have helper waves and take no shift along, so the shifts
-    # still pending then are enqueued alone when the states are read)
+    # (the last block is ragged: its row tiles have waves without query rows, whose launches take no shift along, so its
+    # layers share their launches; what was pending before it is enqueued alone ahead of them)
     w = get_config("llama31_8b").small(n_q_heads=8, n_kv_heads=2, prompt_T=2000)
     N, B, nl = 1024, 128, 4      # 9 chunks per head: ranges of one and of two chunks
     layers = [make_pair(w, N, B, layout=kd.LAYOUT_ORDERED) for _ in range(nl)]
