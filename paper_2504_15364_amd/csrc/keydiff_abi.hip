@@ -696,13 +696,19 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
     plan_attention(c, p);
     if (p.few) return 0;
     // ORDERED, three layers or more: where the row shifts can ride in the attention launches, which leave the memory system to them, they
-    // do, except on caches of many row tiles and few keys, whose attention is too short to hide a selection and a shift (32 / 8 heads, blocks of
-    // 128, us a layer and block riding / together, 3 and 4 layers: 2048 keys 19.2, 19.7 / 13.4, 11.9; 4096 keys 23.1, 23.4 / 21.3, 19.5).
-    // Caches of few row tiles would gain as well (8 / 2 heads of 64, 2048 keys, two layers 22.3 / 11.9 where three ride at 16.8):
-    // that they ride is what tests/test_gpu_parity.py holds.
-    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2 && !(p.batch * p.hkv * p.mtiles >= 16 && p.n <= 6144)) {
+    // do, except on caches of many row tiles and few keys, whose attention is too short to hide a selection and a shift, and there with three
+    // or four layers only as long as the rows of all heads are few: together, the shifts of all layers follow the attention.  Measured, us
+    // a layer and block riding / together, 3, 4 and 8 layers, blocks of 128:
+    //   32 / 8 heads of 128:  2048 keys 20.3 / 14.1, 20.3 / 12.3, 20.7 / 10.4;  4096 keys 26.9 / 22.5, 26.7 / 20.4, 27.3 / 17.7;
+    //                         6144 keys 32.6 / 30.1, 32.1 / 28.4, 33.2 / 24.9;  8192 keys 36.9 / 39.2, 37.8 / 36.0, 39.4 / 33.4
+    //     two sequences:      2048 keys 23.8 / 22.8, 24.5 / 20.5, 24.7 / 17.2;  4096 keys 34.6 / 38.9, 34.2 / 34.9, 38.5 / 32.1
+    //   32 / 8 heads of 64, two sequences: 4096 keys 24.5 / 27.3, 24.6 / 22.7, 24.9 / 19.6;  four: 2048 keys 25.6 / 26.9, 25.9 / 22.0, 26.1 / 19.9
+    // Longer caches would gain with more layers, and caches of few row tiles with any number (8 / 2 heads of 64, 6144 keys, 3 layers 25.0 / 12.0).
+    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2) {
+        const int BH = p.batch * p.hkv;
+        const bool few_rows = BH * p.n <= 8 * 6144 || n_layers > 4 || (n_layers == 4 && p.D == 64);
         kd::StepParams probe = step;
-        if (plan_with_shift(c, probe, step, p.batch * p.hkv) > 0) return 0;
+        if (!(BH * p.mtiles >= 16 && p.n <= 6144 && few_rows) && plan_with_shift(c, probe, step, BH) > 0) return 0;
     }
     // (ORDERED, two layers: layer by layer the shift runs beside the merge and the selection inside the attention, which is worth more than
     // what the layers share where the attention is long.  Measured, us a layer and block by layer / together, tiles a range in brackets: 32 / 8
@@ -711,17 +717,29 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
     if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers == 2 && (p.ntiles + p.splits - 1) / p.splits > 8) return 0;
     const double post_us = p.do_evict ? 12.0 : 3.0;
     const int least = (n_layers + kd::GROUP_LAYERS - 1) / kd::GROUP_LAYERS;
-    int best_k = least;
+    const int target = c->L.target_wgs / 2, BH = p.batch * p.hkv;
+    int best_k = least, best_rounds = 0;
     double best = 0.0;
     for (int k = least; k <= std::min(n_layers, least + 3); ++k) {
         const int more = n_layers % k, layers = n_layers / k;
+        auto rounds = [&](int n) { return (n * BH * p.mtiles * p.splits + target - 1) / target; };   // of the plan left in p
         double us = k * post_us + (k - more) * plan_layers(c, p, layers);
-        if (more) us += more * plan_layers(c, p, layers + 1);
+        int all = (k - more) * rounds(layers);
+        if (more) {
+            us += more * plan_layers(c, p, layers + 1);
+            all += more * rounds(layers + 1);
+        }
         if (k == least || us < best) {
             best = us;
             best_k = k;
+            best_rounds = all;
         }
     }
+    // Sharing that goes over the chip as often as the layers one by one gains nothing, and the evictions, which would have ridden, follow it
+    // (28 / 4 heads, blocks of 200, two layers, us a layer and block by layer / together: eight sequences (192 row tiles a layer),
+    // 2048 keys 72.4 / 76.2, 4096 keys 114.9 / 129.2;  two (48, of which 240 workgroups are one round and 480 two), 8192 keys 64.8 / 67.5;
+    // but 4096 keys, where two ranges in place of five make it one round, 41.8 / 38.4).
+    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_FILL && best_rounds >= n_layers && BH + BH * p.mtiles <= target) return 0;
     return best_k;
 }
 

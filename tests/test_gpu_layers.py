@@ -192,3 +192,41 @@ def test_ordered_eviction_carried_leaves_what_one_inside_the_step_leaves(d, N, E
     assert torch.all(a.positions().diff(dim=-1) > 0)
     for c in (a, b, other):
         c.close()
+
+
+@pytest.mark.parametrize("heads,batch,N,B,layers,lay,want", [
+    # ORDERED, three layers or more: sharing puts the row shifts of all of them behind the attention
+    ((32, 8, 128), 1, 4096, 128, 3, kd.LAYOUT_ORDERED, 4),
+    ((32, 8, 128), 2, 4096, 128, 3, kd.LAYOUT_ORDERED, 2),     # twice the rows: 38.8 us a layer and block shared, 34.4 riding
+    ((32, 8, 64), 4, 2048, 128, 3, kd.LAYOUT_ORDERED, 2),
+    ((32, 8, 64), 4, 2048, 128, 4, kd.LAYOUT_ORDERED, 4),
+    ((32, 8, 128), 2, 4096, 128, 8, kd.LAYOUT_ORDERED, 4),
+    # FILL: 192 row tiles of each layer in 256 compute units, or 48 in ranges of 240 workgroups
+    ((28, 4, 128), 8, 2048, 200, 2, kd.LAYOUT_FILL, 1),
+    ((28, 4, 128), 2, 8192, 200, 2, kd.LAYOUT_FILL, 1),
+    ((28, 4, 128), 2, 4096, 200, 2, kd.LAYOUT_FILL, 4),
+    ((24, 8, 128), 8, 2048, 128, 2, kd.LAYOUT_FILL, 4),
+    ((32, 8, 128), 1, 8192, 128, 4, kd.LAYOUT_FILL, 4),
+    ((28, 4, 128), 1, 8192, 256, 2, kd.LAYOUT_FILL, 4),
+], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_layers_share_launches_where_that_is_faster(heads, batch, N, B, layers, lay, want):
+    # which way calls of the measured shapes go (256 compute units): the bit of plan()[3] on every layer of the second evicting block
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the plans are for 256 compute units")
+    hq, hkv, d = heads
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    caches = [kd.KeyDiffCache(kd.KeyDiffConfig(batch, *heads, N, B, layout=lay)) for _ in range(layers)]
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(batch, hkv, N).contiguous()
+    rows = torch.randn((batch, hkv, N, d), generator=gen, device="cuda").bfloat16()
+    for c in caches:
+        c.load(rows, rows, pos)
+    q = torch.randn((batch, hq, B, d), generator=gen, device="cuda").bfloat16()
+    for i in range(2):
+        k = torch.randn((batch, hkv, B, d), generator=gen, device="cuda").bfloat16()
+        kd.prefill_block_layers(caches, [q] * layers, [k] * layers, [k] * layers, N + i * B)
+    plans = [c.plan() for c in caches]
+    assert all(pl[3] & want for pl in plans), plans
+    for c in caches:
+        c.finish()
+        assert c.status() == 0
+        c.close()
