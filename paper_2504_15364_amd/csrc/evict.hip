@@ -432,13 +432,14 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_layers_kernel(LayerSte
 // it may overwrite -- the ceil(E / ORD_ROWS) chunks before it -- have announced the same, and
 // stores.  Workgroups are numbered chunk-major, so a workgroup only ever waits for lower-numbered
 // ones; the wait is bounded and reports a timeout in the status word instead of hanging.
-template <int D>
-__device__ __forceinline__ void shift_chunk(const ShiftStep &p, int block)
+// (Step: StepParams or ShiftStep)
+template <int D, class Step>
+__device__ __forceinline__ void shift_chunk(const Step &p, int BH, int32_t *flags, int nchunks, int32_t epoch, int block)
 {
     constexpr int UPR = D / 8;
     constexpr int UPT = ORD_ROWS * UPR * 2 / ORD_THREADS;   // 16-byte units (K and V) per thread
     static_assert(UPT * ORD_THREADS == ORD_ROWS * UPR * 2, "the chunk must divide over the threads");
-    const int bh = block % p.BH, chunk = block / p.BH, tid = threadIdx.x;
+    const int bh = block % BH, chunk = block / BH, tid = threadIdx.x;
     uint16_t *kb = p.k + (size_t)bh * p.cap * D;
     uint16_t *vb = p.v + (size_t)bh * p.cap * D;
     const int32_t *dst = p.dstmap + (size_t)bh * p.cap;
@@ -463,12 +464,12 @@ __device__ __forceinline__ void shift_chunk(const ShiftStep &p, int block)
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every row of this chunk is in registers
     __syncthreads();
-    int32_t *myflags = p.flags + (size_t)bh * ((p.n + ORD_ROWS - 1) / ORD_ROWS);
-    if (tid == 0) __hip_atomic_store(&myflags[chunk], p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int32_t *myflags = flags + (size_t)bh * nchunks;
+    if (tid == 0) __hip_atomic_store(&myflags[chunk], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int reach = (p.n - p.N + ORD_ROWS - 1) / ORD_ROWS;   // chunks below this one its rows can land in
     if (tid < reach && chunk - 1 - tid >= 0) {
         int spins = 0;
-        while (__hip_atomic_load(&myflags[chunk - 1 - tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != p.epoch) {
+        while (__hip_atomic_load(&myflags[chunk - 1 - tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
             if (++spins > ORD_SPIN_LIMIT) {
                 atomicOr(p.status, STATUS_ORDER_TIMEOUT);
                 break;
@@ -486,10 +487,21 @@ __device__ __forceinline__ void shift_chunk(const ShiftStep &p, int block)
     }
 }
 
+// One cache, by the parameters of its step.  (From a block of all the shift needs, 64 bytes, or from an array of them, the launch
+// takes 0.4 to 1 us more: 16 of 8208 rows 11.9 us, 12.8 and 13.2; 9 of 10009 15.5 and 16.1.  Reading what the announcement needs
+// ahead of the rows does not change that.)
 template <int D>
-__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_ordered_kernel(ShiftSteps steps)
+__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_ordered_kernel(StepParams p, int32_t *flags, int nchunks, int32_t epoch)
 {
-    shift_chunk<D>(steps.s[blockIdx.y], (int)blockIdx.x);   // (blockIdx.y: the cache)
+    shift_chunk<D>(p, p.batch * p.hkv, flags, nchunks, epoch, (int)blockIdx.x);
+}
+__host__ __device__ static inline int shift_chunks(const ShiftStep &sh) { return (sh.n + ORD_ROWS - 1) / ORD_ROWS; }
+// ... of several caches, blockIdx.y each
+template <int D>
+__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_layers_kernel(ShiftSteps steps)
+{
+    const ShiftStep &p = steps.s[blockIdx.y];
+    shift_chunk<D>(p, p.BH, p.flags, shift_chunks(p), p.epoch, (int)blockIdx.x);
 }
 
 // The merge of one cache's attention partials and the ordered shift of another cache in one launch
@@ -508,7 +520,7 @@ __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 
         merge_rows<D, 4>(pm, (size_t)blockIdx.x * ORD_THREADS + threadIdx.x);
         return;
     }
-    shift_chunk<D>(shift, (int)blockIdx.x - merge_wgs);
+    shift_chunk<D>(shift, shift.BH, shift.flags, shift_chunks(shift), shift.epoch, (int)blockIdx.x - merge_wgs);
 }
 
 // --------------------------------------------------- key sum from scratch (cache load)
@@ -788,16 +800,26 @@ hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStrea
     return hipGetLastError();
 }
 
-static int shift_chunks(const ShiftStep &sh) { return (sh.n + ORD_ROWS - 1) / ORD_ROWS; }
 // one waiting thread per chunk in reach
 static bool shift_fits(const ShiftStep &sh) { return sh.n - sh.N <= ORD_THREADS * ORD_ROWS; }
 
-hipError_t launch_compact_ordered(const ShiftSteps &steps, int layers, int D, hipStream_t s)
+hipError_t launch_compact_ordered(const StepParams &p, const ShiftStep &shift, hipStream_t s)
 {
-    if (layers < 1 || layers > GROUP_LAYERS || !shift_fits(steps.s[0])) return hipErrorInvalidValue;
+    if (!shift_fits(shift)) return hipErrorInvalidValue;
+    const int chunks = shift_chunks(shift);
+    const dim3 grid((unsigned)(shift.BH * chunks));
+    if (p.D == 128) hipLaunchKernelGGL((compact_ordered_kernel<128>), grid, dim3(ORD_THREADS), 0, s, p, shift.flags, chunks, shift.epoch);
+    else if (p.D == 64) hipLaunchKernelGGL((compact_ordered_kernel<64>), grid, dim3(ORD_THREADS), 0, s, p, shift.flags, chunks, shift.epoch);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_compact_layers(const ShiftSteps &steps, int layers, int D, hipStream_t s)
+{
+    if (layers < 2 || layers > GROUP_LAYERS || !shift_fits(steps.s[0])) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(steps.s[0].BH * shift_chunks(steps.s[0])), (unsigned)layers);
-    if (D == 128) hipLaunchKernelGGL((compact_ordered_kernel<128>), grid, dim3(ORD_THREADS), 0, s, steps);
-    else if (D == 64) hipLaunchKernelGGL((compact_ordered_kernel<64>), grid, dim3(ORD_THREADS), 0, s, steps);
+    if (D == 128) hipLaunchKernelGGL((compact_layers_kernel<128>), grid, dim3(ORD_THREADS), 0, s, steps);
+    else if (D == 64) hipLaunchKernelGGL((compact_layers_kernel<64>), grid, dim3(ORD_THREADS), 0, s, steps);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

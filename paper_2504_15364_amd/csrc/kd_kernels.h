@@ -144,8 +144,9 @@ hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, cons
 hipError_t launch_step_score(const StepParams &p, hipStream_t s);
 hipError_t launch_step_post(const StepParams &p, hipStream_t s);
 hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStream_t s);
-// the ordered shift of `layers` caches of the same sizes
-hipError_t launch_compact_ordered(const ShiftSteps &steps, int layers, int D, hipStream_t s);
+// the ordered shift of one cache (p: its step), and of `layers` caches of the same sizes
+hipError_t launch_compact_ordered(const StepParams &p, const ShiftStep &shift, hipStream_t s);
+hipError_t launch_compact_layers(const ShiftSteps &steps, int layers, int D, hipStream_t s);
 // the merge of pm's partials and the ordered shift of another cache in one launch (same head_dim)
 hipError_t launch_merge_shift(const StepParams &pm, const ShiftStep &shift, hipStream_t s);
 hipError_t launch_ksum_rebuild(const StepParams &p, double *partials, hipStream_t s);

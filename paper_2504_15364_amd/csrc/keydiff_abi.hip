@@ -424,9 +424,7 @@ kd::ShiftStep shift_step(keydiff_cache *c, const kd::StepParams &p)
 int compact_ordered(keydiff_cache *c, const kd::StepParams &p, hipStream_t s)
 {
     ProfScope ps(c, KEYDIFF_K_COMPACT, s);
-    kd::ShiftSteps steps;
-    steps.s[0] = shift_step(c, p);
-    KD_LAUNCH(kd::launch_compact_ordered(steps, 1, p.D, s), "ordered compaction kernel");
+    KD_LAUNCH(kd::launch_compact_ordered(p, shift_step(c, p), s), "ordered compaction kernel");
     return KEYDIFF_OK;
 }
 
@@ -826,7 +824,7 @@ int layers_step(keydiff_cache *const *caches, kd::LayerSteps &steps, int layers,
     if (ordered && !shift_here) {
         kd::ShiftSteps shifts;
         for (int l = 0; l < layers; ++l) shifts.s[l] = shift_step(caches[l], steps.p[l]);
-        KD_LAUNCH(kd::launch_compact_ordered(shifts, layers, plan.D, s), "ordered compaction kernel (several layers)");
+        KD_LAUNCH(kd::launch_compact_layers(shifts, layers, plan.D, s), "ordered compaction kernel (several layers)");
     }
     for (int l = 0; l < layers; ++l) step_enqueued(caches[l], steps.p[l], pos0, continues(caches[l], pos0), 4);
     return KEYDIFF_OK;
