@@ -660,21 +660,28 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
 // 2 layers 37.7 -> 36.5; ORDERED, 24 / 8 heads, 4096 keys, 3 layers 25.2 -> 18.2.  Scores are exact here: approximate ones
 // (4 us off 75 of attention for four layers, 3 more for the selection) gained 1 % in the first case and cost 1 % in the other two.
 
-// The plan of `layers` layers in one launch, left in p (shared by all of them), and its estimated time in us (loosely: it only
-// ranks the plans of one call against one another).  More workgroups than compute units run in several rounds.
+// Estimated time, in us, of the attention and merge of `layers` layers in one launch with the mtiles, ntiles and splits of p
+// (loosely: it only ranks the plans of one call against one another).  More workgroups than compute units run in several rounds.
+double launch_us(const keydiff_cache *c, const kd::StepParams &p, int layers)
+{
+    const int target = c->L.target_wgs / 2, BH = p.batch * p.hkv, Mpad = (p.G * p.Bt + 31) / 32 * 32;
+    const int tplain = std::min(p.len / kd::TILE_KEYS, p.ntiles), cost = tplain + 2 * (p.ntiles - tplain);
+    const int rounds = (layers * BH * p.mtiles * p.splits + target - 1) / target;
+    return rounds * (7.0 + (p.D == 128 ? 1.75 : 1.0) * ((cost + p.splits - 1) / p.splits)) +
+           (p.splits > 1 ? 2.0 + 1e-6 * layers * p.splits * BH * Mpad * p.D * 2 / 3.5 : 0.0);
+}
+
+// The plan of `layers` layers in one launch, left in p (shared by all of them), and its estimated time.
 double plan_layers(const keydiff_cache *c, kd::StepParams &p, int layers)
 {
     plan_attention(c, p);
-    const int target = c->L.target_wgs / 2, BH = p.batch * p.hkv, tiles = layers * BH * p.mtiles;
-    const int Mpad = (p.G * p.Bt + 31) / 32 * 32;
-    const int tplain = std::min(p.len / kd::TILE_KEYS, p.ntiles), cost = tplain + 2 * (p.ntiles - tplain);
-    const double tile_us = p.D == 128 ? 1.75 : 1.0;
+    const int BH = p.batch * p.hkv, Mpad = (p.G * p.Bt + 31) / 32 * 32, most = p.splits;
     double best = 0.0;
     int splits = 1;
-    for (int s = 1; s <= p.splits; ++s) {   // (never more ranges than for one layer alone: the scratch buffer holds those)
+    for (int s = 1; s <= most; ++s) {   // (never more ranges than for one layer alone: the scratch buffer holds those)
         if (s > 1 && (long)s * BH * Mpad > c->L.max_part_rows) break;
-        const int rounds = (tiles * s + target - 1) / target;
-        const double us = rounds * (7.0 + tile_us * ((cost + s - 1) / s)) + (s > 1 ? 2.0 + 1e-6 * layers * s * BH * Mpad * p.D * 2 / 3.5 : 0.0);
+        p.splits = s;
+        const double us = launch_us(c, p, layers);
         if (s == 1 || us < best) {
             best = us;
             splits = s;
@@ -733,11 +740,19 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
             best_rounds = all;
         }
     }
-    // Sharing that goes over the chip as often as the layers one by one gains nothing, and the evictions, which would have ridden, follow it
-    // (28 / 4 heads, blocks of 200, two layers, us a layer and block by layer / together: eight sequences (192 row tiles a layer),
-    // 2048 keys 72.4 / 76.2, 4096 keys 114.9 / 129.2;  two (48, of which 240 workgroups are one round and 480 two), 8192 keys 64.8 / 67.5;
-    // but 4096 keys, where two ranges in place of five make it one round, 41.8 / 38.4).
-    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_FILL && best_rounds >= n_layers && BH + BH * p.mtiles <= target) return 0;
+    if (p.do_evict && BH + BH * p.mtiles <= target) {   // (layer by layer, the evictions would ride)
+        // FILL: sharing that goes over the chip as often as the layers one by one gains nothing.  28 / 4 heads, blocks of 200, two layers, us
+        // a layer and block by layer / together: eight sequences (192 row tiles a layer), 2048 keys 72.4 / 76.2, 4096 keys 114.9 / 129.2;
+        // two (48, of which 240 workgroups are one round and 480 two), 8192 keys 64.8 / 67.5; but 4096 keys, where two ranges in place of
+        // five make it one round, 41.8 / 38.4.
+        if (p.layout == KEYDIFF_LAYOUT_FILL && best_rounds >= n_layers) return 0;
+        // ORDERED, three layers or more: by the estimated times.  The same heads, three layers: four sequences (96 row tiles), 2048 keys
+        // 50.5 / 51.8, 4096 keys 78.5 / 82.4, 8192 keys 136.9 / 144.1;  two, 8192 keys 68.6 / 71.4.
+        if (p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2) {
+            plan_attention(c, p, BH);
+            if (n_layers * launch_us(c, p, 1) < best) return 0;
+        }
+    }
     return best_k;
 }
 

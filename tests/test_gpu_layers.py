@@ -205,6 +205,8 @@ def test_ordered_eviction_carried_leaves_what_one_inside_the_step_leaves(d, N, E
     ((28, 4, 128), 8, 2048, 200, 2, kd.LAYOUT_FILL, 1),
     ((28, 4, 128), 2, 8192, 200, 2, kd.LAYOUT_FILL, 1),
     ((28, 4, 128), 2, 4096, 200, 2, kd.LAYOUT_FILL, 4),
+    ((28, 4, 128), 4, 4096, 200, 3, kd.LAYOUT_ORDERED, 1),     # 288 row tiles of three layers: a second round for 32
+    ((28, 4, 128), 1, 4096, 200, 3, kd.LAYOUT_ORDERED, 4),
     ((24, 8, 128), 8, 2048, 128, 2, kd.LAYOUT_FILL, 4),
     ((32, 8, 128), 1, 8192, 128, 4, kd.LAYOUT_FILL, 4),
     ((28, 4, 128), 1, 8192, 256, 2, kd.LAYOUT_FILL, 4),
