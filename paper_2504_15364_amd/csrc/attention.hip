@@ -59,10 +59,15 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // The running reference max may lag the true row max by 2^SLACK before the accumulators are
-// rescaled: weights then reach 2^64 and sums 2^64 * 32768 rows * |v|, far inside fp32 range, and
-// bf16 / fp32 keep their relative precision at any magnitude, so the slack costs no accuracy; it
-// makes the rescale (a pass over all accumulators) a once-per-row event instead of a per-tile one.
-constexpr float RESCALE_SLACK = 64.f;
+// rescaled: weights then reach 2^24 and sums 2^24 * 32768 rows * |v|, far inside fp32 range, and
+// a pass over all accumulators is an event of a few tiles in a range.  Rounded to bf16, weights keep their relative precision at any
+// magnitude, but the one that equals the reference is exact, and where few keys have most of the weight that is a good part of the
+// error: with a slack of 2^64 (no pass but the first in most inputs) the error against 64 bits grows with the length of the ranges.  So a pass
+// that has to be made moves every row of the wave whose maximum has grown.  Error, 1e-3, and time of a pass over the prompt, slack of 64 /
+// this: 32 / 8 heads, 8192 keys, 4 layers in ranges of 34 tiles 1.359 / 1.330, 19.07 / 19.30 ms (in ranges of 9 tiles, layer by layer, with
+// 2^64: 1.348); 28 / 4 heads, 2 layers 1.411 / 1.382, 6.70 / 6.78 ms; ORDERED, 24 / 8, 3 layers 1.209 / 1.184, 5.22 / 5.27 ms.
+// (2^32 1.339, 2^16 1.318 and 2^10 1.309 at 19.21, 19.41 and 19.57 ms in the first case; 2^8 moving only the rows that have to 1.322 at 19.79.)
+constexpr float RESCALE_SLACK = 24.f;
 constexpr int STAGES = 4;             // LDS ring: tiles t - 1 and t in use, STAGES - 2 in flight
 
 // Asynchronous 16-byte-per-lane copy global -> LDS.  `lds_base` is wave uniform; lane i writes
@@ -498,7 +503,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         }
     };
     // reference-max decision for a tile whose per-lane logit maxima are mloc: the reference only
-    // moves when the tile max exceeds it by 2^SLACK (lazy rescale); then O and l are brought to
+    // moves when the tile max of some row exceeds it by 2^SLACK (lazy rescale); then O and l of every row with a larger tile max are brought to
     // the new reference
     auto new_reference = [&](const float (&mloc)[NQ]) {
         float mtile[NQ];
@@ -514,8 +519,9 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (__builtin_amdgcn_ballot_w64(any) != 0) {
 #pragma unroll
             for (int a = 0; a < NQ; ++a) {
-                const float alpha = need[a] ? __builtin_amdgcn_exp2f(mref[a] - mtile[a]) : 1.f;
-                mref[a] = need[a] ? mtile[a] : mref[a];
+                const float up = fmaxf(mref[a], mtile[a]);
+                const float alpha = up == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mref[a] - up);
+                mref[a] = up;
                 const auto ar = __builtin_amdgcn_permlane16_swap(__float_as_uint(alpha), __float_as_uint(alpha), false, false);
                 lsum[a][0] *= __uint_as_float(ar[0]);
                 lsum[a][1] *= __uint_as_float(ar[1]);
