@@ -118,9 +118,10 @@ def workspace_bytes(cfg: KeyDiffConfig):
 def _stream_ptr(stream):
     if stream is None:
         # what torch.cuda.current_stream().cuda_stream is, without the stream object around it (2.8 us a call, of 12 that
-        # a block step took on the host; this way 0.2)
+        # a block step took on the host; this way 0.2); a name of torch's own, so not to be relied on
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
 
 

@@ -137,3 +137,16 @@ evict.hip:255:1: remark:     ScratchSize [bytes/lane]: 700 [-Rpass-analysis=kern
 evict.hip:255:1: remark:     Occupancy [waves/SIMD]: 4 [-Rpass-analysis=kernel-resource-usage]""".splitlines()
     assert scratch_users(remarks) == [("_ZN2kd22compact_ordered_kernelILi128EEEvNS_10StepParamsEPiii", 700)]
     assert scratch_users(remarks[:3]) == []
+
+
+def test_stream_handle_without_torchs_private_name(monkeypatch):
+    # the current stream's handle comes from a name torch does not promise: without it, from the stream object
+    torch = pytest.importorskip("torch")
+    from paper_2504_15364_amd import binding
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: type("S", (), {"cuda_stream": 4711})())
+    assert binding._stream_ptr(None) == 4711
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 42 + device, raising=False)
+    assert binding._stream_ptr(None) == 42
+    assert binding._stream_ptr(7) == 7
