@@ -685,7 +685,7 @@ constexpr size_t LISTS_LDS_MAX = 48 * 1024;
 // 17.1 / 15.5, 18.2 / 17.9;  544 rows 17.9 / 16.6, 18.1 / 16.9, 19.6 / 20.1;  1024 rows 17.1 / 17.5, 17.6 / 17.7, 19.2 / 22.8.
 constexpr int SHIFT_HERE_MAX = 48 * 1024;   // elements of a head's K
 bool shift_fits_selection(const StepParams &p) { return (long)p.n * p.D <= SHIFT_HERE_MAX; }
-static_assert(SHIFT_HERE_MAX / 64 <= 3 * 4 * POST_THREADS, "the selection holds the scores of such a cache in registers");
+static_assert(SHIFT_HERE_MAX / 64 <= 3 * 4 * POST_THREADS, "the selection holds the scores and positions of such a cache in registers");
 
 bool lists_fit_lds(int n, int N) { return n > N && (size_t)(n - N) * 4 <= LISTS_LDS_MAX; }
 

@@ -34,7 +34,6 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int CAND_MAX = 1024;  // rows of the threshold bin ranked in LDS; more fall back to a radix select
 constexpr int MAX_SELECT_WAVES = POST_THREADS / 64;   // PostShared is laid out for the largest workgroup
@@ -851,7 +850,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     // ORDERED, a short cache: the rows behind the first evicted one are shifted here, pass by pass in ascending order (a row
     // moves down, so no pass overwrites what a later one has to read); the first pass is requested ahead of the key sum.
     constexpr int SHIFTU = 8;
-    const bool shift_here = SRC > 0 && p.layout == LAYOUT_SHIFT_HERE;   // uniform
+    const bool shift_here = PREG && p.layout == LAYOUT_SHIFT_HERE;   // uniform (such a cache has at most 768 rows: positions in registers)
     u32x4 moved[SHIFTU];
     auto request_shift = [&](int i0) {
 #pragma unroll
