@@ -233,7 +233,8 @@ def main():
     ap.add_argument("--layout", choices=["fill", "ordered"], default="fill")
     ap.add_argument("--eviction", choices=["deferred", "immediate"], default="deferred",
                     help="deferred: every block through all layers in one call (keydiff_prefill_block_layers: the layers "
-                         "share their launches); immediate: layer by layer (keydiff_prefill_block)")
+                         "share their launches, or evictions are deferred to the next layer's); immediate: layer by layer "
+                         "(keydiff_prefill_block)")
     ap.add_argument("--profile-steps", type=int, default=8, help="extra steps timed per kernel with HIP events")
     ap.add_argument("--seed", type=int, default=20250415)
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -299,14 +300,14 @@ def main():
         for l in range(L):
             caches[l].prefill_block(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l])
 
-    def run_block_by_layer(i):
-        # What the call does with handles that are being profiled, whose kernels have to be their own: layer l takes along the
-        # eviction layer l - 1 left pending (layer 0: the last layer's)
+    def run_block_by_layer(i, profiled):
+        # The steps with launches of their own.  The call on all layers goes layer by layer on handles that are being profiled, and
+        # where its rules say so (ORDERED, long caches: row shifts ride in later launches); else layer l takes along the eviction layer l - 1 left
+        # pending (layer 0: the last layer's), which is what that call does in the FILL layout.
+        if not deferred or profiled or not shared:
+            return run_block(i)
         for l in range(L):
-            if deferred:
-                caches[l].prefill_block_deferred(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l], carry=caches[l - 1])
-            else:
-                caches[l].prefill_block(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l])
+            caches[l].prefill_block_deferred(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l], carry=caches[l - 1])
 
     def finish_all():   # what may still be pending belongs to the timed work
         if deferred:
@@ -350,14 +351,16 @@ def main():
     ms_per_step = elapsed / args.steps * 1e3
     us_per_layer_step = elapsed / (args.steps * L) * 1e6
     tokens_per_s_per_layer = B / (elapsed / (args.steps * L))
+    shared = deferred and bool(caches[0].plan()[3] & 4)   # the timed steps shared their launches
+    plan = caches[0].plan()
 
     # ---- per-kernel durations, HIP events recorded by the library on its launch stream, layer by layer (first without events:
     # what the brackets are compared with)
-    kernels = {}
+    kernels, us_by_layer = {}, None
     if args.profile_steps > 0:
         t_start = time.perf_counter()
         for _ in range(args.profile_steps):
-            run_block_by_layer(i)
+            run_block_by_layer(i, False)
             i += 1
         finish_all()
         torch.cuda.synchronize()
@@ -365,7 +368,7 @@ def main():
         for c in caches:
             c.profile_enable(True)
         for _ in range(args.profile_steps):
-            run_block_by_layer(i)
+            run_block_by_layer(i, True)
             i += 1
         finish_all()
         torch.cuda.synchronize()
@@ -396,22 +399,24 @@ def main():
                    for k, v in tot.items() if v[1]}
     assert all(c.status() == 0 for c in caches)
 
-    # ---- secondary: the same steady-state steps with the eviction inside the step (keydiff_prefill_block,
-    # two launches per layer) and in the stable row layout, on fresh caches with the same data; the
+    # ---- secondary: the same steady-state steps by every entry point a program may call them through, in both row layouts, on fresh
+    # caches with the same data: "layers" all layers in one call, "deferred" layer by layer with the eviction carried by the next layer's
+    # launch (keydiff_prefill_block_deferred), "immediate" layer by layer with the eviction inside the step (keydiff_prefill_block); the
     # keydiff_scores pass over a full cache
-    plan = caches[0].plan()
     modes, scores_pass, ordered_kernels = None, None, None
     if not args.no_extras:
         first = fill_blocks + args.warmup
-        def run_mode(lay, defer):
+        def run_mode(lay, mode):
             cs = [kd.KeyDiffCache(kd.KeyDiffConfig(w.batch, Hq, Hkv, D, N, B, layout=lay)) for _ in range(L)]
             for l in range(L):
                 load_first_N(cs[l], l)
             def blk(i):
-                if defer and L > 1:
-                    kd.prefill_block_layers(cs, [t[i] for t in dq], [t[i] for t in dk], [t[i] for t in dv], i * B, out=outs)
-                else:
-                    for l in range(L):
+                if mode == "layers":
+                    return kd.prefill_block_layers(cs, [t[i] for t in dq], [t[i] for t in dk], [t[i] for t in dv], i * B, out=outs)
+                for l in range(L):
+                    if mode == "deferred":
+                        cs[l].prefill_block_deferred(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l], carry=cs[l - 1] if L > 1 else None)
+                    else:
                         cs[l].prefill_block(dq[l][i], dk[l][i], dv[l][i], i * B, out=outs[l])
             for i in range(fill_blocks, fill_blocks + 3):
                 blk(i)
@@ -421,11 +426,12 @@ def main():
             t0_ = time.perf_counter()
             for i in range(fill_blocks + 3, fill_blocks + 3 + args.mode_steps):
                 blk(i)
-            cs[L - 1].finish()
+            for c in cs:
+                c.finish()
             torch.cuda.synchronize()
             us = (time.perf_counter() - t0_) / (args.mode_steps * L) * 1e6
             prof = None
-            if lay == kd.LAYOUT_ORDERED and not defer:  # per-kernel times of the stable layout (HIP events; deferred, the shift rides in the merge launch)
+            if lay == kd.LAYOUT_ORDERED and mode == "immediate":  # per-kernel times of the stable layout (HIP events; deferred, the shift rides in the merge launch)
                 for c in cs:
                     c.profile_enable(True)
                 for i in range(fill_blocks + 3 + args.mode_steps, fill_blocks + 7 + args.mode_steps):
@@ -444,13 +450,13 @@ def main():
             for c in cs:
                 c.close()
             return us, prof
-        modes = {"deferred_fill": us_per_layer_step if deferred and args.layout == "fill" else None}
-        for key, lay, defer in (("deferred_fill", kd.LAYOUT_FILL, True), ("immediate_fill", kd.LAYOUT_FILL, False),
-                                ("deferred_ordered", kd.LAYOUT_ORDERED, True), ("immediate_ordered", kd.LAYOUT_ORDERED, False)):
-            if modes.get(key) is None:
-                modes[key], prof = run_mode(lay, defer)
-                if prof is not None:
-                    ordered_kernels = prof
+        modes = {"layers_fill": us_per_layer_step if deferred and args.layout == "fill" else None}
+        for name, lay in (("fill", kd.LAYOUT_FILL), ("ordered", kd.LAYOUT_ORDERED)):
+            for mode in ("layers", "deferred", "immediate"):
+                if modes.get(f"{mode}_{name}") is None:
+                    modes[f"{mode}_{name}"], prof = run_mode(lay, mode)
+                    if prof is not None:
+                        ordered_kernels = prof
         modes = {k: {"us_per_layer_step": v, "tokens_per_s_per_layer": B / (v * 1e-6),
                      "frac_of_step_roofline": None} for k, v in modes.items()}
         # keydiff_scores on the caches of all layers in turn, back to back (each cache is at the budget:
@@ -478,18 +484,25 @@ def main():
     flops_attn = 4.0 * Hq * B * D * (N + B / 2.0)
     bytes_step = (2 * Hkv * n * D * 2 + 2 * Hq * B * D * 2 + 2 * Hkv * B * D * 2 + Hkv * n * 4
                   + 2 * 2 * Hkv * B * D * 2)        # K+V once, Q in/O out, new rows, scores, <= B moved rows r+w
-    roofline = None
+    roofline = by_layer = None
     if "step_main" in kernels:
         t_attn = kernels["step_main"]["avg_us"] * 1e-6
         achieved = flops_attn / t_attn / 1e12
-        # (layer by layer; with deferred eviction nearly every launch of the class is the carrying variant of the kernel)
-        roofline = {"bound": "mfma", "kernel": "step_main_carry_kernel" if deferred else "step_main_kernel",
-                    "launches": "one layer each (profiled handles); the timed steps share launches between layers, see step_roofline"
-                                if deferred else "one layer each",
-                    "achieved": achieved,
+        # (one layer a launch; with deferred eviction nearly every launch of the class is the carrying variant of the kernel)
+        by_layer = {"bound": "mfma", "kernel": "step_main_carry_kernel" if deferred else "step_main_kernel",
+                    "launches": "one layer each" + (", layer by layer (profiled handles)" if shared else ""), "achieved": achieved,
                     "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_MFMA_TFLOPS,
                     "traffic": measured_traffic(w.name, args.layout), "flops_per_launch": flops_attn,
                     "avg_launch_us": kernels["step_main"]["avg_us"]}
+        roofline = by_layer
+    if shared:
+        # What the timed steps run: the attention of up to 16 layers a launch, their merges and evictions in another.  The library records no
+        # events inside such a call, so the time is that of both (the attention's alone: the kernel trace under profiles/).
+        achieved = flops_attn / (us_per_layer_step * 1e-6) / 1e12
+        roofline = {"bound": "mfma", "kernel": "step_main_layers_kernel", "launches": "up to 16 layers each; time of the whole call, merge and "
+                    "evictions included", "achieved": achieved, "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s",
+                    "frac": achieved / PEAK_BF16_MFMA_TFLOPS, "traffic": measured_traffic(w.name + "_layers", args.layout),
+                    "flops_per_layer": flops_attn, "key_ranges": plan[0]}
     t_min = max(flops_attn / (PEAK_BF16_MFMA_TFLOPS * 1e12), bytes_step / (PEAK_HBM_GBPS * 1e9))
     step_frac = t_min / (us_per_layer_step * 1e-6)
 
@@ -570,7 +583,7 @@ def main():
     # the merged rows out; the stable shift reads and writes the rows behind the first evicted one,
     # here priced as every row of K and V)
     hbm_kernels = {}
-    if plan[0] > 1 and "step_post" in kernels and deferred:
+    if plan[0] > 1 and "step_post" in kernels and deferred and not shared:
         mb = plan[0] * Hq * B * (D * 2 + 8) + Hq * B * D * 2
         us = kernels["step_post"]["avg_us"]
         hbm_kernels["merge_kernel"] = {"bytes": mb, "us": us, "GBps": mb / us / 1e3,
@@ -597,13 +610,14 @@ def main():
         "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": w.name, "n_q_heads": Hq, "n_kv_heads": Hkv, "head_dim": D, "budget_N": N,
                    "block_B": B, "layers": L, "layout": args.layout,
-                   "eviction": "deferred" if deferred else "immediate", "call": "prefill_block_layers" if deferred else "prefill_block",
+                   "eviction": "in the call" if shared else "deferred" if deferred else "immediate",
+                   "call": "prefill_block_layers" if deferred else "prefill_block", "launches": "shared by layers" if shared else "by layer",
                    "tokens_per_step": B,
                    "step": "one steady-state block step through every layer"},
-        "us_per_layer_step": us_per_layer_step,
+        "us_per_layer_step": us_per_layer_step, "us_per_layer_step_layer_by_layer": us_by_layer,
         "step_roofline": {"binding": "mfma" if flops_attn / 2.5e15 > bytes_step / 8e12 else "hbm",
                           "t_min_us": t_min * 1e6, "frac": step_frac, "flops": flops_attn, "bytes": bytes_step},
-        "roofline": roofline, "kernels": kernels, "modes": modes, "hbm_kernels": hbm_kernels,
+        "roofline": roofline, "roofline_layer_by_layer": by_layer, "kernels": kernels, "modes": modes, "hbm_kernels": hbm_kernels,
         "whole_prompt": whole, "decode": decode, "cpu_baseline": cpu,
     }))
 

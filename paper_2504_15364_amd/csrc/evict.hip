@@ -391,10 +391,7 @@ __device__ __forceinline__ void post_body(const StepParams &p, int block)
     const int n_select = p.do_evict ? p.batch * p.hkv : 0;
     if (block >= n_select) {
 #ifdef KD_TIMELINE
-        unsigned long long *tl = reinterpret_cast<unsigned long long *>(&sh);   // (the selection's tables are not in use here)
-        if (threadIdx.x < 32) tl[threadIdx.x] = 0;
-        __syncthreads();
-        if (threadIdx.x == 0) tl[0] = wall_clock64();
+        const unsigned long long started = wall_clock64();
 #endif
         static_assert(sizeof(PostShared) >= POST_THREADS * 6 * sizeof(float), "the merge of step_few's partials uses the selection's tables");
         if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), block - n_select);
@@ -402,12 +399,11 @@ __device__ __forceinline__ void post_body(const StepParams &p, int block)
 #ifdef KD_TIMELINE
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
-        if (threadIdx.x == 0) {
-            tl[12] = wall_clock64();
-            tl[31] = 4;   // record kind: merging workgroup
+        const unsigned long long ended = wall_clock64();
+        if (p.timeline && threadIdx.x < 32) {   // record kind 4: merging workgroup
+            const unsigned long long v = threadIdx.x == 0 ? started : threadIdx.x == 12 ? ended : threadIdx.x == 31 ? 4 : 0;
+            p.timeline[(size_t)block * 32 + threadIdx.x] = v;
         }
-        __syncthreads();
-        if (p.timeline && threadIdx.x < 32) p.timeline[(size_t)block * 32 + threadIdx.x] = tl[threadIdx.x];
 #endif
         return;
     }

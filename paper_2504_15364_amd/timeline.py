@@ -57,6 +57,18 @@ SEL_PHASES = [
     (9, "key sum stored"),
     (12, "stores acknowledged (workgroup ends)"),
 ]
+FEW_PHASES = [
+    (1, "first tiles requested"),
+    (2, "anchor formed"),
+    (3, "V of the wave's last tile in LDS"),
+    (4, "... scored"),
+    (5, "tiles done"),
+    (6, "scores finished"),
+    (7, "every wave done"),
+    (8, "results and arg-max records in LDS"),
+    (9, "partial stored"),
+    (12, "stores acknowledged (workgroup ends)"),
+]
 TICK_US = 0.01   # wall_clock64 counts a constant 100 MHz clock
 
 
@@ -64,6 +76,7 @@ def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--workload", default="llama31_8b")
     ap.add_argument("--layers", type=int, default=8)
+    ap.add_argument("--batch", type=int, default=0, help="sequences; 0 = the workload's")
     ap.add_argument("--steps", type=int, default=6)
     ap.add_argument("--warmup", type=int, default=2)
     ap.add_argument("--seed", type=int, default=20250415)
@@ -84,6 +97,8 @@ def main():
     lib.keydiff_timeline_buffer.restype = C.c_long
 
     w = get_config(args.workload)
+    if args.batch:
+        w = w.small(batch=args.batch)
     L, B, N, D, Hq, Hkv = args.layers, w.block_B, w.budget_N, w.head_dim, w.n_q_heads, w.n_kv_heads
     fill = N // B
     nsteps = args.warmup + args.steps
@@ -175,6 +190,7 @@ def main():
           f"({dict(deferred='step_main_carry_kernel', immediate='step_main_kernel, then step_post_kernel', layers='step_main_layers_kernel')[args.eviction]})")
     print("# stamps: thread 0 of every workgroup, constant 100 MHz clock (0.01 us resolution)")
     summarise(1, ATTN_PHASES, "attention workgroups")
+    summarise(5, FEW_PHASES, "step_few workgroups")
     summarise(2, SEL_PHASES, "carried selection workgroups" if args.eviction == "deferred"
               else "selection workgroups of step_post (a launch of its own after the attention)")
     summarise(4, [(12, "partials merged, output stored and acknowledged (workgroup ends)")],
