@@ -183,8 +183,9 @@ KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const voi
  * pending): every layer's selection and compaction runs inside the next layer's attention
  * launch, and the last layer's stays pending until the next block (or keydiff_finish, or any
  * other call on that cache).  With n_layers == 1 the call is keydiff_prefill_block.
- * In the ORDERED layout two layers go the second way where one alone would have key ranges of more than eight tiles; three
- * or more, except on caches of at most 6144 rows with 16 row tiles or more, wherever
+ * So do calls whose sharing would take longer by the library's estimate (plan_out[3] of keydiff_cache_plan says which way a step went): in the
+ * ORDERED layout two layers where one alone would have key ranges of more than eight tiles; three
+ * or more, except on caches of at most 6144 rows with 16 row tiles or more (three or four layers: and few rows in all heads), wherever
  * the stable row shift of layer l, whose selection rode in the launch of layer l + 1, can ride in the
  * attention launch of layer l + 2 (a block that evicts at most 128 rows,
  * 256-row query tiles that are full, the same head_dim), so that after the call the shifts of the last
