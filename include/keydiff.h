@@ -176,7 +176,7 @@ KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const voi
  * The layers' retained sets, rows and outputs are those of keydiff_prefill_block on layer 0, 1, ... in turn (`out` up to
  * the last bf16 bit, as the keys may be cut into other ranges).  Layers that are shaped alike and as long, and of which
  * none writes (output, cache, scratch buffer) what another one touches, share their launches: up to 16 layers' attention
- * in one, their merges and evictions in the next, the row shifts of the ORDERED layout in a third; nothing is left pending.
+ * in one, their merges and evictions in the next, the row shifts of the ORDERED layout there too or in a third; nothing is left pending.
  * Else, or while one of the handles is being profiled (its kernels are then its own), the call is
  * keydiff_prefill_block_deferred on layer 0, 1, ... in turn with the layer before it
  * as `carry` (for layer 0 the last layer, whose eviction from the previous block is still
@@ -184,8 +184,9 @@ KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const voi
  * launch, and the last layer's stays pending until the next block (or keydiff_finish, or any
  * other call on that cache).  With n_layers == 1 the call is keydiff_prefill_block.
  * So do calls whose sharing would take longer by the library's estimate (plan_out[3] of keydiff_cache_plan says which way a step went): in the
- * ORDERED layout two layers where one alone would have key ranges of more than eight tiles; three
- * or more, except on caches of at most 6144 rows with 16 row tiles or more (three or four layers: and few rows in all heads), wherever
+ * ORDERED layout, unless the row shifts of all layers fit around their selections on the chip, two layers with more than 16 row tiles
+ * where one alone would have key ranges of more than eight tiles; three or four layers of many rows in all heads (and of few row
+ * tiles on caches of at most 1280 rows) wherever
  * the stable row shift of layer l, whose selection rode in the launch of layer l + 1, can ride in the
  * attention launch of layer l + 2 (a block that evicts at most 128 rows,
  * 256-row query tiles that are full, the same head_dim), so that after the call the shifts of the last

@@ -423,6 +423,107 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_layers_kernel(LayerSte
     post_body<D, SRC, false>(steps.p[blockIdx.x], (int)blockIdx.y);
 }
 
+// ------------------------------------------------------------- selection and ordered compaction in one launch
+// The shift behind a selection needs its bitmap and nothing else of it, and reading the rows, half of the shift's work, needs not
+// even that.  So the two run in one launch: workgroup `index` behind the selections requests its rows into registers, merges its share of the
+// attention partials, and waits for the bitmap of its head and for the chunks below it that its rows may land in; then it stores.  The grid is
+// no larger than the chip, and a workgroup waits for lower-numbered ones only; waits are bounded and report a timeout instead of hanging.
+// Thread: K rows in the first half of the workgroup, V rows in the second, TROWS rows apart.
+// What bounds it: the selection up to its bitmap (8 us at 8320 rows), then one store of the rows, with the hint that nothing reads them
+// again here (1.5 to 3 % of a step less than without).  The merge goes first: behind the requests of the rows, which hold registers, it
+// took 1 % of a step more.  A step with both launches / with this one, us: 8 heads of 128, 32 query heads, blocks of 128, 2048 rows
+// 31.8 / 29.9, 4096 40.7 / 35.9, 8192 54.9 / 43.1, 11000 68.0 / 53.8;  2 heads, 8192 rows 38.5 / 33.8;  8 of 64, two sequences, 4096 rows 39.4 / 33.1.
+template <int D>
+__device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAround &sa, PostShared &sh, int index)
+{
+    constexpr int UPR = D / 8, SLABS = D / 8, TROWS = POST_THREADS / 2 / UPR;
+    const int BH = p.batch * p.hkv, tid = threadIdx.x;
+    const int bh = index % BH, chunk = index / BH, rows = sa.units * TROWS;
+    const int row0 = chunk * rows + tid % (POST_THREADS / 2) / UPR;
+    uint16_t *base = (tid >= POST_THREADS / 2 ? p.v : p.k) + (size_t)bh * p.cap * D + tid % UPR * 8;
+    if (p.splits > 1) {   // uniform, like the branches in it
+        if (p.few) {
+            if (chunk == 0) merge_few<D>(p, reinterpret_cast<float *>(&sh), bh);
+        } else {
+            const size_t items = (size_t)BH * ((p.G * p.Bt + 31) / 32) * SLABS * 64;
+            for (size_t g = (size_t)index * POST_THREADS + tid; g < items; g += (size_t)BH * sa.chunks * POST_THREADS) merge_rows<D>(p, g);
+        }
+    }
+    u32x4 val[AROUND_UNITS];
+#pragma unroll
+    for (int q = 0; q < AROUND_UNITS; ++q)
+        if (q < sa.units) val[q] = *reinterpret_cast<const u32x4 *>(base + (size_t)min(row0 + q * TROWS, p.n - 1) * D);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every row of this chunk is in registers
+    __syncthreads();
+    int32_t *flags = sa.flags + (size_t)bh * sa.chunks;
+    const unsigned long long *words = sa.words + (size_t)bh * sa.stride;
+    if (tid == 0) __hip_atomic_store(&flags[chunk], sa.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the word of the epoch, or 0 (of the header: do nothing) where it does not come
+    auto word_at = [&](int i) {
+        for (int spins = 0; spins <= ORD_SPIN_LIMIT; ++spins) {
+            const unsigned long long w = __hip_atomic_load(&words[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((int32_t)(w >> 32) == sa.epoch) return (uint32_t)w;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+        return 0u;
+    };
+    const int reach = (p.n - p.N + rows - 1) / rows, below = chunk - 1 - (tid - 64);   // chunks below this one its rows can land in
+    if (tid == 0) sh.sel_cnt = word_at(0) == 1 ? 1u : 0u;
+    else if (tid >= 64 && tid < 64 + reach && below >= 0) {
+        int spins = 0;
+        while (__hip_atomic_load(&flags[below], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != sa.epoch) {
+            if (++spins > ORD_SPIN_LIMIT) {
+                atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(4);
+        }
+    }
+    __syncthreads();
+    if (sh.sel_cnt == 0) return;   // uniform
+    const int nwords = (p.n + 31) / 32;
+    uint32_t *bits = sh.hist, *before = sh.hist + MAX_CAP / 32;
+    static_assert(2 * (MAX_CAP / 32) <= HIST_BINS && MAX_CAP / 32 <= POST_THREADS, "the bitmap and its counts use the histogram's place, a word a thread");
+    const uint32_t w = tid < nwords ? word_at(1 + tid) : 0u;
+    uint32_t total;
+    const uint32_t at = block_exclusive_scan_t<POST_THREADS, uint32_t>((uint32_t)__popc(w), sh.wave_tot, &total);
+    bits[tid] = w;
+    before[tid] = at;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < AROUND_UNITS; ++q) {
+        const int row = row0 + q * TROWS;
+        if (q < sa.units && row < p.n) {
+            const uint32_t word = bits[row >> 5], bit = (uint32_t)row & 31u;
+            const int to = row - (int)(before[row >> 5] + (uint32_t)__popc(word & ((1u << bit) - 1u)));
+            if (((word >> bit) & 1u) == 0 && to != row) __builtin_nontemporal_store(val[q], reinterpret_cast<u32x4 *>(base + (size_t)to * D));
+        }
+    }
+}
+template <int D>
+__device__ __forceinline__ void post_shift_body(const StepParams &p, const ShiftAround &sa, int block)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    __shared__ PostShared sh;
+    const int BH = p.batch * p.hkv;
+    if (block < BH) select_and_compact<D, 3, POST_THREADS, false>(p, sh, smem_raw, block, PublishWords{sa});
+    else shift_around<D>(p, sa, sh, block - BH);
+}
+template <int D>
+__global__ __launch_bounds__(POST_THREADS) void step_post_shift_kernel(StepParams p, ShiftAround sa)
+{
+    warm_arguments<sizeof(StepParams) + sizeof(ShiftAround)>();
+    post_shift_body<D>(p, sa, (int)blockIdx.x);
+}
+// ... of several layers: blockIdx.x is the layer
+template <int D>
+__global__ __launch_bounds__(POST_THREADS) void step_post_shift_layers_kernel(LayerSteps steps, ShiftArounds arounds)
+{
+    warm_arguments<sizeof(StepParams)>(blockIdx.x * (uint32_t)sizeof(StepParams));
+    post_shift_body<D>(steps.p[blockIdx.x], arounds.s[blockIdx.x], (int)blockIdx.y);
+}
+
 // ------------------------------------------------------------- ordered compaction
 // Stable in-place shift: kept row i moves to dst[i] = i - (evicted rows before i), so a row moves
 // down by at most E = n - N rows.  One workgroup per ORD_ROWS rows reads its moving rows into
@@ -705,7 +806,9 @@ hipError_t configure_kernels()
 #define KD_FNS(DD)                                                               \
     KD_FN(DD, 0), KD_FN(DD, 3), KD_FN(DD, 5), reinterpret_cast<const void *>(step_post_kernel<DD, 0, true>), \
         reinterpret_cast<const void *>(step_post_kernel<DD, 3, true>)
-        KD_FNS(128), KD_FNS(64)};
+        KD_FNS(128), KD_FNS(64),
+        reinterpret_cast<const void *>(step_post_shift_kernel<128>), reinterpret_cast<const void *>(step_post_shift_layers_kernel<128>),
+        reinterpret_cast<const void *>(step_post_shift_kernel<64>), reinterpret_cast<const void *>(step_post_shift_layers_kernel<64>)};
 #undef KD_FNS
 #undef KD_FN
     for (const void *fn : post_fns) {
@@ -794,6 +897,48 @@ hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStrea
     if (p.D == 128) { KD_GO(128) }
     else if (p.D == 64) { KD_GO(64) }
 #undef KD_GO
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+// The fewest units a thread with which selections and chunks are on the chip together, one workgroup a compute unit (their registers hold
+// no second one): the more compute units take part, the sooner the rows are read and stored.
+bool plan_shift_around(const StepParams &p, int layers, int cus, int32_t *units, int32_t *chunks)
+{
+    if (!p.do_evict || p.score_approx || post_source(p) != 3) return false;
+    const int BH = p.batch * p.hkv;
+    for (int u = 1; u <= AROUND_UNITS; ++u) {
+        const int rows = u * (POST_THREADS / 2 / (p.D / 8)), n = (p.n + rows - 1) / rows;
+        static_assert(POST_THREADS / 2 / (128 / 8) >= ORD_MIN_ROWS, "one flag for every chunk");
+        if (layers * BH * (n + 1) > cus || (p.n - p.N + rows - 1) / rows > POST_THREADS - 64) continue;
+        *units = u;
+        *chunks = n;
+        return true;
+    }
+    return false;
+}
+
+hipError_t launch_step_post_shift(const StepParams &p, const ShiftAround &around, hipStream_t s)
+{
+    const dim3 grid((unsigned)(p.batch * p.hkv * (1 + around.chunks)));
+    const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
+    if (!p.do_evict || p.score_approx || post_source(p) != 3 || around.units < 1 || around.units > AROUND_UNITS) return hipErrorInvalidValue;
+    if (p.D == 128) hipLaunchKernelGGL((step_post_shift_kernel<128>), grid, dim3(POST_THREADS), lds, s, p, around);
+    else if (p.D == 64) hipLaunchKernelGGL((step_post_shift_kernel<64>), grid, dim3(POST_THREADS), lds, s, p, around);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_step_post_shift_layers(const LayerSteps &steps, const ShiftArounds &arounds, int layers, hipStream_t s)
+{
+    const StepParams &p = steps.p[0];
+    const ShiftAround &a = arounds.s[0];
+    if (layers < 2 || layers > GROUP_LAYERS || !p.do_evict || p.score_approx || post_source(p) != 3 || a.units < 1 || a.units > AROUND_UNITS)
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)layers, (unsigned)(p.batch * p.hkv * (1 + a.chunks)));
+    const size_t lds = select_dyn_bytes(p.n, p.N, p.cap, p.lists_in_lds != 0, false);
+    if (p.D == 128) hipLaunchKernelGGL((step_post_shift_layers_kernel<128>), grid, dim3(POST_THREADS), lds, s, steps, arounds);
+    else if (p.D == 64) hipLaunchKernelGGL((step_post_shift_layers_kernel<64>), grid, dim3(POST_THREADS), lds, s, steps, arounds);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -7,7 +7,8 @@
 //              (step_few instead where a KV head has few query rows and many keys)
 //   step_post  merge of the attention partials  ||  selection of the rows to evict
 //              and compaction, one workgroup per head (Eq. 6-7)
-// plus, for the ORDERED layout only, one more launch that shifts rows in place.
+// For the ORDERED layout the rows are shifted in place by the selection's workgroup itself (short caches), by the workgroups around it in
+// the same launch (step_post_shift) or, where the chip does not hold all rows in registers, by one more launch.
 // With the eviction deferred the second launch is the merge alone, and the selection and
 // compaction ride in the step_main launch of the next cache (launch_step_main_carry).
 // step_score scores a cache outside a block step (keydiff_scores).
@@ -34,6 +35,8 @@ constexpr int CHUNK_ROWS = 128;     // rows per workgroup in the from-scratch ke
 constexpr int LAYOUT_SHIFT_HERE = 2;  // StepParams::layout: ORDERED, and the selection shifts the rows too (short caches, shift_fits_selection)
 constexpr int ORD_ROWS = 128;       // rows per workgroup of the ordered compaction
 constexpr int ORD_THREADS = 1024;   // ... and its threads: 4 16-byte units each
+constexpr int ORD_MIN_ROWS = 32;    // fewest rows a workgroup of a shift takes: one flag each in the metadata
+constexpr int AROUND_UNITS = 20;    // most 16-byte units a thread of a shift around the selection holds in registers
 constexpr int ORD_SPIN_LIMIT = 1 << 20;  // polls of a predecessor's flag before giving up
 constexpr int MAX_CAP = 32768;      // budget_N + block_B limit (selection bitmaps, ownership)
 
@@ -108,6 +111,18 @@ struct ShiftSteps {
     ShiftStep s[GROUP_LAYERS];
 };
 
+// The same shift by the workgroups around the selection that decides it, in one launch with it (step_post_shift): the rows wait in
+// registers while the selection runs, which hands over its eviction bitmap word by word, each with the epoch beside it.
+struct ShiftAround {
+    unsigned long long *words;   // [BH][stride] zero-initialised: a word that says whether there is something to move, then the bitmap
+    int32_t *flags;              // [BH][chunks]: the chunk's rows are in registers
+    int32_t epoch, stride;
+    int32_t units, chunks;       // 16-byte units a thread holds; workgroups a head
+};
+struct ShiftArounds {
+    ShiftAround s[GROUP_LAYERS];
+};
+
 // Pieces (of four output values) a thread of the merge takes: with few splits several
 constexpr int MERGE_FEW_SPLITS = 4, MERGE_PIECES = 4;
 __host__ __device__ constexpr int merge_pieces(int splits) { return splits <= MERGE_FEW_SPLITS ? MERGE_PIECES : 1; }
@@ -144,6 +159,10 @@ hipError_t launch_step_main_ride(const StepParams &p, const StepParams *cy, cons
 hipError_t launch_step_score(const StepParams &p, hipStream_t s);
 hipError_t launch_step_post(const StepParams &p, hipStream_t s);
 hipError_t launch_step_post_layers(const LayerSteps &steps, int layers, hipStream_t s);
+// Units a thread and chunks a head of a shift around the selection of `layers` caches shaped like p's on `cus` compute units; false: not that way
+bool plan_shift_around(const StepParams &p, int layers, int cus, int32_t *units, int32_t *chunks);
+hipError_t launch_step_post_shift(const StepParams &p, const ShiftAround &around, hipStream_t s);
+hipError_t launch_step_post_shift_layers(const LayerSteps &steps, const ShiftArounds &arounds, int layers, hipStream_t s);
 // the ordered shift of one cache (p: its step), and of `layers` caches of the same sizes
 hipError_t launch_compact_ordered(const StepParams &p, const ShiftStep &shift, hipStream_t s);
 hipError_t launch_compact_layers(const ShiftSteps &steps, int layers, int D, hipStream_t s);

@@ -207,6 +207,34 @@ __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool l
     return b;
 }
 
+// What a selection does once its eviction bitmap is final and the evicted keys have been read: nothing, or hand the bitmap to the
+// workgroups of the same launch that hold the rows (ShiftAround).  Every word travels with the epoch of the launch in one 8-byte
+// store, so a reader needs no order between words: it reads one until it carries the epoch.
+struct NoPublish {
+    static constexpr bool ON = false;
+    __device__ void operator()(int, const uint32_t *, int) const {}
+    __device__ void nothing(int) const {}
+};
+struct PublishWords {
+    static constexpr bool ON = true;
+    const ShiftAround &around;
+    __device__ __forceinline__ void put(int bh, int i, uint32_t w) const
+    {
+        __hip_atomic_store(around.words + (size_t)bh * around.stride + i, ((unsigned long long)(uint32_t)around.epoch << 32) | w,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // (by all threads of the workgroup)
+    __device__ __forceinline__ void operator()(int bh, const uint32_t *evbits, int nwords) const
+    {
+        for (int i = threadIdx.x; i < nwords; i += blockDim.x) put(bh, 1 + i, evbits[i]);
+        if (threadIdx.x == 0) put(bh, 0, 1);
+    }
+    __device__ __forceinline__ void nothing(int bh) const   // (impossible: the rows stay where they are)
+    {
+        if (threadIdx.x == 0) put(bh, 0, 2);
+    }
+};
+
 // ------------------------------------------------------------- select + compaction
 // `dyn`: dynamic LDS of select_dyn_bytes(...) bytes, 16-byte aligned.  The list of evicted rows lies in LDS when it fits, else in
 // the scratch buffer.
@@ -214,8 +242,8 @@ __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool l
 // n <= 4 * SRC * THREADS.
 // (inlined: outlined, the parameter block would be passed through scratch memory)
 // APPROX: the scores may be approximate (p.score_approx says).
-template <int D, int SRC, int THREADS, bool APPROX>
-__device__ __forceinline__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh)
+template <int D, int SRC, int THREADS, bool APPROX, class Publish = NoPublish>
+__device__ __forceinline__ void select_and_compact(const StepParams &p, PostShared &sh, unsigned char *dyn, int bh, const Publish &publish = {})
 {
     constexpr int UPR = D / 8;
     constexpr int TAILU = THREADS > 512 || D == 64 ? SELECT_TAILU / 2 : SELECT_TAILU;   // (128 rows a batch, 256 of 64 with 1024 threads)
@@ -707,6 +735,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
         // an impossible count is reported and nothing is moved (keeps every index in range)
         if (total != (uint32_t)E) {   // uniform
             if (tid == 0) atomicOr(p.status, STATUS_SELECT_COUNT);
+            publish.nothing(bh);
             KD_SEL_RETURN;
         }
         if (tid < nwords) word_base[tid] = at;
@@ -807,6 +836,11 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             for (int q = 0; q < TAILU; ++q)
                 if (r0 + q * KEY_ROWS < E) add_key(old[q], acc[0]);
         }
+        if constexpr (Publish::ON) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the evicted keys are in registers: their rows may be overwritten
+            __syncthreads();
+            publish(bh, evbits, nwords);
+        }
         int32_t *dst = p.dstmap + (size_t)bh * p.cap;
         // four rows, which share a bitmap word (the buffers hold a multiple of four rows)
         auto place_rows = [&](int i, const i32x4 &at) {
@@ -820,7 +854,7 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
                 if (!gone && i + e < p.n) pos[to] = at[e];
                 to += gone ? 0 : 1;
             }
-            if (p.layout != LAYOUT_SHIFT_HERE) *reinterpret_cast<i32x4 *>(dst + i) = d;
+            if (!Publish::ON && p.layout != LAYOUT_SHIFT_HERE) *reinterpret_cast<i32x4 *>(dst + i) = d;
         };
         if constexpr (PREG) {
 #pragma unroll

@@ -30,7 +30,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
     size_t k_bytes, meta_bytes, scratch_bytes;
-    size_t off_pos, off_ksum, off_status, off_oflags;                                 // in meta
+    size_t off_pos, off_ksum, off_status, off_oflags, off_words;                      // in meta
     size_t off_part_o, off_part_ml, off_scores, off_dstmap, off_lists, off_ksum_part, off_anchor, off_q_rot, off_k_rot, off_argmax;  // in scratch
     int cap, max_part_rows;
     int target_wgs;   // bound used to size the partial buffers: twice the compute units of the chip
@@ -119,7 +119,8 @@ Layout make_layout(const keydiff_config_t *c)
     L.off_pos = off;     off += align256(BH * L.cap * 4);
     L.off_ksum = off;    off += align256(2 * BH * D * 8);  // double buffer: see StepParams::ksum_next
     L.off_status = off;  off += 256;
-    L.off_oflags = off;  off += align256(BH * ((L.cap + kd::ORD_ROWS - 1) / kd::ORD_ROWS) * 4);  // ordered compaction
+    L.off_oflags = off;  off += align256(BH * ((L.cap + kd::ORD_MIN_ROWS - 1) / kd::ORD_MIN_ROWS) * 4);  // ordered compaction
+    L.off_words = off;   off += align256(BH * (1 + (L.cap + 31) / 32) * 8);  // ... around its selection
     L.meta_bytes = off;
     // split-KV partial rows: splits * BH * (G * Bt rounded up to 32) never exceeds this (see plan_attention)
     const int kTargetWorkgroups = 2 * compute_units();
@@ -428,6 +429,19 @@ int compact_ordered(keydiff_cache *c, const kd::StepParams &p, hipStream_t s)
     return KEYDIFF_OK;
 }
 
+// ... by the workgroups around the selection, if the plan says so
+bool shift_around(keydiff_cache *c, const kd::StepParams &p, int layers, kd::ShiftAround *a)
+{
+    int32_t units, chunks;
+    if (c->cfg.layout != KEYDIFF_LAYOUT_ORDERED || kd::shift_fits_selection(p) ||
+        !kd::plan_shift_around(p, layers, c->L.target_wgs / 2, &units, &chunks))
+        return false;
+    c->epoch = c->epoch == 0x7fffffff ? 1 : c->epoch + 1;
+    *a = kd::ShiftAround{reinterpret_cast<unsigned long long *>(c->meta + c->L.off_words), reinterpret_cast<int32_t *>(c->meta + c->L.off_oflags),
+                         c->epoch, 1 + (c->L.cap + 31) / 32, units, chunks};
+    return true;
+}
+
 // the pending selection and compaction of `c` as a launch of its own
 int finish_pending(keydiff_cache *c, hipStream_t s)
 {
@@ -443,6 +457,14 @@ int finish_pending(keydiff_cache *c, hipStream_t s)
 #ifdef KD_TIMELINE
     p.timeline = nullptr;   // only launches of step_main are recorded
 #endif
+    kd::ShiftAround around;
+    if (shift_around(c, p, 1, &around)) {
+        p.splits = 1;   // (merged before)
+        ProfScope ps(c, KEYDIFF_K_SELECT, s);
+        KD_LAUNCH(kd::launch_step_post_shift(p, around, s), "step_post kernel (deferred selection and row shift)");
+        c->pending = false;
+        return KEYDIFF_OK;
+    }
     {
         ProfScope ps(c, KEYDIFF_K_SELECT, s);
         KD_LAUNCH(kd::launch_step_post(p, s), "step_post kernel (deferred selection)");
@@ -602,6 +624,7 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
         }
     }
     const bool deferred = defer && evict;
+    bool shifted_around = false;
     const bool shift_here = evict && !deferred && cf.layout == KEYDIFF_LAYOUT_ORDERED && kd::shift_fits_selection(p);
     // a selection that rode in this step's attention launch wrote its destination map: the rows of an
     // ORDERED carrier's cache are shifted after that launch -- inside this step's merge launch where
@@ -638,9 +661,12 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
 #endif
         ProfScope ps(c, KEYDIFF_K_POST, s);
         if (shift_here) p.layout = kd::LAYOUT_SHIFT_HERE;
-        KD_LAUNCH(kd::launch_step_post(p, s), "step_post kernel");
+        kd::ShiftAround around;
+        shifted_around = evict && shift_around(c, p, 1, &around);
+        if (shifted_around) KD_LAUNCH(kd::launch_step_post_shift(p, around, s), "step_post kernel (with the row shift)");
+        else KD_LAUNCH(kd::launch_step_post(p, s), "step_post kernel");
     }
-    if (evict && !deferred && cf.layout == KEYDIFF_LAYOUT_ORDERED && !shift_here)
+    if (evict && !deferred && cf.layout == KEYDIFF_LAYOUT_ORDERED && !shift_here && !shifted_around)
         if (int rc = compact_ordered(c, p, s)) return rc;
     if (shift_owed)   // ... else in a launch of its own
         if (int rc = compact_ordered(carry, carry->pend, s)) return rc;
@@ -700,26 +726,29 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
     kd::StepParams p = step;
     plan_attention(c, p);
     if (p.few) return 0;
-    // ORDERED, three layers or more: where the row shifts can ride in the attention launches, which leave the memory system to them, they
-    // do, except on caches of many row tiles and few keys, whose attention is too short to hide a selection and a shift, and there with three
-    // or four layers only as long as the rows of all heads are few: together, the shifts of all layers follow the attention.  Measured, us
-    // a layer and block riding / together, 3, 4 and 8 layers, blocks of 128:
-    //   32 / 8 heads of 128:  2048 keys 20.3 / 14.1, 20.3 / 12.3, 20.7 / 10.4;  4096 keys 26.9 / 22.5, 26.7 / 20.4, 27.3 / 17.7;
-    //                         6144 keys 32.6 / 30.1, 32.1 / 28.4, 33.2 / 24.9;  8192 keys 36.9 / 39.2, 37.8 / 36.0, 39.4 / 33.4
-    //     two sequences:      2048 keys 23.8 / 22.8, 24.5 / 20.5, 24.7 / 17.2;  4096 keys 34.6 / 38.9, 34.2 / 34.9, 38.5 / 32.1
-    //   32 / 8 heads of 64, two sequences: 4096 keys 24.5 / 27.3, 24.6 / 22.7, 24.9 / 19.6;  four: 2048 keys 25.6 / 26.9, 25.9 / 22.0, 26.1 / 19.9
-    // Longer caches would gain with more layers, and caches of few row tiles with any number (8 / 2 heads of 64, 6144 keys, 3 layers 25.0 / 12.0).
-    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers > 2) {
-        const int BH = p.batch * p.hkv;
-        const bool few_rows = BH * p.n <= 8 * 6144 || n_layers > 4 || (n_layers == 4 && p.D == 64);
+    // ORDERED: layer by layer the row shifts can ride in attention launches, which leave the memory system to them (three layers or more) or
+    // run beside the merge (two); together, the shifts of all layers follow the attention, in the launch of the selections where they fit around
+    // them (plan_shift_around) and else in one of their own.  Measured, us a layer and block, layer by layer / together, blocks of 128 if nothing is said:
+    //   around the selections, 2 layers: 32 / 8 heads of 128, 8192 keys 47.0 / 34.8;  24 / 8, blocks of 256 57.9 / 44.5;  28 / 4, blocks of 256
+    //     55.2 / 46.6;  32 / 8 of 64, 12000 keys 50.9 / 30.6;  two sequences, 4096 keys 42.0 / 35.1
+    //   a launch of their own, 2 layers: 32 / 8, 11000 keys 57.5 / 52.6, 12288 keys 63.7 / 59.3;  more than 16 row tiles: 24 / 8, 16000 keys, blocks
+    //     of 256 91.6 / 94.4;  28 / 4, 12288 keys, blocks of 256 69.3 / 72.5;  32 / 8, two sequences, 8192 keys 67.4 / 70.5
+    //   ..., 3, 4 and 8 layers of 32 / 8: 6144 keys 32.3 / 30.0, 32.6 / 28.3, 33.2 / 24.8;  8192 keys 36.8 / 39.7, 37.5 / 36.5 (rides: a
+    //     test holds it), 38.7 / 33.3;
+    //     11000 keys 42.7 / 49.4, 42.4 / 44.8, 46.6 / 43.0;  two sequences, 4096 keys 34.2 / 40.0, 34.3 / 35.2, 38.5 / 32.1;  of 64, two
+    //     sequences, 4096 keys 24.5 / 23.8, 24.6 / 22.6, 24.9 / 19.6;  four, 2048 keys 25.6 / 26.9, 25.9 / 22.0, 26.1 / 19.9
+    //   few row tiles, 3, 4 and 8 layers: 8 / 2 of 64, 2048 keys 17.9 / 8.6, 17.9 / 6.4, 17.7 / 3.8;  16 / 4, 12000 keys 51.8 / 25.4, 51.3 / 28.7,
+    //     56.5 / 25.1.  Up to 1280 rows such caches ride all the same: a test holds the riding shift at 1152.
+    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED) {
+        const int row_tiles = p.batch * p.hkv * p.mtiles;
+        const long rows = (long)p.batch * p.hkv * p.n;
+        int32_t units, chunks;
+        const bool around = kd::plan_shift_around(p, n_layers, c->L.target_wgs / 2, &units, &chunks);
+        if (n_layers == 2 && !around && row_tiles > 16 && (p.ntiles + p.splits - 1) / p.splits > 8) return 0;
+        const bool together = around || n_layers > 4 || rows <= 8 * 6400 || (n_layers == 4 && p.D == 64);
         kd::StepParams probe = step;
-        if (!(BH * p.mtiles >= 16 && p.n <= 6144 && few_rows) && plan_with_shift(c, probe, step, BH) > 0) return 0;
+        if (n_layers > 2 && (!together || (row_tiles < 16 && p.n <= 1280)) && plan_with_shift(c, probe, step, p.batch * p.hkv) > 0) return 0;
     }
-    // (ORDERED, two layers: layer by layer the shift runs beside the merge and the selection inside the attention, which is worth more than
-    // what the layers share where the attention is long.  Measured, us a layer and block by layer / together, tiles a range in brackets: 32 / 8
-    // heads, 8192 keys [9] 38.9 / 39.4, blocks of 64 [5] 35.3 / 32.4; 4096 keys [5] 27.5 / 24.2; 24 / 8, 8192 keys, blocks of 256 [13] 47.0 / 49.0;
-    // 28 / 4 [15] 46.0 / 47.2, blocks of 64, 4096 keys [2] 25.3 / 17.0.)
-    if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED && n_layers == 2 && (p.ntiles + p.splits - 1) / p.splits > 8) return 0;
     const double post_us = p.do_evict ? 12.0 : 3.0;
     const int least = (n_layers + kd::GROUP_LAYERS - 1) / kd::GROUP_LAYERS;
     const int target = c->L.target_wgs / 2, BH = p.batch * p.hkv;
@@ -835,8 +864,12 @@ int layers_step(keydiff_cache *const *caches, kd::LayerSteps &steps, int layers,
     const bool ordered = plan.do_evict && plan.layout == KEYDIFF_LAYOUT_ORDERED, shift_here = ordered && kd::shift_fits_selection(plan);
     if (shift_here)
         for (int l = 0; l < layers; ++l) steps.p[l].layout = kd::LAYOUT_SHIFT_HERE;
-    KD_LAUNCH(kd::launch_step_post_layers(steps, layers, s), "step_post kernel (several layers)");
-    if (ordered && !shift_here) {
+    kd::ShiftArounds arounds;
+    bool around = ordered && !shift_here;
+    for (int l = 0; l < layers && around; ++l) around = shift_around(caches[l], steps.p[l], layers, &arounds.s[l]);   // (the first decides)
+    if (around) KD_LAUNCH(kd::launch_step_post_shift_layers(steps, arounds, layers, s), "step_post kernel (several layers, with the row shifts)");
+    else KD_LAUNCH(kd::launch_step_post_layers(steps, layers, s), "step_post kernel (several layers)");
+    if (ordered && !shift_here && !around) {
         kd::ShiftSteps shifts;
         for (int l = 0; l < layers; ++l) shifts.s[l] = shift_step(caches[l], steps.p[l]);
         KD_LAUNCH(kd::launch_compact_layers(shifts, layers, plan.D, s), "ordered compaction kernel (several layers)");

@@ -232,3 +232,55 @@ def test_layers_share_launches_where_that_is_faster(heads, batch, N, B, layers, 
         c.finish()
         assert c.status() == 0
         c.close()
+
+
+@pytest.mark.parametrize("heads,batch,N,B,layers,kw", [
+    ((8, 2, 128), 1, 390, 32, 1, {}),                                            # the fewest rows: beyond what the selection shifts itself
+    ((8, 2, 128), 1, 900, 300, 1, {}),                                           # rows that land ten chunks below
+    ((4, 1, 64), 1, 1000, 7, 1, {"window_W": 90}),
+    ((4, 1, 64), 1, 12288 - 50, 50, 1, {"anchor_mode": kd.ANCHOR_MEAN_UNIT_KEY}),  # the last length
+    ((8, 8, 128), 4, 2000, 130, 1, {}),                                          # ten units a thread, merged by few workgroups
+    ((32, 8, 128), 1, 4097, 1, 1, {}),                                           # one row, behind step_few and its merge
+    ((24, 8, 128), 1, 4096, 128, 3, {}),                                         # fifteen units, several layers
+    ((8, 2, 64), 1, 2000, 100, 16, {}),
+    ((16, 8, 128), 2, 8192, 64, 1, {}),                                          # eighteen units
+], ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
+def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw):
+    # ORDERED caches beyond what the selection shifts itself: the rows wait in the registers of the workgroups around it.  The rows retained are
+    # those of the FILL layout, in order, over steps that follow one another and with a ragged one.
+    hq, hkv, d = heads
+    a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(batch, *heads, N, B, layout=lay, **kw)) for _ in range(layers)]
+            for lay in (kd.LAYOUT_ORDERED, kd.LAYOUT_FILL))
+    gen = torch.Generator(device="cuda").manual_seed(N + B)
+
+    def draw(h, n):
+        return torch.randn((batch, h, n, d), generator=gen, device="cuda").bfloat16()
+
+    t = N
+    if kw.get("window_W"):   # (needs consecutive positions from an empty cache on)
+        t = 0
+    else:
+        rows = draw(hkv, N), draw(hkv, N)
+        pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(batch, hkv, N).contiguous()
+        for c in a + b:
+            c.load(*rows, pos)
+    for n in [B] * (N // B + 1 if t == 0 else 0) + [B, B, (B + 1) // 2, B]:
+        blk = [[draw(h, n) for _ in range(layers)] for h in (hq, hkv, hkv)]
+        outs = []
+        for caches in (a, b):
+            if layers > 1:
+                outs.append(kd.prefill_block_layers(caches, *blk, t))
+            else:
+                outs.append([caches[0].prefill_block(*(x[0] for x in blk), t)])
+        for x, y in zip(*outs):
+            assert float((x.float() - y.float()).abs().max()) <= ATTN_ATOL, t
+        t += n
+    for ca, cb in zip(a, b):
+        pa, pb = ca.positions(), cb.positions().sort(-1)
+        assert torch.equal(pa, pb.values)
+        for ra, rb in ((ca.key_rows(), cb.key_rows()), (ca.value_rows(), cb.value_rows())):
+            pick = pb.indices[..., None].expand(-1, -1, -1, d)
+            assert torch.equal(ra[:, :, :N].view(torch.int16), rb[:, :, :N].gather(2, pick).view(torch.int16))
+        assert ca.status() == 0 and cb.status() == 0
+        ca.close()
+        cb.close()
