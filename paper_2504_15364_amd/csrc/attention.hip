@@ -414,11 +414,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         // fold the lanes that hold the same unit (bu), then the waves
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            if constexpr (UPR == 16) bacc[i] = sum_over_rows_f64(bacc[i]);
-            else {
-#pragma unroll
-                for (int off = UPR; off < 64; off <<= 1) bacc[i] += shfl_xor_f64(bacc[i], off);
-            }
+            bacc[i] = sum_over_units_f64<UPR>(bacc[i]);
         }
         if (lane < UPR) {
 #pragma unroll

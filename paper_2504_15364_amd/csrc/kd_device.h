@@ -132,6 +132,17 @@ __device__ __forceinline__ double sum_over_rows_f64(double x)
     return pair_sum(pair_sum(x, false), true);
 }
 
+// x summed over the lanes of a wave that hold the same 16-byte unit of different rows (lane % UPR), in the order lane ^ 8 (rows of 8
+// units), ^ 16, ^ 32; every lane gets the total.  On the vector ALU alone: through LDS, the sums of eight columns of 64-wide rows took
+// a selection 0.6 us more.
+template <int UPR>
+__device__ __forceinline__ double sum_over_units_f64(double x)
+{
+    static_assert(UPR == 8 || UPR == 16, "a key row spans 8 or 16 lanes");
+    if (UPR == 8) x = dpp_add_f64<0x128>(x);   // row_ror:8
+    return sum_over_rows_f64(x);
+}
+
 // the double another lane holds, fetched by a DPP control word (rows of 16 lanes)
 template <int CTRL>
 __device__ __forceinline__ double dpp_fetch_f64(double x)
