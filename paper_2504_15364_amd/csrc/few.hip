@@ -41,9 +41,8 @@ constexpr float FEW_RESCALE_SLACK = 64.f;   // the reference maximum may lag by 
 template <int D>
 constexpr size_t few_lds_bytes()
 {
-    // V tiles of the waves, later the outputs of the waves (float, 16 rows each)
-    const size_t v = (size_t)FEW_WAVES * FEW_KEYS * D * 2, o = (size_t)FEW_WAVES * 16 * D * 4;
-    return v > o ? v : o;
+    // V tiles of the waves, and their outputs (float, 16 rows each) in a place of their own: a wave that is done waits for no other's V
+    return (size_t)FEW_WAVES * FEW_KEYS * D * 2 + (size_t)FEW_WAVES * 16 * D * 4;
 }
 
 // max over the four 16-lane rows of a wave, position by position (every lane gets it)
@@ -105,10 +104,10 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ double bs_part[NW][D];
-    __shared__ double mu_s[D];
+    __shared__ double mu_s[D], mu_w[NW][D];
     __shared__ double red[D / 16];
     __shared__ float2 ml_s[NW][16];
-    __shared__ unsigned long long rec_s[NW][2];
+    __shared__ unsigned long long rec_s[NW][64];   // every lane's best row, its tie flag in bit 31
 
     KD_TL_DECL
     KD_TL(0);
@@ -138,9 +137,20 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     const bool scoring = p.do_score != 0 && mt == 0;   // one of the workgroups that share a key range scores it
     const bool need_sum = scoring || writer;
     const int bu = tid % UPR, brl = tid / UPR;
+    // One token and the plain anchor: every wave forms the anchor by itself, columns lane and lane + 64, in the arithmetic of the general way.
+    // Nothing waits for the other waves, which are still requesting their tiles (two barriers there ended 5.9 us after the launch began).
+    const bool alone = p.Bt == 1 && p.anchor_mode == 0;   // uniform
+    constexpr int WC = D / 64;   // columns a lane
     u32x4 brow = {0u, 0u, 0u, 0u};
-    double ksum_before = 0.0;
-    if (need_sum) {
+    double ksum_before = 0.0, wsum[WC];
+    uint16_t wkey[WC];
+    if (alone) {
+#pragma unroll
+        for (int i = 0; i < WC; ++i) {
+            wkey[i] = knew[lane + 64 * i];
+            wsum[i] = p.ksum[(size_t)bh * D + lane + 64 * i];
+        }
+    } else if (need_sum) {
         if (brl < p.Bt) brow = *reinterpret_cast<const u32x4 *>(knew + (size_t)brl * D + bu * 8);
         if (tid < D) ksum_before = p.ksum[(size_t)bh * D + tid];
     }
@@ -218,7 +228,24 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     // ---- anchor: key sum after this step = key sum before it + the block's keys (at most 32 rows)
     double ksum_after = 0.0;
     double nmu2 = 0.0;   // |mu|^2
-    if (need_sum) {
+    const double *mu = alone ? mu_w[wave] : mu_s;
+    if (alone) {
+        double sq[WC];
+#pragma unroll
+        for (int i = 0; i < WC; ++i) {
+            wsum[i] += bf16_hi((uint32_t)wkey[i] << 16);
+            const double m = wsum[i] / (double)p.n;
+            mu_w[wave][lane + 64 * i] = m;
+            sq[i] = row_allreduce_f64<16>(m * m);
+        }
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i) {   // piece i is in the lanes of row i % 4
+            const int from = 16 * (i % 4);
+            nmu2 += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(sq[i / 4]), from),
+                                     __builtin_amdgcn_readlane(__double2loint(sq[i / 4]), from));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (the wave reads what it wrote)
+    } else if (need_sum) {
         double bacc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) bacc[i] = 0.0;
@@ -336,7 +363,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
             for (int c = 0; c < NC; ++c) {
                 double m8[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) m8[i] = mu_s[32 * c + 8 * g + i];
+                for (int i = 0; i < 8; ++i) m8[i] = mu[32 * c + 8 * g + i];
 #pragma unroll
                 for (int kg = 0; kg < 2; ++kg)
 #pragma unroll
@@ -412,30 +439,39 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
     KD_TL(5);   // tiles done
     if (scoring) flush_scores();   // (an odd number of tiles leaves half a wave's rows)
 
-    if (writer && tid < D) p.ksum_next[(size_t)bh * D + tid] = ksum_after;
+    if (writer) {
+        if (alone) {
+#pragma unroll
+            for (int i = 0; i < WC; ++i)
+                if (wave == 0) p.ksum_next[(size_t)bh * D + lane + 64 * i] = wsum[i];
+        } else if (tid < D) p.ksum_next[(size_t)bh * D + tid] = ksum_after;
+    }
 
     // ---- the eight results become one
     KD_TL(6);   // scores finished
-    __syncthreads();   // every wave is done with its V tile
-    KD_TL(7);   // every wave done
-    float *ow = reinterpret_cast<float *>(smem) + (size_t)wave * 16 * D;
+    float *const outs = reinterpret_cast<float *>(smem + (size_t)NW * FEW_KEYS * ROWB);
+    float *ow = outs + (size_t)wave * 16 * D;
     if (c16 < mrows) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db) *reinterpret_cast<f32x4 *>(ow + c16 * D + 16 * db + 4 * g) = oacc[db];
         if (g == 0) ml_s[wave][c16] = make_float2(mref, lacc[0]);
     }
-    if (scoring && p.argmax_rec) {   // uniform
-        wave_argmax(am_best, am_tie);
-        if (lane == 0) {
-            rec_s[wave][0] = am_best;
-            rec_s[wave][1] = am_tie ? 1ull : 0ull;
-        }
-    }
+    if (scoring && p.argmax_rec) rec_s[wave][lane] = am_best | (am_tie ? 0x80000000ull : 0ull);   // uniform (a row number takes 15 bits)
     __syncthreads();
     KD_TL(8);   // results and arg-max records in LDS
     if (scoring && p.argmax_rec && wave == NW - 1) {   // (the last wave: with few query rows it has nothing to merge)
-        unsigned long long best = lane < NW ? rec_s[lane & (NW - 1)][0] : 0;
-        bool tie = lane < NW && rec_s[lane & (NW - 1)][1] != 0;
+        unsigned long long best = 0;
+        bool tie = false;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {   // (as the records of different lanes are combined)
+            const unsigned long long r = rec_s[w][lane], row = r & ~0x80000000ull;
+            const bool rt = (r & 0x80000000ull) != 0;
+            const uint32_t hr = (uint32_t)(r >> 32), hb = (uint32_t)(best >> 32);
+            if (hr > hb) {
+                best = row;
+                tie = rt;
+            } else if (hr == hb && hr != 0) tie = true;
+        }
         wave_argmax(best, tie);
         if (lane == 0) {
             unsigned long long *rec = p.argmax_rec + ((size_t)bh * p.splits + sp) * 2;
@@ -454,7 +490,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES) void step_few_kernel(StepParams p)
         for (int w = 0; w < NW; ++w) {
             const float2 ml = ml_s[w][m];
             const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - mx);
-            const f32x4 o = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(smem) + ((size_t)w * 16 + m) * D + d0);
+            const f32x4 o = *reinterpret_cast<const f32x4 *>(outs + ((size_t)w * 16 + m) * D + d0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[i] += f * o[i];
             L += f * ml.y;
