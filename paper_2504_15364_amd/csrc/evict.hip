@@ -266,20 +266,23 @@ __device__ __forceinline__ void merge_thread(const StepParams &p, size_t thread,
     else merge_rows_few_splits<D>(p, thread, threads);
 }
 
-// The merge of step_few's partials (float, [psplits][BH][G * Bt][D], each normalised by its row sum): one
-// workgroup per head, a thread per four output values and share of the splits.  What bounds it is the
-// trip to memory: the splits are dealt over the threads that are left (with 4 rows of 128 eight ways), so
-// that 32 splits are one round of loads, not 32 loads in a row, and the shares are added up through LDS.
+// The merge of step_few's partials (float, [psplits][BH][G * Bt][D], each normalised by its row sum): workgroup
+// `part` of `parts` of a head takes its share of the rows, a thread four output values and a share of the splits.  What bounds it is the
+// trip to memory: the splits are dealt over the threads eight ways, so
+// that 32 splits are one round of loads, not 32 loads in a row, and the shares are added up through LDS; and a compute unit takes in
+// some 57 KB a microsecond, 4 rows of 128 in 32 splits are 64 KB: a workgroup a row ends with the eviction beside it (2.9 -> 2.4 us).
 template <int D>
-__device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int bh)
+__device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int bh, int part_, int parts)
 {
     constexpr int MB = 8;                       // splits requested together
+    constexpr int SHARES = 8;
     const int BH = p.batch * p.hkv, Mtot = p.G * p.Bt;
-    const int items = Mtot * (D / 4);           // at most POST_THREADS (32 rows of 128)
-    const int shares = min(POST_THREADS / items, p.splits);
+    const int m0 = part_ * Mtot / parts, rows = (part_ + 1) * Mtot / parts - m0;
+    const int items = rows * (D / 4);           // at most POST_THREADS (32 rows of 128)
+    const int shares = min(min(POST_THREADS / items, SHARES), p.splits);
     const int it = (int)threadIdx.x % items, share = (int)threadIdx.x / items;
-    const float *part = reinterpret_cast<const float *>(p.part_o) + (size_t)bh * Mtot * D + (size_t)it * 4;
-    const float2 *mls = p.part_ml + (size_t)bh * Mtot + it / (D / 4);
+    const float *part = reinterpret_cast<const float *>(p.part_o) + ((size_t)bh * Mtot + m0) * D + (size_t)it * 4;
+    const float2 *mls = p.part_ml + (size_t)bh * Mtot + m0 + it / (D / 4);
     const size_t pstride = (size_t)BH * Mtot * D, mstride = (size_t)BH * Mtot;
     float mx = -INFINITY, Lsum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -339,7 +342,7 @@ __device__ __forceinline__ void merge_few(const StepParams &p, float *lds, int b
     bf16x4 o;
 #pragma unroll
     for (int r = 0; r < 4; ++r) o[r] = (__bf16)(acc[r] * inv);
-    *reinterpret_cast<bf16x4 *>(p.out + (size_t)bh * p.G * p.Bt * D + (size_t)it * 4) = o;
+    *reinterpret_cast<bf16x4 *>(p.out + ((size_t)bh * Mtot + m0) * D + (size_t)it * 4) = o;
 }
 
 // The merge as a kernel of its own (a step whose eviction is deferred has nothing else to run
@@ -394,7 +397,7 @@ __device__ __forceinline__ void post_body(const StepParams &p, int block)
         const unsigned long long started = wall_clock64();
 #endif
         static_assert(sizeof(PostShared) >= POST_THREADS * 6 * sizeof(float), "the merge of step_few's partials uses the selection's tables");
-        if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), block - n_select);
+        if (p.few) merge_few<D>(p, reinterpret_cast<float *>(&sh), (block - n_select) % (p.batch * p.hkv), (block - n_select) / (p.batch * p.hkv), p.merge_wgs / (p.batch * p.hkv));
         else merge_thread<D>(p, (size_t)(block - n_select) * POST_THREADS + threadIdx.x, (size_t)p.merge_wgs * POST_THREADS);
 #ifdef KD_TIMELINE
         __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -443,7 +446,8 @@ __device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAro
     uint16_t *base = (tid >= POST_THREADS / 2 ? p.v : p.k) + (size_t)bh * p.cap * D + tid % UPR * 8;
     if (p.splits > 1) {   // uniform, like the branches in it
         if (p.few) {
-            if (chunk == 0) merge_few<D>(p, reinterpret_cast<float *>(&sh), bh);
+            const int parts = min(p.merge_wgs / BH, sa.chunks);
+            if (chunk < parts) merge_few<D>(p, reinterpret_cast<float *>(&sh), bh, chunk, parts);
         } else {
             const size_t items = (size_t)BH * ((p.G * p.Bt + 31) / 32) * SLABS * 64;
             for (size_t g = (size_t)index * POST_THREADS + tid; g < items; g += (size_t)BH * sa.chunks * POST_THREADS) merge_rows<D>(p, g);

@@ -329,7 +329,7 @@ void plan_attention(const keydiff_cache *c, kd::StepParams &p, int reserved = 0)
         // the float partials take two of the scratch buffer's fp16 rows each
         while (splits > 1 && 2l * splits * BH * Mtot > c->L.max_part_rows) --splits;
         p.splits = splits;
-        p.merge_wgs = splits > 1 ? BH : 0;
+        p.merge_wgs = splits > 1 ? BH * std::min(Mtot, std::max(1, target / 4 / BH)) : 0;   // (see merge_few)
         return;
     }
     // 8-wave workgroups run one per compute unit: rounding the split count up would push the last
