@@ -788,6 +788,9 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
 
     const int tint = min(t1, max(t0, p.len / TILE_KEYS));  // tiles before it: every key cached, no mask
     f32x16 s[NQ][2];
+    float mloc[NQ];   // per-lane maxima of the logits of the tile whose weights come next
+#pragma unroll
+    for (int a = 0; a < NQ; ++a) mloc[a] = -INFINITY;
     if (ntl > 0) {
         // ---- prologue: every wave has its queries in registers and its part of tiles t0, t0 + 1 in
         // LDS; the staging buffers are free for tile t0 + 2, which flies while S^T of tile t0 is formed
@@ -824,7 +827,6 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (active) {
             qk_tile(smem + (size_t)(t0 % STAGES) * 2 * TILE_B, s);
             if (t0 >= tint) mask_tile(s, t0 * TILE_KEYS);
-            float mloc[NQ];
             tile_max(s, mloc);
 #pragma unroll
             for (int a = 0; a < NQ; ++a)   // first reference: nothing accumulated yet, nothing to rescale
@@ -842,21 +844,33 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     //   stage B  the 4 NDB MFMA groups of O^T += V^T P^T(t), each with the V^T fragment read a few
     //            groups ahead, the rest of the exponentials and one slice of the max scan of tile t + 1;
     //   then the cosine score of tile t's rows if this workgroup owns them.
+    // The reference of tile t is decided behind the first three products of stage A: its chain (lane exchange, comparison, ballot, branch: 200
+    // cycles of a wave) is waited for by the weights, not by them.  With the max scan held in stage B (the compiler had put it behind the
+    // score) a pass over the prompt takes, us: 32 / 8 heads, 8192 keys, 4 layers 19654 / 19505, one 2500 / 2475 (ORDERED), 4096 keys
+    // 3434 / 3409;  28 / 4, 2 layers 6801 / 6746;  24 / 8, 3 layers 4601 / 4548;  16384 keys in blocks of 512 6132 / 6077.
     // The scheduling barriers pin that order.  Tiles t + 2 and t + 3 are in flight meanwhile.
+    auto open_step = [&](int t) {
+        // tile t + 1 has landed when at most the copies of tile t + 2 remain; the barrier
+        // publishes every wave's part and retires the buffer tile t - 1 used
+        if (t + 2 < t1) wait_copies<LPW>();
+        else wait_copies<0>();
+        __syncthreads();
+    };
     // COPY: 0 no tile left to fetch, 1 the tile to fetch lies entirely in the cache, 2 decide per copy
     auto step = [&](int t, f32x16 (&sc)[NQ][2], f32x16 (&sn)[NQ][2], auto next_tag, auto masked_tag, auto copy_tag) {
         constexpr bool NEXT = decltype(next_tag)::value, MASKED = decltype(masked_tag)::value;
         constexpr int COPY = decltype(copy_tag)::value;
         constexpr int NA = 2 * NC, NB = 4 * NDB;
         static_assert((NA == 16 && NB == 16) || (NA == 8 && NB == 8), "slice counts below assume D = 128 or 64");
-        // The exponential slices are spread evenly over stage A and the first half of stage B (whose
-        // second half multiplies with the weights computed last): group g runs in slot g SLOTS / NG,
+        // The exponential slices are spread evenly over stage A, but for its first REF slots, and most of stage B (whose
+        // last quarter multiplies with the weights computed last): group g runs in slot REF + g (SLOTS - REF) / NG,
         // slots [0, NA) being the steps of stage A and [NA, SLOTS) steps of stage B.
+        constexpr int REF = NEXT ? NA * 3 / 16 : 0;
         constexpr int NS = 32 * NQ / SL;           // exponential slices per tile
-        constexpr int SLOTS = NA + NB / 2;
+        constexpr int SLOTS = NEXT ? NA + NB * 3 / 4 : NA + NB / 2;
         constexpr int SPG = NS > SLOTS ? 2 : 1;    // slices per group
         constexpr int NG = NS / SPG;
-        auto slot_of = [](int g) { return g * SLOTS / NG; };
+        auto slot_of = [](int g) { return REF + g * (SLOTS - REF) / NG; };
         // one pipeline beat: E of group g, C of group g - 1, F of group g + 1
         auto beat = [&](int g, float (&arg)[2][SPG][SL], float (&ex)[2][SPG][SL], bf16x8 (&pk)[NQ][4]) {
             if (g < NG) {
@@ -878,34 +892,22 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         bf16x8 pk[NQ][4];
         bf16x8 kf[KAHEAD + 1], vf[VAHEAD + 1];
         float arg[2][SPG][SL], ex[2][SPG][SL];
-        if (NEXT) {
-            // tile t + 1 has landed when at most the copies of tile t + 2 remain; the barrier
-            // publishes every wave's part and retires the buffer tile t - 1 used
-            if (t + 2 < t1) wait_copies<LPW>();
-            else wait_copies<0>();
-            __syncthreads();
-        }
+        if (NEXT) open_step(t);
 #ifdef KD_TIMELINE
         if (t == t0 + 2) KD_TL(16);   // step t0 + 2: barrier passed
         if (t == t0 + 3) KD_TL(20);
 #endif
-        if (HELP && !active) {
-            if (NEXT) {
-#pragma unroll
-                for (int c = 0; c < LPW; ++c) {
-                    if (COPY == 1) issue_copy_cached(t + STAGES - 1, c);
-                    if (COPY == 2 && t + STAGES - 1 < t1) issue_copy(t + STAGES - 1, c);
-                }
-            }
-            if (t == next_score) score_tile(t);
-            return;
-        }
         if (NEXT) {
 #pragma unroll
             for (int i = 0; i < KAHEAD; ++i) kf[i] = read_k(tK, i);
         }
+        // the reference of tile t, decided behind the first products of stage A, which do not wait for it
+        auto first_arguments = [&]() {
+            if (t != t0) new_reference(mloc);   // (the first tile's logits made the first reference)
 #pragma unroll
-        for (int e = 0; e < SPG; ++e) slice_F(sc, e, arg[0][e]);
+            for (int e = 0; e < SPG; ++e) slice_F(sc, e, arg[0][e]);
+        };
+        if (!NEXT) first_arguments();
         const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
@@ -928,6 +930,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
                     if (COPY == 2 && t + STAGES - 1 < t1) issue_copy(t + STAGES - 1, c);
                 }
             }
+            if (NEXT && i == REF - 1) first_arguments();
 #pragma unroll
             for (int g = 0; g < NG; ++g)
                 if (slot_of(g) == i) beat(g, arg, ex, pk);
@@ -978,18 +981,19 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         if (t == t0 + 2) KD_TL(18);   // stage B done
         if (t == t0 + 3) KD_TL(22);
 #endif
+        if (NEXT) {
+#pragma unroll
+            for (int a = 0; a < NQ; ++a) {
+                mloc[a] = max3(mch[a][0], mch[a][1], mch[a][0]);
+                asm volatile("" : "+v"(mloc[a]));   // (here: the compiler would take the max scan out of stage B to where its result is used)
+            }
+        }
         // tile t is still in its buffer (recycled in the next iteration): score its rows
         if (t == next_score) score_tile(t);
 #ifdef KD_TIMELINE
         if (t == t0 + 2) KD_TL(19);   // tile scored (if this workgroup owns it)
         if (t == t0 + 3) KD_TL(23);
 #endif
-        float mloc[NQ];
-#pragma unroll
-        for (int a = 0; a < NQ; ++a) mloc[a] = NEXT ? max3(mch[a][0], mch[a][1], mch[a][0]) : 0.f;
-        if (NEXT) {
-            new_reference(mloc);
-        }
     };
     // Four loops, so that the common iterations carry no decisions: (1) tile t + 1 unmasked and tile
     // t + 3 entirely cached; (2) tile t + 1 unmasked, nothing left to fetch; (3) the general case
@@ -1012,14 +1016,22 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     };
     int t = t0;
     const int lim1 = min(tint, t1);
-    for (; t + STAGES < lim1; t += 2) {
-        step(t, s, s2, T_{}, F_{}, std::integral_constant<int, 1>{});
-        step(t + 1, s2, s, T_{}, F_{}, std::integral_constant<int, 1>{});
+    if (HELP && !active) {   // a wave without query rows: its share of the copies, and rows to score
+        for (; t < t1; ++t) {
+            if (t + 1 < t1) open_step(t);
+            if (t + STAGES - 1 < t1) issue_tile(t + STAGES - 1);
+            if (t == next_score) score_tile(t);
+        }
+    } else {
+        for (; t + STAGES < lim1; t += 2) {
+            step(t, s, s2, T_{}, F_{}, std::integral_constant<int, 1>{});
+            step(t + 1, s2, s, T_{}, F_{}, std::integral_constant<int, 1>{});
+        }
+        for (; t + STAGES - 1 < lim1; ++t) step1(t, T_{}, F_{}, std::integral_constant<int, 1>{});
+        const int lim2 = t + STAGES - 1 >= t1 ? tint : 0;
+        for (; t + 1 < lim2; ++t) step1(t, T_{}, F_{}, std::integral_constant<int, 0>{});
+        for (; t + 1 < t1; ++t) step1(t, T_{}, T_{}, std::integral_constant<int, 2>{});
     }
-    for (; t + STAGES - 1 < lim1; ++t) step1(t, T_{}, F_{}, std::integral_constant<int, 1>{});
-    if (t + STAGES - 1 >= t1)
-        for (; t + 1 < tint; ++t) step1(t, T_{}, F_{}, std::integral_constant<int, 0>{});
-    for (; t + 1 < t1; ++t) step1(t, T_{}, T_{}, std::integral_constant<int, 2>{});
 
     KD_TL(8);   // all steps but the last done
     // ---- append (Eq. 5): this workgroup's slice of the block's rows.  The attention reads the
@@ -1035,7 +1047,7 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
         aval = *reinterpret_cast<const u32x4 *>((which ? vnew : knew) + (size_t)(j0 + rem / UPR) * D + (rem % UPR) * 8);
     }
 
-    if (ntl > 0) step1(t, F_{}, F_{}, std::integral_constant<int, 0>{});
+    if (ntl > 0 && active) step1(t, F_{}, F_{}, std::integral_constant<int, 0>{});
     KD_TL(9);   // last tile done
 
     // ---- output: stored first, so that the write latency runs under the score flush and the append
