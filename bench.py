@@ -593,6 +593,11 @@ def main():
         us = ordered_kernels["compact_ordered"]["event_bracket_us"]
         hbm_kernels["compact_ordered_kernel"] = {"bytes_upper_bound": cb, "event_bracket_us": us, "GBps": cb / us / 1e3,
                                                  "frac_of_hbm_peak": cb / us / 1e3 / PEAK_HBM_GBPS}
+    elif ordered_kernels and "step_post" in ordered_kernels:   # the shift runs around the selection, in one launch with it and the merge
+        cb = 2 * 2 * Hkv * N * D * 2
+        us = ordered_kernels["step_post"]["event_bracket_us"]
+        hbm_kernels["step_post_shift_kernel"] = {"bytes_upper_bound": cb, "event_bracket_us": us, "GBps": cb / us / 1e3,
+                                                 "frac_of_hbm_peak": cb / us / 1e3 / PEAK_HBM_GBPS}
     if scores_pass:
         hbm_kernels["step_score_kernel"] = scores_pass
     if modes:

@@ -272,7 +272,8 @@ enum {
     KEYDIFF_K_SCORE = 1,   /* step_score: cosine scores outside a block step (keydiff_scores)  */
     KEYDIFF_K_POST = 2,    /* step_post: partial merge || selection and compaction of the step (the
                               merge alone when the eviction is deferred)                       */
-    KEYDIFF_K_COMPACT = 3, /* stable in-place row shift (ORDERED layout only)                  */
+    KEYDIFF_K_COMPACT = 3, /* stable in-place row shift (ORDERED layout, where it is a launch of its own
+                              and not part of step_post or of the selection alone)             */
     KEYDIFF_K_AUX = 4,     /* cache load helpers                                               */
     KEYDIFF_K_EVENT_PAIR = 5, /* no kernel: an empty event pair recorded once per profiled block
                               step; its time is what the two records themselves add to every

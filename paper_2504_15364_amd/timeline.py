@@ -64,7 +64,6 @@ FEW_PHASES = [
     (4, "... scored"),
     (5, "tiles done"),
     (6, "scores finished"),
-    (7, "every wave done"),
     (8, "results and arg-max records in LDS"),
     (9, "partial stored"),
     (12, "stores acknowledged (workgroup ends)"),

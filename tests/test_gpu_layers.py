@@ -284,3 +284,49 @@ def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw):
         assert ca.status() == 0 and cb.status() == 0
         ca.close()
         cb.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,Bt,anchor", [
+    (7, 1, 128, 1, kd.ANCHOR_MEAN_KEY),        # seven workgroups for seven rows
+    (28, 4, 128, 1, kd.ANCHOR_MEAN_KEY),
+    (28, 4, 64, 2, kd.ANCHOR_MEAN_KEY),        # fourteen rows of a head
+    (16, 1, 64, 1, kd.ANCHOR_MEAN_UNIT_KEY),   # the anchor by all waves together
+    (1, 1, 128, 3, kd.ANCHOR_MEAN_KEY),
+    (32, 1, 128, 1, kd.ANCHOR_MEAN_KEY),       # two workgroups share a key range
+])
+def test_generation_steps_against_plain_attention(hq, hkv, d, Bt, anchor):
+    # steps of few query rows behind a long cache: every wave forms the anchor of a single token by itself, and the partials are merged by a
+    # workgroup a row.  Outputs against float64; the rows that stay are those of the highest scores' complement, as keydiff_scores of the same rows has them.
+    N, G = 4100, hq // hkv
+    gen = torch.Generator(device="cuda").manual_seed(hq * 131 + d + Bt)
+
+    def draw(h, n):
+        return torch.randn((1, h, n, d), generator=gen, device="cuda").bfloat16()
+
+    cache = kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N, Bt, layout=kd.LAYOUT_ORDERED, anchor_mode=anchor))
+    K, V = draw(hkv, N), draw(hkv, N)
+    cache.load(K, V, torch.arange(N, dtype=torch.int32, device="cuda").expand(1, hkv, N).contiguous())
+    full = kd.KeyDiffCache(kd.KeyDiffConfig(1, hq, hkv, d, N + Bt, Bt, layout=kd.LAYOUT_ORDERED, anchor_mode=anchor))
+    pos = torch.arange(N, device="cuda").expand(hkv, N)
+    for i in range(3):
+        q, k, v = draw(hq, Bt), draw(hkv, Bt), draw(hkv, Bt)
+        t = N + i * Bt
+        out = cache.prefill_block(q, k, v, t)
+        K, V = torch.cat([K, k], 2), torch.cat([V, v], 2)
+        pos = torch.cat([pos, torch.arange(t, t + Bt, device="cuda").expand(hkv, Bt)], 1)
+        kk, vv = (x[0].double().repeat_interleave(G, 0) for x in (K, V))
+        logits = (q[0].double()[:, :, None, :] * kk[:, None]).sum(-1) / d ** 0.5
+        late = torch.arange(N + Bt, device="cuda")[None, :] > N + torch.arange(Bt, device="cuda")[:, None]
+        w = logits.masked_fill(late, -torch.inf).softmax(-1)
+        want = (w[..., None] * vv[:, None]).sum(2)
+        assert float((out[0].double() - want).abs().max()) <= ATTN_ATOL, t
+        full.load(K.contiguous(), V.contiguous(), pos[None].int().contiguous())
+        scores = full.scores()[0].double()
+        leave = torch.zeros_like(scores, dtype=torch.bool).scatter_(1, scores.topk(Bt, 1).indices, True)   # (no two scores are alike)
+        keep = (~leave).nonzero()[:, 1].view(hkv, N)
+        pos = pos.gather(1, keep)
+        K, V = (x.gather(2, keep[None, :, :, None].expand(-1, -1, -1, d)) for x in (K, V))
+        assert torch.equal(cache.positions()[0].long(), pos), t
+    assert cache.status() == 0
+    cache.close()
+    full.close()
