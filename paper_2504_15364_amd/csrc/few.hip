@@ -15,9 +15,9 @@
 // step_post from float partials.  Measured per step against step_main with two waves sharing the key tiles
 // (attention + merge and selection, 32 / 8 heads, N = 8192): one sequence 14.3 + 22.9 -> 15.0 + 4.0 us,
 // sixteen sequences 106.9 + 6.9 -> 98 + 4.8 us (537 MB: 5.5 TB/s).  By the stamps of one sequence the
-// anchor is formed 5.9 us after the launch began, the tiles are done at 8.1 and the partials stored at 10.5; of the chain behind the data
-// the arg-max (six exchanges of 64-bit pairs through LDS, then one thread over eight records) took 2 us more: on the
-// vector ALU, and the eight records by a wave that has nothing to merge, the launch went from 14.5 to 13.7 us.
+// anchor is formed 4.2 us after the launch began (5.9 behind barriers for which every wave had to have requested its tiles), the tiles are done
+// at 6.3 (8.1) and the partials stored at 9.0 (10.5); of the chain behind the data the arg-max (six exchanges of 64-bit pairs through LDS, then
+// one thread over eight records) took 2 us more once: it is the work of one wave that has nothing to merge, on the vector ALU.
 //
 //   S^T = K Q^T  A = K rows, loaded straight from memory in operand layout (lane: row l % 16, 16 bytes at
 //                32 c + 8 (l / 16): 64 contiguous bytes per row and instruction); B = Q^T (registers)
