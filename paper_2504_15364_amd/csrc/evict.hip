@@ -432,29 +432,40 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_layers_kernel(LayerSte
 // The shift behind a selection needs its bitmap and nothing else of it, and reading the rows, half of the shift's work, needs not
 // even that.  So the two run in one launch: workgroup `index` behind the selections requests its rows into registers, merges its share of the
 // attention partials, and waits for the bitmap of its head and for the chunks below it that its rows may land in; then it stores.  The grid is
-// no larger than the chip, and a workgroup waits for lower-numbered ones only; waits are bounded and report a timeout instead of hanging.
+// no larger than the chip.
+// Who does what is dealt by tickets: the first workgroup of a head that starts selects, the ones after it take the chunks from the lowest up.  So
+// a workgroup waits only for ones that have started, and those need nothing but their turn on the compute unit they hold -- whatever order the XCDs
+// start workgroups in, and whatever other launches (other caches on other streams) hold or wait for the rest of the chip.  By block number instead,
+// two such launches could each fill an XCD with workgroups that wait for one queued on the other's.  Workgroups [0, BH) expect the first ticket and
+// begin the selection while it travels (PublishWords); the others merge before they draw, else they often are the first (8192 rows: a step
+// 2 us longer).  Measured against roles by block number, us a step: 8 heads of 128, 8192 rows 43.5 / 44.2, 4096 rows, three layers together
+// 70.4 / 71.5.  Waits are bounded all the same and report a timeout instead of hanging.
 // Thread: K rows in the first half of the workgroup, V rows in the second, TROWS rows apart.
 // What bounds it: the selection up to its bitmap (8 us at 8320 rows), then one store of the rows, with the hint that nothing reads them
 // again here (1.5 to 3 % of a step less than without).  The merge goes first: behind the requests of the rows, which hold registers, it
-// took 1 % of a step more.  A step with both launches / with this one, us: 8 heads of 128, 32 query heads, blocks of 128, 2048 rows
+// took 1 % of a step more.  A step with both launches / with this one (roles by block number), us: 8 heads of 128, 32 query heads, blocks of 128, 2048 rows
 // 31.8 / 29.9, 4096 40.7 / 35.9, 8192 54.9 / 43.1, 11000 68.0 / 53.8;  2 heads, 8192 rows 38.5 / 33.8;  8 of 64, two sequences, 4096 rows 39.4 / 33.1.
 template <int D>
-__device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAround &sa, PostShared &sh, int index)
+__device__ __forceinline__ void merge_around(const StepParams &p, const ShiftAround &sa, PostShared &sh, int index)
 {
-    constexpr int UPR = D / 8, SLABS = D / 8, TROWS = POST_THREADS / 2 / UPR;
-    const int BH = p.batch * p.hkv, tid = threadIdx.x;
-    const int bh = index % BH, chunk = index / BH, rows = sa.units * TROWS;
+    constexpr int SLABS = D / 8;
+    const int BH = p.batch * p.hkv;
+    if (p.splits <= 1) return;   // uniform, like the branches below
+    if (__builtin_expect(p.few != 0, 0)) {
+        const int parts = min(p.merge_wgs / BH, sa.chunks);
+        if (index / BH < parts) merge_few<D>(p, reinterpret_cast<float *>(&sh), index % BH, index / BH, parts);
+    } else {
+        const size_t items = (size_t)BH * ((p.G * p.Bt + 31) / 32) * SLABS * 64;
+        for (size_t g = (size_t)index * POST_THREADS + threadIdx.x; g < items; g += (size_t)BH * sa.chunks * POST_THREADS) merge_rows<D>(p, g);
+    }
+}
+template <int D>
+__device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAround &sa, PostShared &sh, int bh, int chunk)
+{
+    constexpr int UPR = D / 8, TROWS = POST_THREADS / 2 / UPR;
+    const int tid = threadIdx.x, rows = sa.units * TROWS;
     const int row0 = chunk * rows + tid % (POST_THREADS / 2) / UPR;
     uint16_t *base = (tid >= POST_THREADS / 2 ? p.v : p.k) + (size_t)bh * p.cap * D + tid % UPR * 8;
-    if (p.splits > 1) {   // uniform, like the branches in it
-        if (__builtin_expect(p.few != 0, 0)) {
-            const int parts = min(p.merge_wgs / BH, sa.chunks);
-            if (chunk < parts) merge_few<D>(p, reinterpret_cast<float *>(&sh), bh, chunk, parts);
-        } else {
-            const size_t items = (size_t)BH * ((p.G * p.Bt + 31) / 32) * SLABS * 64;
-            for (size_t g = (size_t)index * POST_THREADS + tid; g < items; g += (size_t)BH * sa.chunks * POST_THREADS) merge_rows<D>(p, g);
-        }
-    }
     u32x4 val[AROUND_UNITS];
 #pragma unroll
     for (int q = 0; q < AROUND_UNITS; ++q)
@@ -507,14 +518,37 @@ __device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAro
         }
     }
 }
+// (wrapping at 2^32 - 1, so an addition of 1: an addition would be done for the wave and waited for on the spot)
+__device__ __forceinline__ uint32_t draw_ticket(uint32_t *counter)
+{
+    return __builtin_amdgcn_atomic_inc32(counter, 0xFFFFFFFFu, __ATOMIC_RELAXED, "agent");
+}
 template <int D>
 __device__ __forceinline__ void post_shift_body(const StepParams &p, const ShiftAround &sa, int block)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     __shared__ PostShared sh;
-    const int BH = p.batch * p.hkv;
-    if (block < BH) select_and_compact<D, 3, POST_THREADS, false>(p, sh, smem_raw, block, PublishWords{sa});
-    else shift_around<D>(p, sa, sh, block - BH);
+    __shared__ uint32_t ticket;
+    const int BH = p.batch * p.hkv, bh = block % BH;
+    bool select = block < BH;   // uniform, like the branches below
+    if (!select) merge_around<D>(p, sa, sh, block - BH);
+    uint32_t drawn = 0;
+    if (threadIdx.x == 0) drawn = draw_ticket(sa.tickets + (size_t)bh * TICKET_STRIDE);
+    const PublishWords publish{sa, drawn, &ticket};
+    if (!select) {
+        publish.arrive();
+        __syncthreads();
+        select = publish.mine();
+    }
+    if (select) {
+        select_and_compact<D, 3, POST_THREADS, false>(p, sh, smem_raw, bh, publish);
+        if (publish.mine()) return;
+    }
+    if (ticket > (uint32_t)sa.chunks) {   // (impossible)
+        if (threadIdx.x == 0) atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+        return;
+    }
+    shift_around<D>(p, sa, sh, bh, (int)ticket - 1);
 }
 template <int D>
 __global__ __launch_bounds__(POST_THREADS) void step_post_shift_kernel(StepParams p, ShiftAround sa)

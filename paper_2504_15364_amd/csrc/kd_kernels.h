@@ -36,6 +36,7 @@ constexpr int LAYOUT_SHIFT_HERE = 2;  // StepParams::layout: ORDERED, and the se
 constexpr int ORD_ROWS = 128;       // rows per workgroup of the ordered compaction
 constexpr int ORD_THREADS = 1024;   // ... and its threads: 4 16-byte units each
 constexpr int ORD_MIN_ROWS = 32;    // fewest rows a workgroup of a shift takes: one flag each in the metadata
+constexpr int TICKET_STRIDE = 32;   // words from one head's ticket counter to the next: a cache line
 constexpr int AROUND_UNITS = 20;    // most 16-byte units a thread of a shift around the selection holds in registers
 constexpr int ORD_SPIN_LIMIT = 1 << 20;  // polls of a predecessor's flag before giving up
 constexpr int MAX_CAP = 32768;      // budget_N + block_B limit (selection bitmaps, ownership)
@@ -116,6 +117,8 @@ struct ShiftSteps {
 struct ShiftAround {
     unsigned long long *words;   // [BH][stride] zero-initialised: a word that says whether there is something to move, then the bitmap
     int32_t *flags;              // [BH][chunks]: the chunk's rows are in registers
+    uint32_t *tickets;           // [BH][TICKET_STRIDE] zero-initialised: workgroups of the head that have started, over all launches
+    uint32_t first_ticket;       // ... before this launch
     int32_t epoch, stride;
     int32_t units, chunks;       // 16-byte units a thread holds; workgroups a head
 };

@@ -212,12 +212,23 @@ __host__ __device__ inline size_t select_dyn_bytes(int n, int N, int cap, bool l
 // store, so a reader needs no order between words: it reads one until it carries the epoch.
 struct NoPublish {
     static constexpr bool ON = false;
+    __device__ void arrive() const {}
+    __device__ bool mine() const { return true; }
     __device__ void operator()(int, const uint32_t *, int) const {}
     __device__ void nothing(int) const {}
 };
 struct PublishWords {
     static constexpr bool ON = true;
     const ShiftAround &around;
+    uint32_t drawn;      // thread 0: what the counter held, perhaps still on its way
+    uint32_t *ticket;    // LDS
+    // the ticket is needed before anything is written, and travels behind the scores till then: thread 0 hands it out ahead of a barrier, and
+    // behind it the workgroup learns whether the selection is its own
+    __device__ __forceinline__ void arrive() const
+    {
+        if (threadIdx.x == 0) *ticket = drawn - around.first_ticket;
+    }
+    __device__ __forceinline__ bool mine() const { return *ticket == 0; }
     __device__ __forceinline__ void put(int bh, int i, uint32_t w) const
     {
         __hip_atomic_store(around.words + (size_t)bh * around.stride + i, ((unsigned long long)(uint32_t)around.epoch << 32) | w,
@@ -388,7 +399,9 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
     }
     KD_TL(1);   // loads issued
     if (RES) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's copies have landed
+    if (E == 1) publish.arrive();
     __syncthreads();   // every wave's part of the copies; the cleared histogram and bitmap
+    if (E == 1 && !publish.mine()) return;   // uniform, like the one below; nothing has been written yet
     KD_TL(2);   // scores and positions in LDS
 
     if (E == 1 && !approx) {
@@ -549,7 +562,9 @@ __device__ __forceinline__ void select_and_compact(const StepParams &p, PostShar
             if (!exempt(pi)) count(s, score_place(s));
         });
     }
+    publish.arrive();
     __syncthreads();
+    if (!publish.mine()) return;
     if (approx && tid < D) {   // (whole waves)
         sh.mu[tid] = mu;
         const double sq = row_allreduce_f64<16>(mu * mu);

@@ -30,7 +30,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
     size_t k_bytes, meta_bytes, scratch_bytes;
-    size_t off_pos, off_ksum, off_status, off_oflags, off_words;                      // in meta
+    size_t off_pos, off_ksum, off_status, off_oflags, off_words, off_tickets;         // in meta
     size_t off_part_o, off_part_ml, off_scores, off_dstmap, off_lists, off_ksum_part, off_anchor, off_q_rot, off_k_rot, off_argmax;  // in scratch
     int cap, max_part_rows;
     int target_wgs;   // bound used to size the partial buffers: twice the compute units of the chip
@@ -121,6 +121,7 @@ Layout make_layout(const keydiff_config_t *c)
     L.off_status = off;  off += 256;
     L.off_oflags = off;  off += align256(BH * ((L.cap + kd::ORD_MIN_ROWS - 1) / kd::ORD_MIN_ROWS) * 4);  // ordered compaction
     L.off_words = off;   off += align256(BH * (1 + (L.cap + 31) / 32) * 8);  // ... around its selection
+    L.off_tickets = off; off += align256(BH * kd::TICKET_STRIDE * 4);
     L.meta_bytes = off;
     // split-KV partial rows: splits * BH * (G * Bt rounded up to 32) never exceeds this (see plan_attention)
     const int kTargetWorkgroups = 2 * compute_units();
@@ -166,6 +167,7 @@ struct keydiff_cache {
     bool contiguous;      // every block so far started where the previous one ended
     int64_t next_pos;
     int32_t epoch;        // launches of the ordered compaction so far (its flags compare against it)
+    uint32_t tickets;     // tickets a head's workgroups have drawn in them (kd::ShiftAround)
     int kpar;             // which half of the key-sum double buffer holds the current sum
     bool pending;         // a deferred eviction (selection + compaction) has not been enqueued yet
     kd::StepParams pend;  // ... the parameters of the step it belongs to
@@ -438,7 +440,9 @@ bool shift_around(keydiff_cache *c, const kd::StepParams &p, int layers, kd::Shi
         return false;
     c->epoch = c->epoch == 0x7fffffff ? 1 : c->epoch + 1;
     *a = kd::ShiftAround{reinterpret_cast<unsigned long long *>(c->meta + c->L.off_words), reinterpret_cast<int32_t *>(c->meta + c->L.off_oflags),
+                         reinterpret_cast<uint32_t *>(c->meta + c->L.off_tickets), c->tickets,
                          c->epoch, 1 + (c->L.cap + 31) / 32, units, chunks};
+    c->tickets += 1 + chunks;   // (modulo 2^32, as the counters)
     return true;
 }
 
@@ -933,6 +937,7 @@ int keydiff_init_cache(const keydiff_config_t *cfg, void *k_cache, void *v_cache
     c->profiling = false;
     c->kpar = 0;
     c->epoch = 0;
+    c->tickets = 0;
     c->pending = false;
     c->shift_pending = false;
     c->pend_stream = nullptr;

@@ -286,6 +286,98 @@ def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw):
         cb.close()
 
 
+def _loaded(batch, heads, N, B, seed, layouts, **kw):
+    """Caches of the given layouts, holding the same N rows each."""
+    hq, hkv, d = heads
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    rows = [torch.randn((batch, hkv, N, d), generator=gen, device="cuda").bfloat16() for _ in range(2)]
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").expand(batch, hkv, N).contiguous()
+    caches = [kd.KeyDiffCache(kd.KeyDiffConfig(batch, *heads, N, B, layout=lay, **kw)) for lay in layouts]
+    for c in caches:
+        c.load(*rows, pos)
+    return caches
+
+
+@pytest.mark.parametrize("heads,N,B,layers", [
+    ((6, 3, 128), 6000, 100, 1),      # three heads: a head's workgroups start on all XCDs, the chip holds neither both launches nor half of them
+    ((8, 2, 128), 8192, 128, 1),
+    ((24, 8, 128), 4096, 64, 3),
+    ((4, 1, 64), 3000, 20, 5),
+], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_ordered_caches_on_two_streams(heads, N, B, layers):
+    # Row shifts of different caches overlap on the chip, each in a launch whose workgroups wait for one another.  Every
+    # cache ends as it does where nothing else runs.
+    steps, kinds = 12, [kd.LAYOUT_ORDERED] * 2 * layers
+    groups = []
+    for g in range(2):
+        both = _loaded(1, heads, N, B, 40 + g, kinds)
+        gen = torch.Generator(device="cuda").manual_seed(60 + g)
+        blks = [[[torch.randn((1, h, B, heads[2]), generator=gen, device="cuda").bfloat16() for _ in range(layers)]
+                 for h in (heads[0], heads[1], heads[1])] for _ in range(steps)]
+        outs = [[[torch.empty_like(q) for q in blk[0]] for blk in blks] for _ in range(2)]
+        groups.append((both[:layers], both[layers:], blks, outs))
+
+    def step(caches, blk, out, t):
+        if layers > 1:
+            kd.prefill_block_layers(caches, *blk, t, out=out)
+        else:
+            caches[0].prefill_block(*(x[0] for x in blk), t, out=out[0])
+
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for i in range(steps):
+        for (a, _, blks, outs), s in zip(groups, streams):
+            with torch.cuda.stream(s):
+                step(a, blks[i], outs[0][i], N + i * B)
+    torch.cuda.synchronize()
+    for a, b, blks, outs in groups:
+        for i in range(steps):
+            step(b, blks[i], outs[1][i], N + i * B)
+        torch.cuda.synchronize()
+        for x, y in zip(*outs):
+            assert all(torch.equal(p.view(torch.int16), q.view(torch.int16)) for p, q in zip(x, y))
+        for l in range(layers):
+            _same_state(a[l], b[l], f"layer {l}")
+            a[l].close()
+            b[l].close()
+
+
+def _start_order(cache, by):
+    """Adds `by` to what the cache's metadata says about how many workgroups have started: the counters, one a head and the
+    last thing in it, 32 words apart."""
+    heads = cache.cfg.batch * cache.cfg.n_kv_heads
+    torch.cuda.synchronize()
+    counters = cache._meta[-((heads * 128 + 255) // 256 * 256):].view(torch.int32)
+    counters[:heads * 32:32] += by
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("heads,N,B", [((4, 1, 64), 1000, 40), ((8, 2, 128), 900, 100)])
+def test_selection_by_a_workgroup_that_started_second(heads, N, B):
+    # Whichever workgroup of a head starts first selects, the others take its rows from the lowest up: here the first to start is told that it
+    # is none of them, so that the next one selects, whatever its number, and the topmost rows of a head are nobody's.
+    hq, hkv, d = heads
+    a, b = _loaded(1, heads, N, B, 7, (kd.LAYOUT_ORDERED, kd.LAYOUT_FILL))
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    q, k, v = (torch.randn((1, h, B, d), generator=gen, device="cuda").bfloat16() for h in (hq, hkv, hkv))
+    _start_order(a, -1)
+    out = a.prefill_block(q, k, v, N)
+    want = b.prefill_block(q, k, v, N)
+    assert float((out.float() - want.float()).abs().max()) <= ATTN_ATOL
+    pa, pb = a.positions(), b.positions().sort(-1)
+    assert torch.equal(pa, pb.values)
+    assert a.status() != 0 and b.status() == 0
+    unit = 4096 // d   # rows a chunk: one 16-byte unit a thread, half of 1024 threads for the keys
+    chunks = -(-(N + B) // unit)
+    here = pa < (chunks - 1) * unit           # rows of the chunks that had a workgroup (before it, position = row)
+    assert bool(here.any())
+    for ra, rb in ((a.key_rows(), b.key_rows()), (a.value_rows(), b.value_rows())):
+        got, ref = ra[:, :, :N].view(torch.int16), rb[:, :, :N].gather(2, pb.indices[..., None].expand(-1, -1, -1, d)).view(torch.int16)
+        assert torch.equal(got[here], ref[here])
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d,Bt,anchor", [
     (7, 1, 128, 1, kd.ANCHOR_MEAN_KEY),        # seven workgroups for seven rows
     (28, 4, 128, 1, kd.ANCHOR_MEAN_KEY),
