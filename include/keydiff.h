@@ -259,7 +259,9 @@ KEYDIFF_API int keydiff_cache_load(keydiff_cache_t *cache, const void *k, const 
 
 /* Device-side consistency word: synchronises `stream`, then *status_out (host)
  * is 0 unless a kernel met an impossible state (for instance a selection whose
- * evicted count differs from n - N, or an expired bounded wait).               */
+ * evicted count differs from n - N, or an expired bounded wait).  The rows of a cache
+ * and their positions may then no longer belong together: only keydiff_destroy_cache
+ * may follow.                                                                    */
 KEYDIFF_API int keydiff_cache_status(const keydiff_cache_t *cache, int32_t *status_out, void *stream);
 
 /* Per-kernel timing with HIP events recorded on the stream the kernels run on.

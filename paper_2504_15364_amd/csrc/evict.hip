@@ -437,9 +437,9 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_layers_kernel(LayerSte
 // a workgroup waits only for ones that have started, and those need nothing but their turn on the compute unit they hold -- whatever order the XCDs
 // start workgroups in, and whatever other launches (other caches on other streams) hold or wait for the rest of the chip.  By block number instead,
 // two such launches could each fill an XCD with workgroups that wait for one queued on the other's.  Workgroups [0, BH) expect the first ticket and
-// begin the selection while it travels (PublishWords); the others merge before they draw, else they often are the first (8192 rows: a step
-// 2 us longer).  Measured against roles by block number, us a step: 8 heads of 128, 8192 rows 43.5 / 44.2, 4096 rows, three layers together
-// 70.4 / 71.5.  Waits are bounded all the same and report a timeout instead of hanging.
+// begin the selection while it travels (PublishWords); the others merge before they draw, else they often are the first and select late
+// (a step of 8192 rows 5 us longer).  Measured by block number / by tickets, us: 96 blocks of 128, 32 of which evict, 32 / 8 heads, 8192 rows
+// 2549 / 2584;  96 blocks through three layers, 64 evict, 24 / 8 heads, 4096 rows 4564 / 4615.  Waits are bounded all the same: one that expires is reported in the status word, and its workgroup stores nothing.
 // Thread: K rows in the first half of the workgroup, V rows in the second, TROWS rows apart.
 // What bounds it: the selection up to its bitmap (8 us at 8320 rows), then one store of the rows, with the hint that nothing reads them
 // again here (1.5 to 3 % of a step less than without).  The merge goes first: behind the requests of the rows, which hold registers, it
@@ -460,7 +460,7 @@ __device__ __forceinline__ void merge_around(const StepParams &p, const ShiftAro
     }
 }
 template <int D>
-__device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAround &sa, PostShared &sh, int bh, int chunk)
+__device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAround &sa, PostShared &sh, int &go, int bh, int chunk)
 {
     constexpr int UPR = D / 8, TROWS = POST_THREADS / 2 / UPR;
     const int tid = threadIdx.x, rows = sa.units * TROWS;
@@ -470,35 +470,42 @@ __device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAro
 #pragma unroll
     for (int q = 0; q < AROUND_UNITS; ++q)
         if (q < sa.units) val[q] = *reinterpret_cast<const u32x4 *>(base + (size_t)min(row0 + q * TROWS, p.n - 1) * D);
+    if (tid == 0) go = 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every row of this chunk is in registers
     __syncthreads();
     int32_t *flags = sa.flags + (size_t)bh * sa.chunks;
     const unsigned long long *words = sa.words + (size_t)bh * sa.stride;
     if (tid == 0) __hip_atomic_store(&flags[chunk], sa.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the word of the epoch, or 0 (of the header: do nothing) where it does not come
+    auto expired = [&]() {
+        atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+        go = 0;
+    };
+    // the word of the epoch
     auto word_at = [&](int i) {
         for (int spins = 0; spins <= ORD_SPIN_LIMIT; ++spins) {
             const unsigned long long w = __hip_atomic_load(&words[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((int32_t)(w >> 32) == sa.epoch) return (uint32_t)w;
             __builtin_amdgcn_s_sleep(1);
         }
-        atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+        expired();
         return 0u;
     };
     const int reach = (p.n - p.N + rows - 1) / rows, below = chunk - 1 - (tid - 64);   // chunks below this one its rows can land in
-    if (tid == 0) sh.sel_cnt = word_at(0) == 1 ? 1u : 0u;
-    else if (tid >= 64 && tid < 64 + reach && below >= 0) {
+    if (tid == 0) {
+        if (word_at(0) != 1) go = 0;
+    } else if (tid >= 64 && tid < 64 + reach && below >= 0) {
         int spins = 0;
         while (__hip_atomic_load(&flags[below], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != sa.epoch) {
             if (++spins > ORD_SPIN_LIMIT) {
-                atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+                expired();
                 break;
             }
             __builtin_amdgcn_s_sleep(4);
         }
     }
     __syncthreads();
-    if (sh.sel_cnt == 0) return;   // uniform
+    if (go == 0) return;   // uniform: nothing to move, or a wait has expired
+    __syncthreads();       // (everybody has looked, before a word that does not come changes it)
     const int nwords = (p.n + 31) / 32;
     uint32_t *bits = sh.hist, *before = sh.hist + MAX_CAP / 32;
     static_assert(2 * (MAX_CAP / 32) <= HIST_BINS && MAX_CAP / 32 <= POST_THREADS, "the bitmap and its counts use the histogram's place, a word a thread");
@@ -508,6 +515,7 @@ __device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAro
     bits[tid] = w;
     before[tid] = at;
     __syncthreads();
+    if (go == 0) return;   // uniform
 #pragma unroll
     for (int q = 0; q < AROUND_UNITS; ++q) {
         const int row = row0 + q * TROWS;
@@ -529,6 +537,7 @@ __device__ __forceinline__ void post_shift_body(const StepParams &p, const Shift
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     __shared__ PostShared sh;
     __shared__ uint32_t ticket;
+    __shared__ int go;
     const int BH = p.batch * p.hkv, bh = block % BH;
     bool select = block < BH;   // uniform, like the branches below
     if (!select) merge_around<D>(p, sa, sh, block - BH);
@@ -548,7 +557,7 @@ __device__ __forceinline__ void post_shift_body(const StepParams &p, const Shift
         if (threadIdx.x == 0) atomicOr(p.status, STATUS_ORDER_TIMEOUT);
         return;
     }
-    shift_around<D>(p, sa, sh, bh, (int)ticket - 1);
+    shift_around<D>(p, sa, sh, go, bh, (int)ticket - 1);
 }
 template <int D>
 __global__ __launch_bounds__(POST_THREADS) void step_post_shift_kernel(StepParams p, ShiftAround sa)
@@ -601,6 +610,8 @@ __device__ __forceinline__ void shift_chunk(const Step &p, int BH, int32_t *flag
             if (d >= 0 && d != row) drow[q] = d;
         }
     }
+    __shared__ int go;
+    if (tid == 0) go = 1;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // every row of this chunk is in registers
     __syncthreads();
     int32_t *myflags = flags + (size_t)bh * nchunks;
@@ -611,12 +622,14 @@ __device__ __forceinline__ void shift_chunk(const Step &p, int BH, int32_t *flag
         while (__hip_atomic_load(&myflags[chunk - 1 - tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
             if (++spins > ORD_SPIN_LIMIT) {
                 atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+                go = 0;   // rows that have not been read must not be stored over
                 break;
             }
             __builtin_amdgcn_s_sleep(8);
         }
     }
     __syncthreads();
+    if (go == 0) return;   // uniform
 #pragma unroll
     for (int q = 0; q < UPT; ++q) {
         const int w = q * ORD_THREADS + tid;

@@ -60,7 +60,9 @@ __device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags,
     // 16-byte row pieces; how many loads of the destination map the compiler makes of the rest is its
     // business), so "at most UPT memory operations outstanding" means c - 1 has landed in this thread
     // (stores in flight only make the count stricter), and the barrier extends that to the workgroup.
-    auto ready_to_store = [&](int c, int later_chunks) {
+    __shared__ int go;
+    if (tid == 0) go = 1;
+    auto ready_to_store = [&](int c, int later_chunks) {   // false: the wait has expired, and rows that have not been read would be stored over
         asm volatile("" ::: "memory");
         if (later_chunks >= 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (UPT & 15) | ((UPT >> 4) << 14));
         else __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -74,6 +76,7 @@ __device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags,
                 while (__hip_atomic_load(&myflags[c - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
                     if (++spins > ORD_SPIN_LIMIT) {
                         atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+                        go = 0;
                         break;
                     }
                     __builtin_amdgcn_s_sleep(8);
@@ -81,6 +84,7 @@ __device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags,
             }
             __syncthreads();
         }
+        return c > c0 || go != 0;   // uniform
     };
     // three register sets in rotation: chunk c in one, c - 1 in the next, c - 2 requested into the third
     int c = c1 - 1;
@@ -88,15 +92,15 @@ __device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags,
     if (c - 1 >= c0) load(c - 1, vb2, db);
     while (true) {
         if (c - 2 >= c0) load(c - 2, vc, dc);
-        ready_to_store(c, c - 2 >= c0 ? 1 : 0);
+        if (!ready_to_store(c, c - 2 >= c0 ? 1 : 0)) return;
         store(va, da);
         if (--c < c0) break;
         if (c - 2 >= c0) load(c - 2, va, da);
-        ready_to_store(c, c - 2 >= c0 ? 1 : 0);
+        if (!ready_to_store(c, c - 2 >= c0 ? 1 : 0)) return;
         store(vb2, db);
         if (--c < c0) break;
         if (c - 2 >= c0) load(c - 2, vb2, db);
-        ready_to_store(c, c - 2 >= c0 ? 1 : 0);
+        if (!ready_to_store(c, c - 2 >= c0 ? 1 : 0)) return;
         store(vc, dc);
         if (--c < c0) break;
     }

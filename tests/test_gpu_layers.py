@@ -378,6 +378,21 @@ def test_selection_by_a_workgroup_that_started_second(heads, N, B):
     b.close()
 
 
+def test_rows_stay_where_a_wait_expires():
+    # No workgroup is told that it selects: the waits for the eviction bitmap, which are bounded, expire.  The status word says so and no row has moved.
+    heads, N, B = (4, 1, 64), 1000, 40
+    a, = _loaded(1, heads, N, B, 7, (kd.LAYOUT_ORDERED,))
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    q, k, v = (torch.randn((1, h, B, 64), generator=gen, device="cuda").bfloat16() for h in (4, 1, 1))
+    before = torch.cat([a.key_rows()[:, :, :N], k], 2), torch.cat([a.value_rows()[:, :, :N], v], 2)
+    _start_order(a, 1)
+    a.prefill_block(q, k, v, N)
+    assert a.status() != 0
+    for rows, want in zip((a.key_rows(), a.value_rows()), before):
+        assert torch.equal(rows[:, :, :N + B].view(torch.int16), want.view(torch.int16))
+    a.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d,Bt,anchor", [
     (7, 1, 128, 1, kd.ANCHOR_MEAN_KEY),        # seven workgroups for seven rows
     (28, 4, 128, 1, kd.ANCHOR_MEAN_KEY),
