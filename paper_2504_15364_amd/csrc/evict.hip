@@ -578,16 +578,26 @@ __global__ __launch_bounds__(POST_THREADS) void step_post_shift_layers_kernel(La
 // down by at most E = n - N rows.  One workgroup per ORD_ROWS rows reads its moving rows into
 // registers, announces that (flag = epoch of this launch), waits until the workgroups whose rows
 // it may overwrite -- the ceil(E / ORD_ROWS) chunks before it -- have announced the same, and
-// stores.  Workgroups are numbered chunk-major, so a workgroup only ever waits for lower-numbered
-// ones; the wait is bounded and reports a timeout in the status word instead of hanging.
+// stores.  The workgroups of a head take its chunks from the lowest up in the order in which they start (tickets, as above), so a
+// workgroup only ever waits for ones that have started (by block number / by tickets, us a step: 32 / 8 heads of 128, 13000 rows 76.5 / 77.5;  two
+// layers of 12288 115.5 / 118.2;  8 / 2 of 64, 16000 rows 40.8 / 42.6); the wait is bounded and reports a timeout in the status word instead of hanging.
 // (Step: StepParams or ShiftStep)
 template <int D, class Step>
-__device__ __forceinline__ void shift_chunk(const Step &p, int BH, int32_t *flags, int nchunks, int32_t epoch, int block)
+__device__ __forceinline__ void shift_chunk(const Step &p, int BH, int32_t *flags, int nchunks, int32_t epoch, uint32_t *tickets, uint32_t first_ticket,
+                                            int block)
 {
     constexpr int UPR = D / 8;
     constexpr int UPT = ORD_ROWS * UPR * 2 / ORD_THREADS;   // 16-byte units (K and V) per thread
     static_assert(UPT * ORD_THREADS == ORD_ROWS * UPR * 2, "the chunk must divide over the threads");
-    const int bh = block % BH, chunk = block / BH, tid = threadIdx.x;
+    __shared__ uint32_t ticket;
+    const int bh = block % BH, tid = threadIdx.x;
+    if (tid == 0) ticket = draw_ticket(tickets + (size_t)bh * TICKET_STRIDE) - first_ticket;
+    __syncthreads();
+    if (ticket >= (uint32_t)nchunks) {   // (impossible)
+        if (tid == 0) atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+        return;
+    }
+    const int chunk = (int)ticket;
     uint16_t *kb = p.k + (size_t)bh * p.cap * D;
     uint16_t *vb = p.v + (size_t)bh * p.cap * D;
     const int32_t *dst = p.dstmap + (size_t)bh * p.cap;
@@ -643,9 +653,9 @@ __device__ __forceinline__ void shift_chunk(const Step &p, int BH, int32_t *flag
 // takes 0.4 to 1 us more: 16 of 8208 rows 11.9 us, 12.8 and 13.2; 9 of 10009 15.5 and 16.1.  Reading what the announcement needs
 // ahead of the rows does not change that.)
 template <int D>
-__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_ordered_kernel(StepParams p, int32_t *flags, int nchunks, int32_t epoch)
+__global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_ordered_kernel(StepParams p, int32_t *flags, int nchunks, int32_t epoch, uint32_t *tickets, uint32_t first_ticket)
 {
-    shift_chunk<D>(p, p.batch * p.hkv, flags, nchunks, epoch, (int)blockIdx.x);
+    shift_chunk<D>(p, p.batch * p.hkv, flags, nchunks, epoch, tickets, first_ticket, (int)blockIdx.x);
 }
 __host__ __device__ static inline int shift_chunks(const ShiftStep &sh) { return (sh.n + ORD_ROWS - 1) / ORD_ROWS; }
 // ... of several caches, blockIdx.y each
@@ -653,7 +663,7 @@ template <int D>
 __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void compact_layers_kernel(ShiftSteps steps)
 {
     const ShiftStep &p = steps.s[blockIdx.y];
-    shift_chunk<D>(p, p.BH, p.flags, shift_chunks(p), p.epoch, (int)blockIdx.x);
+    shift_chunk<D>(p, p.BH, p.flags, shift_chunks(p), p.epoch, p.tickets, p.first_ticket, (int)blockIdx.x);
 }
 
 // The merge of one cache's attention partials and the ordered shift of another cache in one launch
@@ -661,8 +671,7 @@ __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 
 // just before, and its rows have no reader until that cache's next step).  The merge is a memory
 // round trip on a chip it leaves mostly idle; the shift is bound by HBM traffic: together they take
 // what the shift takes alone.  Workgroups [0, merge_wgs) merge -- they are dispatched first and
-// the caller waits for their output -- the others shift one chunk each, numbered chunk-major
-// behind them, so a shifting workgroup still only ever waits for lower-numbered ones.
+// the caller waits for their output -- the others shift one chunk each.
 template <int D>
 __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void merge_shift_kernel(StepParams pm, ShiftStep shift, int merge_wgs)
 {
@@ -672,7 +681,7 @@ __global__ __launch_bounds__(ORD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 
         merge_rows<D, 4>(pm, (size_t)blockIdx.x * ORD_THREADS + threadIdx.x);
         return;
     }
-    shift_chunk<D>(shift, shift.BH, shift.flags, shift_chunks(shift), shift.epoch, (int)blockIdx.x - merge_wgs);
+    shift_chunk<D>(shift, shift.BH, shift.flags, shift_chunks(shift), shift.epoch, shift.tickets, shift.first_ticket, (int)blockIdx.x - merge_wgs);
 }
 
 // --------------------------------------------------- key sum from scratch (cache load)
@@ -1004,8 +1013,8 @@ hipError_t launch_compact_ordered(const StepParams &p, const ShiftStep &shift, h
     if (!shift_fits(shift)) return hipErrorInvalidValue;
     const int chunks = shift_chunks(shift);
     const dim3 grid((unsigned)(shift.BH * chunks));
-    if (p.D == 128) hipLaunchKernelGGL((compact_ordered_kernel<128>), grid, dim3(ORD_THREADS), 0, s, p, shift.flags, chunks, shift.epoch);
-    else if (p.D == 64) hipLaunchKernelGGL((compact_ordered_kernel<64>), grid, dim3(ORD_THREADS), 0, s, p, shift.flags, chunks, shift.epoch);
+    if (p.D == 128) hipLaunchKernelGGL((compact_ordered_kernel<128>), grid, dim3(ORD_THREADS), 0, s, p, shift.flags, chunks, shift.epoch, shift.tickets, shift.first_ticket);
+    else if (p.D == 64) hipLaunchKernelGGL((compact_ordered_kernel<64>), grid, dim3(ORD_THREADS), 0, s, p, shift.flags, chunks, shift.epoch, shift.tickets, shift.first_ticket);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -107,6 +107,8 @@ struct ShiftStep {
     int32_t *status, *flags;
     int BH, n, N, cap;
     int32_t epoch;
+    uint32_t *tickets;   // as in ShiftAround
+    uint32_t first_ticket;
 };
 struct ShiftSteps {
     ShiftStep s[GROUP_LAYERS];

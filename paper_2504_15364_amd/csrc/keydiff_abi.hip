@@ -420,8 +420,10 @@ bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
 kd::ShiftStep shift_step(keydiff_cache *c, const kd::StepParams &p)
 {
     c->epoch = c->epoch == 0x7fffffff ? 1 : c->epoch + 1;
-    return kd::ShiftStep{p.k, p.v, p.dstmap, p.status, reinterpret_cast<int32_t *>(c->meta + c->L.off_oflags), p.batch * p.hkv, p.n,
-                         p.N, p.cap, c->epoch};
+    const kd::ShiftStep shift{p.k, p.v, p.dstmap, p.status, reinterpret_cast<int32_t *>(c->meta + c->L.off_oflags), p.batch * p.hkv, p.n,
+                              p.N, p.cap, c->epoch, reinterpret_cast<uint32_t *>(c->meta + c->L.off_tickets), c->tickets};
+    c->tickets += (uint32_t)((p.n + kd::ORD_ROWS - 1) / kd::ORD_ROWS);   // one a chunk
+    return shift;
 }
 
 int compact_ordered(keydiff_cache *c, const kd::StepParams &p, hipStream_t s)

@@ -303,6 +303,8 @@ def _loaded(batch, heads, N, B, seed, layouts, **kw):
     ((8, 2, 128), 8192, 128, 1),
     ((24, 8, 128), 4096, 64, 3),
     ((4, 1, 64), 3000, 20, 5),
+    ((6, 3, 128), 12400, 300, 1),     # too long for the launch of the selection: the shift is one of its own, three chunks to wait for
+    ((12, 6, 64), 12400, 130, 3),
 ], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
 def test_ordered_caches_on_two_streams(heads, N, B, layers):
     # Row shifts of different caches overlap on the chip, each in a launch whose workgroups wait for one another.  Every
