@@ -1222,7 +1222,7 @@ __global__ __launch_bounds__(CARRY_THREADS) void step_main_ride_kernel(RideCount
     }
     if ((int)blockIdx.x < ncarry + nshift) {
         const int i = (int)blockIdx.x - ncarry, heads = ride.p.batch * ride.p.hkv;
-        shift_range<D, CARRY_THREADS>(ride.p, ride.flags, ride.nchunks, ride.epoch, i % heads, i / heads, ride.parts);
+        shift_range<D, CARRY_THREADS>(ride.p, ride.flags, ride.nchunks, ride.epoch, ride.tickets, ride.first_ticket, i % heads, ride.parts);
         return;
     }
     step_main_body<D, false, EXACT>(p, (int)blockIdx.x - ncarry - nshift);

@@ -526,11 +526,6 @@ __device__ __forceinline__ void shift_around(const StepParams &p, const ShiftAro
         }
     }
 }
-// (wrapping at 2^32 - 1, so an addition of 1: an addition would be done for the wave and waited for on the spot)
-__device__ __forceinline__ uint32_t draw_ticket(uint32_t *counter)
-{
-    return __builtin_amdgcn_atomic_inc32(counter, 0xFFFFFFFFu, __ATOMIC_RELAXED, "agent");
-}
 template <int D>
 __device__ __forceinline__ void post_shift_body(const StepParams &p, const ShiftAround &sa, int block)
 {

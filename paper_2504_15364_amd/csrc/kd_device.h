@@ -132,6 +132,12 @@ __device__ __forceinline__ double sum_over_rows_f64(double x)
     return pair_sum(pair_sum(x, false), true);
 }
 
+// One more has started: what `counter` held.  (Wrapping at 2^32 - 1, so an addition of 1: an addition would be done for the wave and waited for on the spot)
+__device__ __forceinline__ uint32_t draw_ticket(uint32_t *counter)
+{
+    return __builtin_amdgcn_atomic_inc32(counter, 0xFFFFFFFFu, __ATOMIC_RELAXED, "agent");
+}
+
 // x summed over the lanes of a wave that hold the same 16-byte unit of different rows (lane % UPR), in the order lane ^ 8 (rows of 8
 // units), ^ 16, ^ 32; every lane gets the total.  On the vector ALU alone: through LDS, the sums of eight columns of 64-wide rows took
 // a selection 0.6 us more.

@@ -157,6 +157,8 @@ struct ShiftRide {
     int32_t *flags;
     int nchunks, parts, nshift;
     int32_t epoch;
+    uint32_t *tickets;   // as in ShiftAround
+    uint32_t first_ticket;
 };
 bool can_host_shift(const StepParams &p, const StepParams &shifted);
 // step_main of `p` with passengers: the selection `cy` (or none: nullptr) and the shift `ride`

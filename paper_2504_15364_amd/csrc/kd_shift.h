@@ -6,9 +6,9 @@
 // A workgroup takes the chunks [c0, c1) of one head from the top down, with the next two chunks
 // already requested while it stores one: chunk c is stored once chunk c - 1 is in registers (its
 // own registers, or -- for its lowest chunk -- those of the workgroup below, which says so with a
-// flag as soon as it has read its top chunk).  A workgroup therefore only ever waits for the first
-// thing another workgroup does, whatever order they start in; the wait is bounded and reports a
-// timeout in the status word instead of hanging.
+// flag as soon as it has read its top chunk).  The ranges are dealt from the lowest up in the order in which the
+// workgroups start, so one only ever waits for the first thing another does that has started; the wait is bounded
+// and reports a timeout in the status word instead of hanging.
 #pragma once
 #include "kd_kernels.h"
 #include "kd_device.h"
@@ -16,8 +16,8 @@
 namespace kd {
 
 template <int D, int THREADS>
-__device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags, int nchunks, int32_t epoch, int bh,
-                                            int part, int parts)
+__device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags, int nchunks, int32_t epoch, uint32_t *tickets,
+                                            uint32_t first_ticket, int bh, int parts)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int UPR = D / 8;
@@ -25,6 +25,14 @@ __device__ __forceinline__ void shift_range(const StepParams &p, int32_t *flags,
     static_assert(UPT * THREADS == ORD_ROWS * UPR * 2, "a chunk must divide over the threads");
     static_assert(UPT < 64, "the wait below names UPT outstanding operations in a 6-bit field");
     const int tid = threadIdx.x;
+    __shared__ uint32_t ticket;
+    if (tid == 0) ticket = draw_ticket(tickets + (size_t)bh * TICKET_STRIDE) - first_ticket;
+    __syncthreads();
+    if (ticket >= (uint32_t)parts) {   // (impossible)
+        if (tid == 0) atomicOr(p.status, STATUS_ORDER_TIMEOUT);
+        return;
+    }
+    const int part = (int)ticket;
     const int c0 = (int)(((long)part * nchunks) / parts), c1 = (int)(((long)(part + 1) * nchunks) / parts);
     if (c0 >= c1) return;   // uniform
     uint16_t *kb = p.k + (size_t)bh * p.cap * D;

@@ -616,6 +616,9 @@ int block_step(keydiff_cache *c, const void *q, const void *k_new, const void *v
             ride.nshift = shift_wgs;
             shifted->epoch = shifted->epoch == 0x7fffffff ? 1 : shifted->epoch + 1;
             ride.epoch = shifted->epoch;
+            ride.tickets = reinterpret_cast<uint32_t *>(shifted->meta + shifted->L.off_tickets);
+            ride.first_ticket = shifted->tickets;
+            shifted->tickets += (uint32_t)shift_parts;
             KD_LAUNCH(kd::launch_step_main_ride(p, riding ? &carry->pend : nullptr, ride, s),
                       "step_main kernel (with carried selection and row shift)");
             shifted->shift_pending = false;

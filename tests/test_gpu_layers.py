@@ -305,6 +305,7 @@ def _loaded(batch, heads, N, B, seed, layouts, **kw):
     ((4, 1, 64), 3000, 20, 5),
     ((6, 3, 128), 12400, 300, 1),     # too long for the launch of the selection: the shift is one of its own, three chunks to wait for
     ((12, 6, 64), 12400, 130, 3),
+    ((32, 8, 128), 8192, 128, 3),     # ... or rides in the attention launch of another layer
 ], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
 def test_ordered_caches_on_two_streams(heads, N, B, layers):
     # Row shifts of different caches overlap on the chip, each in a launch whose workgroups wait for one another.  Every
@@ -331,6 +332,9 @@ def test_ordered_caches_on_two_streams(heads, N, B, layers):
         for (a, _, blks, outs), s in zip(groups, streams):
             with torch.cuda.stream(s):
                 step(a, blks[i], outs[0][i], N + i * B)
+    for (a, *_), s in zip(groups, streams):
+        for c in a:
+            c.finish(s)
     torch.cuda.synchronize()
     for a, b, blks, outs in groups:
         for i in range(steps):
