@@ -183,14 +183,16 @@ KEYDIFF_API int keydiff_prefill_block_deferred(keydiff_cache_t *cache, const voi
  * pending): every layer's selection and compaction runs inside the next layer's attention
  * launch, and the last layer's stays pending until the next block (or keydiff_finish, or any
  * other call on that cache).  With n_layers == 1 the call is keydiff_prefill_block.
- * So do calls whose sharing would take longer by the library's estimate (plan_out[3] of keydiff_cache_plan says which way a step went): in the
- * ORDERED layout, unless the row shifts of all layers fit around their selections on the chip, two layers with more than 16 row tiles
- * where one alone would have key ranges of more than eight tiles; three or four layers of many rows in all heads (and of few row
- * tiles on caches of at most 1280 rows) wherever
- * the stable row shift of layer l, whose selection rode in the launch of layer l + 1, can ride in the
- * attention launch of layer l + 2 (a block that evicts at most 128 rows,
- * 256-row query tiles that are full, the same head_dim), so that after the call the shifts of the last
- * two layers may still be pending as well; like a pending eviction, a pending shift is enqueued
+ * So do calls whose sharing would take longer by the library's estimate (plan_out[3] of keydiff_cache_plan says which way a step went):
+ *   - steps of few query rows that run a kernel of their own (see keydiff_cache_plan's row tiles);
+ *   - evicting steps whose row tiles would go over the chip in as many rounds together as layer by layer (FILL), or by the estimated
+ *     times (ORDERED, three layers or more);
+ *   - ORDERED, unless the row shifts of all layers fit around their selections on the chip: two layers with more than 16 row
+ *     tiles where one alone would have key ranges of more than eight tiles;  three layers, or four of head_dim 128, of more
+ *     than 51200 rows in all heads of a layer, where the stable row shifts can ride in attention launches.
+ * Layer by layer and with three layers or more, the shift of layer l, whose selection rode in the launch of layer l + 1, rides in the
+ * attention launch of layer l + 2 where it can (a block that evicts at most 128 rows, 256-row query tiles that are full, the same
+ * head_dim), so that after the call the shifts of the last two layers may still be pending as well; like a pending eviction, a pending shift is enqueued
  * first by any other call on its cache, and the rows of such a cache are not in position order
  * until then.  All pointers are checked before
  * anything is enqueued; an error met later (a state error of one layer) leaves the layers

@@ -742,12 +742,13 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
     //     55.2 / 46.6;  32 / 8 of 64, 12000 keys 50.9 / 30.6;  two sequences, 4096 keys 42.0 / 35.1
     //   a launch of their own, 2 layers: 32 / 8, 11000 keys 57.5 / 52.6, 12288 keys 63.7 / 59.3;  more than 16 row tiles: 24 / 8, 16000 keys, blocks
     //     of 256 91.6 / 94.4;  28 / 4, 12288 keys, blocks of 256 69.3 / 72.5;  32 / 8, two sequences, 8192 keys 67.4 / 70.5
-    //   ..., 3, 4 and 8 layers of 32 / 8: 6144 keys 32.3 / 30.0, 32.6 / 28.3, 33.2 / 24.8;  8192 keys 36.8 / 39.7, 37.5 / 36.5 (rides: a
-    //     test holds it), 38.7 / 33.3;
+    //   ..., 3, 4 and 8 layers of 32 / 8: 6144 keys 32.3 / 30.0, 32.6 / 28.3, 33.2 / 24.8;  8192 keys 36.8 / 39.7, 37.5 / 36.5, 38.7 / 33.3;
     //     11000 keys 42.7 / 49.4, 42.4 / 44.8, 46.6 / 43.0;  two sequences, 4096 keys 34.2 / 40.0, 34.3 / 35.2, 38.5 / 32.1;  of 64, two
     //     sequences, 4096 keys 24.5 / 23.8, 24.6 / 22.6, 24.9 / 19.6;  four, 2048 keys 25.6 / 26.9, 25.9 / 22.0, 26.1 / 19.9
-    //   few row tiles, 3, 4 and 8 layers: 8 / 2 of 64, 2048 keys 17.9 / 8.6, 17.9 / 6.4, 17.7 / 3.8;  16 / 4, 12000 keys 51.8 / 25.4, 51.3 / 28.7,
-    //     56.5 / 25.1.  Up to 1280 rows such caches ride all the same: a test holds the riding shift at 1152.
+    //   few row tiles, 3, 4 and 8 layers: 8 / 2 of 64, 2048 keys 17.9 / 8.6, 17.9 / 6.4, 17.7 / 3.8;  8 / 2 of 128, 1024 keys 14.0 / 7.9, 14.0 / 6.3,
+    //     14.0 / 3.5;  16 / 4, 12000 keys 51.8 / 25.4, 51.3 / 28.7, 56.5 / 25.1
+    // So from five layers on, or up to 51200 rows in all heads, together.  Three layers cross between 6144 and 8192 keys of eight heads; four of 128
+    // cross at 8192 (36.5 and 37.5, with two sequences of 4096 keys 35.2 and 34.3, alike within 3 %) and have the same line; four of 64 gain beyond it.
     if (p.do_evict && p.layout == KEYDIFF_LAYOUT_ORDERED) {
         const int row_tiles = p.batch * p.hkv * p.mtiles;
         const long rows = (long)p.batch * p.hkv * p.n;
@@ -756,7 +757,7 @@ int layer_groups(const keydiff_cache *c, const kd::StepParams &step, int n_layer
         if (n_layers == 2 && !around && row_tiles > 16 && (p.ntiles + p.splits - 1) / p.splits > 8) return 0;
         const bool together = around || n_layers > 4 || rows <= 8 * 6400 || (n_layers == 4 && p.D == 64);
         kd::StepParams probe = step;
-        if (n_layers > 2 && (!together || (row_tiles < 16 && p.n <= 1280)) && plan_with_shift(c, probe, step, p.batch * p.hkv) > 0) return 0;
+        if (n_layers > 2 && !together && plan_with_shift(c, probe, step, p.batch * p.hkv) > 0) return 0;
     }
     const double post_us = p.do_evict ? 12.0 : 3.0;
     const int least = (n_layers + kd::GROUP_LAYERS - 1) / kd::GROUP_LAYERS;

@@ -201,6 +201,8 @@ def test_ordered_eviction_carried_leaves_what_one_inside_the_step_leaves(d, N, E
     ((32, 8, 64), 4, 2048, 128, 3, kd.LAYOUT_ORDERED, 2),
     ((32, 8, 64), 4, 2048, 128, 4, kd.LAYOUT_ORDERED, 4),
     ((32, 8, 128), 2, 4096, 128, 8, kd.LAYOUT_ORDERED, 4),
+    ((8, 2, 128), 1, 1024, 128, 4, kd.LAYOUT_ORDERED, 4),      # few row tiles: 6.3 us shared, 14.0 riding
+    ((8, 2, 64), 1, 1100, 64, 3, kd.LAYOUT_ORDERED, 4),
     # FILL: 192 row tiles of each layer in 256 compute units, or 48 in ranges of 240 workgroups
     ((28, 4, 128), 8, 2048, 200, 2, kd.LAYOUT_FILL, 1),
     ((28, 4, 128), 2, 8192, 200, 2, kd.LAYOUT_FILL, 1),

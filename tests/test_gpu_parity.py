@@ -490,13 +490,13 @@ def test_ordered_layers_call_shifts_inside_later_attention_launches(check_every)
     # l rides in the attention launch of layer l + 1 and the stable row shift by its destination map in
     # that of layer l + 2 (workgroups that own a range of 128-row chunks each).  Reading a cache's state
     # in between runs whatever is still pending for it in launches of its own.
-    # (the last block is ragged: its row tiles have waves without query rows, whose launches take no shift along, so its
-    # layers share their launches; what was pending before it is enqueued alone ahead of them)
+    # (the last block is ragged: its row tiles have waves without query rows, whose launches take no shift along)
     w = get_config("llama31_8b").small(n_q_heads=8, n_kv_heads=2, prompt_T=2000)
     N, B, nl = 1024, 128, 4      # 9 chunks per head: ranges of one and of two chunks
     layers = [make_pair(w, N, B, layout=kd.LAYOUT_ORDERED) for _ in range(nl)]
     datas = [make_layer(w, seed=131 + l) for l in range(nl)]
     caches = [c for c, _ in layers]
+    caches[0].profile_enable(True)   # (caches this small share their launches: layer by layer only while one is being profiled)
     hosted = 0
     for bi, steps in enumerate(zip(*(blocks(d, B) for d in datas))):
         t = steps[0][0]
