@@ -236,20 +236,39 @@ def test_layers_share_launches_where_that_is_faster(heads, batch, N, B, layers, 
         c.close()
 
 
-@pytest.mark.parametrize("heads,batch,N,B,layers,kw", [
-    ((8, 2, 128), 1, 390, 32, 1, {}),                                            # the fewest rows: beyond what the selection shifts itself
-    ((8, 2, 128), 1, 900, 300, 1, {}),                                           # rows that land ten chunks below
-    ((4, 1, 64), 1, 1000, 7, 1, {"window_W": 90}),
-    ((4, 1, 64), 1, 12288 - 50, 50, 1, {"anchor_mode": kd.ANCHOR_MEAN_UNIT_KEY}),  # the last length
-    ((8, 8, 128), 4, 2000, 130, 1, {}),                                          # ten units a thread, merged by few workgroups
-    ((32, 8, 128), 1, 4097, 1, 1, {}),                                           # one row, behind step_few and its merge
-    ((24, 8, 128), 1, 4096, 128, 3, {}),                                         # fifteen units, several layers
-    ((8, 2, 64), 1, 2000, 100, 16, {}),
-    ((16, 8, 128), 2, 8192, 64, 1, {}),                                          # eighteen units
+def _counters(cache):
+    """The part of a cache's metadata that counts the workgroups of each head that have started in launches that shift rows: the last
+    thing in it, 32 words apart."""
+    heads = cache.cfg.batch * cache.cfg.n_kv_heads
+    torch.cuda.synchronize()
+    return cache._meta[-((heads * 128 + 255) // 256 * 256):].view(torch.int32)[:heads * 32:32]
+
+
+def _started(cache):
+    return _counters(cache).clone()
+
+
+def _start_order(cache, by):
+    """Adds `by` to what a cache says about how many workgroups have started."""
+    _counters(cache).add_(by)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("heads,batch,N,B,layers,kw,units", [
+    ((8, 2, 128), 1, 390, 32, 1, {}, 1),                                         # the fewest rows: beyond what the selection shifts itself
+    ((8, 2, 128), 1, 900, 300, 1, {}, 1),                                         # rows that land ten chunks below
+    ((4, 1, 64), 1, 1000, 7, 1, {"window_W": 90}, 1),
+    ((4, 1, 64), 1, 12288 - 50, 50, 1, {"anchor_mode": kd.ANCHOR_MEAN_UNIT_KEY}, 1),  # the last length
+    ((8, 8, 128), 4, 2000, 130, 1, {}, 10),                                          # ten units a thread, merged by few workgroups
+    ((32, 8, 128), 1, 4097, 1, 1, {}, 5),                                           # one row, behind step_few and its merge
+    ((24, 8, 128), 1, 4096, 128, 3, {}, 15),                                         # fifteen units, several layers
+    ((8, 2, 64), 1, 2000, 100, 16, {}, 5),
+    ((16, 8, 128), 2, 8192, 64, 1, {}, 18),                                          # eighteen units
 ], ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
-def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw):
+def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw, units):
     # ORDERED caches beyond what the selection shifts itself: the rows wait in the registers of the workgroups around it.  The rows retained are
-    # those of the FILL layout, in order, over steps that follow one another and with a ragged one.
+    # those of the FILL layout, in order, over steps that follow one another and with a ragged one; a launch starts a selection and
+    # a workgroup for every `units` times 4096 elements of K of every head.
     hq, hkv, d = heads
     a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(batch, *heads, N, B, layout=lay, **kw)) for _ in range(layers)]
             for lay in (kd.LAYOUT_ORDERED, kd.LAYOUT_FILL))
@@ -268,7 +287,7 @@ def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw):
             c.load(*rows, pos)
     for n in [B] * (N // B + 1 if t == 0 else 0) + [B, B, (B + 1) // 2, B]:
         blk = [[draw(h, n) for _ in range(layers)] for h in (hq, hkv, hkv)]
-        outs = []
+        outs, before = [], [_started(c) for c in a]
         for caches in (a, b):
             if layers > 1:
                 outs.append(kd.prefill_block_layers(caches, *blk, t))
@@ -276,6 +295,9 @@ def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw):
                 outs.append([caches[0].prefill_block(*(x[0] for x in blk), t)])
         for x, y in zip(*outs):
             assert float((x.float() - y.float()).abs().max()) <= ATTN_ATOL, t
+        if a[0].len == N and t >= N and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            want = 1 + -(-(N + n) * d // (units * 4096))
+            assert all(torch.equal(_started(c) - x, torch.full_like(x, want)) for c, x in zip(a, before)), (t, want)
         t += n
     for ca, cb in zip(a, b):
         pa, pb = ca.positions(), cb.positions().sort(-1)
@@ -298,6 +320,32 @@ def _loaded(batch, heads, N, B, seed, layouts, **kw):
     for c in caches:
         c.load(*rows, pos)
     return caches
+
+
+@pytest.mark.parametrize("heads,N,B,how", [((8, 2, 128), 2000, 100, "finish"), ((4, 1, 64), 3000, 33, "scores"), ((32, 8, 128), 4097, 1, "step")])
+def test_pending_eviction_is_finished_around_its_selection(heads, N, B, how):
+    # An eviction that found no launch to ride in, finished by a call on its own cache: with nothing to merge, the workgroups around the
+    # selection only shift.  Positions and rows are those of the step that evicts by itself.
+    a, b = _loaded(1, heads, N, B, 9, [kd.LAYOUT_ORDERED] * 2)
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    hq, hkv, d = heads
+    for i in range(3):
+        q, k, v = (torch.randn((1, h, B, d), generator=gen, device="cuda").bfloat16() for h in (hq, hkv, hkv))
+        t = N + i * B
+        out, before = a.prefill_block_deferred(q, k, v, t), _started(a)
+        if how == "finish":
+            a.finish()
+        elif how == "scores":
+            a.scores()
+        want = b.prefill_block(q, k, v, t)
+        assert float((out.float() - want.float()).abs().max()) <= ATTN_ATOL, t
+        if how != "step":   # (else the next step finishes it)
+            shifted = _started(a) - before
+            assert bool((shifted > 0).all()) and torch.equal(_started(a), _started(b))
+            _same_state(a, b, f"after {t}")
+    _same_state(a, b, "at the end")
+    a.close()
+    b.close()
 
 
 @pytest.mark.parametrize("heads,N,B,layers", [
@@ -348,16 +396,6 @@ def test_ordered_caches_on_two_streams(heads, N, B, layers):
             _same_state(a[l], b[l], f"layer {l}")
             a[l].close()
             b[l].close()
-
-
-def _start_order(cache, by):
-    """Adds `by` to what the cache's metadata says about how many workgroups have started: the counters, one a head and the
-    last thing in it, 32 words apart."""
-    heads = cache.cfg.batch * cache.cfg.n_kv_heads
-    torch.cuda.synchronize()
-    counters = cache._meta[-((heads * 128 + 255) // 256 * 256):].view(torch.int32)
-    counters[:heads * 32:32] += by
-    torch.cuda.synchronize()
 
 
 @pytest.mark.parametrize("heads,N,B", [((4, 1, 64), 1000, 40), ((8, 2, 128), 900, 100)])

@@ -67,6 +67,20 @@ def test_toy_config_whole_prompt(layout):
     run_prompt(w, data, w.budget_N, w.block_B, layout=layout)
 
 
+@pytest.mark.parametrize("hq,hkv,d,N,B,T,kw", [
+    (8, 2, 128, 400, 100, 950, {}),          # ragged last block
+    (4, 1, 64, 800, 260, 1700, {}),          # rows that land five chunks below
+    (6, 3, 128, 400, 1, 404, {}),            # single rows
+    (14, 2, 64, 900, 50, 1200, {"window_W": 200}),
+    (6, 3, 128, 600, 33, 800, {"anchor_mode": kd.ANCHOR_MEAN_UNIT_KEY}),
+])
+def test_rows_shifted_around_the_selection(hq, hkv, d, N, B, T, kw):
+    # ORDERED caches of more rows than the selection shifts itself and few enough for the workgroups around it to hold (the chunks that
+    # start in such a launch are counted in the layers' tests)
+    w = get_config("llama32_3b").small(n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prompt_T=T)
+    run_prompt(w, make_layer(w, seed=300 + hq + N), N, B, layout=kd.LAYOUT_ORDERED, **kw)
+
+
 @pytest.mark.parametrize("layout", [kd.LAYOUT_ORDERED, kd.LAYOUT_FILL])
 @pytest.mark.parametrize("hq,hkv,d,N,B,T", [
     (6, 2, 128, 200, 48, 500),     # G = 3, tiles ragged in keys and rows, ragged last block
