@@ -446,6 +446,7 @@ def main():
                         a[1] += cnt
                 pair = tot.pop("event_pair", [0.0, 0])
                 prof = {k: {"event_bracket_us": v[0] / v[1] * 1e3, "launches": v[1]} for k, v in tot.items() if v[1]}
+                prof["step_post"]["key_ranges"] = cs[0].plan()[0]
             assert all(c.status() == 0 for c in cs)
             for c in cs:
                 c.close()
@@ -593,11 +594,13 @@ def main():
         us = ordered_kernels["compact_ordered"]["event_bracket_us"]
         hbm_kernels["compact_ordered_kernel"] = {"bytes_upper_bound": cb, "event_bracket_us": us, "GBps": cb / us / 1e3,
                                                  "frac_of_hbm_peak": cb / us / 1e3 / PEAK_HBM_GBPS}
-    elif ordered_kernels and "step_post" in ordered_kernels:   # the shift runs around the selection, in one launch with it and the merge
-        cb = 2 * 2 * Hkv * N * D * 2
+    elif ordered_kernels and (N + B) * D > 48 * 1024:   # (shorter caches are shifted by the selection's workgroup itself)
+        # the shift runs around the selection, in one launch with it and the merge: the bytes of shift and merge over all of it
+        ranges = ordered_kernels["step_post"]["key_ranges"]
+        cb = 2 * 2 * w.batch * Hkv * N * D * 2 + (w.batch * (ranges * Hq * B * (D * 2 + 8) + Hq * B * D * 2) if ranges > 1 else 0)
         us = ordered_kernels["step_post"]["event_bracket_us"]
         hbm_kernels["step_post_shift_kernel"] = {"bytes_upper_bound": cb, "event_bracket_us": us, "GBps": cb / us / 1e3,
-                                                 "frac_of_hbm_peak": cb / us / 1e3 / PEAK_HBM_GBPS}
+                                                 "frac_of_hbm_peak": cb / us / 1e3 / PEAK_HBM_GBPS, "key_ranges": ranges}
     if scores_pass:
         hbm_kernels["step_score_kernel"] = scores_pass
     if modes:
