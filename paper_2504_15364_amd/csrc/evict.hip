@@ -455,8 +455,19 @@ __device__ __forceinline__ void merge_around(const StepParams &p, const ShiftAro
         const int parts = min(p.merge_wgs / BH, sa.chunks);
         if (index / BH < parts) merge_few<D>(p, reinterpret_cast<float *>(&sh), index % BH, index / BH, parts);
     } else {
-        const size_t items = (size_t)BH * ((p.G * p.Bt + 31) / 32) * SLABS * 64;
-        for (size_t g = (size_t)index * POST_THREADS + threadIdx.x; g < items; g += (size_t)BH * sa.chunks * POST_THREADS) merge_rows<D>(p, g);
+        // By the number of splits as in merge_thread, but four pieces a thread only where one each takes it more than two rounds.  Always with
+        // the body for many splits / this way, us: 28 / 4 heads, four sequences, 1024 keys, blocks of 200 (three rounds) 46.0 / 39.0;  two layers of 24 / 8,
+        // two sequences, 2048 keys, blocks of 256 63.6 / 59.0;  three of 32 / 8, 4096 keys 54.7 / 53.4;  two of 28 / 4, 8192 keys, blocks of 256 (two
+        // rounds) 85.3 / 84.7, with four pieces 86.2.
+        const size_t items = (size_t)BH * ((p.G * p.Bt + 31) / 32) * SLABS * 64, step = (size_t)BH * sa.chunks * POST_THREADS;
+        const size_t first = (size_t)index * POST_THREADS + threadIdx.x;
+        if (__builtin_expect(p.splits > 8, 1)) {
+            for (size_t g = first; g < items; g += step) merge_rows<D>(p, g);
+        } else if (p.splits > MERGE_FEW_SPLITS || items <= 2 * step) {
+            for (size_t g = first; g < items; g += step) merge_rows<D, 8>(p, g);
+        } else {
+            for (size_t g = first; g < items / MERGE_PIECES; g += step) merge_rows_few_splits<D>(p, g, items / MERGE_PIECES);
+        }
     }
 }
 template <int D>

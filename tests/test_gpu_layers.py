@@ -263,6 +263,8 @@ def _start_order(cache, by):
     ((32, 8, 128), 1, 4097, 1, 1, {}, 5),                                           # one row, behind step_few and its merge
     ((24, 8, 128), 1, 4096, 128, 3, {}, 15),                                         # fifteen units, several layers
     ((8, 2, 64), 1, 2000, 100, 16, {}, 5),
+    ((28, 4, 128), 4, 1024, 200, 1, {}, 3),                                          # few ranges and many rows to merge: four pieces a thread
+    ((24, 8, 128), 2, 2048, 256, 2, {}, 11),                                         # likewise, one a thread
     ((16, 8, 128), 2, 8192, 64, 1, {}, 18),                                          # eighteen units
 ], ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
 def test_rows_shifted_around_the_selection(heads, batch, N, B, layers, kw, units):
