@@ -25,7 +25,8 @@
  *   - Query head h reads KV head h / (n_q_heads / n_kv_heads).
  *   - Every call enqueues its kernels on `stream` (a hipStream_t passed as
  *     void*, NULL = default stream) and returns without synchronising.  Calls on
- *     one handle must be issued in order on one stream.
+ *     one handle must be issued in order on one stream; calls on different handles may overlap on one
+ *     GPU (but not those that share the static scratch array, see keydiff_prefill_block_static).
  *   - Every call reads and updates host-side state of the handle (the row count, which half of
  *     the key-sum double buffer is current, a pending eviction) and bakes it into the launches:
  *     replaying such launches from a captured HIP graph would run them with stale parameters and

@@ -847,7 +847,8 @@ __device__ __forceinline__ void step_main_body(const StepParams &p, const int bl
     // The reference of tile t is decided behind the first three products of stage A: its chain (lane exchange, comparison, ballot, branch: 200
     // cycles of a wave) is waited for by the weights, not by them.  With the max scan held in stage B (the compiler had put it behind the
     // score) a pass over the prompt takes, us: 32 / 8 heads, 8192 keys, 4 layers 19654 / 19505, one 2500 / 2475 (ORDERED), 4096 keys
-    // 3434 / 3409;  28 / 4, 2 layers 6801 / 6746;  24 / 8, 3 layers 4601 / 4548;  16384 keys in blocks of 512 6132 / 6077.
+    // 3434 / 3409;  28 / 4, 2 layers 6801 / 6746;  24 / 8, 3 layers 4601 / 4548;  16384 keys in blocks of 512 6132 / 6077.  (4096 keys and blocks of
+    // 512: on other boxes within what runs of one build differ by.)
     // The scheduling barriers pin that order.  Tiles t + 2 and t + 3 are in flight meanwhile.
     auto open_step = [&](int t) {
         // tile t + 1 has landed when at most the copies of tile t + 2 remain; the barrier

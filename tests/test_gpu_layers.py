@@ -134,7 +134,7 @@ def test_layers_with_long_caches_in_one_launch(heads, N, B, kw):
 @pytest.mark.parametrize("call", ["block", "layers", "deferred"])
 def test_short_ordered_caches_are_shifted_by_the_selection(d, N, B, call):
     # up to 48 K elements of K a head (768 rows of 64, 384 of 128) the selection shifts the rows of an ORDERED cache, in
-    # passes of 512 or 256; beyond, a launch of its own does.  The retained rows are those of the FILL layout, in order.
+    # passes of 512 or 256; beyond, the workgroups around it do, or a launch of its own.  The retained rows are those of the FILL layout, in order.
     heads, layers = (8, 2, d), 2 if call == "layers" else 1
     a, b = ([kd.KeyDiffCache(kd.KeyDiffConfig(1, *heads, N, B, layout=lay)) for _ in range(layers)]
             for lay in (kd.LAYOUT_ORDERED, kd.LAYOUT_FILL))
